@@ -457,18 +457,23 @@ __global__ __launch_bounds__(kThreads) void knorm_score_kernel(BatchParams p) {
 // observation window compete (window tokens are always kept), so the kernel
 // selects the budget-minus-window best of the prefix and appends the window.
 //
-//   1. the un-pooled scores are staged in LDS, max-pooled from LDS and turned
-//      in place into order-preserving 32-bit keys; min and max key are reduced
-//      on the way;
+//   1. the un-pooled scores lie in LDS; they are max-pooled and turned into
+//      order-preserving 32-bit keys, which stay in registers for the rest;
 //   2. the threshold (the k-th largest key) is found by a bucket select: 2048
-//      linear buckets over [min, max] (so the histogram is spread even when
-//      every score shares its exponent), then the keys of the one bucket that
-//      holds the threshold are compacted to a short candidate list, which is
-//      refined with 2048 buckets per pass until a bucket is a single key
-//      (at most 3 passes for 32 bits);
+//      linear buckets over a range that holds it (so the histogram is spread
+//      even when every score shares its exponent), then the keys of the one
+//      bucket that holds the threshold are compacted to a short candidate list,
+//      which is refined with 2048 buckets per pass until a bucket is a single
+//      key (at most 3 passes for 32 bits);
 //   3. the kept indices are emitted in ascending token order by a ballot /
 //      popcount compaction in which keys equal to the threshold are admitted
 //      in index order until the budget is met (ties go to the lower index).
+//
+// Ownership of tokens: a wavefront owns a contiguous segment (a multiple of 256
+// tokens) and a lane four consecutive tokens of each 256.  What bounds this
+// phase is LDS latency (one workgroup has four wavefronts and every step waits
+// for its reads), so the pooling window of a lane's four tokens comes from three
+// 16-byte reads instead of seven dependent 4-byte reads per token.
 
 __device__ __forceinline__ uint32_t score_key(float s) {
   s += 0.0f;  // -0 and +0 compare equal, give them one key
@@ -479,32 +484,139 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 static constexpr int kBuckets = 2048;
 static constexpr int kBucketBits = 11;
 static constexpr int kMaxCand = 2048;
-static constexpr int kStagePerThread = 32;  // staging path handles up to 32*256 tokens
+static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
+// chunks of a wavefront's segment at most: 4 wavefronts take heads of up to 8192 tokens, 16 of up to 32768
+template <int WV>
+static constexpr int kChunksPerWave = 8;
 
-// Finds, among the `n` keys produced by get(j) that lie in [lo, lo + width)
-// (width == 0: all of them do, no check), the bucket (key - lo) >> shift that
-// holds the `remaining`-th largest.  Returns the bucket in sel[0] and the rank
-// inside it in sel[1].  All threads must call.
-template <typename Get>
-__device__ __forceinline__ void bucket_pass(int n, uint32_t lo, int shift, uint32_t width,
-                                            int remaining, int* hist, int* wsum, int* sel,
-                                            Get get) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-  for (int i = 0; i < kBuckets / kThreads; ++i) hist[tid + i * kThreads] = 0;
-  __syncthreads();
-  for (int j = tid; j < n; j += kThreads) {
-    const uint32_t k = get(j);
-    const uint32_t d = k - lo;
-    if (width == 0u || (k >= lo && d < width)) atomicAdd(&hist[d >> shift], 1);
+// LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
+// that the four-token reads of the pooling may touch (filled with the neutral
+// value), then one bit per token.
+static constexpr int kStageFront = 4;
+__host__ __device__ constexpr int stage_words(int len) { return kStageFront + ((len + 3) & ~3) + 8; }
+__host__ __device__ constexpr int need_words(int len) { return (len + kChunk - 1) / kChunk * (kChunk / 32); }
+
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32x4 lds_words4(const uint32_t* p) {
+  return *reinterpret_cast<const uint32x4*>(p);
+}
+__device__ __forceinline__ void set_lds_words4(uint32_t* p, uint32x4 v) {
+  *reinterpret_cast<uint32x4*>(p) = v;
+}
+
+// first token of a wavefront's segment
+template <int WV>
+__device__ __forceinline__ int segment_tokens(int n) {
+  return (((n + WV - 1) / WV) + kChunk - 1) & ~(kChunk - 1);
+}
+
+// Writes `v` to the words around stage[0 .. n) that pooling reads.
+__device__ __forceinline__ void fill_stage_margins(uint32_t* stage, int n, uint32_t v) {
+  if (threadIdx.x < kStageFront) stage[(int)threadIdx.x - kStageFront] = v;
+  if (threadIdx.x < 8) stage[n + threadIdx.x] = v;  // n + 7 < the padded length + 8
+}
+
+struct PoolMaxWord {  // largest whole word (non-negative floats compare like their bits)
+  static constexpr uint32_t neutral = 0u;
+  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w; }
+  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
+};
+struct PoolMaxLow {  // largest low half
+  static constexpr uint32_t neutral = 0u;
+  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
+  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
+};
+struct PoolMinLow {  // smallest low half
+  static constexpr uint32_t neutral = 0xFFFFu;
+  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
+  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return min(a, b); }
+};
+
+// The pooling windows [c + e - h, c + e + h] of the four tokens c + e (c a
+// multiple of 4) over stage[0 .. n) and its margins.  h = 3 (a pooling width of
+// 7, the usual one) has its own code: three 16-byte reads, the part of the
+// windows that all four share once.  Any other h walks the 16-byte groups.
+template <bool kThree>
+struct PoolWindow {
+  uint32x4 left, mid, right;
+  const uint32_t* stage;
+  int c, h, n;
+  __device__ __forceinline__ PoolWindow(const uint32_t* stage_, int c_, int h_, int n_)
+      : stage(stage_), c(c_), h(h_), n(n_) {
+    mid = lds_words4(stage + c);
+    if constexpr (kThree) {
+      left = lds_words4(stage + c - 4);
+      right = lds_words4(stage + c + 4);
+    }
   }
-  __syncthreads();
-  // thread t owns buckets [8t, 8t+8)
-  int own[kBuckets / kThreads];
+  template <typename Op>
+  __device__ __forceinline__ void reduce(uint32_t (&out)[4]) const {
+    if constexpr (kThree) {
+      const uint32_t core = Op::join(Op::join(Op::get(mid[0]), Op::get(mid[1])),
+                                     Op::join(Op::get(mid[2]), Op::get(mid[3])));
+      const uint32_t l2 = Op::get(left[3]), l1 = Op::join(Op::get(left[2]), l2),
+                     l0 = Op::join(Op::get(left[1]), l1);
+      const uint32_t r1 = Op::get(right[0]), r2 = Op::join(r1, Op::get(right[1])),
+                     r3 = Op::join(r2, Op::get(right[2]));
+      out[0] = Op::join(core, l0);
+      out[1] = Op::join(core, Op::join(l1, r1));
+      out[2] = Op::join(core, Op::join(l2, r2));
+      out[3] = Op::join(core, r3);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = Op::get(mid[e]);
+      if (h == 0) return;
+      uint32_t shared = Op::neutral;
+      const int reach = (h + 3) >> 2;  // groups to either side
+      for (int g = -reach; g <= reach; ++g) {
+        const int at = c + 4 * g;
+        if (at < -kStageFront || at >= n) continue;  // (the margins cover one group to either side)
+        const uint32x4 w = lds_words4(stage + at);
+        if (4 * abs(g) + 3 <= h) {  // uniform: in all four windows
+          shared = Op::join(shared, Op::join(Op::join(Op::get(w[0]), Op::get(w[1])),
+                                             Op::join(Op::get(w[2]), Op::get(w[3]))));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (abs(4 * g + k - e) <= h) out[e] = Op::join(out[e], Op::get(w[k]));
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = Op::join(out[e], shared);
+    }
+  }
+};
+
+// hist[b[e]] += 1 for four buckets (kNoBucket: none); neighbouring tokens share
+// their pooled maximum more often than not, so equal neighbours go in one add
+static constexpr uint32_t kNoBucket = 0xFFFFFFFFu;
+__device__ __forceinline__ void hist_add4(int* hist, const uint32_t (&b)[4]) {
+  int run = 1;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (e < 3 && b[e] == b[(e + 1) & 3]) {
+      ++run;
+    } else {
+      if (b[e] != kNoBucket) atomicAdd(&hist[b[e]], run);
+      run = 1;
+    }
+  }
+}
+
+// The bucket that holds the `rank`-th largest entry of a histogram -> sel[0],
+// the rank inside it -> sel[1].  All threads call; ends with a barrier.
+template <int WV>
+__device__ __forceinline__ void bucket_of_rank(const int* hist, int rank, int* wsum, int* sel) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kOwn = kBuckets / (64 * WV);  // thread t owns buckets [kOwn t, kOwn t + kOwn)
+  int own[kOwn];
   int s = 0;
 #pragma unroll
-  for (int i = 0; i < kBuckets / kThreads; ++i) {
-    own[i] = hist[tid * (kBuckets / kThreads) + i];
+  for (int i = 0; i < kOwn; ++i) {
+    own[i] = hist[tid * kOwn + i];
     s += own[i];
   }
   int v = s;
@@ -517,173 +629,218 @@ __device__ __forceinline__ void bucket_pass(int n, uint32_t lo, int shift, uint3
   __syncthreads();
   int base = 0, total = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < WV; ++w) {
     if (w < wave) base += wsum[w];
     total += wsum[w];
   }
   int above = total - (v + base);  // keys in buckets above this thread's
 #pragma unroll
-  for (int i = kBuckets / kThreads - 1; i >= 0; --i) {
-    if (above < remaining && above + own[i] >= remaining) {
-      sel[0] = tid * (kBuckets / kThreads) + i;
-      sel[1] = remaining - above;
+  for (int i = kOwn - 1; i >= 0; --i) {
+    if (above < rank && above + own[i] >= rank) {
+      sel[0] = tid * kOwn + i;
+      sel[1] = rank - above;
     }
     above += own[i];
   }
   __syncthreads();
 }
 
+template <int WV>
 struct SelectShared {
   int hist[kBuckets];
   uint32_t cand[kMaxCand];
-  int wsum[kWaves];
-  uint32_t wmin[kWaves], wmax[kWaves];
+  int wsum[WV];
+  uint32_t wmin[WV], wmax[WV];
   int sel[2];
   int n_cand;
-  int cnt[kWaves][2];
+  int cnt[WV][2];
 };
 
 // Selects the kept tokens of one (request, layer, head) and writes them, in
-// ascending order, to the kept list.  `keys` is LDS room for seq_len words.
-// kRawInLds: the un-pooled scores already sit in keys[] (as floats, written
-// by this workgroup and made visible by a barrier); otherwise they are read
-// from raw_scores.  All threads of the workgroup call.
-template <bool kRawInLds>
-__device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            uint32_t* keys, SelectShared& sh) {
+// ascending order, to the kept list.  stage[0 .. n_sel): the un-pooled scores as
+// floats, written by this workgroup and made visible by a barrier.  hint_lo,
+// hint_hi: keys that are known to enclose the threshold (0, ~0: nothing is
+// known).  All threads of the workgroup call.
+template <bool kThree, int WV>
+__device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDesc& rd, int lh,
+                                              uint32_t* stage, SelectShared<WV>& sh, uint32_t hint_lo,
+                                              uint32_t hint_hi) {
   int* hist = sh.hist;
   uint32_t* cand = sh.cand;
-  int* wsum = sh.wsum;
-  uint32_t* wmin = sh.wmin;
-  uint32_t* wmax = sh.wmax;
   int* sel = sh.sel;
-  int& n_cand = sh.n_cand;
-  int (*cnt)[2] = sh.cnt;
   const int L = rd.seq_len;
   const int B = rd.budget;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
   const int n_sel = snap ? L - rd.window : L;  // tokens that compete
   const int k_sel = snap ? B - rd.window : B;  // how many of them are kept
-  const float* raw = p.raw_scores + rd.raw_off + (size_t)lh * L;
   float* out = p.scores_out ? p.scores_out + rd.score_off + (size_t)lh * L : nullptr;
   int32_t* kept = p.kept + rd.kept_off + (size_t)lh * B;
+  const int seg = segment_tokens<WV>(n_sel);
+  const int j0 = wave * seg;
+  const int j1 = min(n_sel, j0 + seg);
 
   // ---- 1. final scores -> keys, min / max -------------------------------------
+  fill_stage_margins(stage, n_sel, 0u);
+  if (tid == 0) sh.n_cand = 0;
+#pragma unroll
+  for (int i = 0; i < kBuckets / (64 * WV); ++i) hist[tid + i * (64 * WV)] = 0;
+  __syncthreads();
+  uint32_t key[kChunksPerWave<WV>][4];
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  if (snap && (kRawInLds || n_sel <= kStagePerThread * kThreads)) {
-    float* stage = reinterpret_cast<float*>(keys);
-    if (!kRawInLds) {
-      for (int j = tid; j < n_sel; j += kThreads) stage[j] = raw[j];
+#pragma unroll
+  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+    const int c = j0 + i * kChunk + 4 * lane;
+    if (c < j1) {
+      const PoolWindow<kThree> pw(stage, c, rd.pool_kernel >> 1, n_sel);
+      uint32_t v[4];
+      if (snap) {
+        pw.template reduce<PoolMaxWord>(v);  // (sums of exponentials: none is negative)
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = pw.mid[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t k = score_key(__uint_as_float(v[e]));
+        key[i][e] = k;
+        if (c + e < j1) {
+          kmin = min(kmin, k);
+          kmax = max(kmax, k);
+        }
+      }
+    }
+  }
+  if (out) {
+    // back through LDS, so that the stores are contiguous over the lanes
+    if (snap) {
       __syncthreads();
-    }
-    const int h = rd.pool_kernel >> 1;
-    float pv[kStagePerThread];
 #pragma unroll
-    for (int i = 0; i < kStagePerThread; ++i) {
-      const int j = tid + i * kThreads;
-      float s = 0.f;
-      if (j < n_sel) {
-        const int lo = max(0, j - h), hi = min(n_sel - 1, j + h);
-        s = stage[lo];
-        for (int t = lo + 1; t <= hi; ++t) s = fmaxf(s, stage[t]);
-      }
-      pv[i] = s;
-    }
-    __syncthreads();
+      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+        const int c = j0 + i * kChunk + 4 * lane;
+        if (c < j1) {
+          uint32x4 w;
 #pragma unroll
-    for (int i = 0; i < kStagePerThread; ++i) {
-      const int j = tid + i * kThreads;
-      if (j < n_sel) {
-        const uint32_t k = score_key(pv[i]);
-        keys[j] = k;
-        kmin = min(kmin, k);
-        kmax = max(kmax, k);
-        if (out) out[j] = pv[i];
+          for (int e = 0; e < 4; ++e) w[e] = key[i][e] & 0x7FFFFFFFu;
+          set_lds_words4(stage + c, w);
+        }
       }
+      __syncthreads();
+      for (int j = n_sel + tid; j < L; j += (64 * WV)) out[j] = INFINITY;
     }
-  } else if (snap) {
-    const int h = rd.pool_kernel >> 1;
-    for (int j = tid; j < n_sel; j += kThreads) {
-      const int lo = max(0, j - h), hi = min(n_sel - 1, j + h);
-      float s = raw[lo];
-      for (int t = lo + 1; t <= hi; ++t) s = fmaxf(s, raw[t]);
-      const uint32_t k = score_key(s);
-      keys[j] = k;
-      kmin = min(kmin, k);
-      kmax = max(kmax, k);
-      if (out) out[j] = s;
-    }
-  } else {
-    for (int j = tid; j < n_sel; j += kThreads) {
-      const float s = kRawInLds ? reinterpret_cast<float*>(keys)[j] : raw[j];
-      const uint32_t k = score_key(s);
-      keys[j] = k;
-      kmin = min(kmin, k);
-      kmax = max(kmax, k);
-      if (out) out[j] = s;
-    }
+    for (int j = tid; j < n_sel; j += (64 * WV)) out[j] = __uint_as_float(stage[j]);
   }
   if (snap) {
-    if (out)
-      for (int j = n_sel + tid; j < L; j += kThreads) out[j] = INFINITY;
-    for (int j = tid; j < rd.window; j += kThreads) kept[k_sel + j] = n_sel + j;  // forced window
+    for (int j = tid; j < rd.window; j += (64 * WV)) kept[k_sel + j] = n_sel + j;  // forced window
   }
+  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
     kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
   }
-  if (lane == 0) {
-    wmin[wave] = kmin;
-    wmax[wave] = kmax;
-  }
-  if (tid == 0) n_cand = 0;
-  __syncthreads();
-  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
+  // how many keys lie above the hinted range, and how many not below it
+  int n_above = 0, n_reach = 0;
+  if (hint_lo != 0u) {  // uniform
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    kmin = min(kmin, wmin[w]);
-    kmax = max(kmax, wmax[w]);
+    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+      const int c = j0 + i * kChunk + 4 * lane;
+      if (j0 + i * kChunk >= j1) break;  // uniform over the wavefront
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        n_above += __popcll(__ballot(c + e < j1 && key[i][e] > hint_hi));
+        n_reach += __popcll(__ballot(c + e < j1 && key[i][e] >= hint_lo));
+      }
+    }
+  }
+  if (lane == 0) {
+    sh.wmin[wave] = kmin;
+    sh.wmax[wave] = kmax;
+    sh.cnt[wave][0] = n_above;
+    sh.cnt[wave][1] = n_reach;
+  }
+  __syncthreads();
+  n_above = n_reach = 0;
+#pragma unroll
+  for (int w = 0; w < WV; ++w) {
+    kmin = min(kmin, sh.wmin[w]);
+    kmax = max(kmax, sh.wmax[w]);
+    n_above += sh.cnt[w][0];
+    n_reach += sh.cnt[w][1];
+  }
+  // the k_sel-th largest key lies in the hinted range: search only there
+  const bool narrowed = n_above < k_sel && n_reach >= k_sel;  // uniform
+  if (narrowed) {
+    kmin = max(kmin, hint_lo);
+    kmax = min(kmax, hint_hi);
   }
 
   // ---- 2. threshold = k_sel-th largest key ---------------------------------------
+  // one pass over the registers: the keys in [lo, lo + width) into 2048 buckets (width 0: up to kmax)
+  auto count_keys = [&](uint32_t lo, int shift, uint32_t width) {
+#pragma unroll
+    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+      const int c = j0 + i * kChunk + 4 * lane;
+      if (c < j1) {
+        uint32_t b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t k = key[i][e], d = k - lo;
+          b[e] = c + e < j1 && k >= lo && (width == 0u ? k <= kmax : d < width) ? d >> shift : kNoBucket;
+        }
+        hist_add4(hist, b);
+      }
+    }
+  };
   uint32_t thr;
   int need_eq;
-  if (kmin == kmax) {
-    thr = kmin;
-    need_eq = k_sel;
-  } else {
+  {
     uint32_t lo = kmin;
     const uint32_t range = kmax - kmin;
-    int shift = max(0, 32 - __clz(range) - kBucketBits);
-    bucket_pass(n_sel, lo, shift, 0u, k_sel, hist, wsum, sel, [&](int j) { return keys[j]; });
+    int shift = range ? max(0, 32 - __clz(range) - kBucketBits) : 0;
+    count_keys(lo, shift, 0u);
+    __syncthreads();
+    bucket_of_rank<WV>(hist, narrowed ? k_sel - n_above : k_sel, sh.wsum, sel);
     int remaining = sel[1];
     uint32_t bkt = (uint32_t)sel[0];
     if (shift > 0) {
       // candidates: the keys of that one bucket
-      for (int j = tid; j < n_sel; j += kThreads) {
-        const uint32_t k = keys[j];
-        if (((k - lo) >> shift) == bkt) {
-          const int pos = atomicAdd(&n_cand, 1);
-          if (pos < kMaxCand) cand[pos] = k;
+#pragma unroll
+      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+        const int c = j0 + i * kChunk + 4 * lane;
+        if (c < j1) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t k = key[i][e];
+            if (c + e < j1 && k >= lo && k <= kmax && ((k - lo) >> shift) == bkt) {
+              const int pos = atomicAdd(&sh.n_cand, 1);
+              if (pos < kMaxCand) cand[pos] = k;
+            }
+          }
         }
       }
       __syncthreads();
-      const int nc = n_cand;
+      const int nc = sh.n_cand;
       const bool listed = nc <= kMaxCand;  // else refine over all keys with a range check
       while (shift > 0) {
         lo += bkt << shift;
         const uint32_t width = 1u << shift;  // the chosen bucket spans [lo, lo + width)
         shift = max(0, shift - kBucketBits);
-        if (listed)
-          bucket_pass(nc, lo, shift, width, remaining, hist, wsum, sel,
-                      [&](int j) { return cand[j]; });
-        else
-          bucket_pass(n_sel, lo, shift, width, remaining, hist, wsum, sel,
-                      [&](int j) { return keys[j]; });
+#pragma unroll
+        for (int i = 0; i < kBuckets / (64 * WV); ++i) hist[tid + i * (64 * WV)] = 0;
+        __syncthreads();
+        if (listed) {
+          for (int j = tid; j < nc; j += (64 * WV)) {
+            const uint32_t d = cand[j] - lo;
+            if (cand[j] >= lo && d < width) atomicAdd(&hist[d >> shift], 1);
+          }
+        } else {
+          count_keys(lo, shift, width);
+        }
+        __syncthreads();
+        bucket_of_rank<WV>(hist, remaining, sh.wsum, sel);
         remaining = sel[1];
         bkt = (uint32_t)sel[0];
       }
@@ -692,45 +849,69 @@ __device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc&
     need_eq = remaining;
   }
 
-  // ---- 3. ordered compaction; each wavefront owns a contiguous token segment ----
-  const int seg = (((n_sel + kWaves - 1) / kWaves) + 63) & ~63;
-  const int j0 = wave * seg;
-  const int j1 = min(n_sel, j0 + seg);
+  // ---- 3. ordered compaction ------------------------------------------------------
   int n_gt = 0, n_eq = 0;
-  for (int jb = j0; jb < j1; jb += 64) {
-    const int j = jb + lane;
-    const bool in = j < j1;
-    const uint32_t k = in ? keys[j] : 0u;
-    n_gt += __popcll(__ballot(in && k > thr));
-    n_eq += __popcll(__ballot(in && k == thr));
+#pragma unroll
+  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+    const int c = j0 + i * kChunk + 4 * lane;
+    if (j0 + i * kChunk >= j1) break;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      n_gt += __popcll(__ballot(c + e < j1 && key[i][e] > thr));
+      n_eq += __popcll(__ballot(c + e < j1 && key[i][e] == thr));
+    }
   }
   if (lane == 0) {
-    cnt[wave][0] = n_gt;
-    cnt[wave][1] = n_eq;
+    sh.cnt[wave][0] = n_gt;
+    sh.cnt[wave][1] = n_eq;
   }
   __syncthreads();
   int gt_before = 0, eq_before = 0;
   for (int w = 0; w < wave; ++w) {
-    gt_before += cnt[w][0];
-    eq_before += cnt[w][1];
+    gt_before += sh.cnt[w][0];
+    eq_before += sh.cnt[w][1];
   }
   int eq_run = eq_before;
   int kept_run = gt_before + min(eq_before, need_eq);
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  for (int jb = j0; jb < j1; jb += 64) {
-    const int j = jb + lane;
-    const bool in = j < j1;
-    const uint32_t k = in ? keys[j] : 0u;
-    const bool is_gt = in && k > thr;
-    const bool is_eq = in && k == thr;
-    const uint64_t eq_ballot = __ballot(is_eq);
-    const int eq_rank = eq_run + __popcll(eq_ballot & lt_mask);
-    const bool keep = is_gt || (is_eq && eq_rank < need_eq);
-    const uint64_t keep_ballot = __ballot(keep);
-    if (keep) kept[kept_run + __popcll(keep_ballot & lt_mask)] = j;
-    eq_run += __popcll(eq_ballot);
-    kept_run += __popcll(keep_ballot);
+#pragma unroll
+  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+    const int c = j0 + i * kChunk + 4 * lane;
+    if (j0 + i * kChunk >= j1) break;
+    // (lanes are in token order, each with its four tokens in order)
+    uint64_t eq[4], kp[4];
+    int eq_rank = eq_run;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      eq[e] = __ballot(c + e < j1 && key[i][e] == thr);
+      eq_rank += __popcll(eq[e] & lt_mask);
+      eq_run += __popcll(eq[e]);
+    }
+    bool keep[4];
+    int at = kept_run;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool is_eq = (eq[e] >> lane) & 1u;
+      keep[e] = (c + e < j1 && key[i][e] > thr) || (is_eq && eq_rank < need_eq);
+      eq_rank += is_eq ? 1 : 0;
+      kp[e] = __ballot(keep[e]);
+      at += __popcll(kp[e] & lt_mask);
+      kept_run += __popcll(kp[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (keep[e]) kept[at++] = c + e;
   }
+}
+
+template <int WV>
+__device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc& rd, int lh,
+                                            uint32_t* stage, SelectShared<WV>& sh, uint32_t hint_lo = 0u,
+                                            uint32_t hint_hi = 0xFFFFFFFFu) {
+  if (rd.pool_kernel == 7)  // uniform
+    select_unit_h<true, WV>(p, rd, lh, stage, sh, hint_lo, hint_hi);
+  else
+    select_unit_h<false, WV>(p, rd, lh, stage, sh, hint_lo, hint_hi);
 }
 
 // ---------------------------------------------------------------------------
@@ -1134,134 +1315,213 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
 }
 
 // Between the two: which prefix tokens need their exact column sum.  stage[]
-// holds the packed bounds; need[] is set.
-__device__ __forceinline__ void bound_classify(const ReqDesc& rd, const float* stage_f,
-                                               uint32_t* need, SelectShared& sh) {
-  const uint32_t* stage = reinterpret_cast<const uint32_t*>(stage_f);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// holds the packed bounds; need[] is set (one bit per token), stage[j] of every
+// token becomes its upper bound.  Tokens are owned and pooled as in select_unit_h;
+// a sweep reads three 16-byte words per four tokens.  Which tokens are named is
+// found from the token's side: j is needed if some undecided token of its pooling
+// window has a pooled lower bound that j's upper bound reaches, i.e. if j's upper
+// bound is at least the least such lower bound of its window.
+//
+// The selection's threshold is returned between two keys.
+template <bool kThree, int WV>
+__device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* stage, uint32_t* need,
+                                                 SelectShared<WV>& sh, uint32_t& key_lo, uint32_t& key_hi) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_sel = rd.seq_len - rd.window;
   const int k_sel = rd.budget - rd.window;
   const int h = rd.pool_kernel >> 1;
-  float vmax = 0.f;
-  for (int j = tid; j < n_sel; j += kThreads) vmax = fmaxf(vmax, upper_of(stage[j]));
-  for (int j = tid; j < ((n_sel + 31) >> 5); j += kThreads) need[j] = 0u;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o));
-  if (lane == 0) sh.wmax[wave] = __float_as_uint(vmax);
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) vmax = fmaxf(vmax, __uint_as_float(sh.wmax[w]));
-  if (k_sel <= 0 || k_sel >= n_sel) return;  // uniform: window only, or everything is kept
-  auto pooled = [&](int j, float& plo, float& phi) {
-    const int a = max(0, j - h), b = min(n_sel - 1, j + h);
-    plo = 0.f;
-    phi = 0.f;
-    for (int k = a; k <= b; ++k) {
-      const uint32_t w = stage[k];
-      phi = fmaxf(phi, upper_of(w));
-      plo = fmaxf(plo, lower_of(w));
-    }
-  };
-  // thresholds: the buckets that hold the k_sel-th largest lower and the k_sel-th
-  // largest upper bound (two histograms from one evaluation of the pooled bounds)
+  const int seg = segment_tokens<WV>(n_sel);
+  const int j0 = wave * seg;
+  const int j1 = min(n_sel, j0 + seg);
   int* hist_lo = sh.hist;
   int* hist_hi = reinterpret_cast<int*>(sh.cand);
   static_assert(kMaxCand >= kBuckets, "the candidate list doubles as the second histogram");
-  // the bucket of the k_sel-th largest entry of a histogram -> sel[which]
-  auto kth_bucket = [&](const int* hist, int which) {
-    int own[kBuckets / kThreads];
-    int sum = 0;
+  fill_stage_margins(stage, n_sel, 0u);
+  uint32_t vmax = 0u;
 #pragma unroll
-    for (int i = 0; i < kBuckets / kThreads; ++i) {
-      own[i] = hist[tid * (kBuckets / kThreads) + i];
-      sum += own[i];
-    }
-    int v = sum;
+  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+    const int c = j0 + i * kChunk + 4 * lane;
+    if (c < j1) {
+      const uint32x4 w = lds_words4(stage + c);
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(v, o);
-      if (lane >= o) v += t;
+      for (int e = 0; e < 4; ++e)
+        if (c + e < j1) vmax = max(vmax, w[e] & 0xFFFF0000u);
     }
-    if (lane == 63) sh.wsum[wave] = v;
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      if (w < wave) before += sh.wsum[w];
-      total += sh.wsum[w];
-    }
-    int above = total - (v + before);  // entries in buckets above this thread's
-#pragma unroll
-    for (int i = kBuckets / kThreads - 1; i >= 0; --i) {
-      if (above < k_sel && above + own[i] >= k_sel) sh.sel[which] = tid * (kBuckets / kThreads) + i;
-      above += own[i];
-    }
-    __syncthreads();
-  };
-  // buckets of 2^shift keys from kmin upwards; what lies below kmin counts in bucket 0
-  auto find_buckets = [&](uint32_t kmin, int shift) {
-#pragma unroll
-    for (int i = 0; i < kBuckets / kThreads; ++i) {
-      hist_lo[tid + i * kThreads] = 0;
-      hist_hi[tid + i * kThreads] = 0;
-    }
-    __syncthreads();
-    for (int j = tid; j < n_sel; j += kThreads) {
-      float plo, phi;
-      pooled(j, plo, phi);
-      const uint32_t klo = score_key(plo), khi = score_key(phi);
-      // (no key exceeds the largest upper bound; the clamp keeps the index in range whatever the bounds hold)
-      atomicAdd(&hist_lo[klo > kmin ? min((klo - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u], 1);
-      atomicAdd(&hist_hi[khi > kmin ? min((khi - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u], 1);
-    }
-    __syncthreads();
-    kth_bucket(hist_lo, 0);
-    kth_bucket(hist_hi, 1);
-  };
-  // The bounds carry 16 significant bits, the whole range of keys from 0 to the
-  // largest upper bound only fits 2048 buckets that are up to 12 % of a value
-  // wide.  So first with buckets of 1.6 % (2^17 keys) over the 32 octaves below
-  // the largest upper bound; should the k_sel-th largest lower bound lie below
-  // all of that, once more over the whole range.
-  const uint32_t kzero = score_key(0.f), kmax = score_key(vmax);
-  const int coarse = kmax > kzero ? max(0, 32 - __clz(kmax - kzero) - kBucketBits) : 0;
-  constexpr int kFine = 17;
-  uint32_t kmin = kzero;
-  int shift = coarse;
-  if (coarse > kFine) {
-    kmin = kmax - ((uint32_t)kBuckets << kFine) + 1u;
-    shift = kFine;
   }
-  find_buckets(kmin, shift);
-  if (kmin != kzero && sh.sel[0] == 0) {  // uniform: read after a barrier
-    __syncthreads();                      // (everyone has read sel before it is written again)
-    kmin = kzero;
-    shift = coarse;
-    find_buckets(kmin, shift);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, o));
+  if (lane == 0) sh.wmax[wave] = vmax;
+  auto zero_histograms = [&] {
+#pragma unroll
+    for (int i = 0; i < kBuckets / (64 * WV); ++i) {
+      hist_lo[tid + i * (64 * WV)] = 0;
+      hist_hi[tid + i * (64 * WV)] = 0;
+    }
+  };
+  zero_histograms();
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WV; ++w) vmax = max(vmax, sh.wmax[w]);
+  const bool trivial = k_sel <= 0 || k_sel >= n_sel;  // uniform: window only, or everything is kept
+  uint64_t named = 0;  // this lane's tokens, four bits per chunk
+  static_assert(4 * kChunksPerWave<WV> <= 64, "a lane's bits");
+  if (!trivial) {
+    // thresholds: the buckets that hold the k_sel-th largest lower and the k_sel-th
+    // largest upper bound (two histograms from one evaluation of the pooled bounds);
+    // buckets of 2^shift bit patterns from kmin upwards, what lies below kmin counts in bucket 0
+    auto find_buckets = [&](uint32_t kmin, int shift) {
+#pragma unroll
+      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+        const int c = j0 + i * kChunk + 4 * lane;
+        if (c < j1) {
+          const PoolWindow<kThree> pw(stage, c, h, n_sel);
+          uint32_t hi[4], lo[4];
+          pw.template reduce<PoolMaxWord>(hi);
+          pw.template reduce<PoolMaxLow>(lo);
+          // (no bound exceeds the largest upper bound; the clamp keeps the index in range whatever the bounds hold)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t kh = hi[e] & 0xFFFF0000u, kl = lo[e] << 16;
+            hi[e] = kh > kmin ? min((kh - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
+            lo[e] = kl > kmin ? min((kl - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
+            if (c + e >= j1) hi[e] = lo[e] = kNoBucket;
+          }
+          hist_add4(hist_hi, hi);
+          hist_add4(hist_lo, lo);
+        }
+      }
+      __syncthreads();
+      bucket_of_rank<WV>(hist_lo, k_sel, sh.wsum, sh.sel);
+      const int blo = sh.sel[0];
+      __syncthreads();
+      bucket_of_rank<WV>(hist_hi, k_sel, sh.wsum, sh.sel);
+      const int bhi = sh.sel[0];
+      return make_int2(blo, bhi);
+    };
+    // The bounds carry 16 significant bits, the whole range from 0 to the largest
+    // upper bound only fits 2048 buckets that are up to 12 % of a value wide.  So
+    // first with buckets of 1.6 % (2^17 bit patterns) over the 32 octaves below
+    // the largest upper bound; should the k_sel-th largest lower bound lie below
+    // all of that, once more over the whole range.
+    const int coarse = vmax ? max(0, 32 - __clz(vmax) - kBucketBits) : 0;
+    constexpr int kFine = 17;
+    uint32_t kmin = 0u;
+    int shift = coarse;
+    if (coarse > kFine) {
+      kmin = vmax - ((uint32_t)kBuckets << kFine) + 1u;
+      shift = kFine;
+    }
+    int2 bkt = find_buckets(kmin, shift);
+    if (kmin != 0u && bkt.x == 0) {  // uniform
+      __syncthreads();               // (everyone has read the histograms before they are cleared)
+      zero_histograms();
+      __syncthreads();
+      kmin = 0u;
+      shift = coarse;
+      bkt = find_buckets(kmin, shift);
+    }
+    // (bucket 0 also holds what lies below kmin)
+    const uint32_t t_lo = bkt.x == 0 ? 0u : kmin + ((uint32_t)bkt.x << shift);  // <= the threshold
+    const uint32_t t_hi = kmin + (((uint32_t)bkt.y + 1u) << shift) - 1u;         // >= the threshold
+    key_lo = t_lo | 0x80000000u;  // (score_key of a non-negative value)
+    key_hi = t_hi | 0x80000000u;
+    // the low half of every undecided token's word becomes its pooled lower bound,
+    // of every other token's 0xFFFF
+    uint32_t low[kChunksPerWave<WV>][2];
+#pragma unroll
+    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+      const int c = j0 + i * kChunk + 4 * lane;
+      if (c < j1) {
+        const PoolWindow<kThree> pw(stage, c, h, n_sel);
+        uint32_t hi[4], lo[4];
+        pw.template reduce<PoolMaxWord>(hi);
+        pw.template reduce<PoolMaxLow>(lo);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e >= j1 || (hi[e] & 0xFFFF0000u) < t_lo || (lo[e] << 16) > t_hi) lo[e] = 0xFFFFu;
+        low[i][0] = lo[0] | (lo[1] << 16);
+        low[i][1] = lo[2] | (lo[3] << 16);
+      }
+    }
+    __syncthreads();  // the lower bounds have been read by everyone
+#pragma unroll
+    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+      const int c = j0 + i * kChunk + 4 * lane;
+      if (c < j1) {
+        uint32x4 w = lds_words4(stage + c);
+        w[0] = (w[0] & 0xFFFF0000u) | (low[i][0] & 0xFFFFu);
+        w[1] = (w[1] & 0xFFFF0000u) | (low[i][0] >> 16);
+        w[2] = (w[2] & 0xFFFF0000u) | (low[i][1] & 0xFFFFu);
+        w[3] = (w[3] & 0xFFFF0000u) | (low[i][1] >> 16);
+        set_lds_words4(stage + c, w);
+      }
+    }
+    if (tid < kStageFront) stage[tid - kStageFront] = 0xFFFFu;
+    if (tid < 4) stage[((n_sel + 3) & ~3) + tid] = 0xFFFFu;  // (the last group's own words are set above)
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+      const int c = j0 + i * kChunk + 4 * lane;
+      if (c < j1) {
+        const PoolWindow<kThree> pw(stage, c, h, n_sel);
+        uint32_t least[4];
+        pw.template reduce<PoolMinLow>(least);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e < j1 && (pw.mid[e] >> 16) >= least[e]) named |= 1ull << (4 * i + e);
+      }
+    }
+    __syncthreads();  // (the low halves are about to go)
   }
-  // (bucket 0 also holds what lies below kmin)
-  const uint32_t t_lo = sh.sel[0] == 0 ? kzero : kmin + ((uint32_t)sh.sel[0] << shift);  // <= the threshold's key
-  const uint32_t t_hi = kmin + (((uint32_t)sh.sel[1] + 1u) << shift) - 1u;                // >= the threshold's key
-  for (int j = tid; j < n_sel; j += kThreads) {
-    float plo, phi;
-    pooled(j, plo, phi);
-    if (score_key(phi) >= t_lo && score_key(plo) <= t_hi) {
-      const int a = max(0, j - h), b = min(n_sel - 1, j + h);
-      for (int k = a; k <= b; ++k)
-        if (upper_of(stage[k]) >= plo) atomicOr(&need[k >> 5], 1u << (k & 31));
+#pragma unroll
+  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
+    const int c = j0 + i * kChunk + 4 * lane;
+    if (j0 + i * kChunk < j1) {  // uniform over the wavefront
+      // eight lanes' nibbles make one word of the bit map
+      uint32_t bits = (uint32_t)((named >> (4 * i)) & 0xFu) << (4 * (lane & 7));
+      bits |= __shfl_xor(bits, 1);
+      bits |= __shfl_xor(bits, 2);
+      bits |= __shfl_xor(bits, 4);
+      if ((lane & 7) == 0) need[(j0 + i * kChunk) / 32 + (lane >> 3)] = bits;
+    }
+    if (c < j1) {
+      uint32x4 w = lds_words4(stage + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
+      set_lds_words4(stage + c, w);
     }
   }
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kThreads) void select_kernel(BatchParams p) {
-  extern __shared__ uint32_t keys[];
-  __shared__ SelectShared sh;
+template <int WV>
+__device__ __forceinline__ void bound_classify(const ReqDesc& rd, uint32_t* stage, uint32_t* need,
+                                               SelectShared<WV>& sh, uint32_t& key_lo, uint32_t& key_hi) {
+  key_lo = 0u;
+  key_hi = 0xFFFFFFFFu;
+  if (rd.pool_kernel == 7)  // uniform
+    bound_classify_h<true, WV>(rd, stage, need, sh, key_lo, key_hi);
+  else
+    bound_classify_h<false, WV>(rd, stage, need, sh, key_lo, key_hi);
+}
+
+// Heads of up to 32768 tokens whose scores come from a kernel of their own: 16
+// wavefronts, so that a lane's share of the keys is that of a short head.
+static constexpr int kSelectWaves = 16;
+__global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  __shared__ SelectShared<kSelectWaves> sh;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_all[slot]];
-  select_unit<false>(p, rd, lh, keys, sh);
+  uint32_t* stage = lds + kStageFront;
+  const float* raw = p.raw_scores + rd.raw_off + (size_t)lh * rd.seq_len;
+  const int n_sel = rd.method == 1 /* FC_METHOD_SNAPKV */ ? rd.seq_len - rd.window : rd.seq_len;
+  for (int j = threadIdx.x; j < n_sel; j += 64 * kSelectWaves) stage[j] = __float_as_uint(raw[j]);
+  __syncthreads();
+  select_unit<kSelectWaves>(p, rd, lh, stage, sh);
 }
 
 // Streaming requests need no score: the first min(n_sink, budget) tokens and
@@ -1371,16 +1631,17 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
 
 template <int D, int NT>
 __global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
-  extern __shared__ uint32_t keys[];
+  extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
     ScoreShared score;
-    SelectShared select;
+    SelectShared<kWaves> select;
   } sh;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_fused[slot]];
-  float* stage = reinterpret_cast<float*>(keys);
+  uint32_t* words = lds + kStageFront;
+  float* stage = reinterpret_cast<float*>(words);
   // the request's block ids, read once per workgroup (every later use is an LDS read)
   __shared__ int32_t sm_ids[kFusedMaxLen / 16];
   const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
@@ -1400,7 +1661,7 @@ __global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
       knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
-    select_unit<true>(p, rd, lh, keys, sh.select);
+    select_unit<kWaves>(p, rd, lh, words, sh.select);
   }
   __syncthreads();  // the kept list (global memory, this workgroup's own) is complete
   gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off);
@@ -1411,10 +1672,10 @@ __global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
 // fused_unit_kernel.  Dynamic LDS: seq_len words of scores, then one bit per token.
 template <int D, int NT>
 __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams p) {  // 3 wavefronts per SIMD
-  extern __shared__ uint32_t keys[];
+  extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
     ScoreShared score;
-    SelectShared select;
+    SelectShared<kWaves> select;
     BoundShared bound;
   } sh;
   __shared__ BoundKeep keep;
@@ -1422,8 +1683,9 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_fused[slot]];
-  float* stage = reinterpret_cast<float*>(keys);
-  uint32_t* need = keys + ((rd.seq_len + 31) & ~31);
+  uint32_t* words = lds + kStageFront;  // per token: its bounds, then its score
+  float* stage = reinterpret_cast<float*>(words);
+  uint32_t* need = lds + stage_words(rd.seq_len);
   __shared__ int32_t sm_ids[kFusedMaxLen / 16];
   const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
   if (ids_in_lds)
@@ -1434,6 +1696,7 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
     streaming_unit(p, rd, lh);
   } else {
+    uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
     if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
       constexpr int KS = D / 32;
       const int q4 = (threadIdx.x & 63) >> 4;
@@ -1452,18 +1715,14 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
 #pragma unroll
           for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.bound.fin[nt * 16 + q4 * 4 + r];
         __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
-        bound_classify(rd, stage, need, sh.select);
-        __syncthreads();
-        // every token not named keeps its upper bound as its value
-        for (int j = threadIdx.x; j < rd.seq_len - rd.window; j += kThreads)
-          if (!((need[j >> 5] >> (j & 31)) & 1u)) stage[j] = upper_of(keys[j]);
+        bound_classify<kWaves>(rd, words, need, sh.select, key_lo, key_hi);
         snapkv_rescore<D, NT>(p, rd, lh, sm_ids, need, stage, qreg, mrow);
       }
     } else {
       knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
-    select_unit<true>(p, rd, lh, keys, sh.select);
+    select_unit<kWaves>(p, rd, lh, words, sh.select, key_lo, key_hi);
   }
   __syncthreads();  // the kept list (global memory, this workgroup's own) is complete
   gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off);
@@ -1484,7 +1743,7 @@ hipError_t kernels_one_time_setup() {
   // the select kernel may need more than the default 64 KiB of dynamic LDS
   // (the fused kernel never does: kFusedMaxLen * 4 = 32 KiB)
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 32768 * 4);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, stage_words(32768) * 4);
   return e;
 }
 
@@ -1582,8 +1841,8 @@ hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s) {
 
 hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads;
-  const size_t lds = (size_t)max_seq_len * sizeof(uint32_t);
-  select_kernel<<<grid, kThreads, lds, s>>>(p);
+  const size_t lds = (size_t)stage_words(max_seq_len) * sizeof(uint32_t);
+  select_kernel<<<grid, 64 * kSelectWaves, lds, s>>>(p);
   return hipGetLastError();
 }
 
@@ -1614,9 +1873,8 @@ static hipError_t launch_fused_d(const BatchParams& p, bool any_snap, size_t lds
 hipError_t launch_fused(const BatchParams& p, bool any_snap, int max_seq_len, hipStream_t s) {
   if (p.n_fused == 0) return hipSuccess;
   // (with the pruned second pass: one bit per token behind the scores)
-  const size_t lds = p.bounded && any_snap
-                         ? ((size_t)((max_seq_len + 31) & ~31) + (size_t)((max_seq_len + 31) >> 5)) * sizeof(uint32_t)
-                         : (size_t)max_seq_len * sizeof(uint32_t);
+  const size_t lds = (size_t)(stage_words(max_seq_len) +
+                              (p.bounded && any_snap ? need_words(max_seq_len) : 0)) * sizeof(uint32_t);
   if (p.head_dim == 128) return launch_fused_d<128>(p, any_snap, lds, s);
   if (p.head_dim == 64) return launch_fused_d<64>(p, any_snap, lds, s);
   return hipErrorInvalidValue;

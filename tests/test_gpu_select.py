@@ -1,0 +1,39 @@
+"""Selection and classification on the four-tokens-per-lane layout: competing
+token counts at the edges of a lane's four tokens, of a wavefront's 256-token
+chunk and of its segment, crossed with pooling widths that stay inside, reach
+and cross the neighbouring lanes' tokens.  With scores the kept list must be
+the exact top budget of the GPU's own scores; without, the oracle's."""
+
+import numpy as np
+import pytest
+
+from oracle import fastcache_oracle as fo
+from test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("width", [1, 3, 5, 7, 9, 11, 17, 63])
+@pytest.mark.parametrize("scores", [True, False])
+def test_token_counts_at_layout_edges(width, scores):
+    from parity_util import SideBySide
+    W = 16
+    # competing tokens: 1..5, around 256 (one chunk), 1024 (a segment per wavefront), 2048
+    n_sel = [1, 2, 3, 4, 5, 31, 63, 255, 256, 257, 511, 513, 1023, 1024, 1025, 1027, 2047, 2049]
+    lens = [n + W for n in n_sel]
+    budgets = [W + max(1, n // 3) for n in n_sel]
+    s = SideBySide(_custom(lens, budgets, [fo.METHOD_SNAPKV] * len(lens), W=W, d=64, n_heads=2))
+    try:
+        s.compress_and_compare(scores=scores, pool_kernel=width)
+    finally:
+        s.close()
+
+
+def test_key_norm_counts_at_layout_edges():
+    from parity_util import SideBySide
+    lens = [1, 3, 4, 5, 255, 256, 257, 1023, 1025, 2048, 8191, 8192, 8193]
+    s = SideBySide(_custom(lens, [max(1, n // 2) for n in lens], [fo.METHOD_KNORM] * len(lens), d=64, n_heads=2))
+    try:
+        s.compress_and_compare()
+    finally:
+        s.close()
