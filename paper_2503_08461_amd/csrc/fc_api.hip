@@ -551,7 +551,10 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     dev_meta = reinterpret_cast<char*>(p->fixed_scratch + kNoAllocMetaOff);
   } else {
     // (growth waits for the device and frees: it happens before anything is queued)
-    if (!dev_kept_out && (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK) return rc;
+    // (the fused kernels keep their lists in LDS)
+    if (!dev_kept_out && !plan.lists[LIST_ALL].empty() &&
+        (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK)
+      return rc;
     if ((rc = grow(&p->ids, &p->ids_cap, n_ids)) != FC_OK) return rc;
     if ((rc = grow(&p->raw_scores, &p->raw_cap, plan.raw_floats)) != FC_OK) return rc;
     if ((rc = grow_meta(p, meta_bytes)) != FC_OK) return rc;
@@ -603,6 +606,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   bp.raw_scores = p->raw_scores;
   bp.scores_out = dev_scores_out;
   bp.kept = kept_buf;
+  bp.kept_out = dev_kept_out;
   bp.error_flag = p->error_flag;
   bp.owner = p->debug_checks ? p->owner : nullptr;
   bp.bounded = pruned_call ? 1 : 0;

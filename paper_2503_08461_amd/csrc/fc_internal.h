@@ -72,7 +72,8 @@ struct BatchParams {
   float scale_log2e;           // scale * log2(e)
   float* raw_scores;           // un-pooled scores of the units that take the separate kernels
   float* scores_out;           // nullable
-  int32_t* kept;               // kept indices, packed
+  int32_t* kept;               // kept indices, packed, of the units that take the separate kernels
+  int32_t* kept_out;           // nullable: the caller's copy of them, written by the fused kernels
   int32_t* error_flag;         // set if a kernel finds something wrong (an ownership check that fails)
   int32_t bounded;             // 1: the fused kernel prunes the second pass of its SnapKV units
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,

@@ -657,14 +657,16 @@ struct SelectShared {
 };
 
 // Selects the kept tokens of one (request, layer, head) and writes them, in
-// ascending order, to the kept list.  stage[0 .. n_sel): the un-pooled scores as
+// ascending order, to `kept` (nullable, global memory) and, over the words of
+// stage[] (the keys are in registers by then), as 16-bit indices for the copy
+// that follows in the same workgroup.  stage[0 .. n_sel): the un-pooled scores as
 // floats, written by this workgroup and made visible by a barrier.  hint_lo,
 // hint_hi: keys that are known to enclose the threshold (0, ~0: nothing is
 // known).  All threads of the workgroup call.
 template <bool kThree, int WV>
 __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              uint32_t* stage, SelectShared<WV>& sh, uint32_t hint_lo,
-                                              uint32_t hint_hi) {
+                                              uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
+                                              uint32_t hint_lo, uint32_t hint_hi) {
   int* hist = sh.hist;
   uint32_t* cand = sh.cand;
   int* sel = sh.sel;
@@ -677,7 +679,11 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
   const int n_sel = snap ? L - rd.window : L;  // tokens that compete
   const int k_sel = snap ? B - rd.window : B;  // how many of them are kept
   float* out = p.scores_out ? p.scores_out + rd.score_off + (size_t)lh * L : nullptr;
-  int32_t* kept = p.kept + rd.kept_off + (size_t)lh * B;
+  uint16_t* kept16 = reinterpret_cast<uint16_t*>(stage);  // (budget <= length: half of the words)
+  auto keep_token = [&](int t, int j) {
+    kept16[t] = (uint16_t)j;
+    if (kept) kept[t] = j;
+  };
   const int seg = segment_tokens<WV>(n_sel);
   const int j0 = wave * seg;
   const int j1 = min(n_sel, j0 + seg);
@@ -732,10 +738,6 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     }
     for (int j = tid; j < n_sel; j += (64 * WV)) out[j] = __uint_as_float(stage[j]);
   }
-  if (snap) {
-    for (int j = tid; j < rd.window; j += (64 * WV)) kept[k_sel + j] = n_sel + j;  // forced window
-  }
-  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
@@ -772,6 +774,10 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
   }
   // the k_sel-th largest key lies in the hinted range: search only there
   const bool narrowed = n_above < k_sel && n_reach >= k_sel;  // uniform
+  // (every read of stage[] lies before the barrier above)
+  if (snap)
+    for (int j = tid; j < rd.window; j += (64 * WV)) keep_token(k_sel + j, n_sel + j);  // forced window
+  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
   if (narrowed) {
     kmin = max(kmin, hint_lo);
     kmax = min(kmax, hint_hi);
@@ -900,18 +906,18 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (keep[e]) kept[at++] = c + e;
+      if (keep[e]) keep_token(at++, c + e);
   }
 }
 
 template <int WV>
 __device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            uint32_t* stage, SelectShared<WV>& sh, uint32_t hint_lo = 0u,
-                                            uint32_t hint_hi = 0xFFFFFFFFu) {
+                                            uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
+                                            uint32_t hint_lo = 0u, uint32_t hint_hi = 0xFFFFFFFFu) {
   if (rd.pool_kernel == 7)  // uniform
-    select_unit_h<true, WV>(p, rd, lh, stage, sh, hint_lo, hint_hi);
+    select_unit_h<true, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
   else
-    select_unit_h<false, WV>(p, rd, lh, stage, sh, hint_lo, hint_hi);
+    select_unit_h<false, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
 }
 
 // ---------------------------------------------------------------------------
@@ -1521,23 +1527,26 @@ __global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p
   const int n_sel = rd.method == 1 /* FC_METHOD_SNAPKV */ ? rd.seq_len - rd.window : rd.seq_len;
   for (int j = threadIdx.x; j < n_sel; j += 64 * kSelectWaves) stage[j] = __float_as_uint(raw[j]);
   __syncthreads();
-  select_unit<kSelectWaves>(p, rd, lh, stage, sh);
+  select_unit<kSelectWaves>(p, rd, lh, stage, p.kept + rd.kept_off + (size_t)lh * rd.budget, sh);
 }
 
 // Streaming requests need no score: the first min(n_sink, budget) tokens and
 // the most recent budget - sinks tokens are kept.
-__device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDesc& rd, int lh) {
+__device__ __forceinline__ int streaming_token(const ReqDesc& rd, int n_sink, int t) {
+  return t < min(n_sink, rd.budget) ? t : rd.seq_len - rd.budget + t;
+}
+
+__device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDesc& rd, int lh,
+                                               int32_t* kept) {
   const int L = rd.seq_len;
   const int B = rd.budget;
-  const int sinks = min(p.n_sink, B);
-  const int first_recent = L - (B - sinks);
-  int32_t* kept = p.kept + rd.kept_off + (size_t)lh * B;
-  for (int t = threadIdx.x; t < B; t += kThreads)
-    kept[t] = (t < sinks) ? t : first_recent + (t - sinks);
+  if (kept)
+    for (int t = threadIdx.x; t < B; t += kThreads) kept[t] = streaming_token(rd, p.n_sink, t);
   if (p.scores_out) {
+    const int sinks = min(p.n_sink, B);
     float* out = p.scores_out + rd.score_off + (size_t)lh * L;
     for (int j = threadIdx.x; j < L; j += kThreads)
-      out[j] = (j < sinks || j >= first_recent) ? INFINITY : 0.f;
+      out[j] = (j < sinks || j >= L - (B - sinks)) ? INFINITY : 0.f;
   }
 }
 
@@ -1548,11 +1557,15 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 // One workgroup per (request, layer, head); a wavefront fills one new block
 // (16 output slots) at a time for K and V.  D/8 lanes move one row with
 // 128-bit accesses, so a wavefront instruction moves 64/(D/8) rows; the
-// destination chunk is contiguous.
+// destination chunk is contiguous.  kept_at(t) is the token that goes to slot t.
+//
+// Bound by HBM when the chip is full and by the latency of one block's chain
+// (kept index, block id, row) when it is not; the rows of a wavefront's next
+// block are therefore requested before those of this one are stored.
 
-template <int D>
+template <int D, typename KeptAt>
 __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            const int32_t* old_ids) {
+                                            const int32_t* old_ids, KeptAt kept_at) {
   constexpr int LPR = D / 8;
   constexpr int RPI = 64 / LPR;
   constexpr int NI = 16 / RPI;
@@ -1563,46 +1576,60 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // destination blocks: freshly popped ones, or the request's own first blocks
   const int32_t* new_ids = p.in_place ? old_ids : p.new_ids + rd.new_off;
-  const int32_t* kept = p.kept + rd.kept_off + (size_t)lh * B;
   const size_t chunk = (size_t)16 * D;               // one (block, kv, head)
   const size_t v_off = (size_t)p.n_heads * chunk;    // K chunk -> V chunk of a block
   const size_t blk_stride = 2 * v_off;
   _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * chunk +
                    (lane % LPR) * 8;
   const int row_in_instr = lane / LPR;
-  // In place, output t overwrites slot t while kept[t] >= t: a chunk of
-  // kWaves*16 outputs only reads slots at or after its own start, so reading
-  // the whole chunk, a barrier, then writing it never destroys a row that is
-  // still needed (later chunks read strictly later slots).
-  for (int c0 = 0; c0 < rd.n_new; c0 += kWaves) {
-    const int nbk = c0 + wave;
-    half8 kk[NI], vv[NI];
-    bool ok[NI];
+  auto load = [&](int nbk, half8 (&kk)[NI], half8 (&vv)[NI]) {
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+      // (slots past the budget load the last kept row again and drop it)
+      const int t = min(nbk * 16 + k * RPI + row_in_instr, B - 1);
+      const int idx = min(max(kept_at(t), 0), rd.seq_len - 1);
+      const int sblk = clamp_block(old_ids[idx >> 4], p.n_blocks);
+      const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
+      kk[k] = load_half8_nt(src);
+      vv[k] = load_half8_nt(src + v_off);
+    }
+  };
+  auto store = [&](int nbk, const half8 (&kk)[NI], const half8 (&vv)[NI]) {
+    const int dblk = clamp_block(new_ids[nbk], p.n_blocks);
+    _Float16* dst = base + (size_t)dblk * blk_stride;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       const int row = k * RPI + row_in_instr;
-      const int t = nbk * 16 + row;
-      ok[k] = nbk < rd.n_new && t < B;
-      if (ok[k]) {
-        const int idx = min(max(kept[t], 0), rd.seq_len - 1);
-        const int sblk = clamp_block(old_ids[idx >> 4], p.n_blocks);
-        const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
-        kk[k] = load_half8_nt(src);
-        vv[k] = load_half8_nt(src + v_off);
+      if (nbk * 16 + row < B) {
+        store_half8_nt(dst + (size_t)row * D, kk[k]);
+        store_half8_nt(dst + (size_t)row * D + v_off, vv[k]);
       }
     }
-    if (p.in_place) __syncthreads();  // uniform: c0 and in_place are the same for all threads
-    if (nbk < rd.n_new) {
-      const int dblk = clamp_block(new_ids[nbk], p.n_blocks);
-      _Float16* dst = base + (size_t)dblk * blk_stride;
+  };
+  half8 kc[NI], vc[NI];
+  if (p.in_place) {
+    // Output t overwrites slot t while kept[t] >= t: a chunk of kWaves*16
+    // outputs only reads slots at or after its own start, so reading the whole
+    // chunk, a barrier, then writing it never destroys a row that is still
+    // needed (later chunks read strictly later slots).
+    for (int c0 = 0; c0 < rd.n_new; c0 += kWaves) {
+      const int nbk = c0 + wave;
+      if (nbk < rd.n_new) load(nbk, kc, vc);
+      __syncthreads();  // uniform: c0 and in_place are the same for all threads
+      if (nbk < rd.n_new) store(nbk, kc, vc);
+    }
+    return;
+  }
+  half8 kn[NI], vn[NI];
+  int nbk = wave;
+  if (nbk < rd.n_new) load(nbk, kc, vc);
+  for (; nbk < rd.n_new; nbk += kWaves) {
+    if (nbk + kWaves < rd.n_new) load(nbk + kWaves, kn, vn);
+    store(nbk, kc, vc);
 #pragma unroll
-      for (int k = 0; k < NI; ++k) {
-        if (ok[k]) {
-          const int row = k * RPI + row_in_instr;
-          store_half8_nt(dst + (size_t)row * D, kk[k]);
-          store_half8_nt(dst + (size_t)row * D + v_off, vv[k]);
-        }
-      }
+    for (int k = 0; k < NI; ++k) {
+      kc[k] = kn[k];
+      vc[k] = vn[k];
     }
   }
 }
@@ -1613,7 +1640,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_all[slot]];
-  gather_unit<D>(p, rd, lh, p.old_ids + rd.old_off);
+  const int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
+  gather_unit<D>(p, rd, lh, p.old_ids + rd.old_off, [&](int t) { return kept[t]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -1644,13 +1672,17 @@ __global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
   float* stage = reinterpret_cast<float*>(words);
   // the request's block ids, read once per workgroup (every later use is an LDS read)
   __shared__ int32_t sm_ids[kFusedMaxLen / 16];
+  int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
   const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
   if (ids_in_lds)
     for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
       sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
-    streaming_unit(p, rd, lh);
+    streaming_unit(p, rd, lh, kept);
+    gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
+                   [&](int t) { return streaming_token(rd, p.n_sink, t); });
+    return;
   } else {
     bool snap = false;
     if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
@@ -1661,10 +1693,11 @@ __global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
       knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
-    select_unit<kWaves>(p, rd, lh, words, sh.select);
+    select_unit<kWaves>(p, rd, lh, words, kept, sh.select);
   }
-  __syncthreads();  // the kept list (global memory, this workgroup's own) is complete
-  gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off);
+  __syncthreads();  // the kept list is complete
+  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
+  gather_unit<D>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
 }
 
 // The fused kernel with the pruned second pass for its SnapKV units (see
@@ -1687,6 +1720,7 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
   float* stage = reinterpret_cast<float*>(words);
   uint32_t* need = lds + stage_words(rd.seq_len);
   __shared__ int32_t sm_ids[kFusedMaxLen / 16];
+  int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
   const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
   if (ids_in_lds)
     for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
@@ -1694,7 +1728,10 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
   if (threadIdx.x == 0) keep.bad = 0;
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
-    streaming_unit(p, rd, lh);
+    streaming_unit(p, rd, lh, kept);
+    gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
+                   [&](int t) { return streaming_token(rd, p.n_sink, t); });
+    return;
   } else {
     uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
     if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
@@ -1722,10 +1759,11 @@ __global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams 
       knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
-    select_unit<kWaves>(p, rd, lh, words, sh.select, key_lo, key_hi);
+    select_unit<kWaves>(p, rd, lh, words, kept, sh.select, key_lo, key_hi);
   }
-  __syncthreads();  // the kept list (global memory, this workgroup's own) is complete
-  gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off);
+  __syncthreads();  // the kept list is complete
+  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
+  gather_unit<D>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
 }
 
 // a fill kernel for small device arrays (flags, verdict words): calls may be
