@@ -1052,7 +1052,8 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
       float zr = zacc[nt];
       zr += __shfl_xor(zr, 16);
       zr += __shfl_xor(zr, 32);
-      if (q4 == 0) bs.pub[buf][wave][nt * 16 + c16] = zr > 0.f ? ref[nt] + log2f(zr) : -INFINITY;
+      // (a sum that is not a number stays one: see merged)
+      if (q4 == 0) bs.pub[buf][wave][nt * 16 + c16] = zr == 0.f ? -INFINITY : ref[nt] + log2f(zr);
     }
   };
   // log2 of the workgroup's row sum from the published shares; own = this wavefront's share
@@ -1067,11 +1068,13 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     own = l[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) own = wave == w ? l[w] : own;
-    if (mx == -INFINITY) return 0.f;  // nothing visible yet: any finite reference will do
+    // Numerators that overflowed make a share infinite and the sum below not a
+    // number; from there on that row's references, sums and log-sum-exp are none
+    // either, which is how the head is found to need the two-pass code.
     float zz = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) zz += __builtin_amdgcn_exp2f(l[w] - mx);
-    return mx + log2f(zz);
+    for (int w = 0; w < kWaves; ++w) zz += l[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[w] - mx);
+    return zz == 0.f ? 0.f : mx + log2f(zz);  // 0: nothing visible yet, any finite reference will do
   };
 
   const int T = (nb + kWaves - 1) / kWaves;  // steps; every wavefront walks all of them
@@ -1090,7 +1093,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
         const int row = nt * 16 + c16;
         float own;
         const float nr = merged(buf, row, own);
-        zacc[nt] = (q4 == 0 && own > -INFINITY) ? __builtin_amdgcn_exp2f(own - nr) : 0.f;
+        zacc[nt] = (q4 == 0 && own != -INFINITY) ? __builtin_amdgcn_exp2f(own - nr) : 0.f;
         ref[nt] = nr;
         if (wave == 0 && q4 == 0) bs.ref[epoch][row] = nr;
       }

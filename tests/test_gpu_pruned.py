@@ -116,6 +116,31 @@ def test_logits_that_outrun_the_reference_fall_back_to_two_passes():
     _run_pruned(wl, sbs_kw={"kv_host": kv, "q_host": q})
 
 
+@pytest.mark.parametrize("fillers", [0, 300])
+def test_rows_that_overflow_do_not_hide_behind_rows_that_do_not(fillers):
+    """The late large key is seen by every other window row only.  Those rows
+    overflow in the middle of the head and give the other tokens nothing; the
+    rest of the rows, whose references stay fine, decide the selection.  (With
+    300 short key-norm requests next to them the heads run in small workgroups.)"""
+    from parity_util import SideBySide
+    wl = _custom([3000, 2500] + [9] * fillers, [600, 500] + [4] * fillers,
+                 [fo.METHOD_SNAPKV] * 2 + [fo.METHOD_KNORM] * fillers, W=32, d=128, n_heads=2)
+    kv = synth.fill_pool_host(wl)
+    s0 = SideBySide(wl)     # only to learn where the tokens live
+    try:
+        bt = s0.bt_host.copy()
+    finally:
+        s0.close()
+    for r, tok in ((0, 700), (1, 600)):
+        blk, slot = bt[r, tok // 16], tok % 16
+        kv[:, blk, 0, :, slot, :64] = np.float16(1200.0)
+        kv[:, blk, 0, :, slot, 64:] = np.float16(0.0)
+    q = synth.fill_q_window_host(wl)
+    q[..., 0::2, :64] = np.abs(q[..., 0::2, :64]) + np.float16(1.0)
+    q[..., 1::2, :64] = np.float16(0.0)
+    _run_pruned(wl, sbs_kw={"kv_host": kv, "q_host": q})
+
+
 def _keys_by_token(wl, make_key):
     """The synthetic pool with the K row of every (request, token) replaced by
     make_key(r, tok) -> fp16 [head_dim] (same for all layers and heads)."""
