@@ -2,25 +2,26 @@
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libfastcache.so")
 
-SOURCES = ["fc_api.hip", "fc_kernels.hip", "fc_mlp.hip", "fc_decode.hip", "fc_sched.cpp", "fc_plan.cpp"]
+# (longest compilations first)
+SOURCES = ["fc_fused_wide_128.hip", "fc_fused_narrow_128.hip", "fc_fused_wide_64.hip", "fc_fused_narrow_64.hip",
+           "fc_mlp.hip", "fc_kernels.hip", "fc_decode.hip", "fc_api.hip", "fc_sched.cpp", "fc_plan.cpp"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # no packed-fp32 instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 
 
-def build_library(verbose=False):
-    """Compiles every HIP source of the package into LIB_PATH (always rebuilds)."""
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -31,6 +32,19 @@ def build_library(verbose=False):
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out, flush=True)
+
+
+def build_library(verbose=False):
+    """Compiles every HIP source of the package, side by side, and links them into LIB_PATH
+    (always rebuilds)."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    jobs = min(8, os.cpu_count() or 1, int(os.environ.get("MAX_JOBS") or 8))
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(jobs) as pool:
+        objs = [os.path.join(tmp, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+        for done in [pool.submit(_run, [hipcc] + HIPCC_FLAGS + ["-c", os.path.join(CSRC, s), "-o", o], verbose)
+                     for s, o in zip(SOURCES, objs)]:
+            done.result()
+        _run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared"] + objs + ["-o", LIB_PATH], verbose)
     return LIB_PATH
 
 

@@ -151,6 +151,7 @@ struct fc_pool {
   hipEvent_t meta_event = nullptr;
   bool meta_pending = false;
 
+  int n_cu = 0;                   // compute units of the pool's device
   int32_t* error_flag = nullptr;  // device, one int, zero unless a kernel found something wrong
   int score_mode = FC_SCORE_AUTO;
   bool score_pruning = true;       // the fused kernel prunes the second pass of SnapKV units
@@ -227,11 +228,15 @@ int fc_pool_create(fc_pool** out, void* kv_base, size_t kv_bytes, int n_blocks, 
                 need);
   FC_HIP(kernels_one_time_setup());
   FC_HIP(mlp_one_time_setup());
+  int dev = 0, n_cu = 0;
+  FC_HIP(hipGetDevice(&dev));
+  FC_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   // this device's copy of the allocation-free entry point's scratch array
   unsigned char* fixed = nullptr;
   if (int rc = fixed_scratch_of_current_device(&fixed)) return rc;
   fc_pool* p = new fc_pool();
   p->fixed_scratch = fixed;
+  p->n_cu = std::max(n_cu, 1);
   p->kv = static_cast<_Float16*>(kv_base);
   p->kv_bytes = kv_bytes;
   p->n_blocks = n_blocks;
@@ -521,10 +526,24 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   const int n_comp = (int)plan.descs.size();
   if (n_comp == 0) return FC_OK;
 
+  // ---- launches: the fused kernels, or (FC_SCORE_TWO_PASS) the separate ones ---
+  const std::vector<FusedLaunch> fused = plan_fused_launches(pv, plan, p->n_cu);
+  const bool separate = pv.score_mode != FC_SCORE_AUTO && !plan.lists[LIST_ALL].empty();
+
   // ---- scratch: kept lists, saved ids, un-pooled scores, descriptors -----------
   const size_t desc_bytes = round_up((size_t)n_comp * sizeof(ReqDesc), 16);
-  const size_t order_bytes = round_up((size_t)n_comp * sizeof(int32_t), 16);
-  const size_t meta_bytes = desc_bytes + N_LISTS * order_bytes;
+  std::vector<int32_t> lists;  // work lists, one after the other
+  auto add_list = [&](const std::vector<int32_t>& list) {
+    const size_t at = lists.size();
+    lists.insert(lists.end(), list.begin(), list.end());
+    return at;
+  };
+  size_t list_at[N_LISTS] = {};
+  if (separate)
+    for (int i = LIST_SNAP; i < N_LISTS; ++i) list_at[i] = add_list(plan.lists[i]);
+  std::vector<size_t> fused_at;
+  for (const FusedLaunch& l : fused) fused_at.push_back(add_list(l.units));
+  const size_t meta_bytes = desc_bytes + round_up(lists.size() * sizeof(int32_t), 16);
   const size_t n_ids = (size_t)plan.total_old + plan.total_new;
   int32_t* kept_buf = dev_kept_out;
   int32_t* ids_buf = nullptr;
@@ -552,11 +571,11 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   } else {
     // (growth waits for the device and frees: it happens before anything is queued)
     // (the fused kernels keep their lists in LDS)
-    if (!dev_kept_out && !plan.lists[LIST_ALL].empty() &&
+    if (!dev_kept_out && separate &&
         (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK)
       return rc;
     if ((rc = grow(&p->ids, &p->ids_cap, n_ids)) != FC_OK) return rc;
-    if ((rc = grow(&p->raw_scores, &p->raw_cap, plan.raw_floats)) != FC_OK) return rc;
+    if (separate && (rc = grow(&p->raw_scores, &p->raw_cap, plan.raw_floats)) != FC_OK) return rc;
     if ((rc = grow_meta(p, meta_bytes)) != FC_OK) return rc;
     if (!kept_buf) kept_buf = p->kept;
     ids_buf = p->ids;
@@ -564,14 +583,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   }
   std::vector<char> image(meta_bytes, 0);
   memcpy(image.data(), plan.descs.data(), (size_t)n_comp * sizeof(ReqDesc));
-  size_t list_off[N_LISTS];
-  int n_list[N_LISTS];
-  for (int i = 0; i < N_LISTS; ++i) {
-    list_off[i] = desc_bytes + (size_t)i * order_bytes;
-    n_list[i] = (int)plan.lists[i].size();
-    if (n_list[i] > 0)
-      memcpy(image.data() + list_off[i], plan.lists[i].data(), (size_t)n_list[i] * sizeof(int32_t));
-  }
+  memcpy(image.data() + desc_bytes, lists.data(), lists.size() * sizeof(int32_t));
   if ((rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK) return rc;
 
   BatchParams bp = {};
@@ -585,12 +597,13 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   bp.total_new = plan.total_new;
   bp.total_old = plan.total_old;
   bp.descs = reinterpret_cast<const ReqDesc*>(dev_meta);
-  auto dev_list = [&](int i) { return reinterpret_cast<const int32_t*>(dev_meta + list_off[i]); };
-  bp.order_all = dev_list(LIST_ALL);
-  bp.order_knorm = dev_list(LIST_KNORM);
+  const int32_t* dev_lists = reinterpret_cast<const int32_t*>(dev_meta + desc_bytes);
+  auto n_list = [&](int i) { return separate ? (int)plan.lists[i].size() : 0; };
+  bp.order_all = dev_lists + list_at[LIST_ALL];
+  bp.order_knorm = dev_lists + list_at[LIST_KNORM];
   bp.n_comp = n_comp;  // plan_alloc / reclaim walk every descriptor
-  bp.n_knorm = n_list[LIST_KNORM];
-  bp.n_unfused = n_list[LIST_ALL];
+  bp.n_knorm = n_list(LIST_KNORM);
+  bp.n_unfused = n_list(LIST_ALL);
   // per launch: order_snap / n_snap, order_fused / n_fused, window (of the class)
   bp.block_tables = dev_block_tables;
   bp.max_blocks = max_blocks_per_req;
@@ -622,11 +635,8 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   }
 
   // ---- the stage ------------------------------------------------------------
-  int ns = 0, n_fused = 0;
-  for (int c = 0; c < kPlanClasses; ++c) {
-    ns += n_list[LIST_SNAP + c];
-    n_fused += n_list[LIST_FUSED + c];
-  }
+  int ns = 0;
+  for (int c = 0; c < kPlanClasses; ++c) ns += n_list(LIST_SNAP + c);
   const int ring = p->prof_calls % kProfRing;
   if (p->profiling) {
     for (int k = 0; k < K_COUNT; ++k) p->timed[ring][k] = false;
@@ -647,10 +657,10 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   FC_HIP_STAGE(p, run(K_SNAPKV_SCORE, ns > 0, [&] {
     hipError_t e = hipSuccess;
     for (int c = 1; c < kPlanClasses && e == hipSuccess; ++c) {
-      if (n_list[LIST_SNAP + c] == 0) continue;
+      if (n_list(LIST_SNAP + c) == 0) continue;
       BatchParams bc = bp;
-      bc.order_snap = dev_list(LIST_SNAP + c);
-      bc.n_snap = n_list[LIST_SNAP + c];
+      bc.order_snap = dev_lists + list_at[LIST_SNAP + c];
+      bc.n_snap = n_list(LIST_SNAP + c);
       bc.window = 16 * c;
       e = launch_snapkv_score(bc, stream);
     }
@@ -660,15 +670,15 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   FC_HIP_STAGE(p, run(K_SELECT, bp.n_unfused > 0,
                       [&] { return launch_select(bp, plan.max_len[LIST_ALL], stream); }));
   FC_HIP_STAGE(p, run(K_GATHER, bp.n_unfused > 0, [&] { return launch_gather(bp, stream); }));
-  FC_HIP_STAGE(p, run(K_FUSED, n_fused > 0, [&] {
+  FC_HIP_STAGE(p, run(K_FUSED, !fused.empty(), [&] {
     hipError_t e = hipSuccess;
-    for (int c = 0; c < kPlanClasses && e == hipSuccess; ++c) {
-      if (n_list[LIST_FUSED + c] == 0) continue;
+    for (size_t i = 0; i < fused.size() && e == hipSuccess; ++i) {
+      const FusedLaunch& l = fused[i];
       BatchParams bc = bp;
-      bc.order_fused = dev_list(LIST_FUSED + c);
-      bc.n_fused = n_list[LIST_FUSED + c];
-      bc.window = 16 * c;
-      e = launch_fused(bc, c > 0, plan.max_len[LIST_FUSED + c], stream);
+      bc.order_fused = dev_lists + fused_at[i];
+      bc.n_fused = (int)l.units.size();
+      bc.window = 16 * l.query_tiles;
+      e = launch_fused(bc, l.query_tiles > 0, l.max_len, l.max_blocks, l.wide, stream);
     }
     return e;
   }));
@@ -880,12 +890,7 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
   mp.jobs = reinterpret_cast<const MlpJob*>(p->dev_meta + desc_bytes);
   mp.n_jobs = (int)plan.jobs.size();
   mp.n_tiles = (int)plan.n_tiles;
-  {
-    int dev = 0, cus = 0;
-    FC_HIP(hipGetDevice(&dev));
-    FC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    mp.max_grid = std::max(cus, 1) * mlp_workgroups_per_cu();
-  }
+  mp.max_grid = p->n_cu * mlp_workgroups_per_cu();
   mp.k = p->mlp_k;
   mp.hidden = p->mlp_hidden;
   mp.activation = p->mlp_activation;

@@ -75,6 +75,7 @@ struct BatchParams {
   int32_t* kept;               // kept indices, packed, of the units that take the separate kernels
   int32_t* kept_out;           // nullable: the caller's copy of them, written by the fused kernels
   int32_t* error_flag;         // set if a kernel finds something wrong (an ownership check that fails)
+  int32_t ids_at, ids_room;    // fused kernels: where the block ids lie in LDS (words), room for how many
   int32_t bounded;             // 1: the fused kernel prunes the second pass of its SnapKV units
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,
                                // 2 being released; NULL when the checks are off
@@ -122,10 +123,21 @@ hipError_t launch_zero_ints(int32_t* p, int n, hipStream_t s);
 hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s);
 hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s);
 hipError_t launch_gather(const BatchParams& p, hipStream_t s);
-// score -> select -> gather of every unit of order_fused in one launch; needs
-// max_seq_len <= kFusedMaxLen; any_snap: the list holds a SnapKV request
-hipError_t launch_fused(const BatchParams& p, bool any_snap, int max_seq_len, hipStream_t s);
+// score -> select -> gather of every unit of order_fused in one launch.
+// max_seq_len: longest head that is scored, at most kFusedMaxLen (kFusedWideMaxLen
+// with wide workgroups); max_blocks: most blocks of any of the units; any_snap:
+// the list holds a SnapKV request
+hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_blocks, bool wide,
+                        hipStream_t s);
+// (per head size and workgroup shape; lds: dynamic LDS bytes)
+hipError_t launch_fused_narrow_64(const BatchParams& p, int query_tiles, size_t lds, hipStream_t s);
+hipError_t launch_fused_narrow_128(const BatchParams& p, int query_tiles, size_t lds, hipStream_t s);
+hipError_t launch_fused_wide_64(const BatchParams& p, int query_tiles, size_t lds, hipStream_t s);
+hipError_t launch_fused_wide_128(const BatchParams& p, int query_tiles, size_t lds, hipStream_t s);
+hipError_t fused_wide_setup_64();
+hipError_t fused_wide_setup_128();
 static constexpr int kFusedMaxLen = 8192;
+static constexpr int kFusedWideMaxLen = 32768;
 hipError_t launch_reclaim(const BatchParams& p, hipStream_t s);
 hipError_t launch_meta_upload(const MetaChunk& c, char* dst, int n_bytes, hipStream_t s);
 hipError_t kernels_one_time_setup();

@@ -6,9 +6,7 @@
 // so one (layer, block, kv, head) chunk is 16*d contiguous halves (4 KiB at
 // d = 128) and one token row is d contiguous halves.
 
-#include "fc_device.h"
-
-#include <float.h>
+#include "fc_unit.h"
 
 namespace fc {
 
@@ -150,239 +148,12 @@ __global__ __launch_bounds__(kThreads) void reclaim_kernel(BatchParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// SnapKV-style observation-window score
+// separate kernels (FC_SCORE_TWO_PASS, fc_window_lse): scores through HBM
 // ---------------------------------------------------------------------------
-//
-// One workgroup per (request, layer, head).  A wavefront takes pool blocks
-// (16 tokens) round-robin and feeds them to v_mfma_f32_16x16x32_f16 straight
-// from global memory: lane l holds 8 consecutive channels
-// [32*ks + 8*(l/16), +8) of token l%16, which is both the A-operand layout
-// (rows = tokens) and the B-operand layout (columns = tokens) of that
-// instruction, and 4 lanes cover 64 contiguous bytes of a token row.
-//
-// Pass 1 (A = keys, B = queries): the 16x16 result has the window query on the
-// lane (l%16) and 4 tokens in the lane's registers, so every lane keeps an
-// online (max, sum-of-exp) pair for its query with no cross-lane traffic.
-// Pass 2 (A = queries, B = keys): the result has the token on the lane and 4
-// queries in registers, so the sum over window queries is an in-lane add plus
-// two cross-lane adds.  Softmax uses exp2 with scale*log2(e) folded in.
-//
-// The un-pooled column sums of the prefix are written to raw_scores; pooling
-// and the forced window are applied by the select kernel.
-
-// Epochs of the bound-keeping first pass: wavefront w takes blocks w, w + kWaves,
-// ...; its t-th block belongs to epoch 0 (t = 0), 1 (t = 1), 2 (t = 2, 3) and
-// then to 2 + t / 4: the references are renewed before t = 1, 2 and every
-// multiple of 4, by all wavefronts together.
-static constexpr int kBoundSeg = 4;
-static constexpr int kBoundMinLen = 512;  // shorter heads take the two passes
-static constexpr int kBoundMaxEpochs = 3 + (kFusedMaxLen / 16 / kWaves + kBoundSeg - 1) / kBoundSeg;
-__host__ __device__ constexpr int bound_epoch_of_step(int t) {
-  return t < 2 ? t : (t < kBoundSeg ? 2 : 2 + t / kBoundSeg);
-}
-__host__ __device__ constexpr bool bound_renews_before(int t) {
-  return t == 1 || t == 2 || (t >= kBoundSeg && t % kBoundSeg == 0);
-}
-
-struct ScoreShared {
-  float m[kWaves][4][64];
-  float z[kWaves][4][64];
-  float fin[64];
-};
-
-// Scores one (request, layer, head); store(j, a_j) receives the un-pooled
-// column sum of every prefix token j.  All threads of the workgroup call.
-// `old_ids` are the request's pre-compression block ids (global or LDS copy).
-// The window queries of a (request, layer, head) in MFMA operand layout (rows
-// past the window are zero), resident in registers for every pass over K.
-template <int D, int NT>
-__device__ __forceinline__ void load_window_queries(const BatchParams& p, const ReqDesc& rd, int lh,
-                                                    half8 (&qreg)[NT][D / 32]) {
-  constexpr int KS = D / 32;
-  const int lane = threadIdx.x & 63;
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-  const int W = rd.window;
-  const _Float16* qbase = p.q_window + rd.q_off + (size_t)lh * W * D;
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int row = nt * 16 + c16;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      half8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-      qreg[nt][ks] = (row < W) ? load_half8(qbase + (size_t)row * D + ks * 32 + q4 * 8) : z;
-    }
-  }
-}
-
-template <int D, int NT, typename Store>
-__device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              const int32_t* old_ids, ScoreShared& sh,
-                                              half8 (&qreg)[NT][D / 32], Store store) {
-  constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int L = rd.seq_len;
-  const int W = rd.window;  // <= 16 NT; the rows past it are padding
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                          (size_t)head * 16 * D + (size_t)c16 * D + q4 * 8;
-  const float c = p.scale_log2e;
-  const int nb = (L + 15) >> 4;
-  const int n_unmasked = (L - W) >> 4;  // blocks that lie wholly before the window
-
-  // last use of a block (second pass)
-  auto load_block_nt = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
-  };
-  auto load_block = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8(kp + ks * 32);
-  };
-
-  // log2 of every row's soft-max denominator goes to sh.fin: handed in by the
-  // caller (natural log, from its attention kernel), or pass 1 below
-  const size_t lse_off = (size_t)(rd.q_off / D) + (size_t)lh * W;
-  if (p.lse_window != nullptr) {  // uniform
-    if (threadIdx.x < 64)
-      sh.fin[threadIdx.x] = (int)threadIdx.x < W
-                                ? p.lse_window[lse_off + threadIdx.x] * 1.44269504088896340736f
-                                : INFINITY;  // padded rows contribute exp2(-inf) = 0
-    __syncthreads();
-  } else {
-  // ---- pass 1: row maxima and normalisers --------------------------------
-  float m[NT], z[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    m[nt] = -3.0e38f;
-    z[nt] = 0.f;
-  }
-  {
-    half8 kc[KS], kn[KS];
-    int b = wave;
-    if (b < nb) load_block(b, kc);
-    for (; b < nb; b += kWaves) {
-      if (b + kWaves < nb) load_block(b + kWaves, kn);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kc[ks], qreg[nt][ks], acc, 0, 0, 0);
-        float t[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t[r] = acc[r] * c;
-        if (b >= n_unmasked) {
-          // query i at position L-W+i sees tokens <= its own position
-          const int limit = L - W + nt * 16 + c16;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int tok = b * 16 + q4 * 4 + r;
-            if (tok > limit) t[r] = -INFINITY;
-          }
-        }
-        const float bm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-        const float mn = fmaxf(m[nt], bm);
-        float zz = z[nt] * __builtin_amdgcn_exp2f(m[nt] - mn);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) zz += __builtin_amdgcn_exp2f(t[r] - mn);
-        z[nt] = zz;
-        m[nt] = mn;
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
-    }
-  }
-
-  // combine the 16 partial (max, sum) pairs of every query
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    sh.m[wave][q4][nt * 16 + c16] = m[nt];
-    sh.z[wave][q4][nt * 16 + c16] = z[nt];
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int row = threadIdx.x;
-    float out = INFINITY;  // padded rows contribute exp2(-inf) = 0
-    if (row < W) {
-      float mm = -3.0e38f;
-      for (int w = 0; w < kWaves; ++w)
-        for (int q = 0; q < 4; ++q) mm = fmaxf(mm, sh.m[w][q][row]);
-      float zz = 0.f;
-      for (int w = 0; w < kWaves; ++w)
-        for (int q = 0; q < 4; ++q)
-          zz += sh.z[w][q][row] * __builtin_amdgcn_exp2f(sh.m[w][q][row] - mm);
-      out = mm + log2f(zz);
-    }
-    sh.fin[row] = out;
-  }
-  __syncthreads();
-  }
-  if (p.lse_out != nullptr) {  // uniform: the caller asked for the denominators only
-    if ((int)threadIdx.x < W)
-      p.lse_out[lse_off + threadIdx.x] = sh.fin[threadIdx.x] * 0.69314718055994530942f;
-    return;
-  }
-
-  // ---- pass 2: column sums of the soft-maxed rows over the prefix ---------
-  const int n_prefix = L - W;
-  const int nb2 = (n_prefix + 15) >> 4;
-  float mrow[NT][4];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.fin[nt * 16 + q4 * 4 + r];
-
-  {
-    // from the end of the prefix backwards: the blocks that the first pass read
-    // last are the ones most likely to be still in a cache
-    half8 kc[KS], kn[KS];
-    int b = nb2 - 1 - wave;
-    if (b >= 0) load_block_nt(b, kc);
-    for (; b >= 0; b -= kWaves) {
-      if (b - kWaves >= 0) load_block_nt(b - kWaves, kn);
-      float colsum = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
-      }
-      colsum += __shfl_xor(colsum, 16);
-      colsum += __shfl_xor(colsum, 32);
-      const int tok = b * 16 + c16;
-      if (q4 == 0 && tok < n_prefix) store(tok, colsum);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
-    }
-  }
-}
-
-template <int D, int NT, typename Store>
-__device__ __forceinline__ void snapkv_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            const int32_t* old_ids, ScoreShared& sh, Store store) {
-  half8 qreg[NT][D / 32];
-  load_window_queries<D, NT>(p, rd, lh, qreg);
-  snapkv_unit_q<D, NT>(p, rd, lh, old_ids, sh, qreg, store);
-}
 
 template <int D, int NT>
 __global__ __launch_bounds__(kThreads) void snapkv_score_kernel(BatchParams p) {
-  __shared__ ScoreShared sh;
+  __shared__ ScoreShared<kWaves> sh;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
@@ -391,52 +162,7 @@ __global__ __launch_bounds__(kThreads) void snapkv_score_kernel(BatchParams p) {
   // the denominators-only call runs outside a compression: no saved ids, the table row itself
   const int32_t* ids = p.lse_out != nullptr ? p.block_tables + (size_t)rd.table_row * p.max_blocks
                                             : p.old_ids + rd.old_off;
-  snapkv_unit<D, NT>(p, rd, lh, ids, sh, [&](int j, float v) { raw[j] = v; });
-}
-
-// ---------------------------------------------------------------------------
-// key-norm score: raw[j] = -||k_j||_2
-// ---------------------------------------------------------------------------
-//
-// One workgroup per (request, layer, head); a wavefront reads one 16-token
-// chunk with fully coalesced 128-bit loads (64 lanes x 16 B = 1 KiB per
-// instruction) and reduces the squares over the lanes that share a row.
-
-template <int D, typename Store>
-__device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                           const int32_t* old_ids, Store store) {
-  constexpr int LPR = D / 8;     // lanes per token row
-  constexpr int RPI = 64 / LPR;  // rows per load instruction
-  constexpr int NI = 16 / RPI;   // load instructions per block
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int L = rd.seq_len;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                          (size_t)head * 16 * D + lane * 8;
-  const int nb = (L + 15) >> 4;
-  for (int b = wave; b < nb; b += kWaves) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-    half8 v[NI];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) v[k] = load_half8(kp + k * 512);
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      float s = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = (float)v[k][e];
-        s += x * x;
-      }
-#pragma unroll
-      for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o);
-      const int tok = b * 16 + k * RPI + lane / LPR;
-      if ((lane % LPR) == 0 && tok < L) store(tok, -sqrtf(s));
-    }
-  }
+  snapkv_unit<D, NT, kWaves>(p, rd, lh, ids, sh, [&](int j, float v) { raw[j] = v; });
 }
 
 template <int D>
@@ -446,1073 +172,7 @@ __global__ __launch_bounds__(kThreads) void knorm_score_kernel(BatchParams p) {
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_knorm[slot]];
   float* raw = p.raw_scores + rd.raw_off + (size_t)lh * rd.seq_len;
-  knorm_unit<D>(p, rd, lh, p.old_ids + rd.old_off, [&](int j, float v) { raw[j] = v; });
-}
-
-// ---------------------------------------------------------------------------
-// per-head top-budget selection
-// ---------------------------------------------------------------------------
-//
-// One workgroup per (request, layer, head).  Only the tokens before the
-// observation window compete (window tokens are always kept), so the kernel
-// selects the budget-minus-window best of the prefix and appends the window.
-//
-//   1. the un-pooled scores lie in LDS; they are max-pooled and turned into
-//      order-preserving 32-bit keys, which stay in registers for the rest;
-//   2. the threshold (the k-th largest key) is found by a bucket select: 2048
-//      linear buckets over a range that holds it (so the histogram is spread
-//      even when every score shares its exponent), then the keys of the one
-//      bucket that holds the threshold are compacted to a short candidate list,
-//      which is refined with 2048 buckets per pass until a bucket is a single
-//      key (at most 3 passes for 32 bits);
-//   3. the kept indices are emitted in ascending token order by a ballot /
-//      popcount compaction in which keys equal to the threshold are admitted
-//      in index order until the budget is met (ties go to the lower index).
-//
-// Ownership of tokens: a wavefront owns a contiguous segment (a multiple of 256
-// tokens) and a lane four consecutive tokens of each 256.  What bounds this
-// phase is LDS latency (one workgroup has four wavefronts and every step waits
-// for its reads), so the pooling window of a lane's four tokens comes from three
-// 16-byte reads instead of seven dependent 4-byte reads per token.
-
-__device__ __forceinline__ uint32_t score_key(float s) {
-  s += 0.0f;  // -0 and +0 compare equal, give them one key
-  const uint32_t u = __float_as_uint(s);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-static constexpr int kBuckets = 2048;
-static constexpr int kBucketBits = 11;
-static constexpr int kMaxCand = 2048;
-static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
-// chunks of a wavefront's segment at most: 4 wavefronts take heads of up to 8192 tokens, 16 of up to 32768
-template <int WV>
-static constexpr int kChunksPerWave = 8;
-
-// LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
-// that the four-token reads of the pooling may touch (filled with the neutral
-// value), then one bit per token.
-static constexpr int kStageFront = 4;
-__host__ __device__ constexpr int stage_words(int len) { return kStageFront + ((len + 3) & ~3) + 8; }
-__host__ __device__ constexpr int need_words(int len) { return (len + kChunk - 1) / kChunk * (kChunk / 32); }
-
-typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32x4 lds_words4(const uint32_t* p) {
-  return *reinterpret_cast<const uint32x4*>(p);
-}
-__device__ __forceinline__ void set_lds_words4(uint32_t* p, uint32x4 v) {
-  *reinterpret_cast<uint32x4*>(p) = v;
-}
-
-// first token of a wavefront's segment
-template <int WV>
-__device__ __forceinline__ int segment_tokens(int n) {
-  return (((n + WV - 1) / WV) + kChunk - 1) & ~(kChunk - 1);
-}
-
-// Writes `v` to the words around stage[0 .. n) that pooling reads.
-__device__ __forceinline__ void fill_stage_margins(uint32_t* stage, int n, uint32_t v) {
-  if (threadIdx.x < kStageFront) stage[(int)threadIdx.x - kStageFront] = v;
-  if (threadIdx.x < 8) stage[n + threadIdx.x] = v;  // n + 7 < the padded length + 8
-}
-
-struct PoolMaxWord {  // largest whole word (non-negative floats compare like their bits)
-  static constexpr uint32_t neutral = 0u;
-  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w; }
-  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
-};
-struct PoolMaxLow {  // largest low half
-  static constexpr uint32_t neutral = 0u;
-  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
-  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
-};
-struct PoolMinLow {  // smallest low half
-  static constexpr uint32_t neutral = 0xFFFFu;
-  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
-  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return min(a, b); }
-};
-
-// The pooling windows [c + e - h, c + e + h] of the four tokens c + e (c a
-// multiple of 4) over stage[0 .. n) and its margins.  h = 3 (a pooling width of
-// 7, the usual one) has its own code: three 16-byte reads, the part of the
-// windows that all four share once.  Any other h walks the 16-byte groups.
-template <bool kThree>
-struct PoolWindow {
-  uint32x4 left, mid, right;
-  const uint32_t* stage;
-  int c, h, n;
-  __device__ __forceinline__ PoolWindow(const uint32_t* stage_, int c_, int h_, int n_)
-      : stage(stage_), c(c_), h(h_), n(n_) {
-    mid = lds_words4(stage + c);
-    if constexpr (kThree) {
-      left = lds_words4(stage + c - 4);
-      right = lds_words4(stage + c + 4);
-    }
-  }
-  template <typename Op>
-  __device__ __forceinline__ void reduce(uint32_t (&out)[4]) const {
-    if constexpr (kThree) {
-      const uint32_t core = Op::join(Op::join(Op::get(mid[0]), Op::get(mid[1])),
-                                     Op::join(Op::get(mid[2]), Op::get(mid[3])));
-      const uint32_t l2 = Op::get(left[3]), l1 = Op::join(Op::get(left[2]), l2),
-                     l0 = Op::join(Op::get(left[1]), l1);
-      const uint32_t r1 = Op::get(right[0]), r2 = Op::join(r1, Op::get(right[1])),
-                     r3 = Op::join(r2, Op::get(right[2]));
-      out[0] = Op::join(core, l0);
-      out[1] = Op::join(core, Op::join(l1, r1));
-      out[2] = Op::join(core, Op::join(l2, r2));
-      out[3] = Op::join(core, r3);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = Op::get(mid[e]);
-      if (h == 0) return;
-      uint32_t shared = Op::neutral;
-      const int reach = (h + 3) >> 2;  // groups to either side
-      for (int g = -reach; g <= reach; ++g) {
-        const int at = c + 4 * g;
-        if (at < -kStageFront || at >= n) continue;  // (the margins cover one group to either side)
-        const uint32x4 w = lds_words4(stage + at);
-        if (4 * abs(g) + 3 <= h) {  // uniform: in all four windows
-          shared = Op::join(shared, Op::join(Op::join(Op::get(w[0]), Op::get(w[1])),
-                                             Op::join(Op::get(w[2]), Op::get(w[3]))));
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (abs(4 * g + k - e) <= h) out[e] = Op::join(out[e], Op::get(w[k]));
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = Op::join(out[e], shared);
-    }
-  }
-};
-
-// hist[b[e]] += 1 for four buckets (kNoBucket: none); neighbouring tokens share
-// their pooled maximum more often than not, so equal neighbours go in one add
-static constexpr uint32_t kNoBucket = 0xFFFFFFFFu;
-__device__ __forceinline__ void hist_add4(int* hist, const uint32_t (&b)[4]) {
-  int run = 1;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if (e < 3 && b[e] == b[(e + 1) & 3]) {
-      ++run;
-    } else {
-      if (b[e] != kNoBucket) atomicAdd(&hist[b[e]], run);
-      run = 1;
-    }
-  }
-}
-
-// The bucket that holds the `rank`-th largest entry of a histogram -> sel[0],
-// the rank inside it -> sel[1].  All threads call; ends with a barrier.
-template <int WV>
-__device__ __forceinline__ void bucket_of_rank(const int* hist, int rank, int* wsum, int* sel) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kOwn = kBuckets / (64 * WV);  // thread t owns buckets [kOwn t, kOwn t + kOwn)
-  int own[kOwn];
-  int s = 0;
-#pragma unroll
-  for (int i = 0; i < kOwn; ++i) {
-    own[i] = hist[tid * kOwn + i];
-    s += own[i];
-  }
-  int v = s;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(v, o);
-    if (lane >= o) v += t;
-  }
-  if (lane == 63) wsum[wave] = v;
-  __syncthreads();
-  int base = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < WV; ++w) {
-    if (w < wave) base += wsum[w];
-    total += wsum[w];
-  }
-  int above = total - (v + base);  // keys in buckets above this thread's
-#pragma unroll
-  for (int i = kOwn - 1; i >= 0; --i) {
-    if (above < rank && above + own[i] >= rank) {
-      sel[0] = tid * kOwn + i;
-      sel[1] = rank - above;
-    }
-    above += own[i];
-  }
-  __syncthreads();
-}
-
-template <int WV>
-struct SelectShared {
-  int hist[kBuckets];
-  uint32_t cand[kMaxCand];
-  int wsum[WV];
-  uint32_t wmin[WV], wmax[WV];
-  int sel[2];
-  int n_cand;
-  int cnt[WV][2];
-};
-
-// Selects the kept tokens of one (request, layer, head) and writes them, in
-// ascending order, to `kept` (nullable, global memory) and, over the words of
-// stage[] (the keys are in registers by then), as 16-bit indices for the copy
-// that follows in the same workgroup.  stage[0 .. n_sel): the un-pooled scores as
-// floats, written by this workgroup and made visible by a barrier.  hint_lo,
-// hint_hi: keys that are known to enclose the threshold (0, ~0: nothing is
-// known).  All threads of the workgroup call.
-template <bool kThree, int WV>
-__device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
-                                              uint32_t hint_lo, uint32_t hint_hi) {
-  int* hist = sh.hist;
-  uint32_t* cand = sh.cand;
-  int* sel = sh.sel;
-  const int L = rd.seq_len;
-  const int B = rd.budget;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
-  const int n_sel = snap ? L - rd.window : L;  // tokens that compete
-  const int k_sel = snap ? B - rd.window : B;  // how many of them are kept
-  float* out = p.scores_out ? p.scores_out + rd.score_off + (size_t)lh * L : nullptr;
-  uint16_t* kept16 = reinterpret_cast<uint16_t*>(stage);  // (budget <= length: half of the words)
-  auto keep_token = [&](int t, int j) {
-    kept16[t] = (uint16_t)j;
-    if (kept) kept[t] = j;
-  };
-  const int seg = segment_tokens<WV>(n_sel);
-  const int j0 = wave * seg;
-  const int j1 = min(n_sel, j0 + seg);
-
-  // ---- 1. final scores -> keys, min / max -------------------------------------
-  fill_stage_margins(stage, n_sel, 0u);
-  if (tid == 0) sh.n_cand = 0;
-#pragma unroll
-  for (int i = 0; i < kBuckets / (64 * WV); ++i) hist[tid + i * (64 * WV)] = 0;
-  __syncthreads();
-  uint32_t key[kChunksPerWave<WV>][4];
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (c < j1) {
-      const PoolWindow<kThree> pw(stage, c, rd.pool_kernel >> 1, n_sel);
-      uint32_t v[4];
-      if (snap) {
-        pw.template reduce<PoolMaxWord>(v);  // (sums of exponentials: none is negative)
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = pw.mid[e];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t k = score_key(__uint_as_float(v[e]));
-        key[i][e] = k;
-        if (c + e < j1) {
-          kmin = min(kmin, k);
-          kmax = max(kmax, k);
-        }
-      }
-    }
-  }
-  if (out) {
-    // back through LDS, so that the stores are contiguous over the lanes
-    if (snap) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-          uint32x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = key[i][e] & 0x7FFFFFFFu;
-          set_lds_words4(stage + c, w);
-        }
-      }
-      __syncthreads();
-      for (int j = n_sel + tid; j < L; j += (64 * WV)) out[j] = INFINITY;
-    }
-    for (int j = tid; j < n_sel; j += (64 * WV)) out[j] = __uint_as_float(stage[j]);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-  }
-  // how many keys lie above the hinted range, and how many not below it
-  int n_above = 0, n_reach = 0;
-  if (hint_lo != 0u) {  // uniform
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (j0 + i * kChunk >= j1) break;  // uniform over the wavefront
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        n_above += __popcll(__ballot(c + e < j1 && key[i][e] > hint_hi));
-        n_reach += __popcll(__ballot(c + e < j1 && key[i][e] >= hint_lo));
-      }
-    }
-  }
-  if (lane == 0) {
-    sh.wmin[wave] = kmin;
-    sh.wmax[wave] = kmax;
-    sh.cnt[wave][0] = n_above;
-    sh.cnt[wave][1] = n_reach;
-  }
-  __syncthreads();
-  n_above = n_reach = 0;
-#pragma unroll
-  for (int w = 0; w < WV; ++w) {
-    kmin = min(kmin, sh.wmin[w]);
-    kmax = max(kmax, sh.wmax[w]);
-    n_above += sh.cnt[w][0];
-    n_reach += sh.cnt[w][1];
-  }
-  // the k_sel-th largest key lies in the hinted range: search only there
-  const bool narrowed = n_above < k_sel && n_reach >= k_sel;  // uniform
-  // (every read of stage[] lies before the barrier above)
-  if (snap)
-    for (int j = tid; j < rd.window; j += (64 * WV)) keep_token(k_sel + j, n_sel + j);  // forced window
-  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
-  if (narrowed) {
-    kmin = max(kmin, hint_lo);
-    kmax = min(kmax, hint_hi);
-  }
-
-  // ---- 2. threshold = k_sel-th largest key ---------------------------------------
-  // one pass over the registers: the keys in [lo, lo + width) into 2048 buckets (width 0: up to kmax)
-  auto count_keys = [&](uint32_t lo, int shift, uint32_t width) {
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        uint32_t b[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t k = key[i][e], d = k - lo;
-          b[e] = c + e < j1 && k >= lo && (width == 0u ? k <= kmax : d < width) ? d >> shift : kNoBucket;
-        }
-        hist_add4(hist, b);
-      }
-    }
-  };
-  uint32_t thr;
-  int need_eq;
-  {
-    uint32_t lo = kmin;
-    const uint32_t range = kmax - kmin;
-    int shift = range ? max(0, 32 - __clz(range) - kBucketBits) : 0;
-    count_keys(lo, shift, 0u);
-    __syncthreads();
-    bucket_of_rank<WV>(hist, narrowed ? k_sel - n_above : k_sel, sh.wsum, sel);
-    int remaining = sel[1];
-    uint32_t bkt = (uint32_t)sel[0];
-    if (shift > 0) {
-      // candidates: the keys of that one bucket
-#pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t k = key[i][e];
-            if (c + e < j1 && k >= lo && k <= kmax && ((k - lo) >> shift) == bkt) {
-              const int pos = atomicAdd(&sh.n_cand, 1);
-              if (pos < kMaxCand) cand[pos] = k;
-            }
-          }
-        }
-      }
-      __syncthreads();
-      const int nc = sh.n_cand;
-      const bool listed = nc <= kMaxCand;  // else refine over all keys with a range check
-      while (shift > 0) {
-        lo += bkt << shift;
-        const uint32_t width = 1u << shift;  // the chosen bucket spans [lo, lo + width)
-        shift = max(0, shift - kBucketBits);
-#pragma unroll
-        for (int i = 0; i < kBuckets / (64 * WV); ++i) hist[tid + i * (64 * WV)] = 0;
-        __syncthreads();
-        if (listed) {
-          for (int j = tid; j < nc; j += (64 * WV)) {
-            const uint32_t d = cand[j] - lo;
-            if (cand[j] >= lo && d < width) atomicAdd(&hist[d >> shift], 1);
-          }
-        } else {
-          count_keys(lo, shift, width);
-        }
-        __syncthreads();
-        bucket_of_rank<WV>(hist, remaining, sh.wsum, sel);
-        remaining = sel[1];
-        bkt = (uint32_t)sel[0];
-      }
-    }
-    thr = lo + bkt;
-    need_eq = remaining;
-  }
-
-  // ---- 3. ordered compaction ------------------------------------------------------
-  int n_gt = 0, n_eq = 0;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk >= j1) break;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      n_gt += __popcll(__ballot(c + e < j1 && key[i][e] > thr));
-      n_eq += __popcll(__ballot(c + e < j1 && key[i][e] == thr));
-    }
-  }
-  if (lane == 0) {
-    sh.cnt[wave][0] = n_gt;
-    sh.cnt[wave][1] = n_eq;
-  }
-  __syncthreads();
-  int gt_before = 0, eq_before = 0;
-  for (int w = 0; w < wave; ++w) {
-    gt_before += sh.cnt[w][0];
-    eq_before += sh.cnt[w][1];
-  }
-  int eq_run = eq_before;
-  int kept_run = gt_before + min(eq_before, need_eq);
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk >= j1) break;
-    // (lanes are in token order, each with its four tokens in order)
-    uint64_t eq[4], kp[4];
-    int eq_rank = eq_run;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      eq[e] = __ballot(c + e < j1 && key[i][e] == thr);
-      eq_rank += __popcll(eq[e] & lt_mask);
-      eq_run += __popcll(eq[e]);
-    }
-    bool keep[4];
-    int at = kept_run;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool is_eq = (eq[e] >> lane) & 1u;
-      keep[e] = (c + e < j1 && key[i][e] > thr) || (is_eq && eq_rank < need_eq);
-      eq_rank += is_eq ? 1 : 0;
-      kp[e] = __ballot(keep[e]);
-      at += __popcll(kp[e] & lt_mask);
-      kept_run += __popcll(kp[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (keep[e]) keep_token(at++, c + e);
-  }
-}
-
-template <int WV>
-__device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
-                                            uint32_t hint_lo = 0u, uint32_t hint_hi = 0xFFFFFFFFu) {
-  if (rd.pool_kernel == 7)  // uniform
-    select_unit_h<true, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
-  else
-    select_unit_h<false, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
-}
-
-// ---------------------------------------------------------------------------
-// SnapKV-style score with a pruned second pass
-// ---------------------------------------------------------------------------
-//
-// The second pass over K only serves the selection, and the selection only
-// needs exact column sums near its threshold.  The first pass can bound every
-// column sum: it accumulates the soft-max numerators 2^(logit - ref_i) against a
-// per-row reference ref_i that is known when the token is read (log2 of the
-// row's sum over what the workgroup has read so far, renewed at fixed steps by
-// all wavefronts together), so the exact weight of logit (i, j) is that
-// numerator times rho_i = 2^(ref_i - lse_i) <= 1, a factor that is only known at
-// the end but is the same for every token of an epoch.  With c_j the sum of a
-// token's numerators e_ij over the window rows and s_j the root of the sum of
-// their squares, for any number m
-//     a_j = sum_i e_ij rho_i = m c_j + sum_i e_ij (rho_i - m),
-// and because no e_ij is negative, with (x)+ = max(x, 0) and Cauchy-Schwarz,
-//     a_j <= m c_j + s_j sqrt(sum_i ((rho_i - m)+)^2),
-//     a_j >= m c_j - s_j sqrt(sum_i ((m - rho_i)+)^2).
-// A few values of m around the mean of the rho_i are tried for
-// each side (the least upper bound over all m is the exact maximum of a_j over
-// all non-negative e_ij with these two sums), next to
-// c_j min_i rho_i <= a_j <= c_j max_i rho_i.  Both numbers of a token
-// share its word of the LDS score array until the pass ends (c_j in the leading
-// 20 bits, s_j / c_j <= 1 in the other 12), so the bounds cost no memory traffic.
-// After the pass: bounds of the max-pooled scores, a lower and an upper bound of
-// the selection threshold from two histograms, and the tokens whose pooled
-// interval contains neither are decided without a second look.  For the others
-// the tokens of their pooling window that can carry the maximum are re-scored
-// exactly, row by row (256 bytes each), and everything else keeps its upper
-// bound: the plain selection that follows then returns exactly the set it
-// would return from exact scores (a decided-out token stays below the
-// threshold, a decided-in one above it, an undecided one carries its exact
-// pooled score; ties can only occur among those).
-//
-// The scores themselves are not produced (callers that ask for them take the
-// two-pass path).  A reference can be overtaken by more than the fp32 exponent
-// range only by inputs far outside any attention layer; the numerators then
-// overflow, the row's log-sum-exp is not finite, and the head falls back to
-// the two-pass code.
-
-static constexpr int kBoundCentres = 3;  // values of m tried per side
-
-struct BoundEpoch {  // the factors rho_i of one epoch over the window rows
-  float rmax, rmin;               // largest (widened), smallest (narrowed)
-  float m_up[kBoundCentres];      // centres for the upper bound ...
-  float p_up[kBoundCentres];      // ... and sqrt(sum ((rho_i - m)+)^2) for each (widened)
-  float m_dn[kBoundCentres];      // the same for the lower bound, with (m - rho_i)+
-  float p_dn[kBoundCentres];
-};
-
-struct BoundShared {
-  float fin[64];                   // log2 of every row's soft-max denominator
-  float pub[2][kWaves][64];        // the wavefronts' row sums at a renewal, absolute log2
-  float ref[kBoundMaxEpochs][64];  // the reference of every epoch
-  BoundEpoch stat[kBoundMaxEpochs];
-};
-
-struct BoundKeep {  // what survives into the selection's LDS
-  int bad;          // a row's log-sum-exp is not finite: fall back
-};
-
-// A token's two sums during the pass, in one word: the leading 20 bits of the
-// sum c of its numerators (truncated: at most 2^-11 below c) and, in 12 bits, a
-// number k with sqrt(s2) <= k / 4095 * c, s2 the sum of their squares (the ratio
-// is at most 1; where the squares left the fp32 range, or c is too small for
-// them to be trusted, k = 4095 says just that).
-__device__ __forceinline__ uint32_t pack_sums(float c, float s2) {
-  const float r = sqrtf(s2) / c;  // not a number <= 1 when c is 0 or either sum overflowed
-  const uint32_t k = (c >= 1.0e-12f && r <= 1.f) ? min(4095u, (uint32_t)(r * 4095.f) + 2u) : 4095u;
-  return (__float_as_uint(c) & 0xFFFFF000u) | k;
-}
-
-// A token's bounds share one 32-bit word of LDS: the upper bound rounded up to
-// its leading 16 bits, the lower bound rounded down to its leading 16 bits
-// (both are non-negative floats).  0.8 % of slack against bounds that are tens
-// of per cent apart.
-__device__ __forceinline__ uint32_t pack_bounds(float lo, float hi) {
-  const uint32_t h = (__float_as_uint(hi) + 0xFFFFu) >> 16;
-  const uint32_t l = __float_as_uint(lo) >> 16;
-  return (h << 16) | l;
-}
-__device__ __forceinline__ float upper_of(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-__device__ __forceinline__ float lower_of(uint32_t w) { return __uint_as_float(w << 16); }
-
-__device__ __forceinline__ int bound_epoch_of_token(int j) {
-  return bound_epoch_of_step((j >> 4) / kWaves);
-}
-
-// First pass with bounds.  On return stage[j] holds the packed bounds of the
-// column sum of every prefix token j and bs.fin the rows' log-sum-exps.  All
-// threads of the workgroup call; ends with a barrier.
-template <int D, int NT>
-__device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              const int32_t* old_ids, BoundShared& bs,
-                                              BoundKeep& keep, float* stage,
-                                              half8 (&qreg)[NT][D / 32]) {
-  constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int L = rd.seq_len;
-  const int W = rd.window;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                          (size_t)head * 16 * D + (size_t)c16 * D + q4 * 8;
-  const float c = p.scale_log2e;
-  const int nb = (L + 15) >> 4;
-  const int n_prefix = L - W;
-  const int n_unmasked = n_prefix >> 4;
-  auto load_block = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8(kp + ks * 32);
-  };
-
-  float ref[NT], zacc[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    ref[nt] = 0.f;
-    zacc[nt] = 0.f;
-  }
-  // the wavefront's row sums in absolute log2 units -> pub[buf]
-  auto publish = [&](int buf) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float zr = zacc[nt];
-      zr += __shfl_xor(zr, 16);
-      zr += __shfl_xor(zr, 32);
-      // (a sum that is not a number stays one: see merged)
-      if (q4 == 0) bs.pub[buf][wave][nt * 16 + c16] = zr == 0.f ? -INFINITY : ref[nt] + log2f(zr);
-    }
-  };
-  // log2 of the workgroup's row sum from the published shares; own = this wavefront's share
-  auto merged = [&](int buf, int row, float& own) {
-    float l[kWaves];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      l[w] = bs.pub[buf][w][row];
-      mx = fmaxf(mx, l[w]);
-    }
-    own = l[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) own = wave == w ? l[w] : own;
-    // Numerators that overflowed make a share infinite and the sum below not a
-    // number; from there on that row's references, sums and log-sum-exp are none
-    // either, which is how the head is found to need the two-pass code.
-    float zz = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) zz += l[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[w] - mx);
-    return zz == 0.f ? 0.f : mx + log2f(zz);  // 0: nothing visible yet, any finite reference will do
-  };
-
-  const int T = (nb + kWaves - 1) / kWaves;  // steps; every wavefront walks all of them
-  int epoch = 0, buf = 0;
-  half8 kc[KS], kn[KS];
-  if (wave < nb) load_block(wave, kc);
-  for (int t = 0; t < T; ++t) {
-    const int b = wave + kWaves * t;
-    if (b + kWaves < nb) load_block(b + kWaves, kn);
-    if (bound_renews_before(t)) {  // uniform over the workgroup
-      publish(buf);
-      __syncthreads();
-      ++epoch;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int row = nt * 16 + c16;
-        float own;
-        const float nr = merged(buf, row, own);
-        zacc[nt] = (q4 == 0 && own != -INFINITY) ? __builtin_amdgcn_exp2f(own - nr) : 0.f;
-        ref[nt] = nr;
-        if (wave == 0 && q4 == 0) bs.ref[epoch][row] = nr;
-      }
-      buf ^= 1;  // the other buffer is written next: its readers passed a barrier since
-    }
-    if (b < nb) {  // uniform per wavefront
-      float cs[4] = {0.f, 0.f, 0.f, 0.f}, ss[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kc[ks], qreg[nt][ks], acc, 0, 0, 0);
-        float tv[4];
-        const bool row_ok = nt * 16 + c16 < W;  // padded rows carry no weight
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tv[r] = row_ok ? acc[r] * c : -INFINITY;
-        if (b >= n_unmasked) {
-          const int limit = L - W + nt * 16 + c16;
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (b * 16 + q4 * 4 + r > limit) tv[r] = -INFINITY;
-        }
-        if (t == 0) {
-          // no reference yet: the block's own row maximum (these tokens get the
-          // trivial bounds, whatever they accumulate here)
-          float bm = fmaxf(fmaxf(tv[0], tv[1]), fmaxf(tv[2], tv[3]));
-          bm = fmaxf(bm, __shfl_xor(bm, 16));
-          bm = fmaxf(bm, __shfl_xor(bm, 32));
-          ref[nt] = bm == -INFINITY ? 0.f : bm;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float e = __builtin_amdgcn_exp2f(tv[r] - ref[nt]);
-          zacc[nt] += e;
-          cs[r] += e;
-          ss[r] = fmaf(e, e, ss[r]);
-        }
-      }
-      // sums over the window rows (the lanes of a row of 16, after the tiles in
-      // the lane); lane c16 < 4 of each row keeps those of token 4 q4 + c16
-      float mc = 0.f, ms = 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float vc = row16_sum(cs[r]);
-        const float vs = row16_sum(ss[r]);
-        mc = c16 == r ? vc : mc;
-        ms = c16 == r ? vs : ms;
-      }
-      const int tok = b * 16 + q4 * 4 + c16;
-      if (c16 < 4 && tok < n_prefix) reinterpret_cast<uint32_t*>(stage)[tok] = pack_sums(mc, ms);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
-  }
-  publish(buf);
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int row = threadIdx.x;
-    float own;
-    const float lse = merged(buf, row, own);
-    bs.fin[row] = row < W ? lse : INFINITY;  // padded rows contribute exp2(-inf) = 0
-    if (row < W && !(fabsf(lse) < 3.0e38f)) keep.bad = 1;
-  }
-  __syncthreads();
-  // the factors of every epoch, rho_i = 2^(ref_i - lse_i) over the window rows
-  // (one per lane): range, and for centres at the mean and half a standard
-  // deviation to either side of it the one-sided deviations
-  for (int e = 1 + wave; e <= epoch; e += kWaves) {
-    const bool ok = lane < W;
-    const float rho = ok ? __builtin_amdgcn_exp2f(bs.ref[e][lane] - bs.fin[lane]) : 0.f;
-    float lo = ok ? rho : INFINITY, hi = rho, sum = rho;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o));
-      hi = fmaxf(hi, __shfl_xor(hi, o));
-      sum += __shfl_xor(sum, o);
-    }
-    const float mean = sum / (float)W;
-    float var = ok ? (rho - mean) * (rho - mean) : 0.f;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) var += __shfl_xor(var, o);
-    const float half_sd = 0.5f * sqrtf(var / (float)W);
-    float m_up[kBoundCentres], m_dn[kBoundCentres], p_up[kBoundCentres], p_dn[kBoundCentres];
-#pragma unroll
-    for (int k = 0; k < kBoundCentres; ++k) {
-      // (any centre gives a valid bound; none below zero, so that widening the sum widens the bound)
-      m_up[k] = fmaxf(mean + (float)(k - 1) * half_sd, 0.f);
-      m_dn[k] = fmaxf(mean - (float)(k - 1) * half_sd, 0.f);
-      const float du = ok ? fmaxf(rho - m_up[k], 0.f) : 0.f;
-      const float dd = ok ? fmaxf(m_dn[k] - rho, 0.f) : 0.f;
-      p_up[k] = du * du;
-      p_dn[k] = dd * dd;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-      for (int k = 0; k < kBoundCentres; ++k) {
-        p_up[k] += __shfl_xor(p_up[k], o);
-        p_dn[k] += __shfl_xor(p_dn[k], o);
-      }
-    }
-    if (lane == 0) {
-      // (margins far above the rounding of the numerators, the sums and the factors)
-      BoundEpoch& st = bs.stat[e];
-      st.rmax = hi * 1.0002f;
-      st.rmin = lo * 0.9998f;
-#pragma unroll
-      for (int k = 0; k < kBoundCentres; ++k) {
-        st.m_up[k] = m_up[k];
-        st.m_dn[k] = m_dn[k];
-        st.p_up[k] = sqrtf(p_up[k]) * 1.001f + 1.0e-6f * hi;
-        st.p_dn[k] = sqrtf(p_dn[k]) * 1.001f + 1.0e-6f * hi;
-      }
-    }
-  }
-  __syncthreads();
-  // per token: the two sums -> bounds, packed in place
-  {
-    const float trivial = (float)W;  // every row contributes at most 1
-    for (int j = threadIdx.x; j < n_prefix; j += kThreads) {
-      const int e = bound_epoch_of_token(j);
-      const uint32_t w = reinterpret_cast<const uint32_t*>(stage)[j];
-      const float c_lo = __uint_as_float(w & 0xFFFFF000u);
-      float lo = 0.f, hi = trivial;
-      if (e > 0 && c_lo < 3.0e38f) {  // (a sum that left the fp32 range says nothing)
-        const BoundEpoch& st = bs.stat[e];
-        const float c_hi = c_lo * 1.00049f + 1.0e-30f;  // what the truncation to 20 bits took, at most
-        const float s_hi = (float)(w & 0xFFFu) * (1.f / 4095.f) * c_hi;
-        float h = c_hi * st.rmax, l = c_lo * st.rmin;
-#pragma unroll
-        for (int k = 0; k < kBoundCentres; ++k) {
-          h = fminf(h, (st.m_up[k] * c_hi + s_hi * st.p_up[k]) * 1.0002f);
-          l = fmaxf(l, (st.m_dn[k] * c_lo - s_hi * st.p_dn[k]) * 0.9998f);
-        }
-        lo = fmaxf(l, 0.f);
-        hi = fminf(h, trivial);
-      }
-      reinterpret_cast<uint32_t*>(stage)[j] = pack_bounds(lo, hi);
-    }
-  }
-  __syncthreads();
-}
-
-// Exact column sums of the tokens named by need[] (one bit per prefix token),
-// row by row -> stage[].  mrow: the rows' log-sum-exps as the second product
-// leaves the rows in registers.
-template <int D, int NT>
-__device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDesc& rd, int lh,
-                                               const int32_t* old_ids, const uint32_t* need,
-                                               float* stage, half8 (&qreg)[NT][D / 32],
-                                               const float (&mrow)[NT][4]) {
-  constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * 16 * D + q4 * 8;
-  const float c = p.scale_log2e;
-  const int n_prefix = rd.seq_len - rd.window;
-  const int n_words = (n_prefix + 31) >> 5;
-  // Tiles of 16 named tokens (a wavefront walks its words of the bit map and
-  // fills a tile across them), the rows of the next tile requested before this
-  // one is multiplied.
-  int w = wave - kWaves;
-  uint32_t bits = 0u;
-  auto next_tile = [&](int& tok) -> bool {  // uniform over the wavefront
-    tok = -1;
-    int filled = 0;
-    while (filled < 16) {
-      while (bits == 0u) {
-        w += kWaves;
-        if (w >= n_words) return filled > 0;
-        bits = __builtin_amdgcn_readfirstlane(need[w]);
-      }
-#pragma unroll 1
-      for (; filled < 16 && bits; ++filled) {
-        const int pos = __ffs(bits) - 1;
-        bits &= bits - 1;
-        tok = c16 == filled ? (w << 5) + pos : tok;
-      }
-    }
-    return true;
-  };
-  auto load_rows = [&](int tok, half8 (&k)[KS]) {
-    // (a lane without a token reads the head's first row and drops the result)
-    const int tk = max(tok, 0);
-    const int blk = clamp_block(old_ids[tk >> 4], p.n_blocks);
-    const _Float16* kp = base + (size_t)blk * blk_stride + (size_t)(tk & 15) * D;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
-  };
-  half8 kc[KS], kn[KS], kf[KS];
-  int tok_c = -1, tok_n = -1, tok_f = -1;
-  bool have = next_tile(tok_c);
-  if (have) load_rows(tok_c, kc);
-  bool have_n = have && next_tile(tok_n);
-  if (have_n) load_rows(tok_n, kn);
-  while (have) {
-    const bool have_f = have_n && next_tile(tok_f);
-    if (have_f) load_rows(tok_f, kf);
-    float colsum = 0.f;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
-    }
-    colsum += __shfl_xor(colsum, 16);
-    colsum += __shfl_xor(colsum, 32);
-    if (q4 == 0 && tok_c >= 0) stage[tok_c] = colsum;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kc[ks] = kn[ks];
-      kn[ks] = kf[ks];
-    }
-    tok_c = tok_n;
-    tok_n = tok_f;
-    have = have_n;
-    have_n = have_f;
-  }
-}
-
-// Between the two: which prefix tokens need their exact column sum.  stage[]
-// holds the packed bounds; need[] is set (one bit per token), stage[j] of every
-// token becomes its upper bound.  Tokens are owned and pooled as in select_unit_h;
-// a sweep reads three 16-byte words per four tokens.  Which tokens are named is
-// found from the token's side: j is needed if some undecided token of its pooling
-// window has a pooled lower bound that j's upper bound reaches, i.e. if j's upper
-// bound is at least the least such lower bound of its window.
-//
-// The selection's threshold is returned between two keys.
-template <bool kThree, int WV>
-__device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* stage, uint32_t* need,
-                                                 SelectShared<WV>& sh, uint32_t& key_lo, uint32_t& key_hi) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_sel = rd.seq_len - rd.window;
-  const int k_sel = rd.budget - rd.window;
-  const int h = rd.pool_kernel >> 1;
-  const int seg = segment_tokens<WV>(n_sel);
-  const int j0 = wave * seg;
-  const int j1 = min(n_sel, j0 + seg);
-  int* hist_lo = sh.hist;
-  int* hist_hi = reinterpret_cast<int*>(sh.cand);
-  static_assert(kMaxCand >= kBuckets, "the candidate list doubles as the second histogram");
-  fill_stage_margins(stage, n_sel, 0u);
-  uint32_t vmax = 0u;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (c < j1) {
-      const uint32x4 w = lds_words4(stage + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (c + e < j1) vmax = max(vmax, w[e] & 0xFFFF0000u);
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, o));
-  if (lane == 0) sh.wmax[wave] = vmax;
-  auto zero_histograms = [&] {
-#pragma unroll
-    for (int i = 0; i < kBuckets / (64 * WV); ++i) {
-      hist_lo[tid + i * (64 * WV)] = 0;
-      hist_hi[tid + i * (64 * WV)] = 0;
-    }
-  };
-  zero_histograms();
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < WV; ++w) vmax = max(vmax, sh.wmax[w]);
-  const bool trivial = k_sel <= 0 || k_sel >= n_sel;  // uniform: window only, or everything is kept
-  uint64_t named = 0;  // this lane's tokens, four bits per chunk
-  static_assert(4 * kChunksPerWave<WV> <= 64, "a lane's bits");
-  if (!trivial) {
-    // thresholds: the buckets that hold the k_sel-th largest lower and the k_sel-th
-    // largest upper bound (two histograms from one evaluation of the pooled bounds);
-    // buckets of 2^shift bit patterns from kmin upwards, what lies below kmin counts in bucket 0
-    auto find_buckets = [&](uint32_t kmin, int shift) {
-#pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-          const PoolWindow<kThree> pw(stage, c, h, n_sel);
-          uint32_t hi[4], lo[4];
-          pw.template reduce<PoolMaxWord>(hi);
-          pw.template reduce<PoolMaxLow>(lo);
-          // (no bound exceeds the largest upper bound; the clamp keeps the index in range whatever the bounds hold)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t kh = hi[e] & 0xFFFF0000u, kl = lo[e] << 16;
-            hi[e] = kh > kmin ? min((kh - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
-            lo[e] = kl > kmin ? min((kl - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
-            if (c + e >= j1) hi[e] = lo[e] = kNoBucket;
-          }
-          hist_add4(hist_hi, hi);
-          hist_add4(hist_lo, lo);
-        }
-      }
-      __syncthreads();
-      bucket_of_rank<WV>(hist_lo, k_sel, sh.wsum, sh.sel);
-      const int blo = sh.sel[0];
-      __syncthreads();
-      bucket_of_rank<WV>(hist_hi, k_sel, sh.wsum, sh.sel);
-      const int bhi = sh.sel[0];
-      return make_int2(blo, bhi);
-    };
-    // The bounds carry 16 significant bits, the whole range from 0 to the largest
-    // upper bound only fits 2048 buckets that are up to 12 % of a value wide.  So
-    // first with buckets of 1.6 % (2^17 bit patterns) over the 32 octaves below
-    // the largest upper bound; should the k_sel-th largest lower bound lie below
-    // all of that, once more over the whole range.
-    const int coarse = vmax ? max(0, 32 - __clz(vmax) - kBucketBits) : 0;
-    constexpr int kFine = 17;
-    uint32_t kmin = 0u;
-    int shift = coarse;
-    if (coarse > kFine) {
-      kmin = vmax - ((uint32_t)kBuckets << kFine) + 1u;
-      shift = kFine;
-    }
-    int2 bkt = find_buckets(kmin, shift);
-    if (kmin != 0u && bkt.x == 0) {  // uniform
-      __syncthreads();               // (everyone has read the histograms before they are cleared)
-      zero_histograms();
-      __syncthreads();
-      kmin = 0u;
-      shift = coarse;
-      bkt = find_buckets(kmin, shift);
-    }
-    // (bucket 0 also holds what lies below kmin)
-    const uint32_t t_lo = bkt.x == 0 ? 0u : kmin + ((uint32_t)bkt.x << shift);  // <= the threshold
-    const uint32_t t_hi = kmin + (((uint32_t)bkt.y + 1u) << shift) - 1u;         // >= the threshold
-    key_lo = t_lo | 0x80000000u;  // (score_key of a non-negative value)
-    key_hi = t_hi | 0x80000000u;
-    // the low half of every undecided token's word becomes its pooled lower bound,
-    // of every other token's 0xFFFF
-    uint32_t low[kChunksPerWave<WV>][2];
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        const PoolWindow<kThree> pw(stage, c, h, n_sel);
-        uint32_t hi[4], lo[4];
-        pw.template reduce<PoolMaxWord>(hi);
-        pw.template reduce<PoolMaxLow>(lo);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e >= j1 || (hi[e] & 0xFFFF0000u) < t_lo || (lo[e] << 16) > t_hi) lo[e] = 0xFFFFu;
-        low[i][0] = lo[0] | (lo[1] << 16);
-        low[i][1] = lo[2] | (lo[3] << 16);
-      }
-    }
-    __syncthreads();  // the lower bounds have been read by everyone
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        uint32x4 w = lds_words4(stage + c);
-        w[0] = (w[0] & 0xFFFF0000u) | (low[i][0] & 0xFFFFu);
-        w[1] = (w[1] & 0xFFFF0000u) | (low[i][0] >> 16);
-        w[2] = (w[2] & 0xFFFF0000u) | (low[i][1] & 0xFFFFu);
-        w[3] = (w[3] & 0xFFFF0000u) | (low[i][1] >> 16);
-        set_lds_words4(stage + c, w);
-      }
-    }
-    if (tid < kStageFront) stage[tid - kStageFront] = 0xFFFFu;
-    if (tid < 4) stage[((n_sel + 3) & ~3) + tid] = 0xFFFFu;  // (the last group's own words are set above)
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        const PoolWindow<kThree> pw(stage, c, h, n_sel);
-        uint32_t least[4];
-        pw.template reduce<PoolMinLow>(least);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e < j1 && (pw.mid[e] >> 16) >= least[e]) named |= 1ull << (4 * i + e);
-      }
-    }
-    __syncthreads();  // (the low halves are about to go)
-  }
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk < j1) {  // uniform over the wavefront
-      // eight lanes' nibbles make one word of the bit map
-      uint32_t bits = (uint32_t)((named >> (4 * i)) & 0xFu) << (4 * (lane & 7));
-      bits |= __shfl_xor(bits, 1);
-      bits |= __shfl_xor(bits, 2);
-      bits |= __shfl_xor(bits, 4);
-      if ((lane & 7) == 0) need[(j0 + i * kChunk) / 32 + (lane >> 3)] = bits;
-    }
-    if (c < j1) {
-      uint32x4 w = lds_words4(stage + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
-      set_lds_words4(stage + c, w);
-    }
-  }
-  __syncthreads();
-}
-
-template <int WV>
-__device__ __forceinline__ void bound_classify(const ReqDesc& rd, uint32_t* stage, uint32_t* need,
-                                               SelectShared<WV>& sh, uint32_t& key_lo, uint32_t& key_hi) {
-  key_lo = 0u;
-  key_hi = 0xFFFFFFFFu;
-  if (rd.pool_kernel == 7)  // uniform
-    bound_classify_h<true, WV>(rd, stage, need, sh, key_lo, key_hi);
-  else
-    bound_classify_h<false, WV>(rd, stage, need, sh, key_lo, key_hi);
+  knorm_unit<D, kWaves>(p, rd, lh, p.old_ids + rd.old_off, [&](int j, float v) { raw[j] = v; });
 }
 
 // Heads of up to 32768 tokens whose scores come from a kernel of their own: 16
@@ -1533,110 +193,6 @@ __global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p
   select_unit<kSelectWaves>(p, rd, lh, stage, p.kept + rd.kept_off + (size_t)lh * rd.budget, sh);
 }
 
-// Streaming requests need no score: the first min(n_sink, budget) tokens and
-// the most recent budget - sinks tokens are kept.
-__device__ __forceinline__ int streaming_token(const ReqDesc& rd, int n_sink, int t) {
-  return t < min(n_sink, rd.budget) ? t : rd.seq_len - rd.budget + t;
-}
-
-__device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                               int32_t* kept) {
-  const int L = rd.seq_len;
-  const int B = rd.budget;
-  if (kept)
-    for (int t = threadIdx.x; t < B; t += kThreads) kept[t] = streaming_token(rd, p.n_sink, t);
-  if (p.scores_out) {
-    const int sinks = min(p.n_sink, B);
-    float* out = p.scores_out + rd.score_off + (size_t)lh * L;
-    for (int j = threadIdx.x; j < L; j += kThreads)
-      out[j] = (j < sinks || j >= L - (B - sinks)) ? INFINITY : 0.f;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// gather / compact
-// ---------------------------------------------------------------------------
-//
-// One workgroup per (request, layer, head); a wavefront fills one new block
-// (16 output slots) at a time for K and V.  D/8 lanes move one row with
-// 128-bit accesses, so a wavefront instruction moves 64/(D/8) rows; the
-// destination chunk is contiguous.  kept_at(t) is the token that goes to slot t.
-//
-// Bound by HBM when the chip is full and by the latency of one block's chain
-// (kept index, block id, row) when it is not; the rows of a wavefront's next
-// block are therefore requested before those of this one are stored.
-
-template <int D, typename KeptAt>
-__device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            const int32_t* old_ids, KeptAt kept_at) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = 64 / LPR;
-  constexpr int NI = 16 / RPI;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int B = rd.budget;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // destination blocks: freshly popped ones, or the request's own first blocks
-  const int32_t* new_ids = p.in_place ? old_ids : p.new_ids + rd.new_off;
-  const size_t chunk = (size_t)16 * D;               // one (block, kv, head)
-  const size_t v_off = (size_t)p.n_heads * chunk;    // K chunk -> V chunk of a block
-  const size_t blk_stride = 2 * v_off;
-  _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * chunk +
-                   (lane % LPR) * 8;
-  const int row_in_instr = lane / LPR;
-  auto load = [&](int nbk, half8 (&kk)[NI], half8 (&vv)[NI]) {
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      // (slots past the budget load the last kept row again and drop it)
-      const int t = min(nbk * 16 + k * RPI + row_in_instr, B - 1);
-      const int idx = min(max(kept_at(t), 0), rd.seq_len - 1);
-      const int sblk = clamp_block(old_ids[idx >> 4], p.n_blocks);
-      const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
-      kk[k] = load_half8_nt(src);
-      vv[k] = load_half8_nt(src + v_off);
-    }
-  };
-  auto store = [&](int nbk, const half8 (&kk)[NI], const half8 (&vv)[NI]) {
-    const int dblk = clamp_block(new_ids[nbk], p.n_blocks);
-    _Float16* dst = base + (size_t)dblk * blk_stride;
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      const int row = k * RPI + row_in_instr;
-      if (nbk * 16 + row < B) {
-        store_half8_nt(dst + (size_t)row * D, kk[k]);
-        store_half8_nt(dst + (size_t)row * D + v_off, vv[k]);
-      }
-    }
-  };
-  half8 kc[NI], vc[NI];
-  if (p.in_place) {
-    // Output t overwrites slot t while kept[t] >= t: a chunk of kWaves*16
-    // outputs only reads slots at or after its own start, so reading the whole
-    // chunk, a barrier, then writing it never destroys a row that is still
-    // needed (later chunks read strictly later slots).
-    for (int c0 = 0; c0 < rd.n_new; c0 += kWaves) {
-      const int nbk = c0 + wave;
-      if (nbk < rd.n_new) load(nbk, kc, vc);
-      __syncthreads();  // uniform: c0 and in_place are the same for all threads
-      if (nbk < rd.n_new) store(nbk, kc, vc);
-    }
-    return;
-  }
-  half8 kn[NI], vn[NI];
-  int nbk = wave;
-  if (nbk < rd.n_new) load(nbk, kc, vc);
-  for (; nbk < rd.n_new; nbk += kWaves) {
-    if (nbk + kWaves < rd.n_new) load(nbk + kWaves, kn, vn);
-    store(nbk, kc, vc);
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      kc[k] = kn[k];
-      vc[k] = vn[k];
-    }
-  }
-}
-
 template <int D>
 __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const int n_lh = p.n_layers * p.n_heads;
@@ -1644,129 +200,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_all[slot]];
   const int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
-  gather_unit<D>(p, rd, lh, p.old_ids + rd.old_off, [&](int t) { return kept[t]; });
-}
-
-// ---------------------------------------------------------------------------
-// fused per-unit kernel: score -> select -> gather in one workgroup
-// ---------------------------------------------------------------------------
-//
-// For heads whose scores fit the workgroup's LDS share the three steps run
-// back to back in the workgroup that owns the (request, layer, head): the
-// column sums (or key norms) go straight into LDS, the selection works on
-// them in place and the copy follows.  The scores never travel through HBM,
-// the stage is one launch per method, and the LDS/ALU-bound selection of one
-// workgroup overlaps the HBM-bound streaming of the others on the same CU.
-// One launch serves both methods (the unit's descriptor says which); NT =
-// ceil(window / 16), or 0 when the launch holds no SnapKV unit.
-
-template <int D, int NT>
-__global__ __launch_bounds__(kThreads) void fused_unit_kernel(BatchParams p) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  __shared__ union {
-    ScoreShared score;
-    SelectShared<kWaves> select;
-  } sh;
-  const int n_lh = p.n_layers * p.n_heads;
-  const int slot = blockIdx.x / n_lh;
-  const int lh = blockIdx.x - slot * n_lh;
-  const ReqDesc rd = p.descs[p.order_fused[slot]];
-  uint32_t* words = lds + kStageFront;
-  float* stage = reinterpret_cast<float*>(words);
-  // the request's block ids, read once per workgroup (every later use is an LDS read)
-  __shared__ int32_t sm_ids[kFusedMaxLen / 16];
-  int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
-  const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
-  if (ids_in_lds)
-    for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
-      sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
-  __syncthreads();
-  if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
-    streaming_unit(p, rd, lh, kept);
-    gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
-                   [&](int t) { return streaming_token(rd, p.n_sink, t); });
-    return;
-  } else {
-    bool snap = false;
-    if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
-    if (snap) {
-      if constexpr (NT > 0)
-        snapkv_unit<D, NT>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
-    } else {
-      knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
-    }
-    __syncthreads();
-    select_unit<kWaves>(p, rd, lh, words, kept, sh.select);
-  }
-  __syncthreads();  // the kept list is complete
-  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
-  gather_unit<D>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
-}
-
-// The fused kernel with the pruned second pass for its SnapKV units (see
-// snapkv_bounds); key-norm and streaming units that ride in the launch run as in
-// fused_unit_kernel.  Dynamic LDS: seq_len words of scores, then one bit per token.
-template <int D, int NT>
-__global__ __launch_bounds__(kThreads, 3) void fused_bounded_kernel(BatchParams p) {  // 3 wavefronts per SIMD
-  extern __shared__ __align__(16) uint32_t lds[];
-  __shared__ union {
-    ScoreShared score;
-    SelectShared<kWaves> select;
-    BoundShared bound;
-  } sh;
-  __shared__ BoundKeep keep;
-  const int n_lh = p.n_layers * p.n_heads;
-  const int slot = blockIdx.x / n_lh;
-  const int lh = blockIdx.x - slot * n_lh;
-  const ReqDesc rd = p.descs[p.order_fused[slot]];
-  uint32_t* words = lds + kStageFront;  // per token: its bounds, then its score
-  float* stage = reinterpret_cast<float*>(words);
-  uint32_t* need = lds + stage_words(rd.seq_len);
-  __shared__ int32_t sm_ids[kFusedMaxLen / 16];
-  int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
-  const bool ids_in_lds = rd.n_old <= kFusedMaxLen / 16;  // streaming units may be longer
-  if (ids_in_lds)
-    for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
-      sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
-  if (threadIdx.x == 0) keep.bad = 0;
-  __syncthreads();
-  if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
-    streaming_unit(p, rd, lh, kept);
-    gather_unit<D>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
-                   [&](int t) { return streaming_token(rd, p.n_sink, t); });
-    return;
-  } else {
-    uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
-    if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
-      constexpr int KS = D / 32;
-      const int q4 = (threadIdx.x & 63) >> 4;
-      half8 qreg[NT][KS];
-      load_window_queries<D, NT>(p, rd, lh, qreg);
-      // Short heads gain nothing (the tokens of the first step have no bounds,
-      // those of the next few loose ones): they take the two passes.
-      const bool prune = rd.seq_len >= kBoundMinLen;  // uniform
-      if (prune) snapkv_bounds<D, NT>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
-      if (!prune || keep.bad) {  // bad: not representable against a running reference
-        snapkv_unit_q<D, NT>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
-      } else {
-        float mrow[NT][4];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.bound.fin[nt * 16 + q4 * 4 + r];
-        __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
-        bound_classify<kWaves>(rd, words, need, sh.select, key_lo, key_hi);
-        snapkv_rescore<D, NT>(p, rd, lh, sm_ids, need, stage, qreg, mrow);
-      }
-    } else {
-      knorm_unit<D>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
-    }
-    __syncthreads();
-    select_unit<kWaves>(p, rd, lh, words, kept, sh.select, key_lo, key_hi);
-  }
-  __syncthreads();  // the kept list is complete
-  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
-  gather_unit<D>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
+  gather_unit<D, kWaves>(p, rd, lh, p.old_ids + rd.old_off, [&](int t) { return kept[t]; });
 }
 
 // a fill kernel for small device arrays (flags, verdict words): calls may be
@@ -1781,10 +215,12 @@ __global__ void zero_ints_kernel(int32_t* p, int n) {
 // ---------------------------------------------------------------------------
 
 hipError_t kernels_one_time_setup() {
-  // the select kernel may need more than the default 64 KiB of dynamic LDS
-  // (the fused kernel never does: kFusedMaxLen * 4 = 32 KiB)
+  // kernels that may need more than the default 64 KiB of dynamic LDS
+  // (the narrow fused kernels never do)
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, stage_words(32768) * 4);
+  if (e == hipSuccess) e = fused_wide_setup_64();
+  if (e == hipSuccess) e = fused_wide_setup_128();
   return e;
 }
 
@@ -1887,37 +323,19 @@ hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D>
-static hipError_t launch_fused_d(const BatchParams& p, bool any_snap, size_t lds, hipStream_t s) {
-  const unsigned grid = (unsigned)p.n_fused * p.n_layers * p.n_heads;
-  if (any_snap && p.bounded) {
-    switch ((p.window + 15) / 16) {
-      case 1: fused_bounded_kernel<D, 1><<<grid, kThreads, lds, s>>>(p); break;
-      case 2: fused_bounded_kernel<D, 2><<<grid, kThreads, lds, s>>>(p); break;
-      case 3: fused_bounded_kernel<D, 3><<<grid, kThreads, lds, s>>>(p); break;
-      case 4: fused_bounded_kernel<D, 4><<<grid, kThreads, lds, s>>>(p); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
-  switch (any_snap ? (p.window + 15) / 16 : 0) {
-    case 0: fused_unit_kernel<D, 0><<<grid, kThreads, lds, s>>>(p); break;
-    case 1: fused_unit_kernel<D, 1><<<grid, kThreads, lds, s>>>(p); break;
-    case 2: fused_unit_kernel<D, 2><<<grid, kThreads, lds, s>>>(p); break;
-    case 3: fused_unit_kernel<D, 3><<<grid, kThreads, lds, s>>>(p); break;
-    case 4: fused_unit_kernel<D, 4><<<grid, kThreads, lds, s>>>(p); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_fused(const BatchParams& p, bool any_snap, int max_seq_len, hipStream_t s) {
+hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_blocks, bool wide,
+                        hipStream_t s) {
   if (p.n_fused == 0) return hipSuccess;
-  // (with the pruned second pass: one bit per token behind the scores)
-  const size_t lds = (size_t)(stage_words(max_seq_len) +
-                              (p.bounded && any_snap ? need_words(max_seq_len) : 0)) * sizeof(uint32_t);
-  if (p.head_dim == 128) return launch_fused_d<128>(p, any_snap, lds, s);
-  if (p.head_dim == 64) return launch_fused_d<64>(p, any_snap, lds, s);
+  if (max_seq_len > (wide ? kFusedWideMaxLen : kFusedMaxLen)) return hipErrorInvalidValue;
+  const FusedLds f = fused_lds(p.bounded && any_snap, max_seq_len, max_blocks, wide);
+  p.ids_at = f.ids_at;
+  p.ids_room = f.ids_room;
+  const size_t lds = (size_t)f.words * sizeof(uint32_t);
+  const int tiles = any_snap ? (p.window + 15) / 16 : 0;
+  if (p.head_dim == 128)
+    return wide ? launch_fused_wide_128(p, tiles, lds, s) : launch_fused_narrow_128(p, tiles, lds, s);
+  if (p.head_dim == 64)
+    return wide ? launch_fused_wide_64(p, tiles, lds, s) : launch_fused_narrow_64(p, tiles, lds, s);
   return hipErrorInvalidValue;
 }
 

@@ -143,8 +143,9 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
                                                       : d.method == PLAN_METHOD_KNORM ? 1 : 0;
     return (int64_t)d.seq_len * passes + (int64_t)d.budget * 4;
   };
+  for (int i = 0; i < n_comp; ++i) plan->weights.push_back(weight(i));
   std::stable_sort(sorted.begin(), sorted.end(),
-                   [&](int x, int y) { return weight(x) > weight(y); });
+                   [&](int x, int y) { return plan->weights[x] > plan->weights[y]; });
   const bool allow_fused = pool.score_mode == PLAN_SCORE_AUTO;
   auto fused = [&](int i) {
     const ReqDesc& d = descs[i];
@@ -185,6 +186,48 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
   }
   plan->raw_floats = raw_need;
   return PLAN_OK;
+}
+
+std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu) {
+  const size_t n_lh = (size_t)pool.n_layers * pool.n_heads;
+  std::vector<FusedLaunch> launches;
+  // One launch per number of query tiles and workgroup shape.  Narrow workgroups
+  // (three or four to a CU) take heads of up to 8192 tokens; wide ones (one to a
+  // CU, three to four times the wavefronts) take the longer heads, whose scores
+  // fill the LDS of a CU, and lists with so few units that narrow workgroups would
+  // leave most of the chip's wavefronts idle.
+  FusedLaunch wide[kPlanClasses], narrow[kPlanClasses];
+  for (int c = 0; c < kPlanClasses; ++c) {
+    const std::vector<int32_t>& list = plan.lists[LIST_FUSED + c];
+    FusedLaunch& to = list.size() * n_lh <= 2 * (size_t)n_cu ? wide[c] : narrow[c];
+    to.units = list;
+    if (pool.score_mode == PLAN_SCORE_AUTO)
+      wide[c].units.insert(wide[c].units.end(), plan.lists[LIST_SNAP + c].begin(), plan.lists[LIST_SNAP + c].end());
+  }
+  if (pool.score_mode == PLAN_SCORE_AUTO) {
+    // units without queries ride in the fullest wide launch
+    int home = 0;
+    for (int c = 1; c < kPlanClasses; ++c)
+      if (wide[c].units.size() > wide[home].units.size()) home = c;
+    const std::vector<int32_t>& list = plan.lists[LIST_KNORM];
+    wide[home].units.insert(wide[home].units.end(), list.begin(), list.end());
+  }
+  for (int w = 1; w >= 0; --w)
+    for (int c = 0; c < kPlanClasses; ++c) {
+      FusedLaunch& l = w ? wide[c] : narrow[c];
+      if (l.units.empty()) continue;
+      l.wide = w != 0;
+      std::stable_sort(l.units.begin(), l.units.end(),
+                       [&](int x, int y) { return plan.weights[x] > plan.weights[y]; });
+      for (int i : l.units) {
+        const ReqDesc& d = plan.descs[i];
+        if (d.method != PLAN_METHOD_STREAMING) l.max_len = std::max(l.max_len, d.seq_len);
+        l.max_blocks = std::max(l.max_blocks, d.n_old);
+        if (d.method == PLAN_METHOD_SNAPKV) l.query_tiles = c;
+      }
+      launches.push_back(std::move(l));
+    }
+  return launches;
 }
 
 int plan_window_lse(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,

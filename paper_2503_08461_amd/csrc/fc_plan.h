@@ -62,6 +62,7 @@ struct CompressPlan {
   int code = PLAN_OK;
   char message[256] = "";
   std::vector<ReqDesc> descs;                 // compressed requests, batch order
+  std::vector<int64_t> weights;               // per descriptor: what its units move, in rows
   std::vector<int32_t> lists[N_LISTS];
   int max_len[N_LISTS] = {};
   int total_new = 0, total_old = 0, total_released = 0;
@@ -75,6 +76,17 @@ struct CompressPlan {
 // Fills `plan`; returns plan->code.  On an error nothing else in the plan is
 // meaningful.  A batch with nothing to compress gives PLAN_OK and no descs.
 int plan_compress(const PoolView& pool, const CompressArgs& args, CompressPlan* plan);
+
+// The launches of the fused kernels (score -> select -> gather in one workgroup
+// per unit) of a planned call, heaviest unit first in each.
+struct FusedLaunch {
+  std::vector<int32_t> units;  // descriptor indices
+  int query_tiles = 0;         // 16-row query tiles of its SnapKV units (0: it holds none)
+  bool wide = false;           // wide workgroups, one per CU
+  int max_len = 0;             // longest head that is scored
+  int max_blocks = 0;          // most blocks of a unit
+};
+std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu);
 
 // fc_window_lse: one descriptor per SnapKV request (all if method is NULL),
 // longest first, queries packed as [n_req][...][window].

@@ -102,7 +102,7 @@ class DeviceWorkload:
         kept = int(wl.budgets[comp].astype(np.int64).sum())
         return n_lh * (tokens * row + kept * 4 * row)
 
-    def kernel_algorithmic_bytes(self, score_mode="auto", fused_max_len=8192):
+    def kernel_algorithmic_bytes(self, score_mode="auto", fused_max_len=32768):
         """Algorithmic bytes per launch of each kernel that moves bulk data,
         following the library's scheduling: with auto, heads of at most
         `fused_max_len` tokens run in the fused kernel (score + gather bytes);
