@@ -20,18 +20,22 @@ __device__ __forceinline__ int clamp_block(int blk, int n_blocks) {
   return ((unsigned)blk < (unsigned)n_blocks) ? blk : 0;
 }
 
-// v + (the same register of another lane of the 16-lane row), by DPP control
+// the same register of another lane of the 16-lane row, by DPP control
 template <int CTRL>
-__device__ __forceinline__ float add_across_row(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+__device__ __forceinline__ float from_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-// sum over the 16 lanes of a row, left in every one of them
-__device__ __forceinline__ float row16_sum(float v) {
-  v = add_across_row<0xB1>(v);   // quad_perm [1,0,3,2]
-  v = add_across_row<0x4E>(v);   // quad_perm [2,3,0,1]
-  v = add_across_row<0x141>(v);  // row_half_mirror: lane i <-> 7 - i of each 8
-  v = add_across_row<0x140>(v);  // row_mirror: lane i <-> 15 - i
-  return v;
+template <int CTRL>
+__device__ __forceinline__ uint32_t from_lane_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+// sum over the four lanes that share lane % 16, left in every one of them:
+// neighbouring rows of 16 change places, then the halves of the wavefront
+__device__ __forceinline__ float quarter_sum(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 __device__ __forceinline__ half8 load_half8(const _Float16* p) {

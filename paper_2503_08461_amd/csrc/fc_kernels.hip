@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p
   const int n_sel = rd.method == 1 /* FC_METHOD_SNAPKV */ ? rd.seq_len - rd.window : rd.seq_len;
   for (int j = threadIdx.x; j < n_sel; j += 64 * kSelectWaves) stage[j] = __float_as_uint(raw[j]);
   __syncthreads();
-  select_unit<kSelectWaves>(p, rd, lh, stage, p.kept + rd.kept_off + (size_t)lh * rd.budget, sh);
+  select_unit<kSelectWaves>(p, rd, lh, stage, lds + stage_words(rd.seq_len), p.kept + rd.kept_off + (size_t)lh * rd.budget, sh);
 }
 
 template <int D>
@@ -200,7 +200,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_all[slot]];
   const int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
-  gather_unit<D, kWaves>(p, rd, lh, p.old_ids + rd.old_off, [&](int t) { return kept[t]; });
+  gather_unit<D, kWaves>(p, rd, lh, [&](int i) { return p.old_ids[rd.old_off + i]; },
+                         [&](int t) { return kept[t]; });
 }
 
 // a fill kernel for small device arrays (flags, verdict words): calls may be
@@ -218,7 +219,7 @@ hipError_t kernels_one_time_setup() {
   // kernels that may need more than the default 64 KiB of dynamic LDS
   // (the narrow fused kernels never do)
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, stage_words(32768) * 4);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (stage_words(32768) + need_words(32768)) * 4);
   if (e == hipSuccess) e = fused_wide_setup_64();
   if (e == hipSuccess) e = fused_wide_setup_128();
   return e;
@@ -318,7 +319,7 @@ hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s) {
 
 hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads;
-  const size_t lds = (size_t)stage_words(max_seq_len) * sizeof(uint32_t);
+  const size_t lds = (size_t)(stage_words(max_seq_len) + need_words(max_seq_len)) * sizeof(uint32_t);
   select_kernel<<<grid, 64 * kSelectWaves, lds, s>>>(p);
   return hipGetLastError();
 }
@@ -327,7 +328,7 @@ hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_b
                         hipStream_t s) {
   if (p.n_fused == 0) return hipSuccess;
   if (max_seq_len > (wide ? kFusedWideMaxLen : kFusedMaxLen)) return hipErrorInvalidValue;
-  const FusedLds f = fused_lds(p.bounded && any_snap, max_seq_len, max_blocks, wide);
+  const FusedLds f = fused_lds(max_seq_len, max_blocks, wide);
   p.ids_at = f.ids_at;
   p.ids_room = f.ids_room;
   const size_t lds = (size_t)f.words * sizeof(uint32_t);

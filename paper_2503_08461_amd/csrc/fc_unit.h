@@ -4,6 +4,8 @@
 // compile side by side).
 #pragma once
 
+#include <type_traits>
+
 #include "fc_device.h"
 
 namespace fc {
@@ -264,8 +266,7 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
         for (int r = 0; r < 4; ++r)
           colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
       }
-      colsum += __shfl_xor(colsum, 16);
-      colsum += __shfl_xor(colsum, 32);
+      colsum = quarter_sum(colsum);
       const int tok = b * 16 + c16;
       if (q4 == 0 && tok < n_prefix) store(tok, colsum);
 #pragma unroll
@@ -350,8 +351,12 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
 // Ownership of tokens: a wavefront owns a contiguous segment (a multiple of 256
 // tokens) and a lane four consecutive tokens of each 256.  What bounds this
 // phase is LDS latency (one workgroup has four wavefronts and every step waits
-// for its reads), so the pooling window of a lane's four tokens comes from three
-// 16-byte reads instead of seven dependent 4-byte reads per token.
+// for its reads) and, for short heads, instruction fetch: the pooling window of a
+// lane's four tokens comes from three 16-byte reads instead of seven dependent
+// 4-byte reads per token, and every sweep is a loop over chunks whose per-token
+// words stay in LDS (with the chunks unrolled and the words in registers the
+// kernels were 200 KB of code against 64 KB of instruction cache, and a head of
+// 640 tokens spent as long in the selection as one of 4000 should).
 
 __device__ __forceinline__ uint32_t score_key(float s) {
   s += 0.0f;  // -0 and +0 compare equal, give them one key
@@ -363,9 +368,6 @@ static constexpr int kBuckets = 2048;
 static constexpr int kBucketBits = 11;
 static constexpr int kMaxCand = 2048;
 static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
-// chunks of a wavefront's segment at most
-template <int WV>
-static constexpr int kChunksPerWave = (kMaxLen<WV> + kChunk * WV - 1) / (kChunk * WV);
 
 // LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
 // that the four-token reads of the pooling may touch (filled with the neutral
@@ -387,6 +389,49 @@ __device__ __forceinline__ void set_lds_words4(uint32_t* p, uint32x4 v) {
 template <int WV>
 __device__ __forceinline__ int segment_tokens(int n) {
   return (((n + WV - 1) / WV) + kChunk - 1) & ~(kChunk - 1);
+}
+
+// Replaces the words of a wavefront's segment [j0, j1) by f(c), which may read any
+// word in reach of a pooling window (at most 31 tokens): a chunk is written only
+// after the next one has been read, and the first and the last, which other
+// wavefronts' windows reach, by finish(), after a barrier.
+struct SegmentRewrite {
+  uint32x4 first, pending;
+  int n = 0;
+  template <typename F>
+  __device__ __forceinline__ void run(uint32_t* stage, int j0, int j1, F f) {
+    const int lane4 = 4 * (threadIdx.x & 63);
+    for (int base = j0; base < j1; base += kChunk, ++n) {  // uniform over the wavefront
+      const int c = base + lane4;
+      uint32x4 v = {0u, 0u, 0u, 0u};
+      if (c < j1) v = f(c);
+      if (n == 0) {
+        first = v;
+      } else {
+        if (n > 1) set_lds_words4(stage + c - kChunk, pending);  // (a chunk before the last is whole)
+        pending = v;
+      }
+    }
+  }
+  __device__ __forceinline__ void finish(uint32_t* stage, int j0, int j1) const {
+    const int c0 = j0 + 4 * (threadIdx.x & 63), c1 = c0 + (n - 1) * kChunk;
+    if (n > 0 && c0 < j1) set_lds_words4(stage + c0, first);
+    if (n > 1 && c1 < j1) set_lds_words4(stage + c1, pending);
+  }
+};
+
+// four bits per lane -> one bit per token of the chunk at `base`
+__device__ __forceinline__ void set_token_bits(uint32_t* map, int base, uint32_t nibble) {
+  const int lane = threadIdx.x & 63;
+  uint32_t bits = nibble << (4 * (lane & 7));
+  bits |= from_lane_u32<0xB1>(bits);   // the other lane of the pair,
+  bits |= from_lane_u32<0x4E>(bits);   // the other pair of the quad,
+  bits |= from_lane_u32<0x141>(bits);  // the other quad of the eight
+  if ((lane & 7) == 0) map[base / 32 + (lane >> 3)] = bits;
+}
+__device__ __forceinline__ uint32_t token_bits(const uint32_t* map, int base) {
+  const int lane = threadIdx.x & 63;
+  return (map[base / 32 + (lane >> 3)] >> (4 * (lane & 7))) & 0xFu;
 }
 
 // Writes `v` to the words around stage[0 .. n) that pooling reads.
@@ -538,15 +583,16 @@ struct SelectShared {
 
 // Selects the kept tokens of one (request, layer, head) and writes them, in
 // ascending order, to `kept` (nullable, global memory) and, over the words of
-// stage[] (the keys are in registers by then), as 16-bit indices for the copy
-// that follows in the same workgroup.  stage[0 .. n_sel): the un-pooled scores as
-// floats, written by this workgroup and made visible by a barrier.  hint_lo,
-// hint_hi: keys that are known to enclose the threshold (0, ~0: nothing is
-// known).  All threads of the workgroup call.
+// stage[] (which hold the keys until a barrier before that), as 16-bit indices for
+// the copy that follows in the same workgroup.  stage[0 .. n_sel): the un-pooled
+// scores as floats, written by this workgroup and made visible by a barrier;
+// map: room for one bit per token.  hint_lo, hint_hi: keys that are known to
+// enclose the threshold (0, ~0: nothing is known).  All threads of the workgroup
+// call.
 template <bool kThree, int WV>
 __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
-                                              uint32_t hint_lo, uint32_t hint_hi) {
+                                              uint32_t* stage, uint32_t* map, int32_t* kept,
+                                              SelectShared<WV>& sh, uint32_t hint_lo, uint32_t hint_hi) {
   int* hist = sh.hist;
   uint32_t* cand = sh.cand;
   int* sel = sh.sel;
@@ -573,68 +619,39 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
   if (tid == 0) sh.n_cand = 0;
   for (int i = tid; i < kBuckets; i += 64 * WV) hist[i] = 0;
   __syncthreads();
-  uint32_t key[kChunksPerWave<WV>][4];
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (c < j1) {
-      const PoolWindow<kThree> pw(stage, c, rd.pool_kernel >> 1, n_sel);
-      uint32_t v[4];
-      if (snap) {
-        pw.template reduce<PoolMaxWord>(v);  // (sums of exponentials: none is negative)
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = pw.mid[e];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t k = score_key(__uint_as_float(v[e]));
-        key[i][e] = k;
-        if (c + e < j1) {
-          kmin = min(kmin, k);
-          kmax = max(kmax, k);
-        }
-      }
-    }
-  }
-  if (out) {
-    // back through LDS, so that the stores are contiguous over the lanes
+  int n_above = 0, n_reach = 0;  // keys above the hinted range, keys not below it
+  SegmentRewrite keys;
+  keys.run(stage, j0, j1, [&](int c) {
+    const PoolWindow<kThree> pw(stage, c, rd.pool_kernel >> 1, n_sel);
+    uint32_t v[4];
     if (snap) {
-      __syncthreads();
+      pw.template reduce<PoolMaxWord>(v);  // (sums of exponentials: none is negative)
+    } else {
 #pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-          uint32x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = key[i][e] & 0x7FFFFFFFu;
-          set_lds_words4(stage + c, w);
-        }
-      }
-      __syncthreads();
-      for (int j = n_sel + tid; j < L; j += 64 * WV) out[j] = INFINITY;
+      for (int e = 0; e < 4; ++e) v[e] = pw.mid[e];
     }
-    for (int j = tid; j < n_sel; j += 64 * WV) out[j] = __uint_as_float(stage[j]);
-  }
+    uint32x4 k4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint32_t k = 0u;  // no token: below every key
+      if (c + e < j1) {
+        k = score_key(__uint_as_float(v[e]));
+        kmin = min(kmin, k);
+        kmax = max(kmax, k);
+        n_above += k > hint_hi ? 1 : 0;
+        n_reach += k >= hint_lo ? 1 : 0;
+      }
+      k4[e] = k;
+    }
+    return k4;
+  });
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
     kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-  }
-  // how many keys lie above the hinted range, and how many not below it
-  int n_above = 0, n_reach = 0;
-  if (hint_lo != 0u) {  // uniform
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (j0 + i * kChunk >= j1) break;  // uniform over the wavefront
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        n_above += __popcll(__ballot(c + e < j1 && key[i][e] > hint_hi));
-        n_reach += __popcll(__ballot(c + e < j1 && key[i][e] >= hint_lo));
-      }
-    }
+    n_above += __shfl_xor(n_above, o);
+    n_reach += __shfl_xor(n_reach, o);
   }
   if (lane == 0) {
     sh.wmin[wave] = kmin;
@@ -643,6 +660,15 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     sh.cnt[wave][1] = n_reach;
   }
   __syncthreads();
+  keys.finish(stage, j0, j1);
+  if (out) {
+    __syncthreads();
+    for (int j = tid; j < n_sel; j += 64 * WV) {
+      const uint32_t k = stage[j];
+      out[j] = __uint_as_float((k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k);
+    }
+    for (int j = n_sel + tid; j < L; j += 64 * WV) out[j] = INFINITY;
+  }
   n_above = n_reach = 0;
 #pragma unroll
   for (int w = 0; w < WV; ++w) {
@@ -653,35 +679,35 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
   }
   // the k_sel-th largest key lies in the hinted range: search only there
   const bool narrowed = n_above < k_sel && n_reach >= k_sel;  // uniform
-  // (every read of stage[] lies before the barrier above)
-  if (snap)
-    for (int j = tid; j < rd.window; j += 64 * WV) keep_token(k_sel + j, n_sel + j);  // forced window
-  if (k_sel == 0) return;  // only the window is kept (uniform across the workgroup)
   if (narrowed) {
     kmin = max(kmin, hint_lo);
     kmax = min(kmax, hint_hi);
   }
 
-  // ---- 2. threshold = k_sel-th largest key ---------------------------------------
-  // one pass over the registers: the keys in [lo, lo + width) into 2048 buckets (width 0: up to kmax)
-  auto count_keys = [&](uint32_t lo, int shift, uint32_t width) {
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
+  int t0 = 0;  // where this wavefront's kept tokens begin in the list
+  if (k_sel > 0) {  // uniform
+    // ---- 2. threshold = k_sel-th largest key -------------------------------------
+    // each sweep: this wavefront's keys, four per lane, 0 where there is no token
+    auto sweep = [&](auto f) {
+      for (int base = j0; base < j1; base += kChunk) {  // uniform over the wavefront
+        const int c = base + 4 * lane;
+        uint32x4 k4 = {0u, 0u, 0u, 0u};
+        if (c < j1) k4 = lds_words4(stage + c);
+        f(base, k4);
+      }
+    };
+    // the keys in [lo, lo + width) into 2048 buckets (width 0: up to kmax)
+    auto count_keys = [&](uint32_t lo, int shift, uint32_t width) {
+      sweep([&](int, uint32x4 k4) {
         uint32_t b[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const uint32_t k = key[i][e], d = k - lo;
-          b[e] = c + e < j1 && k >= lo && (width == 0u ? k <= kmax : d < width) ? d >> shift : kNoBucket;
+          const uint32_t k = k4[e], d = k - lo;
+          b[e] = k >= lo && k != 0u && (width == 0u ? k <= kmax : d < width) ? d >> shift : kNoBucket;
         }
         hist_add4(hist, b);
-      }
-    }
-  };
-  uint32_t thr;
-  int need_eq;
-  {
+      });
+    };
     uint32_t lo = kmin;
     const uint32_t range = kmax - kmin;
     int shift = range ? max(0, 32 - __clz(range) - kBucketBits) : 0;
@@ -692,20 +718,16 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     uint32_t bkt = (uint32_t)sel[0];
     if (shift > 0) {
       // candidates: the keys of that one bucket
+      sweep([&](int, uint32x4 k4) {
 #pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t k = key[i][e];
-            if (c + e < j1 && k >= lo && k <= kmax && ((k - lo) >> shift) == bkt) {
-              const int pos = atomicAdd(&sh.n_cand, 1);
-              if (pos < kMaxCand) cand[pos] = k;
-            }
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t k = k4[e];
+          if (k >= lo && k != 0u && k <= kmax && ((k - lo) >> shift) == bkt) {
+            const int pos = atomicAdd(&sh.n_cand, 1);
+            if (pos < kMaxCand) cand[pos] = k;
           }
         }
-      }
+      });
       __syncthreads();
       const int nc = sh.n_cand;
       const bool listed = nc <= kMaxCand;  // else refine over all keys with a range check
@@ -729,73 +751,83 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
         bkt = (uint32_t)sel[0];
       }
     }
-    thr = lo + bkt;
-    need_eq = remaining;
-  }
+    const uint32_t thr = lo + bkt;
+    const int need_eq = remaining;
 
-  // ---- 3. ordered compaction ------------------------------------------------------
-  int n_gt = 0, n_eq = 0;
+    // ---- 3. which tokens are kept, one bit each -----------------------------------
+    int n_gt = 0, n_eq = 0;
+    sweep([&](int, uint32x4 k4) {
 #pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk >= j1) break;
+      for (int e = 0; e < 4; ++e) {
+        n_gt += __popcll(__ballot(k4[e] > thr));
+        n_eq += __popcll(__ballot(k4[e] == thr));
+      }
+    });
+    if (lane == 0) {
+      sh.cnt[wave][0] = n_gt;
+      sh.cnt[wave][1] = n_eq;
+    }
+    __syncthreads();
+    int gt_before = 0, eq_before = 0;
+    for (int w = 0; w < wave; ++w) {
+      gt_before += sh.cnt[w][0];
+      eq_before += sh.cnt[w][1];
+    }
+    t0 = gt_before + min(eq_before, need_eq);
+    int eq_run = eq_before;
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    sweep([&](int base, uint32x4 k4) {
+      // (lanes are in token order, each with its four tokens in order)
+      uint64_t eq[4];
+      int eq_rank = eq_run;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      n_gt += __popcll(__ballot(c + e < j1 && key[i][e] > thr));
-      n_eq += __popcll(__ballot(c + e < j1 && key[i][e] == thr));
+      for (int e = 0; e < 4; ++e) {
+        eq[e] = __ballot(k4[e] == thr);
+        eq_rank += __popcll(eq[e] & lt_mask);
+        eq_run += __popcll(eq[e]);
+      }
+      uint32_t nibble = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool is_eq = k4[e] == thr;
+        if (k4[e] > thr || (is_eq && eq_rank < need_eq)) nibble |= 1u << e;
+        eq_rank += is_eq ? 1 : 0;
+      }
+      set_token_bits(map, base, nibble);
+    });
+  }
+  __syncthreads();  // nobody reads a key any more: the kept list takes over the words
+
+  // ---- 4. the list ------------------------------------------------------------------
+  if (k_sel > 0) {
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    for (int base = j0; base < j1; base += kChunk) {
+      const uint32_t nibble = token_bits(map, base);
+      int at = t0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t kp = __ballot((nibble >> e) & 1u);
+        at += __popcll(kp & lt_mask);
+        t0 += __popcll(kp);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((nibble >> e) & 1u) keep_token(at++, base + 4 * lane + e);
     }
   }
-  if (lane == 0) {
-    sh.cnt[wave][0] = n_gt;
-    sh.cnt[wave][1] = n_eq;
-  }
-  __syncthreads();
-  int gt_before = 0, eq_before = 0;
-  for (int w = 0; w < wave; ++w) {
-    gt_before += sh.cnt[w][0];
-    eq_before += sh.cnt[w][1];
-  }
-  int eq_run = eq_before;
-  int kept_run = gt_before + min(eq_before, need_eq);
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk >= j1) break;
-    // (lanes are in token order, each with its four tokens in order)
-    uint64_t eq[4], kp[4];
-    int eq_rank = eq_run;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      eq[e] = __ballot(c + e < j1 && key[i][e] == thr);
-      eq_rank += __popcll(eq[e] & lt_mask);
-      eq_run += __popcll(eq[e]);
-    }
-    bool keep[4];
-    int at = kept_run;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool is_eq = (eq[e] >> lane) & 1u;
-      keep[e] = (c + e < j1 && key[i][e] > thr) || (is_eq && eq_rank < need_eq);
-      eq_rank += is_eq ? 1 : 0;
-      kp[e] = __ballot(keep[e]);
-      at += __popcll(kp[e] & lt_mask);
-      kept_run += __popcll(kp[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (keep[e]) keep_token(at++, c + e);
-  }
+  if (snap)
+    for (int j = tid; j < rd.window; j += 64 * WV) keep_token(k_sel + j, n_sel + j);  // forced window
 }
 
 template <int WV>
 __device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            uint32_t* stage, int32_t* kept, SelectShared<WV>& sh,
-                                            uint32_t hint_lo = 0u, uint32_t hint_hi = 0xFFFFFFFFu) {
+                                            uint32_t* stage, uint32_t* map, int32_t* kept,
+                                            SelectShared<WV>& sh, uint32_t hint_lo = 0u,
+                                            uint32_t hint_hi = 0xFFFFFFFFu) {
   if (rd.pool_kernel == 7)  // uniform
-    select_unit_h<true, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
+    select_unit_h<true, WV>(p, rd, lh, stage, map, kept, sh, hint_lo, hint_hi);
   else
-    select_unit_h<false, WV>(p, rd, lh, stage, kept, sh, hint_lo, hint_hi);
+    select_unit_h<false, WV>(p, rd, lh, stage, map, kept, sh, hint_lo, hint_hi);
 }
 
 // ---------------------------------------------------------------------------
@@ -866,7 +898,8 @@ struct BoundKeep {  // what survives into the selection's LDS
 // is at most 1; where the squares left the fp32 range, or c is too small for
 // them to be trusted, k = 4095 says just that).
 __device__ __forceinline__ uint32_t pack_sums(float c, float s2) {
-  const float r = sqrtf(s2) / c;  // not a number <= 1 when c is 0 or either sum overflowed
+  // (hardware square root and reciprocal, 1 ulp each: the two steps added to k are 5e-4 of c)
+  const float r = __builtin_amdgcn_sqrtf(s2) * __builtin_amdgcn_rcpf(c);  // not a number <= 1 when c is 0 or either sum overflowed
   const uint32_t k = (c >= 1.0e-12f && r <= 1.f) ? min(4095u, (uint32_t)(r * 4095.f) + 2u) : 4095u;
   return (__float_as_uint(c) & 0xFFFFF000u) | k;
 }
@@ -909,32 +942,74 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   const int n_prefix = L - W;
   const int n_unmasked = n_prefix >> 4;
   auto load_block = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
+    // (the block is the wavefront's: scalar address arithmetic)
+    const int blk = __builtin_amdgcn_readfirstlane(old_ids[b]);
     const _Float16* kp = kbase + (size_t)blk * blk_stride;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8(kp + ks * 32);
   };
 
+  // Lane (q4, c16) holds the logits of token c16 of a block for the rows
+  // 16 nt + 4 q4 + r: sums over the rows are in-lane adds, and row sums stay in
+  // registers until a renewal.
   const int seg = bound_seg<WV>(L);
-  float ref[NT], zacc[NT];
+  float z[NT][4];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    ref[nt] = 0.f;
-    zacc[nt] = 0.f;
-  }
-  // the wavefront's row sums in absolute log2 units -> pub[buf]
-  auto publish = [&](int buf) {
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float zr = zacc[nt];
-      zr += __shfl_xor(zr, 16);
-      zr += __shfl_xor(zr, 32);
-      // (a sum that is not a number stays one: see merged)
-      if (q4 == 0) bs.pub[buf][wave][nt * 16 + c16] = zr == 0.f ? -INFINITY : ref[nt] + log2f(zr);
+    for (int r = 0; r < 4; ++r) z[nt][r] = 0.f;
+  // One row per lane at renewals: the row 16 nt + 4 q4 + r belongs to the lanes
+  // with c16 = 4 nt + r (modulo kRows), which is where the reduction below leaves
+  // its sum.
+  constexpr int kRows = NT == 1 ? 4 : NT == 2 ? 8 : 16;
+  const int my_slot = c16 & (kRows - 1);
+  const int my_row = (my_slot >> 2) * 16 + q4 * 4 + (my_slot & 3);
+  float my_ref = 0.f, my_share = -INFINITY;  // its reference; log2 of this wavefront's sum so far
+  // sums of z[][] over the 16 lanes of a DPP row: plain additions while there are
+  // fewer values than lanes, then halving exchanges
+  auto row_sums = [&]() -> float {
+    float v[kRows];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) v[i] = i < 4 * NT ? z[(i / 4) % NT][i % 4] : 0.f;
+    const bool b3 = c16 & 8, b2 = c16 & 4, b1 = c16 & 2, b0 = c16 & 1;
+    if constexpr (kRows == 16) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        v[i] = (b3 ? v[i + 8] : v[i]) + from_lane<0x140>(b3 ? v[i] : v[i + 8]);  // row_mirror: bit 3 flips
+    } else {
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) v[i] += from_lane<0x140>(v[i]);
     }
+    if constexpr (kRows >= 8) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        v[i] = (b2 ? v[i + 4] : v[i]) + from_lane<0x141>(b2 ? v[i] : v[i + 4]);  // row_half_mirror: bit 2
+    } else {
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) v[i] += from_lane<0x141>(v[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      v[i] = (b1 ? v[i + 2] : v[i]) + from_lane<0x4E>(b1 ? v[i] : v[i + 2]);  // quad_perm [2,3,0,1]
+    return (b0 ? v[1] : v[0]) + from_lane<0xB1>(b0 ? v[0] : v[1]);           // quad_perm [1,0,3,2]
   };
-  // log2 of the workgroup's row sum from the published shares; own = this wavefront's share
-  auto merged = [&](int buf, int row, float& own) {
+  // this wavefront's row sums so far, absolute log2 -> pub[buf]; starts new ones
+  auto publish = [&](int buf) {
+    const float zs = row_sums();
+    // (a sum that is not a number stays one: see merged)
+    const float l = zs == 0.f ? -INFINITY : my_ref + log2f(zs);
+    const float mx = fmaxf(my_share, l);
+    const float both = (my_share == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(my_share - mx)) +
+                       (l == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l - mx));
+    my_share = both == 0.f ? -INFINITY : mx + log2f(both);
+    bs.pub[buf][wave][my_row] = my_share;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[nt][r] = 0.f;
+  };
+  // log2 of the workgroup's row sum from the published shares
+  auto merged = [&](int buf, int row) {
     float l[WV];
     float mx = -INFINITY;
 #pragma unroll
@@ -942,9 +1017,6 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
       l[w] = bs.pub[buf][w][row];
       mx = fmaxf(mx, l[w]);
     }
-    own = l[0];
-#pragma unroll
-    for (int w = 1; w < WV; ++w) own = wave == w ? l[w] : own;
     // Numerators that overflowed make a share infinite and the sum below not a
     // number; from there on that row's references, sums and log-sum-exp are none
     // either, which is how the head is found to need the two-pass code.
@@ -956,82 +1028,82 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
 
   const int T = (nb + WV - 1) / WV;  // steps; every wavefront walks all of them
   int epoch = 0, buf = 0;
-  half8 kc[KS], kn[KS];
-  if (wave < nb) load_block(wave, kc);
-  for (int t = 0; t < T; ++t) {
+  // one block's numerators.  kMode 0: the first block, no reference yet; 1: a
+  // block before the window; 2: one that reaches into it
+  auto numerators = [&](auto mode, int b, const half8 (&kc)[KS]) {
+    constexpr int kMode = decltype(mode)::value;
+    const int tok = b * 16 + c16;
+    float cs = 0.f, ss = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
+      floatx4* const at = reinterpret_cast<floatx4*>(&bs.pub[buf][wave][nt * 16 + q4 * 4]);
+      floatx4 ref;
+      if constexpr (kMode == 0) {
+        // the logits of the block's first token (none of the block's is masked; they
+        // all get the trivial bounds, whatever they accumulate here)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          ref[r] = nt * 16 + q4 * 4 + r < W ? from_lane<0x150>(acc[r] * c)  // row_newbcast:0
+                                            : INFINITY;                    // (padded rows: every numerator 0)
+        if (c16 == 0) *at = ref;
+      } else {
+        ref = *at;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float x = fmaf(acc[r], c, -ref[r]);
+        if constexpr (kMode == 2)  // query i at position L - W + i
+          if (tok > L - W + nt * 16 + q4 * 4 + r) x = -INFINITY;
+        const float e = __builtin_amdgcn_exp2f(x);
+        z[nt][r] += e;
+        cs += e;
+        ss = fmaf(e, e, ss);
+      }
+    }
+    cs = quarter_sum(cs);
+    ss = quarter_sum(ss);
+    if (q4 == 0 && tok < n_prefix) reinterpret_cast<uint32_t*>(stage)[tok] = pack_sums(cs, ss);
+  };
+  // one step: kc holds this wavefront's block b, kn takes the next one
+  auto step = [&](int t, const half8 (&kc)[KS], half8 (&kn)[KS]) {
     const int b = wave + WV * t;
     if (b + WV < nb) load_block(b + WV, kn);
     if (bound_renews_before(t, seg)) {  // uniform over the workgroup
+      if (t == 1) my_ref = bs.pub[buf][wave][my_row];
       publish(buf);
       __syncthreads();
       ++epoch;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int row = nt * 16 + c16;
-        float own;
-        const float nr = merged(buf, row, own);
-        zacc[nt] = (q4 == 0 && own != -INFINITY) ? __builtin_amdgcn_exp2f(own - nr) : 0.f;
-        ref[nt] = nr;
-        if (wave == 0 && q4 == 0) bs.ref[epoch][row] = nr;
-      }
-      buf ^= 1;  // the other buffer is written next: its readers passed a barrier since
+      const float nr = merged(buf, my_row);
+      if (wave == 0) bs.ref[epoch][my_row] = nr;
+      my_ref = my_row < W ? nr : INFINITY;
+      // to the lanes that use it, through the wavefront's own words of the other
+      // buffer (its readers of the last renewal have passed a barrier since)
+      buf ^= 1;
+      bs.pub[buf][wave][my_row] = my_ref;
     }
-    if (b < nb) {  // uniform per wavefront
-      float cs[4] = {0.f, 0.f, 0.f, 0.f}, ss[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kc[ks], qreg[nt][ks], acc, 0, 0, 0);
-        float tv[4];
-        const bool row_ok = nt * 16 + c16 < W;  // padded rows carry no weight
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tv[r] = row_ok ? acc[r] * c : -INFINITY;
-        if (b >= n_unmasked) {
-          const int limit = L - W + nt * 16 + c16;
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (b * 16 + q4 * 4 + r > limit) tv[r] = -INFINITY;
-        }
-        if (t == 0) {
-          // no reference yet: the block's own row maximum (these tokens get the
-          // trivial bounds, whatever they accumulate here)
-          float bm = fmaxf(fmaxf(tv[0], tv[1]), fmaxf(tv[2], tv[3]));
-          bm = fmaxf(bm, __shfl_xor(bm, 16));
-          bm = fmaxf(bm, __shfl_xor(bm, 32));
-          ref[nt] = bm == -INFINITY ? 0.f : bm;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float e = __builtin_amdgcn_exp2f(tv[r] - ref[nt]);
-          zacc[nt] += e;
-          cs[r] += e;
-          ss[r] = fmaf(e, e, ss[r]);
-        }
-      }
-      // sums over the window rows (the lanes of a row of 16, after the tiles in
-      // the lane); lane c16 < 4 of each row keeps those of token 4 q4 + c16
-      float mc = 0.f, ms = 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float vc = row16_sum(cs[r]);
-        const float vs = row16_sum(ss[r]);
-        mc = c16 == r ? vc : mc;
-        ms = c16 == r ? vs : ms;
-      }
-      const int tok = b * 16 + q4 * 4 + c16;
-      if (c16 < 4 && tok < n_prefix) reinterpret_cast<uint32_t*>(stage)[tok] = pack_sums(mc, ms);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
+    if (b < n_unmasked)  // uniform per wavefront
+      numerators(std::integral_constant<int, 1>{}, b, kc);
+    else if (b < nb)
+      numerators(std::integral_constant<int, 2>{}, b, kc);
+  };
+  static_assert(kBoundMinLen<WV> - 64 >= 16 * WV, "the first step lies before the window");
+  half8 ka[KS], kb[KS];
+  load_block(wave, ka);
+  if (wave + WV < nb) load_block(wave + WV, kb);
+  numerators(std::integral_constant<int, 0>{}, wave, ka);
+  for (int t = 1; t < T; t += 2) {
+    step(t, kb, ka);
+    if (t + 1 < T) step(t + 1, ka, kb);
   }
   publish(buf);
   __syncthreads();
   if (threadIdx.x < 64) {
     const int row = threadIdx.x;
-    float own;
-    const float lse = merged(buf, row, own);
+    const float lse = merged(buf, row);
     bs.fin[row] = row < W ? lse : INFINITY;  // padded rows contribute exp2(-inf) = 0
     if (row < W && !(fabsf(lse) < 3.0e38f)) keep.bad = 1;
   }
@@ -1185,8 +1257,7 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
 #pragma unroll
       for (int r = 0; r < 4; ++r) colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
     }
-    colsum += __shfl_xor(colsum, 16);
-    colsum += __shfl_xor(colsum, 32);
+    colsum = quarter_sum(colsum);
     if (q4 == 0 && tok_c >= 0) stage[tok_c] = colsum;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -1225,15 +1296,11 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
   static_assert(kMaxCand >= kBuckets, "the candidate list doubles as the second histogram");
   fill_stage_margins(stage, n_sel, 0u);
   uint32_t vmax = 0u;
+  for (int c = j0 + 4 * lane; c < j1; c += kChunk) {
+    const uint32x4 w = lds_words4(stage + c);
 #pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (c < j1) {
-      const uint32x4 w = lds_words4(stage + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (c + e < j1) vmax = max(vmax, w[e] & 0xFFFF0000u);
-    }
+    for (int e = 0; e < 4; ++e)
+      if (c + e < j1) vmax = max(vmax, w[e] & 0xFFFF0000u);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, o));
@@ -1246,32 +1313,26 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
 #pragma unroll
   for (int w = 0; w < WV; ++w) vmax = max(vmax, sh.wmax[w]);
   const bool trivial = k_sel <= 0 || k_sel >= n_sel;  // uniform: window only, or everything is kept
-  uint64_t named = 0;  // this lane's tokens, four bits per chunk
-  static_assert(4 * kChunksPerWave<WV> <= 64, "a lane's bits");
   if (!trivial) {
     // thresholds: the buckets that hold the k_sel-th largest lower and the k_sel-th
     // largest upper bound (two histograms from one evaluation of the pooled bounds);
     // buckets of 2^shift bit patterns from kmin upwards, what lies below kmin counts in bucket 0
     auto find_buckets = [&](uint32_t kmin, int shift) {
+      for (int c = j0 + 4 * lane; c < j1; c += kChunk) {
+        const PoolWindow<kThree> pw(stage, c, h, n_sel);
+        uint32_t hi[4], lo[4];
+        pw.template reduce<PoolMaxWord>(hi);
+        pw.template reduce<PoolMaxLow>(lo);
+        // (no bound exceeds the largest upper bound; the clamp keeps the index in range whatever the bounds hold)
 #pragma unroll
-      for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-        const int c = j0 + i * kChunk + 4 * lane;
-        if (c < j1) {
-          const PoolWindow<kThree> pw(stage, c, h, n_sel);
-          uint32_t hi[4], lo[4];
-          pw.template reduce<PoolMaxWord>(hi);
-          pw.template reduce<PoolMaxLow>(lo);
-          // (no bound exceeds the largest upper bound; the clamp keeps the index in range whatever the bounds hold)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t kh = hi[e] & 0xFFFF0000u, kl = lo[e] << 16;
-            hi[e] = kh > kmin ? min((kh - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
-            lo[e] = kl > kmin ? min((kl - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
-            if (c + e >= j1) hi[e] = lo[e] = kNoBucket;
-          }
-          hist_add4(hist_hi, hi);
-          hist_add4(hist_lo, lo);
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t kh = hi[e] & 0xFFFF0000u, kl = lo[e] << 16;
+          hi[e] = kh > kmin ? min((kh - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
+          lo[e] = kl > kmin ? min((kl - kmin) >> shift, (uint32_t)kBuckets - 1u) : 0u;
+          if (c + e >= j1) hi[e] = lo[e] = kNoBucket;
         }
+        hist_add4(hist_hi, hi);
+        hist_add4(hist_lo, lo);
       }
       __syncthreads();
       bucket_of_rank<WV>(hist_lo, k_sel, sh.wsum, sh.sel);
@@ -1310,69 +1371,47 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
     key_hi = t_hi | 0x80000000u;
     // the low half of every undecided token's word becomes its pooled lower bound,
     // of every other token's 0xFFFF
-    uint32_t low[kChunksPerWave<WV>][2];
+    SegmentRewrite words;
+    words.run(stage, j0, j1, [&](int c) {
+      const PoolWindow<kThree> pw(stage, c, h, n_sel);
+      uint32_t hi[4], lo[4];
+      pw.template reduce<PoolMaxWord>(hi);
+      pw.template reduce<PoolMaxLow>(lo);
+      uint32x4 w;
 #pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        const PoolWindow<kThree> pw(stage, c, h, n_sel);
-        uint32_t hi[4], lo[4];
-        pw.template reduce<PoolMaxWord>(hi);
-        pw.template reduce<PoolMaxLow>(lo);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e >= j1 || (hi[e] & 0xFFFF0000u) < t_lo || (lo[e] << 16) > t_hi) lo[e] = 0xFFFFu;
-        low[i][0] = lo[0] | (lo[1] << 16);
-        low[i][1] = lo[2] | (lo[3] << 16);
+      for (int e = 0; e < 4; ++e) {
+        if (c + e >= j1 || (hi[e] & 0xFFFF0000u) < t_lo || (lo[e] << 16) > t_hi) lo[e] = 0xFFFFu;
+        w[e] = (pw.mid[e] & 0xFFFF0000u) | lo[e];
       }
-    }
+      return w;
+    });
     __syncthreads();  // the lower bounds have been read by everyone
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
-      if (c < j1) {
-        uint32x4 w = lds_words4(stage + c);
-        w[0] = (w[0] & 0xFFFF0000u) | (low[i][0] & 0xFFFFu);
-        w[1] = (w[1] & 0xFFFF0000u) | (low[i][0] >> 16);
-        w[2] = (w[2] & 0xFFFF0000u) | (low[i][1] & 0xFFFFu);
-        w[3] = (w[3] & 0xFFFF0000u) | (low[i][1] >> 16);
-        set_lds_words4(stage + c, w);
-      }
-    }
+    words.finish(stage, j0, j1);
     if (tid < kStageFront) stage[tid - kStageFront] = 0xFFFFu;
     if (tid < 4) stage[((n_sel + 3) & ~3) + tid] = 0xFFFFu;  // (the last group's own words are set above)
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-      const int c = j0 + i * kChunk + 4 * lane;
+    for (int base = j0; base < j1; base += kChunk) {  // uniform over the wavefront
+      const int c = base + 4 * lane;
+      uint32_t named = 0u;
       if (c < j1) {
         const PoolWindow<kThree> pw(stage, c, h, n_sel);
         uint32_t least[4];
         pw.template reduce<PoolMinLow>(least);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (c + e < j1 && (pw.mid[e] >> 16) >= least[e]) named |= 1ull << (4 * i + e);
+          if (c + e < j1 && (pw.mid[e] >> 16) >= least[e]) named |= 1u << e;
       }
+      set_token_bits(need, base, named);
     }
     __syncthreads();  // (the low halves are about to go)
+  } else {
+    for (int base = j0; base < j1; base += kChunk) set_token_bits(need, base, 0u);
   }
+  for (int c = j0 + 4 * lane; c < j1; c += kChunk) {
+    uint32x4 w = lds_words4(stage + c);
 #pragma unroll
-  for (int i = 0; i < kChunksPerWave<WV>; ++i) {
-    const int c = j0 + i * kChunk + 4 * lane;
-    if (j0 + i * kChunk < j1) {  // uniform over the wavefront
-      // eight lanes' nibbles make one word of the bit map
-      uint32_t bits = (uint32_t)((named >> (4 * i)) & 0xFu) << (4 * (lane & 7));
-      bits |= __shfl_xor(bits, 1);
-      bits |= __shfl_xor(bits, 2);
-      bits |= __shfl_xor(bits, 4);
-      if ((lane & 7) == 0) need[(j0 + i * kChunk) / 32 + (lane >> 3)] = bits;
-    }
-    if (c < j1) {
-      uint32x4 w = lds_words4(stage + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
-      set_lds_words4(stage + c, w);
-    }
+    for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
+    set_lds_words4(stage + c, w);
   }
   __syncthreads();
 }
@@ -1422,9 +1461,9 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 // (kept index, block id, row) when it is not; the rows of a wavefront's next
 // block are therefore requested before those of this one are stored.
 
-template <int D, int WV, typename KeptAt>
+template <int D, int WV, typename BlockAt, typename KeptAt>
 __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            const int32_t* old_ids, KeptAt kept_at) {
+                                            BlockAt block_at, KeptAt kept_at) {
   constexpr int LPR = D / 8;
   constexpr int RPI = 64 / LPR;
   constexpr int NI = 16 / RPI;
@@ -1433,8 +1472,6 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
   const int B = rd.budget;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // destination blocks: freshly popped ones, or the request's own first blocks
-  const int32_t* new_ids = p.in_place ? old_ids : p.new_ids + rd.new_off;
   const size_t chunk = (size_t)16 * D;               // one (block, kv, head)
   const size_t v_off = (size_t)p.n_heads * chunk;    // K chunk -> V chunk of a block
   const size_t blk_stride = 2 * v_off;
@@ -1447,14 +1484,15 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
       // (slots past the budget load the last kept row again and drop it)
       const int t = min(nbk * 16 + k * RPI + row_in_instr, B - 1);
       const int idx = min(max(kept_at(t), 0), rd.seq_len - 1);
-      const int sblk = clamp_block(old_ids[idx >> 4], p.n_blocks);
+      const int sblk = clamp_block(block_at(idx >> 4), p.n_blocks);
       const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
       kk[k] = load_half8_nt(src);
       vv[k] = load_half8_nt(src + v_off);
     }
   };
   auto store = [&](int nbk, const half8 (&kk)[NI], const half8 (&vv)[NI]) {
-    const int dblk = clamp_block(new_ids[nbk], p.n_blocks);
+    // freshly popped blocks, or the request's own first ones
+    const int dblk = clamp_block(p.in_place ? block_at(nbk) : p.new_ids[rd.new_off + nbk], p.n_blocks);
     _Float16* dst = base + (size_t)dblk * blk_stride;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
@@ -1493,6 +1531,18 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
   }
 }
 
+// The copy at the end of a fused kernel: the kept list is where the selection
+// left it in LDS, streaming units compute theirs; ids_in_lds: sm_ids holds the
+// block ids (streaming units may have more blocks than fit).
+template <int D, int WV>
+__device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc& rd, int lh,
+                                             const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds) {
+  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
+  const bool streaming = rd.method == 3 /* FC_METHOD_STREAMING */;  // uniform
+  gather_unit<D, WV>(p, rd, lh, [&](int i) { return ids_in_lds ? sm_ids[i] : p.old_ids[rd.old_off + i]; },
+                     [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
+}
+
 // ---------------------------------------------------------------------------
 // fused per-unit kernel: score -> select -> gather in one workgroup
 // ---------------------------------------------------------------------------
@@ -1519,6 +1569,7 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
   const ReqDesc rd = p.descs[p.order_fused[slot]];
   uint32_t* words = lds + kStageFront;
   float* stage = reinterpret_cast<float*>(words);
+  uint32_t* map = lds + stage_words(rd.seq_len);  // one bit per token
   // the request's block ids, read once per workgroup (every later use is an LDS read)
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
@@ -1529,23 +1580,20 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
     streaming_unit<WV>(p, rd, lh, kept);
-    gather_unit<D, WV>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
-                       [&](int t) { return streaming_token(rd, p.n_sink, t); });
-    return;
-  }
-  bool snap = false;
-  if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
-  if (snap) {
-    if constexpr (NT > 0)
-      snapkv_unit<D, NT, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
   } else {
-    knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+    bool snap = false;
+    if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
+    if (snap) {
+      if constexpr (NT > 0)
+        snapkv_unit<D, NT, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
+    } else {
+      knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+    }
+    __syncthreads();
+    select_unit<WV>(p, rd, lh, words, map, kept, sh.select);
   }
-  __syncthreads();
-  select_unit<WV>(p, rd, lh, words, kept, sh.select);
   __syncthreads();  // the kept list is complete
-  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
-  gather_unit<D, WV>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
+  gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
 }
 
 // The fused kernel with the pruned second pass for its SnapKV units (see
@@ -1567,7 +1615,7 @@ __global__ __launch_bounds__(64 * WV, WV == kNarrow ? 3 : WV / 4) void fused_bou
   const ReqDesc rd = p.descs[p.order_fused[slot]];
   uint32_t* words = lds + kStageFront;  // per token: its bounds, then its score
   float* stage = reinterpret_cast<float*>(words);
-  uint32_t* need = lds + stage_words(rd.seq_len);
+  uint32_t* map = lds + stage_words(rd.seq_len);  // one bit per token
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
   const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
@@ -1578,48 +1626,44 @@ __global__ __launch_bounds__(64 * WV, WV == kNarrow ? 3 : WV / 4) void fused_bou
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
     streaming_unit<WV>(p, rd, lh, kept);
-    gather_unit<D, WV>(p, rd, lh, ids_in_lds ? sm_ids : p.old_ids + rd.old_off,
-                       [&](int t) { return streaming_token(rd, p.n_sink, t); });
-    return;
-  }
-  uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
-  if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
-    constexpr int KS = D / 32;
-    const int q4 = (threadIdx.x & 63) >> 4;
-    half8 qreg[NT][KS];
-    load_window_queries<D, NT>(p, rd, lh, qreg);
-    const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
-    if (prune) snapkv_bounds<D, NT, WV>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
-    if (!prune || keep.bad) {  // bad: not representable against a running reference
-      snapkv_unit_q<D, NT, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
-    } else {
-      float mrow[NT][4];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.bound.fin[nt * 16 + q4 * 4 + r];
-      __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
-      bound_classify<WV>(rd, words, need, sh.select, key_lo, key_hi);
-      snapkv_rescore<D, NT, WV>(p, rd, lh, sm_ids, need, stage, qreg, mrow);
-    }
   } else {
-    knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+    uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
+    if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
+      constexpr int KS = D / 32;
+      const int q4 = (threadIdx.x & 63) >> 4;
+      half8 qreg[NT][KS];
+      load_window_queries<D, NT>(p, rd, lh, qreg);
+      const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
+      if (prune) snapkv_bounds<D, NT, WV>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
+      if (!prune || keep.bad) {  // bad: not representable against a running reference
+        snapkv_unit_q<D, NT, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
+      } else {
+        float mrow[NT][4];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.bound.fin[nt * 16 + q4 * 4 + r];
+        __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
+        bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
+        snapkv_rescore<D, NT, WV>(p, rd, lh, sm_ids, map, stage, qreg, mrow);
+      }
+    } else {
+      knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+    }
+    __syncthreads();
+    select_unit<WV>(p, rd, lh, words, map, kept, sh.select, key_lo, key_hi);
   }
-  __syncthreads();
-  select_unit<WV>(p, rd, lh, words, kept, sh.select, key_lo, key_hi);
   __syncthreads();  // the kept list is complete
-  const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
-  gather_unit<D, WV>(p, rd, lh, sm_ids, [&](int t) { return (int)kept16[t]; });
+  gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
 }
 
-// LDS words of a fused launch: scores, then (pruned second pass) one bit per
-// token, then the block ids.
+// LDS words of a fused launch: scores, then one bit per token, then the block ids.
 struct FusedLds {
   int ids_at, ids_room, words;
 };
-static constexpr FusedLds fused_lds(bool bounded, int max_len, int max_blocks, bool wide) {
+static constexpr FusedLds fused_lds(int max_len, int max_blocks, bool wide) {
   FusedLds f = {};
-  f.ids_at = stage_words(max_len) + (bounded ? need_words(max_len) : 0);
+  f.ids_at = stage_words(max_len) + need_words(max_len);
   const int most = (wide ? kFusedWideMaxLen : kFusedMaxLen) / 16;
   f.ids_room = max_blocks < most ? max_blocks : most;
   f.words = f.ids_at + ((f.ids_room + 3) & ~3);
@@ -1659,7 +1703,7 @@ static hipError_t launch_fused_d(const BatchParams& p, int query_tiles, size_t l
 template <int D, int NT>
 static hipError_t wide_setup_one() {
   constexpr int WV = kWide<D, NT>;
-  constexpr int most = fused_lds(true, kFusedWideMaxLen, kFusedWideMaxLen / 16, true).words * 4;
+  constexpr int most = fused_lds(kFusedWideMaxLen, kFusedWideMaxLen / 16, true).words * 4;
   static_assert(most + (int)sizeof(BoundShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(SelectShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(ScoreShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
