@@ -29,6 +29,44 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t from_lane_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
+// Scan and reductions over a wavefront by DPP (row_shr 1, 2, 4, 8, then
+// row_bcast:15 and :31): a handful of vector instructions each, where the same
+// steps by __shfl are six LDS round trips one after the other.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t identity, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, uint32_t identity, Op op) {  // inclusive
+  v = op(v, dpp_or<0x111, 0xF>(identity, v));
+  v = op(v, dpp_or<0x112, 0xF>(identity, v));
+  v = op(v, dpp_or<0x114, 0xF>(identity, v));
+  v = op(v, dpp_or<0x118, 0xF>(identity, v));
+  v = op(v, dpp_or<0x142, 0xA>(identity, v));
+  return op(v, dpp_or<0x143, 0xC>(identity, v));
+}
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t identity, Op op) {  // uniform
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(v, identity, op), 63);
+}
+__device__ __forceinline__ int wave_scan_add(int v) {
+  return (int)wave_scan((uint32_t)v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ int wave_sum(int v) {
+  return (int)wave_reduce((uint32_t)v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  return wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  return wave_reduce(v, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return __uint_as_float(wave_reduce(__float_as_uint(v), 0u, [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
+}
+
 // sum over the four lanes that share lane % 16, left in every one of them:
 // neighbouring rows of 16 change places, then the halves of the wavefront
 __device__ __forceinline__ float quarter_sum(float v) {

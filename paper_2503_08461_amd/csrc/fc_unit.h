@@ -341,9 +341,9 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
 //   2. the threshold (the k-th largest key) is found by a bucket select: 2048
 //      linear buckets over a range that holds it (so the histogram is spread
 //      even when every score shares its exponent), then the keys of the one
-//      bucket that holds the threshold are compacted to a short candidate list,
-//      which is refined with 2048 buckets per pass until a bucket is a single
-//      key (at most 3 passes for 32 bits);
+//      bucket that holds the threshold are compacted to a candidate list; up to
+//      256 candidates are ranked against each other at once, a longer list is
+//      refined with 2048 buckets per pass until a bucket is a single key;
 //   3. the kept indices are emitted in ascending token order by a ballot /
 //      popcount compaction in which keys equal to the threshold are admitted
 //      in index order until the budget is met (ties go to the lower index).
@@ -544,12 +544,7 @@ __device__ __forceinline__ void bucket_of_rank(const int* hist, int rank, int* w
     own[i] = tid < kScan ? hist[tid * kOwn + i] : 0;
     s += own[i];
   }
-  int v = s;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(v, o);
-    if (lane >= o) v += t;
-  }
+  const int v = wave_scan_add(s);
   if (lane == 63) wsum[wave] = v;
   __syncthreads();
   int base = 0, total = 0;
@@ -571,7 +566,7 @@ __device__ __forceinline__ void bucket_of_rank(const int* hist, int rank, int* w
 }
 
 template <int WV>
-struct SelectShared {
+struct alignas(16) SelectShared {
   int hist[kBuckets];
   uint32_t cand[kMaxCand];
   int wsum[WV];
@@ -646,13 +641,10 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     }
     return k4;
   });
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    n_above += __shfl_xor(n_above, o);
-    n_reach += __shfl_xor(n_reach, o);
-  }
+  kmin = wave_min(kmin);
+  kmax = wave_max(kmax);
+  n_above = wave_sum(n_above);
+  n_reach = wave_sum(n_reach);
   if (lane == 0) {
     sh.wmin[wave] = kmin;
     sh.wmax[wave] = kmax;
@@ -708,50 +700,81 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
         hist_add4(hist, b);
       });
     };
-    uint32_t lo = kmin;
-    const uint32_t range = kmax - kmin;
-    int shift = range ? max(0, 32 - __clz(range) - kBucketBits) : 0;
-    count_keys(lo, shift, 0u);
-    __syncthreads();
-    bucket_of_rank<WV>(hist, narrowed ? k_sel - n_above : k_sel, sh.wsum, sel);
-    int remaining = sel[1];
-    uint32_t bkt = (uint32_t)sel[0];
-    if (shift > 0) {
-      // candidates: the keys of that one bucket
+    // the keys of [lo, hi], in no particular order, to the candidate list
+    auto list_candidates = [&](uint32_t lo, uint32_t hi) {
       sweep([&](int, uint32x4 k4) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t k = k4[e];
-          if (k >= lo && k != 0u && k <= kmax && ((k - lo) >> shift) == bkt) {
+          if (k >= lo && k <= hi && k != 0u) {
             const int pos = atomicAdd(&sh.n_cand, 1);
             if (pos < kMaxCand) cand[pos] = k;
           }
         }
       });
+    };
+    // A short list is ranked by comparing every candidate with every other one: one
+    // barrier instead of the six of two more histograms.  Up to one candidate per
+    // thread, at most kDirect (the reads are 16 bytes, the same for all lanes).
+    constexpr int kDirect = 256;
+    int remaining = narrowed ? k_sel - n_above : k_sel;  // rank among the keys up to kmax
+    uint32_t lo = kmin, hi = kmax;
+    if (!(narrowed && n_reach - n_above <= kDirect)) {
+      const uint32_t range = kmax - kmin;
+      const int shift = range ? max(0, 32 - __clz(range) - kBucketBits) : 0;
+      count_keys(lo, shift, 0u);
+      __syncthreads();
+      bucket_of_rank<WV>(hist, remaining, sh.wsum, sel);
+      remaining = sel[1];
+      lo = kmin + ((uint32_t)sel[0] << shift);
+      hi = min(kmax, lo + ((1u << shift) - 1u));
+    }
+    if (lo != hi) {
+      list_candidates(lo, hi);
       __syncthreads();
       const int nc = sh.n_cand;
-      const bool listed = nc <= kMaxCand;  // else refine over all keys with a range check
-      while (shift > 0) {
-        lo += bkt << shift;
-        const uint32_t width = 1u << shift;  // the chosen bucket spans [lo, lo + width)
-        shift = max(0, shift - kBucketBits);
-        for (int i = tid; i < kBuckets; i += 64 * WV) hist[i] = 0;
-        __syncthreads();
-        if (listed) {
-          for (int j = tid; j < nc; j += 64 * WV) {
-            const uint32_t d = cand[j] - lo;
-            if (cand[j] >= lo && d < width) atomicAdd(&hist[d >> shift], 1);
+      if (nc <= kDirect) {
+        const uint32_t mine = tid < nc ? cand[tid] : 0u;
+        int gt = 0, eq = 0;
+        for (int j = 0; j < nc; j += 4) {
+          const uint32x4 c4 = lds_words4(cand + j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            gt += j + e < nc && c4[e] > mine ? 1 : 0;
+            eq += j + e < nc && c4[e] == mine ? 1 : 0;
           }
-        } else {
-          count_keys(lo, shift, width);
+        }
+        if (tid < nc && gt < remaining && gt + eq >= remaining) {  // (equal candidates write the same)
+          sel[0] = (int)mine;
+          sel[1] = remaining - gt;
         }
         __syncthreads();
-        bucket_of_rank<WV>(hist, remaining, sh.wsum, sel);
+        lo = hi = (uint32_t)sel[0];
         remaining = sel[1];
-        bkt = (uint32_t)sel[0];
+      } else {
+        const bool listed = nc <= kMaxCand;  // else refine over all keys with a range check
+        while (lo != hi) {
+          const uint32_t width = hi - lo + 1u;  // (0 only if the range is all keys, which pass 1 rules out)
+          const int shift = max(0, 32 - __clz(hi - lo) - kBucketBits);
+          for (int i = tid; i < kBuckets; i += 64 * WV) hist[i] = 0;
+          __syncthreads();
+          if (listed) {
+            for (int j = tid; j < nc; j += 64 * WV) {
+              const uint32_t d = cand[j] - lo;
+              if (cand[j] >= lo && d < width) atomicAdd(&hist[d >> shift], 1);
+            }
+          } else {
+            count_keys(lo, shift, width);
+          }
+          __syncthreads();
+          bucket_of_rank<WV>(hist, remaining, sh.wsum, sel);
+          remaining = sel[1];
+          lo += (uint32_t)sel[0] << shift;
+          hi = min(hi, lo + ((1u << shift) - 1u));
+        }
       }
     }
-    const uint32_t thr = lo + bkt;
+    const uint32_t thr = lo;
     const int need_eq = remaining;
 
     // ---- 3. which tokens are kept, one bit each -----------------------------------
@@ -1114,17 +1137,12 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   for (int e = 1 + wave; e <= epoch; e += WV) {
     const bool ok = lane < W;
     const float rho = ok ? __builtin_amdgcn_exp2f(bs.ref[e][lane] - bs.fin[lane]) : 0.f;
-    float lo = ok ? rho : INFINITY, hi = rho, sum = rho;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o));
-      hi = fmaxf(hi, __shfl_xor(hi, o));
-      sum += __shfl_xor(sum, o);
-    }
-    const float mean = sum / (float)W;
-    float var = ok ? (rho - mean) * (rho - mean) : 0.f;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) var += __shfl_xor(var, o);
+    // (non-negative: their bits compare like the values; what is not a number makes
+    // the head fall back, whatever comes out here)
+    const float lo = __uint_as_float(wave_min(ok ? __float_as_uint(rho) : 0x7F800000u));
+    const float hi = __uint_as_float(wave_max(__float_as_uint(rho)));
+    const float mean = wave_sum(rho) / (float)W;
+    const float var = wave_sum(ok ? (rho - mean) * (rho - mean) : 0.f);
     const float half_sd = 0.5f * sqrtf(var / (float)W);
     float m_up[kBoundCentres], m_dn[kBoundCentres], p_up[kBoundCentres], p_dn[kBoundCentres];
 #pragma unroll
@@ -1134,16 +1152,8 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
       m_dn[k] = fmaxf(mean - (float)(k - 1) * half_sd, 0.f);
       const float du = ok ? fmaxf(rho - m_up[k], 0.f) : 0.f;
       const float dd = ok ? fmaxf(m_dn[k] - rho, 0.f) : 0.f;
-      p_up[k] = du * du;
-      p_dn[k] = dd * dd;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-      for (int k = 0; k < kBoundCentres; ++k) {
-        p_up[k] += __shfl_xor(p_up[k], o);
-        p_dn[k] += __shfl_xor(p_dn[k], o);
-      }
+      p_up[k] = wave_sum(du * du);
+      p_dn[k] = wave_sum(dd * dd);
     }
     if (lane == 0) {
       // (margins far above the rounding of the numerators, the sums and the factors)
@@ -1302,8 +1312,7 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
     for (int e = 0; e < 4; ++e)
       if (c + e < j1) vmax = max(vmax, w[e] & 0xFFFF0000u);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, o));
+  vmax = wave_max(vmax);
   if (lane == 0) sh.wmax[wave] = vmax;
   auto zero_histograms = [&] {
     for (int i = tid; i < kBuckets; i += 64 * WV) hist_lo[i] = hist_hi[i] = 0;
