@@ -527,8 +527,18 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   if (n_comp == 0) return FC_OK;
 
   // ---- launches: the fused kernels, or (FC_SCORE_TWO_PASS) the separate ones ---
-  const std::vector<FusedLaunch> fused = plan_fused_launches(pv, plan, p->n_cu);
-  const bool separate = pv.score_mode != FC_SCORE_AUTO && !plan.lists[LIST_ALL].empty();
+  // or, with few long heads, kernels that split them over workgroups
+  const bool beyond_narrow = plan.raw_floats > 0;  // (a unit that the default narrow workgroups cannot take)
+  int n_split = plan_split(pv, p->n_cu, &plan);
+  // score scratch; of split heads the row pairs of every segment behind the scores
+  const size_t raw_floats = plan.raw_floats + (size_t)n_split * n_comp * p->n_layers * p->n_heads * 128;
+  // the allocation-free call has them behind the kept lists in its fixed scratch
+  // (room for any split on this chip: 128 heads of 32768 tokens)
+  const size_t fixed_kept = dev_kept_out ? 0 : plan.kept_entries;
+  if (no_alloc && fixed_kept + raw_floats > kNoAllocKeptInts) n_split = 0;
+  std::vector<FusedLaunch> fused;
+  if (n_split == 0) fused = plan_fused_launches(pv, plan, p->n_cu);
+  const bool separate = n_split == 0 && pv.score_mode != FC_SCORE_AUTO && !plan.lists[LIST_ALL].empty();
 
   // ---- scratch: kept lists, saved ids, un-pooled scores, descriptors -----------
   const size_t desc_bytes = round_up((size_t)n_comp * sizeof(ReqDesc), 16);
@@ -541,12 +551,16 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   size_t list_at[N_LISTS] = {};
   if (separate)
     for (int i = LIST_SNAP; i < N_LISTS; ++i) list_at[i] = add_list(plan.lists[i]);
+  std::vector<int32_t> split_list(n_split ? n_comp : 0);
+  std::iota(split_list.begin(), split_list.end(), 0);
+  if (n_split) list_at[LIST_ALL] = add_list(split_list);
   std::vector<size_t> fused_at;
   for (const FusedLaunch& l : fused) fused_at.push_back(add_list(l.units));
   const size_t meta_bytes = desc_bytes + round_up(lists.size() * sizeof(int32_t), 16);
   const size_t n_ids = (size_t)plan.total_old + plan.total_new;
   int32_t* kept_buf = dev_kept_out;
   int32_t* ids_buf = nullptr;
+  float* raw_buf = nullptr;
   char* dev_meta = nullptr;
   int rc;
   const bool pruned_call = p->score_pruning && !dev_scores_out && !need_lse;
@@ -555,7 +569,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     if (n_comp > FC_NOALLOC_MAX_REQUESTS)
       return fail(FC_EINVAL, "%d requests exceed the %d of the allocation-free call", n_comp,
                   FC_NOALLOC_MAX_REQUESTS);
-    if (plan.raw_floats > 0)
+    if (beyond_narrow)
       return fail(FC_EINVAL, "the allocation-free call takes heads of at most %d tokens with "
                              "the default scheduling", kFusedMaxLen);
     if (!dev_kept_out && plan.kept_entries > kNoAllocKeptInts)
@@ -566,18 +580,20 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
                   kNoAllocIdInts);
     if (meta_bytes > kNoAllocMetaBytes) return fail(FC_EINVAL, "descriptors exceed the fixed scratch");
     if (!kept_buf) kept_buf = reinterpret_cast<int32_t*>(p->fixed_scratch + kNoAllocKeptOff);
+    if (n_split) raw_buf = reinterpret_cast<float*>(p->fixed_scratch + kNoAllocKeptOff) + fixed_kept;
     ids_buf = reinterpret_cast<int32_t*>(p->fixed_scratch + kNoAllocIdsOff);
     dev_meta = reinterpret_cast<char*>(p->fixed_scratch + kNoAllocMetaOff);
   } else {
     // (growth waits for the device and frees: it happens before anything is queued)
     // (the fused kernels keep their lists in LDS)
-    if (!dev_kept_out && separate &&
+    if (!dev_kept_out && (separate || n_split) &&
         (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK)
       return rc;
     if ((rc = grow(&p->ids, &p->ids_cap, n_ids)) != FC_OK) return rc;
-    if (separate && (rc = grow(&p->raw_scores, &p->raw_cap, plan.raw_floats)) != FC_OK) return rc;
+    if ((separate || n_split) && (rc = grow(&p->raw_scores, &p->raw_cap, raw_floats)) != FC_OK) return rc;
     if ((rc = grow_meta(p, meta_bytes)) != FC_OK) return rc;
     if (!kept_buf) kept_buf = p->kept;
+    raw_buf = p->raw_scores;
     ids_buf = p->ids;
     dev_meta = p->dev_meta;
   }
@@ -603,7 +619,9 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   bp.order_knorm = dev_lists + list_at[LIST_KNORM];
   bp.n_comp = n_comp;  // plan_alloc / reclaim walk every descriptor
   bp.n_knorm = n_list(LIST_KNORM);
-  bp.n_unfused = n_list(LIST_ALL);
+  bp.n_unfused = n_split ? n_comp : n_list(LIST_ALL);
+  bp.n_split = std::max(n_split, 1);
+  bp.split_part = n_split ? raw_buf + plan.raw_floats : nullptr;
   // per launch: order_snap / n_snap, order_fused / n_fused, window (of the class)
   bp.block_tables = dev_block_tables;
   bp.max_blocks = max_blocks_per_req;
@@ -616,7 +634,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   bp.in_place = pv.in_place ? 1 : 0;
   const float sc = (scale > 0.f) ? scale : 1.0f / sqrtf((float)p->head_dim);
   bp.scale_log2e = sc * 1.44269504088896340736f;
-  bp.raw_scores = p->raw_scores;
+  bp.raw_scores = raw_buf;
   bp.scores_out = dev_scores_out;
   bp.kept = kept_buf;
   bp.kept_out = dev_kept_out;
@@ -667,8 +685,11 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     return e;
   }));
   FC_HIP_STAGE(p, run(K_KNORM_SCORE, bp.n_knorm > 0, [&] { return launch_knorm_score(bp, stream); }));
-  FC_HIP_STAGE(p, run(K_SELECT, bp.n_unfused > 0,
-                      [&] { return launch_select(bp, plan.max_len[LIST_ALL], stream); }));
+  FC_HIP_STAGE(p, run(K_SNAPKV_SCORE, n_split > 0, [&] { return launch_split_scores(bp, stream); }));
+  int select_len = plan.max_len[LIST_ALL];
+  if (n_split)
+    for (const ReqDesc& d : plan.descs) select_len = std::max(select_len, d.seq_len);
+  FC_HIP_STAGE(p, run(K_SELECT, bp.n_unfused > 0, [&] { return launch_select(bp, select_len, stream); }));
   FC_HIP_STAGE(p, run(K_GATHER, bp.n_unfused > 0, [&] { return launch_gather(bp, stream); }));
   FC_HIP_STAGE(p, run(K_FUSED, !fused.empty(), [&] {
     hipError_t e = hipSuccess;

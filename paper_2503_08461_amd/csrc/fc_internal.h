@@ -75,6 +75,9 @@ struct BatchParams {
   int32_t* kept;               // kept indices, packed, of the units that take the separate kernels
   int32_t* kept_out;           // nullable: the caller's copy of them, written by the fused kernels
   int32_t* error_flag;         // set if a kernel finds something wrong (an ownership check that fails)
+  int32_t n_split;             // heads split over workgroups: segments per head (1: gather of the
+                               // separate kernels)
+  float* split_part;           // ... [unit][segment][2][64]: the segments' row (max, sum) pairs
   int32_t ids_at, ids_room;    // fused kernels: where the block ids lie in LDS (words), room for how many
   int32_t bounded;             // 1: the fused kernel prunes the second pass of its SnapKV units
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,
@@ -121,6 +124,8 @@ hipError_t launch_snapkv_score(const BatchParams& p, hipStream_t s);
 // a fill kernel (not a memset: calls may be captured into a graph)
 hipError_t launch_zero_ints(int32_t* p, int n, hipStream_t s);
 hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s);
+// scores of heads split over workgroups (order_all; select and gather follow)
+hipError_t launch_split_scores(const BatchParams& p, hipStream_t s);
 hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s);
 hipError_t launch_gather(const BatchParams& p, hipStream_t s);
 // score -> select -> gather of every unit of order_fused in one launch.

@@ -172,7 +172,108 @@ __global__ __launch_bounds__(kThreads) void knorm_score_kernel(BatchParams p) {
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_knorm[slot]];
   float* raw = p.raw_scores + rd.raw_off + (size_t)lh * rd.seq_len;
-  knorm_unit<D, kWaves>(p, rd, lh, p.old_ids + rd.old_off, [&](int j, float v) { raw[j] = v; });
+  knorm_unit<D, kWaves>(p, rd, lh, p.old_ids + rd.old_off, 0, rd.n_old, [&](int j, float v) { raw[j] = v; });
+}
+
+// ---------------------------------------------------------------------------
+// heads split over workgroups
+// ---------------------------------------------------------------------------
+//
+// A call with few heads (one layer, one or two requests) leaves most CUs idle in
+// the fused kernels, and one CU gets no more than about 27 GB/s out of HBM
+// whatever its wavefronts have in flight (16 wavefronts: 64 KB per 5600 cycles).
+// So the heads of such a call are cut into p.n_split segments of whole blocks, one
+// workgroup each:
+//   split_rows    row (max, sum) pairs of the segment -> p.split_part; key norms
+//   split_scores  the rows' denominators from all segments' pairs, then the
+//                 segment's column sums (K again, by then mostly from the
+//                 memory-side cache)
+//   select        one workgroup per head
+//   gather        the kept blocks, cut into p.n_split segments as well
+static constexpr int kSplitIds = 2048;  // blocks of the longest head
+
+struct SplitUnit {
+  int unit, seg, lh;
+  ReqDesc rd;
+};
+__device__ __forceinline__ SplitUnit split_unit(const BatchParams& p) {
+  SplitUnit u;
+  const int n_lh = p.n_layers * p.n_heads;
+  u.unit = blockIdx.x / p.n_split;
+  u.seg = blockIdx.x - u.unit * p.n_split;
+  const int slot = u.unit / n_lh;
+  u.lh = u.unit - slot * n_lh;
+  u.rd = p.descs[p.order_all[slot]];
+  return u;
+}
+// segment of [0, n): [first, last)
+__device__ __forceinline__ void split_range(const BatchParams& p, int seg, int n, int& first, int& last) {
+  const int per = (n + p.n_split - 1) / p.n_split;
+  first = min(n, seg * per);
+  last = min(n, first + per);
+}
+
+template <int D, int NT>
+__global__ __launch_bounds__(kThreads) void split_rows_kernel(BatchParams p) {
+  __shared__ ScoreShared<kWaves> sh;
+  __shared__ int32_t sm_ids[kSplitIds];
+  const SplitUnit u = split_unit(p);
+  int b0, b1;
+  split_range(p, u.seg, u.rd.n_old, b0, b1);
+  const bool snap = u.rd.method == 1 /* FC_METHOD_SNAPKV */;
+  if (u.rd.method == 3 /* FC_METHOD_STREAMING */ || (snap && p.lse_window != nullptr)) return;  // uniform
+  for (int i = b0 + threadIdx.x; i < b1; i += kThreads) sm_ids[i] = p.old_ids[u.rd.old_off + i];
+  __syncthreads();
+  if (snap) {
+    if constexpr (NT > 0) {
+      half8 qreg[NT][D / 32];
+      load_window_queries<D, NT>(p, u.rd, u.lh, qreg);
+      snapkv_rows<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, sh, qreg);
+      __syncthreads();
+      if (threadIdx.x < 16 * NT) {
+        float mm, zz;
+        merged_row<kWaves>(sh, threadIdx.x, mm, zz);
+        float* part = p.split_part + ((size_t)u.unit * p.n_split + u.seg) * 128;
+        part[threadIdx.x] = mm;
+        part[64 + threadIdx.x] = zz;
+      }
+    }
+  } else {
+    float* raw = p.raw_scores + u.rd.raw_off + (size_t)u.lh * u.rd.seq_len;
+    knorm_unit<D, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, [&](int j, float v) { raw[j] = v; });
+  }
+}
+
+template <int D, int NT>
+__global__ __launch_bounds__(kThreads) void split_scores_kernel(BatchParams p) {
+  __shared__ float fin[64];
+  __shared__ int32_t sm_ids[kSplitIds];
+  const SplitUnit u = split_unit(p);
+  if (u.rd.method != 1 /* FC_METHOD_SNAPKV */) return;  // uniform
+  int b0, b1;
+  split_range(p, u.seg, (u.rd.seq_len - u.rd.window + 15) >> 4, b0, b1);
+  for (int i = b0 + threadIdx.x; i < b1; i += kThreads) sm_ids[i] = p.old_ids[u.rd.old_off + i];
+  const int row = threadIdx.x;
+  if (row < 64) {
+    float out = INFINITY;  // padded rows contribute exp2(-inf) = 0
+    if (row < u.rd.window) {
+      if (p.lse_window != nullptr) {
+        out = p.lse_window[lse_offset<D>(u.rd, u.lh) + row] * 1.44269504088896340736f;
+      } else {
+        const float* part = p.split_part + (size_t)u.unit * p.n_split * 128 + row;
+        float mm = -3.0e38f, zz = 0.f;
+        for (int g = 0; g < p.n_split; ++g) mm = fmaxf(mm, part[g * 128]);
+        for (int g = 0; g < p.n_split; ++g) zz += part[g * 128 + 64] * __builtin_amdgcn_exp2f(part[g * 128] - mm);
+        out = mm + log2f(zz);
+      }
+    }
+    fin[row] = out;
+  }
+  half8 qreg[NT][D / 32];
+  load_window_queries<D, NT>(p, u.rd, u.lh, qreg);
+  __syncthreads();
+  float* raw = p.raw_scores + u.rd.raw_off + (size_t)u.lh * u.rd.seq_len;
+  snapkv_columns<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, fin, qreg, [&](int j, float v) { raw[j] = v; });
 }
 
 // Heads of up to 32768 tokens whose scores come from a kernel of their own: 16
@@ -186,21 +287,25 @@ __global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p
   const int lh = blockIdx.x - slot * n_lh;
   const ReqDesc rd = p.descs[p.order_all[slot]];
   uint32_t* stage = lds + kStageFront;
+  int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
+  if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform (heads split over workgroups only)
+    streaming_unit<kSelectWaves>(p, rd, lh, kept);
+    return;
+  }
   const float* raw = p.raw_scores + rd.raw_off + (size_t)lh * rd.seq_len;
   const int n_sel = rd.method == 1 /* FC_METHOD_SNAPKV */ ? rd.seq_len - rd.window : rd.seq_len;
   for (int j = threadIdx.x; j < n_sel; j += 64 * kSelectWaves) stage[j] = __float_as_uint(raw[j]);
   __syncthreads();
-  select_unit<kSelectWaves>(p, rd, lh, stage, lds + stage_words(rd.seq_len), p.kept + rd.kept_off + (size_t)lh * rd.budget, sh);
+  select_unit<kSelectWaves>(p, rd, lh, stage, lds + stage_words(rd.seq_len), kept, sh);
 }
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
-  const int n_lh = p.n_layers * p.n_heads;
-  const int slot = blockIdx.x / n_lh;
-  const int lh = blockIdx.x - slot * n_lh;
-  const ReqDesc rd = p.descs[p.order_all[slot]];
-  const int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
-  gather_unit<D, kWaves>(p, rd, lh, [&](int i) { return p.old_ids[rd.old_off + i]; },
+  const SplitUnit u = split_unit(p);
+  const int32_t* kept = p.kept + u.rd.kept_off + (size_t)u.lh * u.rd.budget;
+  int nb0, nb1;
+  split_range(p, u.seg, u.rd.n_new, nb0, nb1);
+  gather_unit<D, kWaves>(p, u.rd, u.lh, nb0, nb1, [&](int i) { return p.old_ids[u.rd.old_off + i]; },
                          [&](int t) { return kept[t]; });
 }
 
@@ -317,6 +422,32 @@ hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int D, int NT>
+static void launch_split_one(const BatchParams& p, hipStream_t s) {
+  const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads * p.n_split;
+  split_rows_kernel<D, NT><<<grid, kThreads, 0, s>>>(p);
+  if constexpr (NT > 0) split_scores_kernel<D, NT><<<grid, kThreads, 0, s>>>(p);
+}
+
+template <int D>
+static hipError_t launch_split_d(const BatchParams& p, hipStream_t s) {
+  switch ((p.window + 15) / 16) {
+    case 0: launch_split_one<D, 0>(p, s); break;
+    case 1: launch_split_one<D, 1>(p, s); break;
+    case 2: launch_split_one<D, 2>(p, s); break;
+    case 3: launch_split_one<D, 3>(p, s); break;
+    case 4: launch_split_one<D, 4>(p, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_split_scores(const BatchParams& p, hipStream_t s) {
+  if (p.head_dim == 128) return launch_split_d<128>(p, s);
+  if (p.head_dim == 64) return launch_split_d<64>(p, s);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads;
   const size_t lds = (size_t)(stage_words(max_seq_len) + need_words(max_seq_len)) * sizeof(uint32_t);
@@ -341,7 +472,7 @@ hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_b
 }
 
 hipError_t launch_gather(const BatchParams& p, hipStream_t s) {
-  const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads;
+  const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads * p.n_split;
   if (p.head_dim == 128)
     gather_kernel<128><<<grid, kThreads, 0, s>>>(p);
   else if (p.head_dim == 64)

@@ -19,6 +19,9 @@ namespace fc {
 
 namespace {
 
+// Heads shorter than this are not worth the launches of the split path.
+constexpr int kSplitMinLen = 2048;
+
 int blocks_for(int tokens) { return (tokens + kPlanBlockSize - 1) / kPlanBlockSize; }
 
 template <typename Plan>
@@ -228,6 +231,23 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
       launches.push_back(std::move(l));
     }
   return launches;
+}
+
+int plan_split(const PoolView& pool, int n_cu, CompressPlan* plan) {
+  if (pool.score_mode != PLAN_SCORE_AUTO || pool.in_place || plan->descs.empty()) return 0;
+  const size_t units = (size_t)pool.n_layers * pool.n_heads * plan->descs.size();
+  int longest = 0;
+  for (const ReqDesc& d : plan->descs)
+    if (d.method != PLAN_METHOD_STREAMING) longest = std::max(longest, d.seq_len);
+  if (units > (size_t)n_cu / 2 || longest < kSplitMinLen) return 0;
+  size_t raw = 0;
+  for (ReqDesc& d : plan->descs) {
+    d.raw_off = (int64_t)raw;
+    raw += (size_t)pool.n_layers * pool.n_heads * d.seq_len;
+  }
+  plan->raw_floats = raw;
+  // two workgroups per CU, segments of at least 256 tokens of the longest head
+  return (int)std::min<size_t>(std::max<size_t>(2 * (size_t)n_cu / units, 2), longest / 256);
 }
 
 int plan_window_lse(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,

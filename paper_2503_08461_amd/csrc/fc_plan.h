@@ -88,6 +88,11 @@ struct FusedLaunch {
 };
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu);
 
+// A call with so few heads that they are better split over workgroups: segments
+// per head, or 0 (not split).  Otherwise all requests of the call run that way;
+// plan->descs get their offsets in the score scratch, plan->raw_floats its size.
+int plan_split(const PoolView& pool, int n_cu, CompressPlan* plan);
+
 // fc_window_lse: one descriptor per SnapKV request (all if method is NULL),
 // longest first, queries packed as [n_req][...][window].
 struct LsePlan {

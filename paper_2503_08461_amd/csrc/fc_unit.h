@@ -107,52 +107,47 @@ __device__ __forceinline__ void load_window_queries(const BatchParams& p, const 
   }
 }
 
-template <int D, int NT, int WV, typename Store>
-__device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              const int32_t* old_ids, ScoreShared<WV>& sh,
-                                              half8 (&qreg)[NT][D / 32], Store store) {
+// Where a lane finds its part of a block's keys of one (layer, head).
+template <int D>
+struct KeyBlocks {
+  const _Float16* base;
+  size_t stride;
+  int n_blocks;
+  __device__ __forceinline__ KeyBlocks(const BatchParams& p, int lh) : n_blocks(p.n_blocks) {
+    const int layer = lh / p.n_heads, head = lh - layer * p.n_heads;
+    const int lane = threadIdx.x & 63;
+    stride = (size_t)2 * p.n_heads * 16 * D;
+    base = p.kv + (size_t)layer * p.n_blocks * stride + (size_t)head * 16 * D + (size_t)(lane & 15) * D +
+           (lane >> 4) * 8;
+  }
+  __device__ __forceinline__ void load(int id, half8 (&k)[D / 32]) const {
+    const _Float16* kp = base + (size_t)clamp_block(id, n_blocks) * stride;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) k[ks] = load_half8(kp + ks * 32);
+  }
+  __device__ __forceinline__ void load_last_use(int id, half8 (&k)[D / 32]) const {
+    const _Float16* kp = base + (size_t)clamp_block(id, n_blocks) * stride;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
+  }
+};
+
+// Pass 1 over blocks [b0, b1): every lane's online (max, sum) of its query rows'
+// logits -> sh.m, sh.z.  ids: the block ids, indexed from block 0.
+template <int D, int NT, int WV>
+__device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc& rd, int lh,
+                                            const int32_t* ids, int b0, int b1, ScoreShared<WV>& sh,
+                                            const half8 (&qreg)[NT][D / 32]) {
   constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
   const int L = rd.seq_len;
   const int W = rd.window;  // <= 16 NT; the rows past it are padding
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                          (size_t)head * 16 * D + (size_t)c16 * D + q4 * 8;
+  const KeyBlocks<D> keys(p, lh);
   const float c = p.scale_log2e;
-  const int nb = (L + 15) >> 4;
   const int n_unmasked = (L - W) >> 4;  // blocks that lie wholly before the window
-
-  // last use of a block (second pass)
-  auto load_block_nt = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
-  };
-  auto load_block = [&](int b, half8 (&k)[KS]) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8(kp + ks * 32);
-  };
-
-  // log2 of every row's soft-max denominator goes to sh.fin: handed in by the
-  // caller (natural log, from its attention kernel), or pass 1 below
-  const size_t lse_off = (size_t)(rd.q_off / D) + (size_t)lh * W;
-  if (p.lse_window != nullptr) {  // uniform
-    if (threadIdx.x < 64)
-      sh.fin[threadIdx.x] = (int)threadIdx.x < W
-                                ? p.lse_window[lse_off + threadIdx.x] * 1.44269504088896340736f
-                                : INFINITY;  // padded rows contribute exp2(-inf) = 0
-    __syncthreads();
-  } else {
-  // ---- pass 1: row maxima and normalisers --------------------------------
   float m[NT], z[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -161,10 +156,10 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
   }
   {
     half8 kc[KS], kn[KS];
-    int b = wave;
-    if (b < nb) load_block(b, kc);
-    for (; b < nb; b += WV) {
-      if (b + WV < nb) load_block(b + WV, kn);
+    int b = b0 + wave;
+    if (b < b1) keys.load(ids[b], kc);
+    for (; b < b1; b += WV) {
+      if (b + WV < b1) keys.load(ids[b + WV], kn);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -195,8 +190,6 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
       for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
     }
   }
-
-  // combine the partial (max, sum) pairs of every query
   constexpr int kParts = ScoreShared<WV>::kParts;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -214,65 +207,103 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
       sh.z[wave][q4 % kParts][nt * 16 + c16] = z[nt];
     }
   }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int row = threadIdx.x;
-    float out = INFINITY;  // padded rows contribute exp2(-inf) = 0
-    if (row < W) {
-      float mm = -3.0e38f;
-      for (int w = 0; w < WV; ++w)
-        for (int q = 0; q < kParts; ++q) mm = fmaxf(mm, sh.m[w][q][row]);
-      float zz = 0.f;
-      for (int w = 0; w < WV; ++w)
-        for (int q = 0; q < kParts; ++q)
-          zz += sh.z[w][q][row] * __builtin_amdgcn_exp2f(sh.m[w][q][row] - mm);
-      out = mm + log2f(zz);
-    }
-    sh.fin[row] = out;
-  }
-  __syncthreads();
-  }
-  if (p.lse_out != nullptr) {  // uniform: the caller asked for the denominators only
-    if ((int)threadIdx.x < W)
-      p.lse_out[lse_off + threadIdx.x] = sh.fin[threadIdx.x] * 0.69314718055994530942f;
-    return;
-  }
+}
 
-  // ---- pass 2: column sums of the soft-maxed rows over the prefix ---------
-  const int n_prefix = L - W;
-  const int nb2 = (n_prefix + 15) >> 4;
+// The workgroup's (max, sum) of a row from the partial pairs of snapkv_rows.
+template <int WV>
+__device__ __forceinline__ void merged_row(const ScoreShared<WV>& sh, int row, float& mm, float& zz) {
+  constexpr int kParts = ScoreShared<WV>::kParts;
+  mm = -3.0e38f;
+  for (int w = 0; w < WV; ++w)
+    for (int q = 0; q < kParts; ++q) mm = fmaxf(mm, sh.m[w][q][row]);
+  zz = 0.f;
+  for (int w = 0; w < WV; ++w)
+    for (int q = 0; q < kParts; ++q)
+      zz += sh.z[w][q][row] * __builtin_amdgcn_exp2f(sh.m[w][q][row] - mm);
+}
+
+// Pass 2 over blocks [b0, b1) of the prefix: column sums of the soft-maxed rows;
+// fin: log2 of every row's denominator.
+template <int D, int NT, int WV, typename Store>
+__device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDesc& rd, int lh,
+                                               const int32_t* ids, int b0, int b1, const float* fin,
+                                               const half8 (&qreg)[NT][D / 32], Store store) {
+  constexpr int KS = D / 32;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15;
+  const int q4 = lane >> 4;
+  const KeyBlocks<D> keys(p, lh);
+  const float c = p.scale_log2e;
+  const int n_prefix = rd.seq_len - rd.window;
   float mrow[NT][4];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.fin[nt * 16 + q4 * 4 + r];
-
-  {
-    // from the end of the prefix backwards: the blocks that the first pass read
-    // last are the ones most likely to be still in a cache
-    half8 kc[KS], kn[KS];
-    int b = nb2 - 1 - wave;
-    if (b >= 0) load_block_nt(b, kc);
-    for (; b >= 0; b -= WV) {
-      if (b - WV >= 0) load_block_nt(b - WV, kn);
-      float colsum = 0.f;
+    for (int r = 0; r < 4; ++r) mrow[nt][r] = fin[nt * 16 + q4 * 4 + r];
+  // from the end of the prefix backwards: the blocks that the first pass read
+  // last are the ones most likely to be still in a cache
+  half8 kc[KS], kn[KS];
+  int b = b1 - 1 - wave;
+  if (b >= b0) keys.load_last_use(ids[b], kc);
+  for (; b >= b0; b -= WV) {
+    if (b - WV >= b0) keys.load_last_use(ids[b - WV], kn);
+    float colsum = 0.f;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < NT; ++nt) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
+      for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
-      }
-      colsum = quarter_sum(colsum);
-      const int tok = b * 16 + c16;
-      if (q4 == 0 && tok < n_prefix) store(tok, colsum);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
+      for (int r = 0; r < 4; ++r)
+        colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
     }
+    colsum = quarter_sum(colsum);
+    const int tok = b * 16 + c16;
+    if (q4 == 0 && tok < n_prefix) store(tok, colsum);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
   }
+}
+
+// where a unit's window rows begin in the packed log-sum-exps
+template <int D>
+__device__ __forceinline__ size_t lse_offset(const ReqDesc& rd, int lh) {
+  return (size_t)(rd.q_off / D) + (size_t)lh * rd.window;
+}
+
+template <int D, int NT, int WV, typename Store>
+__device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDesc& rd, int lh,
+                                              const int32_t* old_ids, ScoreShared<WV>& sh,
+                                              half8 (&qreg)[NT][D / 32], Store store) {
+  const int L = rd.seq_len;
+  const int W = rd.window;
+  // log2 of every row's soft-max denominator goes to sh.fin: handed in by the
+  // caller (natural log, from its attention kernel), or pass 1
+  if (p.lse_window != nullptr) {  // uniform
+    if (threadIdx.x < 64)
+      sh.fin[threadIdx.x] = (int)threadIdx.x < W
+                                ? p.lse_window[lse_offset<D>(rd, lh) + threadIdx.x] * 1.44269504088896340736f
+                                : INFINITY;  // padded rows contribute exp2(-inf) = 0
+    __syncthreads();
+  } else {
+    snapkv_rows<D, NT, WV>(p, rd, lh, old_ids, 0, (L + 15) >> 4, sh, qreg);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      float mm, zz;
+      merged_row<WV>(sh, threadIdx.x, mm, zz);
+      sh.fin[threadIdx.x] = (int)threadIdx.x < W ? mm + log2f(zz)
+                                                 : INFINITY;  // padded rows contribute exp2(-inf) = 0
+    }
+    __syncthreads();
+  }
+  if (p.lse_out != nullptr) {  // uniform: the caller asked for the denominators only
+    if ((int)threadIdx.x < W)
+      p.lse_out[lse_offset<D>(rd, lh) + threadIdx.x] = sh.fin[threadIdx.x] * 0.69314718055994530942f;
+    return;
+  }
+  snapkv_columns<D, NT, WV>(p, rd, lh, old_ids, 0, (L - W + 15) >> 4, sh.fin, qreg, store);
 }
 
 template <int D, int NT, int WV, typename Store>
@@ -293,7 +324,7 @@ __device__ __forceinline__ void snapkv_unit(const BatchParams& p, const ReqDesc&
 
 template <int D, int WV, typename Store>
 __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                           const int32_t* old_ids, Store store) {
+                                           const int32_t* old_ids, int b0, int b1, Store store) {
   constexpr int LPR = D / 8;     // lanes per token row
   constexpr int RPI = 64 / LPR;  // rows per load instruction
   constexpr int NI = 16 / RPI;   // load instructions per block
@@ -305,8 +336,7 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
   const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
   const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
                           (size_t)head * 16 * D + lane * 8;
-  const int nb = (L + 15) >> 4;
-  for (int b = wave; b < nb; b += WV) {
+  for (int b = b0 + wave; b < b1; b += WV) {
     const int blk = clamp_block(old_ids[b], p.n_blocks);
     const _Float16* kp = kbase + (size_t)blk * blk_stride;
     half8 v[NI];
@@ -1464,7 +1494,8 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 // One workgroup per (request, layer, head); a wavefront fills one new block
 // (16 output slots) at a time for K and V.  D/8 lanes move one row with
 // 128-bit accesses, so a wavefront instruction moves 64/(D/8) rows; the
-// destination chunk is contiguous.  kept_at(t) is the token that goes to slot t.
+// destination chunk is contiguous.  kept_at(t) is the token that goes to slot t;
+// the workgroup fills the new blocks [nb0, nb1).
 //
 // Bound by HBM when the chip is full and by the latency of one block's chain
 // (kept index, block id, row) when it is not; the rows of a wavefront's next
@@ -1472,7 +1503,7 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 
 template <int D, int WV, typename BlockAt, typename KeptAt>
 __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            BlockAt block_at, KeptAt kept_at) {
+                                            int nb0, int nb1, BlockAt block_at, KeptAt kept_at) {
   constexpr int LPR = D / 8;
   constexpr int RPI = 64 / LPR;
   constexpr int NI = 16 / RPI;
@@ -1518,19 +1549,20 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
     // outputs only reads slots at or after its own start, so reading the whole
     // chunk, a barrier, then writing it never destroys a row that is still
     // needed (later chunks read strictly later slots).
-    for (int c0 = 0; c0 < rd.n_new; c0 += WV) {
+    // (one workgroup then copies all blocks of a head)
+    for (int c0 = nb0; c0 < nb1; c0 += WV) {
       const int nbk = c0 + wave;
-      if (nbk < rd.n_new) load(nbk, kc, vc);
+      if (nbk < nb1) load(nbk, kc, vc);
       __syncthreads();  // uniform: c0 and in_place are the same for all threads
-      if (nbk < rd.n_new) store(nbk, kc, vc);
+      if (nbk < nb1) store(nbk, kc, vc);
     }
     return;
   }
   half8 kn[NI], vn[NI];
-  int nbk = wave;
-  if (nbk < rd.n_new) load(nbk, kc, vc);
-  for (; nbk < rd.n_new; nbk += WV) {
-    if (nbk + WV < rd.n_new) load(nbk + WV, kn, vn);
+  int nbk = nb0 + wave;
+  if (nbk < nb1) load(nbk, kc, vc);
+  for (; nbk < nb1; nbk += WV) {
+    if (nbk + WV < nb1) load(nbk + WV, kn, vn);
     store(nbk, kc, vc);
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
@@ -1548,7 +1580,7 @@ __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc
                                              const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds) {
   const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
   const bool streaming = rd.method == 3 /* FC_METHOD_STREAMING */;  // uniform
-  gather_unit<D, WV>(p, rd, lh, [&](int i) { return ids_in_lds ? sm_ids[i] : p.old_ids[rd.old_off + i]; },
+  gather_unit<D, WV>(p, rd, lh, 0, rd.n_new, [&](int i) { return ids_in_lds ? sm_ids[i] : p.old_ids[rd.old_off + i]; },
                      [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
 }
 
@@ -1596,7 +1628,7 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
       if constexpr (NT > 0)
         snapkv_unit<D, NT, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
     } else {
-      knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+      knorm_unit<D, WV>(p, rd, lh, sm_ids, 0, rd.n_old, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
     select_unit<WV>(p, rd, lh, words, map, kept, sh.select);
@@ -1657,7 +1689,7 @@ __global__ __launch_bounds__(64 * WV, WV == kNarrow ? 3 : WV / 4) void fused_bou
         snapkv_rescore<D, NT, WV>(p, rd, lh, sm_ids, map, stage, qreg, mrow);
       }
     } else {
-      knorm_unit<D, WV>(p, rd, lh, sm_ids, [&](int j, float v) { stage[j] = v; });
+      knorm_unit<D, WV>(p, rd, lh, sm_ids, 0, rd.n_old, [&](int j, float v) { stage[j] = v; });
     }
     __syncthreads();
     select_unit<WV>(p, rd, lh, words, map, kept, sh.select, key_lo, key_hi);

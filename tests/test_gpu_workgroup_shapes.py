@@ -1,9 +1,9 @@
-"""Both workgroup shapes of the fused kernels against the oracle: narrow ones
-(a launch with more heads than fit the chip as wide workgroups) and wide ones
-(few heads, or heads of more than 8192 tokens), with the pruned second pass,
-with the scores asked for, and in place."""
+"""The three ways a head is spread over the chip, against the oracle: narrow
+workgroups (a launch with more heads than fit the chip as wide workgroups), wide
+ones (fewer heads, or heads of more than 8192 tokens), heads split over several
+workgroups (very few heads); with the pruned second pass and with the scores
+asked for."""
 
-import numpy as np
 import pytest
 
 from oracle import fastcache_oracle as fo
@@ -14,42 +14,61 @@ pytestmark = pytest.mark.gpu
 SNAP, KNORM, STREAM = fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING
 
 
+# requests of nine tokens, two heads each, that bring a batch to more than 128 and to more than
+# 512 heads: half of a chip's 256 compute units, and two per compute unit
+WIDE, NARROW = 70, 300
+
+
 def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, **kw):
-    from paper_2503_08461_amd import fastcache as fc
     from parity_util import SideBySide
     lens = list(lens) + [9] * fillers        # key-norm requests of nine tokens that only add heads
     budgets = list(budgets) + [4] * fillers
     methods = list(methods) + [KNORM] * fillers
-    s = SideBySide(_custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads))
+    s = SideBySide(_custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads), in_place=in_place)
     try:
-        if in_place:
-            fc.fc_set_compaction_mode(s.pool, fc.FC_COMPACT_IN_PLACE)
-            s.in_place = True
         return s.compress_and_compare(scores=scores, **kw)
     finally:
         s.close()
 
 
+SHAPES = [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 64)]
+
+
 @pytest.mark.parametrize("scores", [True, False])
-@pytest.mark.parametrize("W,d", [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 64)])
+@pytest.mark.parametrize("W,d", SHAPES)
 def test_narrow_workgroups(W, d, scores):
-    # (2 heads x more than 256 requests: more heads than two per compute unit)
     lens = [W, 511, 512, 700, 2047, 2049, 4100, 8192]
-    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, fillers=300)
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW)
 
 
 @pytest.mark.parametrize("scores", [True, False])
-@pytest.mark.parametrize("W,d", [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 64)])
+@pytest.mark.parametrize("W,d", SHAPES)
 def test_wide_workgroups(W, d, scores):
     # both sides of the pruning limit of wide workgroups, of the narrow ones' longest head, of the
     # longer epochs and of a wavefront's last chunk; the longest head of all
     lens = [W, 300, 2047, 2048 + W, 8192, 8193, 16384, 16385, 32768]
+    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1)
+
+
+@pytest.mark.parametrize("scores", [True, False])
+@pytest.mark.parametrize("W,d", SHAPES)
+def test_split_heads(W, d, scores):
+    # segments that end inside the window, heads with fewer blocks than segments, empty prefixes
+    lens = [W, W + 1, 100, 2047, 2048, 4097, 16384, 32768]
     _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, n_heads=1)
 
 
-def test_long_heads_of_every_method_in_one_batch():
+@pytest.mark.parametrize("fillers", [0, WIDE, NARROW])
+def test_every_method_in_one_batch(fillers):
     lens = [9000, 20000, 12345, 32768, 8200, 600]
+    budgets = [1800, 19999, 4000, 5, 8200, 300]
     methods = [SNAP, KNORM, STREAM, KNORM, SNAP, SNAP]
     for scores in (True, False):
-        _run(lens, [1800, 19999, 4000, 5, 8200, 300], methods, 32, 128, scores, n_heads=2)
-        _run(lens, [1800, 19999, 4000, 5, 8200, 300], methods, 32, 128, scores, fillers=300)
+        _run(lens, budgets, methods, 32, 128, scores, fillers)
+    _run(lens, budgets, methods, 32, 128, False, fillers, in_place=True)
+
+
+@pytest.mark.parametrize("fillers", [0, WIDE, NARROW])
+def test_log_sum_exp_handed_in(fillers):
+    lens = [2500, 9000, 700]
+    _run(lens, [500, 1800, 300], [SNAP] * 3, 32, 128, True, fillers, lse="library")
