@@ -698,8 +698,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
       BatchParams bc = bp;
       bc.order_fused = dev_lists + fused_at[i];
       bc.n_fused = (int)l.units.size();
-      bc.window = 16 * l.query_tiles;
-      e = launch_fused(bc, l.query_tiles > 0, l.max_len, l.max_blocks, l.wide, stream);
+      e = launch_fused(bc, l.query_tiles, l.max_len, l.max_blocks, l.wide, stream);
     }
     return e;
   }));

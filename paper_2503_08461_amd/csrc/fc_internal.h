@@ -130,9 +130,9 @@ hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s);
 hipError_t launch_gather(const BatchParams& p, hipStream_t s);
 // score -> select -> gather of every unit of order_fused in one launch.
 // max_seq_len: longest head that is scored, at most kFusedMaxLen (kFusedWideMaxLen
-// with wide workgroups); max_blocks: most blocks of any of the units; any_snap:
-// the list holds a SnapKV request
-hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_blocks, bool wide,
+// with wide workgroups); max_blocks: most blocks of any of the units; query_tiles:
+// 16-row tiles of its SnapKV units (0: none, 5: of several classes)
+hipError_t launch_fused(BatchParams p, int query_tiles, int max_seq_len, int max_blocks, bool wide,
                         hipStream_t s);
 // (per head size and workgroup shape; lds: dynamic LDS bytes)
 hipError_t launch_fused_narrow_64(const BatchParams& p, int query_tiles, size_t lds, hipStream_t s);

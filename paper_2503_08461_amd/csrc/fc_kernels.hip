@@ -455,7 +455,7 @@ hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_blocks, bool wide,
+hipError_t launch_fused(BatchParams p, int query_tiles, int max_seq_len, int max_blocks, bool wide,
                         hipStream_t s) {
   if (p.n_fused == 0) return hipSuccess;
   if (max_seq_len > (wide ? kFusedWideMaxLen : kFusedMaxLen)) return hipErrorInvalidValue;
@@ -463,11 +463,10 @@ hipError_t launch_fused(BatchParams p, bool any_snap, int max_seq_len, int max_b
   p.ids_at = f.ids_at;
   p.ids_room = f.ids_room;
   const size_t lds = (size_t)f.words * sizeof(uint32_t);
-  const int tiles = any_snap ? (p.window + 15) / 16 : 0;
   if (p.head_dim == 128)
-    return wide ? launch_fused_wide_128(p, tiles, lds, s) : launch_fused_narrow_128(p, tiles, lds, s);
+    return wide ? launch_fused_wide_128(p, query_tiles, lds, s) : launch_fused_narrow_128(p, query_tiles, lds, s);
   if (p.head_dim == 64)
-    return wide ? launch_fused_wide_64(p, tiles, lds, s) : launch_fused_narrow_64(p, tiles, lds, s);
+    return wide ? launch_fused_wide_64(p, query_tiles, lds, s) : launch_fused_narrow_64(p, query_tiles, lds, s);
   return hipErrorInvalidValue;
 }
 

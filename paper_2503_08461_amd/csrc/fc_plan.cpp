@@ -19,6 +19,9 @@ namespace fc {
 
 namespace {
 
+// FusedLaunch::query_tiles of a launch whose windows need different numbers of tiles.
+constexpr int kMixedQueryTiles = kPlanClasses;
+
 // Heads shorter than this are not worth the launches of the split path.
 constexpr int kSplitMinLen = 2048;
 
@@ -193,43 +196,40 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
 
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu) {
   const size_t n_lh = (size_t)pool.n_layers * pool.n_heads;
-  std::vector<FusedLaunch> launches;
-  // One launch per number of query tiles and workgroup shape.  Narrow workgroups
-  // (three or four to a CU) take heads of up to 8192 tokens; wide ones (one to a
-  // CU, three to four times the wavefronts) take the longer heads, whose scores
-  // fill the LDS of a CU, and lists with so few units that narrow workgroups would
-  // leave most of the chip's wavefronts idle.
-  FusedLaunch wide[kPlanClasses], narrow[kPlanClasses];
+  // Narrow workgroups (three or four to a CU) take heads of up to 8192 tokens; wide
+  // ones (one to a CU, three to four times the wavefronts) take the longer heads,
+  // whose scores fill the LDS of a CU, and calls with so few units that narrow
+  // workgroups would leave most of the chip's wavefronts idle.  One launch per
+  // shape, whatever windows its requests have: a launch per window class ends in a
+  // tail of its own (24 requests with windows 1..64, 2 layers of 32 heads: 776 us
+  // as four launches, 661-715 as one, by box).
+  FusedLaunch wide, narrow;
+  auto add = [](FusedLaunch& to, const std::vector<int32_t>& list) {
+    to.units.insert(to.units.end(), list.begin(), list.end());
+  };
+  size_t short_units = 0;
+  for (int c = 0; c < kPlanClasses; ++c) short_units += plan.lists[LIST_FUSED + c].size() * n_lh;
   for (int c = 0; c < kPlanClasses; ++c) {
-    const std::vector<int32_t>& list = plan.lists[LIST_FUSED + c];
-    FusedLaunch& to = list.size() * n_lh <= 2 * (size_t)n_cu ? wide[c] : narrow[c];
-    to.units = list;
-    if (pool.score_mode == PLAN_SCORE_AUTO)
-      wide[c].units.insert(wide[c].units.end(), plan.lists[LIST_SNAP + c].begin(), plan.lists[LIST_SNAP + c].end());
+    add(short_units <= 2 * (size_t)n_cu ? wide : narrow, plan.lists[LIST_FUSED + c]);
+    if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_SNAP + c]);
   }
-  if (pool.score_mode == PLAN_SCORE_AUTO) {
-    // units without queries ride in the fullest wide launch
-    int home = 0;
-    for (int c = 1; c < kPlanClasses; ++c)
-      if (wide[c].units.size() > wide[home].units.size()) home = c;
-    const std::vector<int32_t>& list = plan.lists[LIST_KNORM];
-    wide[home].units.insert(wide[home].units.end(), list.begin(), list.end());
-  }
-  for (int w = 1; w >= 0; --w)
-    for (int c = 0; c < kPlanClasses; ++c) {
-      FusedLaunch& l = w ? wide[c] : narrow[c];
-      if (l.units.empty()) continue;
-      l.wide = w != 0;
-      std::stable_sort(l.units.begin(), l.units.end(),
-                       [&](int x, int y) { return plan.weights[x] > plan.weights[y]; });
-      for (int i : l.units) {
-        const ReqDesc& d = plan.descs[i];
-        if (d.method != PLAN_METHOD_STREAMING) l.max_len = std::max(l.max_len, d.seq_len);
-        l.max_blocks = std::max(l.max_blocks, d.n_old);
-        if (d.method == PLAN_METHOD_SNAPKV) l.query_tiles = c;
-      }
-      launches.push_back(std::move(l));
+  if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_KNORM]);
+  wide.wide = true;
+  std::vector<FusedLaunch> launches;
+  for (FusedLaunch* l : {&wide, &narrow}) {
+    if (l->units.empty()) continue;
+    std::stable_sort(l->units.begin(), l->units.end(),
+                     [&](int x, int y) { return plan.weights[x] > plan.weights[y]; });
+    for (int i : l->units) {
+      const ReqDesc& d = plan.descs[i];
+      if (d.method != PLAN_METHOD_STREAMING) l->max_len = std::max(l->max_len, d.seq_len);
+      l->max_blocks = std::max(l->max_blocks, d.n_old);
+      if (d.method != PLAN_METHOD_SNAPKV) continue;
+      const int tiles = (d.window + 15) / 16;
+      l->query_tiles = l->query_tiles == 0 || l->query_tiles == tiles ? tiles : kMixedQueryTiles;
     }
+    launches.push_back(std::move(*l));
+  }
   return launches;
 }
 

@@ -81,7 +81,7 @@ int plan_compress(const PoolView& pool, const CompressArgs& args, CompressPlan* 
 // per unit) of a planned call, heaviest unit first in each.
 struct FusedLaunch {
   std::vector<int32_t> units;  // descriptor indices
-  int query_tiles = 0;         // 16-row query tiles of its SnapKV units (0: it holds none)
+  int query_tiles = 0;         // 16-row query tiles of its SnapKV units (0: it holds none, 5: they differ)
   bool wide = false;           // wide workgroups, one per CU
   int max_len = 0;             // longest head that is scored
   int max_blocks = 0;          // most blocks of a unit

@@ -487,9 +487,9 @@ struct PoolMinLow {  // smallest low half
 };
 
 // The pooling windows [c + e - h, c + e + h] of the four tokens c + e (c a
-// multiple of 4) over stage[0 .. n) and its margins.  h = 3 (a pooling width of
-// 7, the usual one) has its own code: three 16-byte reads, the part of the
-// windows that all four share once.  Any other h walks the 16-byte groups.
+// multiple of 4) over stage[0 .. n) and its margins: three 16-byte reads up to
+// h = 4, more groups beyond.  h = 3 (a pooling width of 7, the usual one) has code
+// of its own, in which the part of the windows that all four share is taken once.
 template <bool kThree>
 struct PoolWindow {
   uint32x4 left, mid, right;
@@ -519,7 +519,24 @@ struct PoolWindow {
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) out[e] = Op::get(mid[e]);
-      if (h == 0) return;
+      if (h == 0) return;  // uniform, as all that follows
+      if (h <= 4) {
+        const uint32x4 w0 = lds_words4(stage + c - 4), w1 = lds_words4(stage + c + 4);
+        uint32_t v[12];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = Op::get(w0[e]);
+          v[4 + e] = out[e];
+          v[8 + e] = Op::get(w1[e]);
+        }
+#pragma unroll
+        for (int d = 1; d <= 4; ++d) {
+          if (d > h) break;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) out[e] = Op::join(out[e], Op::join(v[4 + e - d], v[4 + e + d]));
+        }
+        return;
+      }
       uint32_t shared = Op::neutral;
       const int reach = (h + 3) >> 2;  // groups to either side
       for (int g = -reach; g <= reach; ++g) {
@@ -1597,6 +1614,23 @@ __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc
 // One launch serves both methods (the unit's descriptor says which); NT =
 // ceil(window / 16), or 0 when the launch holds no SnapKV unit.
 
+// f(the number of query tiles): NT itself, or (kMixedTiles: a launch whose SnapKV
+// units have windows of different classes) what the unit's window needs.
+static constexpr int kMixedTiles = 5;
+template <int NT, typename F>
+__device__ __forceinline__ void for_query_tiles(int window, F f) {
+  if constexpr (NT == kMixedTiles) {
+    switch ((window + 15) >> 4) {  // uniform
+      case 1: f(std::integral_constant<int, 1>{}); break;
+      case 2: f(std::integral_constant<int, 2>{}); break;
+      case 3: f(std::integral_constant<int, 3>{}); break;
+      default: f(std::integral_constant<int, 4>{}); break;
+    }
+  } else if constexpr (NT > 0) {
+    f(std::integral_constant<int, NT>{});
+  }
+}
+
 template <int D, int NT, int WV>
 __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
   extern __shared__ __align__(16) uint32_t lds[];
@@ -1625,8 +1659,9 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
     bool snap = false;
     if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
     if (snap) {
-      if constexpr (NT > 0)
-        snapkv_unit<D, NT, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
+      for_query_tiles<NT>(rd.window, [&](auto nt) {
+        snapkv_unit<D, decltype(nt)::value, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
+      });
     } else {
       knorm_unit<D, WV>(p, rd, lh, sm_ids, 0, rd.n_old, [&](int j, float v) { stage[j] = v; });
     }
@@ -1637,12 +1672,18 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
   gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
 }
 
+// Wavefronts per SIMD that the registers must allow: what the kernel needs without
+// spilling in its loops.
+__host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
+  return wv != kNarrow ? wv / 4 : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
+}
+
 // The fused kernel with the pruned second pass for its SnapKV units (see
 // snapkv_bounds); key-norm and streaming units that ride in the launch run as in
 // fused_unit_kernel.  Dynamic LDS: the scores, then one bit per token, then the
 // block ids.
 template <int D, int NT, int WV>
-__global__ __launch_bounds__(64 * WV, WV == kNarrow ? 3 : WV / 4) void fused_bounded_kernel(BatchParams p) {
+__global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_bounded_kernel(BatchParams p) {
   extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
     ScoreShared<WV> score;
@@ -1670,24 +1711,27 @@ __global__ __launch_bounds__(64 * WV, WV == kNarrow ? 3 : WV / 4) void fused_bou
   } else {
     uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
     if (rd.method == 1 /* FC_METHOD_SNAPKV */) {
-      constexpr int KS = D / 32;
-      const int q4 = (threadIdx.x & 63) >> 4;
-      half8 qreg[NT][KS];
-      load_window_queries<D, NT>(p, rd, lh, qreg);
-      const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
-      if (prune) snapkv_bounds<D, NT, WV>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
-      if (!prune || keep.bad) {  // bad: not representable against a running reference
-        snapkv_unit_q<D, NT, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
-      } else {
-        float mrow[NT][4];
+      for_query_tiles<NT>(rd.window, [&](auto nt) {
+        constexpr int N = decltype(nt)::value;
+        constexpr int KS = D / 32;
+        const int q4 = (threadIdx.x & 63) >> 4;
+        half8 qreg[N][KS];
+        load_window_queries<D, N>(p, rd, lh, qreg);
+        const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
+        if (prune) snapkv_bounds<D, N, WV>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
+        if (!prune || keep.bad) {  // bad: not representable against a running reference
+          snapkv_unit_q<D, N, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
+        } else {
+          float mrow[N][4];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+          for (int t = 0; t < N; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) mrow[nt][r] = sh.bound.fin[nt * 16 + q4 * 4 + r];
-        __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
-        bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
-        snapkv_rescore<D, NT, WV>(p, rd, lh, sm_ids, map, stage, qreg, mrow);
-      }
+            for (int r = 0; r < 4; ++r) mrow[t][r] = sh.bound.fin[t * 16 + q4 * 4 + r];
+          __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
+          bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
+          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, qreg, mrow);
+        }
+      });
     } else {
       knorm_unit<D, WV>(p, rd, lh, sm_ids, 0, rd.n_old, [&](int j, float v) { stage[j] = v; });
     }
@@ -1736,6 +1780,7 @@ static hipError_t launch_fused_d(const BatchParams& p, int query_tiles, size_t l
     case 2: launch_fused_one<D, 2, kWideShape>(p, lds, s); break;
     case 3: launch_fused_one<D, 3, kWideShape>(p, lds, s); break;
     case 4: launch_fused_one<D, 4, kWideShape>(p, lds, s); break;
+    case kMixedTiles: launch_fused_one<D, kMixedTiles, kWideShape>(p, lds, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1764,6 +1809,7 @@ static hipError_t wide_setup_d() {
   if (e == hipSuccess) e = wide_setup_one<D, 2>();
   if (e == hipSuccess) e = wide_setup_one<D, 3>();
   if (e == hipSuccess) e = wide_setup_one<D, 4>();
+  if (e == hipSuccess) e = wide_setup_one<D, kMixedTiles>();
   return e;
 }
 

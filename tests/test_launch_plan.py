@@ -1,0 +1,93 @@
+"""How a compress call's heads are spread over workgroups (csrc/fc_plan.cpp):
+every unit in exactly one launch, heads within the launch's limits, the sizes at
+which the shapes change, and offsets of split heads.  Host code, built with the
+sanitizers, no GPU."""
+
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+SNAP, KNORM, STREAM = 1, 2, 3
+N_CU = 256
+
+
+def _case(nl, nh, reqs, mode=0, in_place=0, d=128, n_cu=N_CU):
+    return (nl, nh, d, mode, in_place, n_cu, reqs)
+
+
+def _random_case(rng):
+    nl, nh = rng.choice([(1, 4), (1, 32), (2, 32), (32, 32)])
+    reqs = []
+    for _ in range(rng.randrange(1, 40)):
+        m = rng.choice([SNAP, SNAP, KNORM, STREAM])
+        w = rng.randrange(1, 65)
+        L = max(w, int(2 ** rng.uniform(0, 15)))
+        reqs.append((L, m, rng.randrange(w, L + 1) if m == SNAP else rng.randrange(1, L + 1), w))
+    return _case(nl, nh, reqs, rng.choice([0, 0, 0, 1]), rng.choice([0, 0, 1]))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_launch_plan(tmp_path):
+    exe = str(tmp_path / "launch_plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-static-libasan", "-static-libubsan", os.path.join(ROOT, "tests", "launch_plan_driver.cpp"),
+                    os.path.join(ROOT, "paper_2503_08461_amd", "csrc", "fc_plan.cpp"), "-o", exe], check=True)
+    long1 = [(2048, SNAP, 400, 32)]
+    edges = [
+        (_case(1, 128, long1), "split"),                 # one head per two compute units
+        (_case(1, 129, long1), "wide"),
+        (_case(1, 128, [(2047, SNAP, 400, 32)]), "wide"),  # too short to split
+        (_case(1, 128, long1, in_place=1), "wide"),      # one workgroup per head copies in place
+        (_case(1, 512, long1), "wide"),                  # two heads per compute unit
+        (_case(1, 513, long1), "narrow"),
+        (_case(1, 513, [(8192, SNAP, 400, 32)]), "narrow"),
+        (_case(1, 513, [(8193, SNAP, 400, 32)]), "wide"),
+    ]
+    rng = random.Random(7)
+    cases = [c for c, _ in edges] + [_random_case(rng) for _ in range(300)]
+    text = "".join("%d %d %d %d %d %d %d\n%s\n" % (c[:6] + (len(c[6]), "\n".join("%d %d %d %d" % r for r in c[6])))
+                   for c in cases)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+    parsed = []
+    for line in out.splitlines():
+        row = [int(x) for x in line.split()[1:]]
+        if line[0] == "C":
+            parsed.append((row, []))
+        else:
+            parsed[-1][1].append(row)
+    assert len(parsed) == len(cases)
+    for (head, launches), (_, want) in zip(parsed, edges):
+        got = "split" if head[0] else "wide" if launches[0][0] else "narrow"
+        assert got == want and len(launches) == 1
+    n_split = 0
+    for ((split, raw_floats, *raw_offs), launches), (nl, nh, _, mode, in_place, n_cu, reqs) in zip(parsed, cases):
+        units = nl * nh
+        if split:
+            n_split += 1
+            assert mode == 0 and not in_place and units * len(reqs) <= n_cu // 2
+            at = 0
+            for (L, *_), off in zip(reqs, raw_offs):
+                assert off == at
+                at += units * L
+            assert raw_floats == at and 2 <= split <= max(L for L, m, *_ in reqs if m != STREAM) // 256
+        seen = []
+        for wide, tiles, max_len, max_blocks, *members in launches:
+            seen += members
+            lens = [reqs[i][0] for i in members]
+            scored = [reqs[i][0] for i in members if reqs[i][1] != STREAM]
+            classes = {(reqs[i][3] + 15) // 16 for i in members if reqs[i][1] == SNAP}
+            assert max_len == max(scored, default=0) <= (32768 if wide else 8192)
+            assert max_blocks == max((L + 15) // 16 for L in lens)
+            assert tiles == (0 if not classes else 5 if len(classes) > 1 else classes.pop())
+            weight = [2 * reqs[i][0] * (reqs[i][1] == SNAP) + reqs[i][0] * (reqs[i][1] == KNORM) + 4 * reqs[i][2]
+                      for i in members]
+            assert weight == sorted(weight, reverse=True)
+        # (with the separate scheduling only streaming requests run in the fused kernels)
+        assert sorted(seen) == [i for i, r in enumerate(reqs) if mode == 0 or r[1] == STREAM]
+        assert len(launches) <= 2
+    assert n_split > 5
