@@ -466,12 +466,15 @@ int release_verdict(fc_pool* p, hipStream_t stream, const char* what) {
               "nothing was changed");
 }
 
-// Descriptors and work lists to the device.  With the library's own scratch
-// they go through the pinned staging buffer and one asynchronous copy; the
-// allocation-free path sends them as kernel arguments, a few KB per launch.
+// Descriptors and work lists to the device (bytes: a multiple of 16).  Up to four
+// launches' worth go as kernel arguments, and whatever the allocation-free call
+// needs; more go through the pinned staging buffer and one asynchronous copy, whose
+// price (10 to 40 us of an idle GPU, see plan_alloc_inline_kernel) is that of four to
+// eight launches and does not grow with the size.
+constexpr size_t kMaxArgumentMeta = 4 * sizeof(MetaChunk);
 int upload_meta(fc_pool* p, const char* image, size_t bytes, char* dev_dst, bool no_alloc,
                 hipStream_t stream) {
-  if (no_alloc) {
+  if (no_alloc || bytes <= kMaxArgumentMeta) {
     for (size_t off = 0; off < bytes; off += sizeof(MetaChunk)) {
       MetaChunk c;
       const size_t n = std::min(sizeof(MetaChunk), bytes - off);
@@ -490,6 +493,14 @@ int upload_meta(fc_pool* p, const char* image, size_t bytes, char* dev_dst, bool
   FC_HIP(hipEventRecord(p->meta_event, stream));
   p->meta_pending = true;
   return FC_OK;
+}
+
+// Whether plan_alloc can take the descriptors as its own argument: they fit, and no
+// ownership check reads them first.
+bool fits_inline(const fc_pool* p, const char* image, size_t bytes, MetaChunk* c) {
+  if (p->debug_checks || bytes > sizeof(MetaChunk)) return false;
+  memcpy(c->bytes, image, bytes);
+  return true;
 }
 
 // All entry points of the pruning stage.  host_window / host_pool_kernel are
@@ -600,7 +611,10 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   std::vector<char> image(meta_bytes, 0);
   memcpy(image.data(), plan.descs.data(), (size_t)n_comp * sizeof(ReqDesc));
   memcpy(image.data() + desc_bytes, lists.data(), lists.size() * sizeof(int32_t));
-  if ((rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK) return rc;
+  MetaChunk inline_meta;
+  const bool meta_inline = fits_inline(p, image.data(), meta_bytes, &inline_meta);
+  if (!meta_inline && (rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK)
+    return rc;
 
   BatchParams bp = {};
   bp.kv = p->kv;
@@ -671,7 +685,9 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     }
     return e;
   };
-  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, true, [&] { return launch_plan_alloc(bp, stream); }));
+  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, true, [&] {
+    return launch_plan_alloc(bp, meta_inline ? &inline_meta : nullptr, (int)meta_bytes, stream);
+  }));
   FC_HIP_STAGE(p, run(K_SNAPKV_SCORE, ns > 0, [&] {
     hipError_t e = hipSuccess;
     for (int c = 1; c < kPlanClasses && e == hipSuccess; ++c) {
@@ -885,7 +901,10 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
   std::vector<char> image(desc_bytes + job_bytes, 0);
   memcpy(image.data(), plan.descs.data(), (size_t)n_comp * sizeof(ReqDesc));
   memcpy(image.data() + desc_bytes, plan.jobs.data(), plan.jobs.size() * sizeof(MlpJob));
-  if ((rc = upload_meta(p, image.data(), image.size(), p->dev_meta, false, stream)) != FC_OK)
+  MetaChunk inline_meta;
+  const bool meta_inline = fits_inline(p, image.data(), image.size(), &inline_meta);
+  if (!meta_inline &&
+      (rc = upload_meta(p, image.data(), image.size(), p->dev_meta, false, stream)) != FC_OK)
     return rc;
 
   BatchParams bp = {};
@@ -944,7 +963,9 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
     }
     return e;
   };
-  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, [&] { return launch_plan_alloc(bp, stream); }));
+  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, [&] {
+    return launch_plan_alloc(bp, meta_inline ? &inline_meta : nullptr, (int)image.size(), stream);
+  }));
   FC_HIP_STAGE(p, run(K_MLP, [&] { return launch_mlp_compress(bp, mp, stream); }));
   FC_HIP_STAGE(p, run(K_RECLAIM, [&] { return launch_reclaim(bp, stream); }));
 
@@ -975,13 +996,20 @@ hipError_t run_profiled(fc_pool* p, int slot, hipStream_t stream, F&& launch) {
   return e;
 }
 
-// descriptors of a decode step to the device through the pinned staging buffer
-int upload_decode_reqs(fc_pool* p, const std::vector<DecodeReq>& reqs, hipStream_t stream) {
+// requests of a decode step: as kernel arguments (dp->reqs stays NULL) if they fit,
+// else to the device
+int pass_decode_reqs(fc_pool* p, const std::vector<DecodeReq>& reqs, DecodeParams* dp,
+                     DecodeReqs* inline_reqs, hipStream_t stream) {
+  if (reqs.size() <= DecodeReqs::kInline) {
+    std::copy(reqs.begin(), reqs.end(), inline_reqs->req);
+    return FC_OK;
+  }
   const size_t bytes = round_up(reqs.size() * sizeof(DecodeReq), 16);
   int rc;
   if ((rc = grow_meta(p, bytes)) != FC_OK) return rc;
   std::vector<char> image(bytes, 0);
   memcpy(image.data(), reqs.data(), reqs.size() * sizeof(DecodeReq));
+  dp->reqs = reinterpret_cast<const DecodeReq*>(p->dev_meta);
   return upload_meta(p, image.data(), bytes, p->dev_meta, false, stream);
 }
 
@@ -994,7 +1022,6 @@ DecodeParams decode_params(fc_pool* p) {
   dp.head_dim = p->head_dim;
   dp.stack = p->stack;
   dp.top_before = p->top;
-  dp.reqs = reinterpret_cast<const DecodeReq*>(p->dev_meta);
   dp.owner = p->debug_checks ? p->owner : nullptr;
   dp.error_flag = p->error_flag;
   return dp;
@@ -1015,9 +1042,9 @@ int decode_attention_impl(fc_pool* p, const int32_t* dev_block_tables, int max_b
   if (plan_decode_attention(pool_view(p), n_req, max_blocks_per_req, host_seq_lens,
                             dev_kept ? host_budget : nullptr, &plan) != PLAN_OK)
     return fail(plan.code, "%s", plan.message);
-  int rc;
-  if ((rc = upload_decode_reqs(p, plan.reqs, stream)) != FC_OK) return rc;
   DecodeParams dp = decode_params(p);
+  DecodeReqs inline_reqs;
+  if (int rc = pass_decode_reqs(p, plan.reqs, &dp, &inline_reqs, stream)) return rc;
   dp.block_tables = const_cast<int32_t*>(dev_block_tables);
   dp.max_blocks = max_blocks_per_req;
   dp.n_req = n_req;
@@ -1027,7 +1054,7 @@ int decode_attention_impl(fc_pool* p, const int32_t* dev_block_tables, int max_b
   const float sc = (scale > 0.f) ? scale : 1.0f / sqrtf((float)p->head_dim);
   dp.scale_log2e = sc * 1.44269504088896340736f;
   FC_HIP(run_profiled(p, K_DECODE_ATTENTION, stream,
-                      [&] { return launch_decode_attention(dp, stream); }));
+                      [&] { return launch_decode_attention(dp, inline_reqs, stream); }));
   return FC_OK;
 }
 
@@ -1050,14 +1077,14 @@ int fc_append_batch(fc_pool* p, int32_t* dev_block_tables, int max_blocks_per_re
                   &plan) != PLAN_OK)
     return fail(plan.code, "%s", plan.message);
   if (plan.reqs.empty()) return FC_OK;
-  int rc;
-  if ((rc = upload_decode_reqs(p, plan.reqs, stream)) != FC_OK) return rc;
   DecodeParams dp = decode_params(p);
+  DecodeReqs inline_reqs;
+  if (int rc = pass_decode_reqs(p, plan.reqs, &dp, &inline_reqs, stream)) return rc;
   dp.block_tables = dev_block_tables;
   dp.max_blocks = max_blocks_per_req;
   dp.n_req = (int)plan.reqs.size();
   dp.new_kv = static_cast<const _Float16*>(dev_new_kv);
-  FC_HIP_STAGE(p, run_profiled(p, K_APPEND, stream, [&] { return launch_append(dp, stream); }));
+  FC_HIP_STAGE(p, run_profiled(p, K_APPEND, stream, [&] { return launch_append(dp, inline_reqs, stream); }));
   p->top -= plan.n_pop;
   for (const DecodeReq& q : plan.reqs) host_seq_lens[q.table_row] = q.seq_len + 1;
   return FC_OK;

@@ -16,10 +16,10 @@ namespace fc {
 // stack (pops in batch order) and the layer-0 workgroup records it in the table.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p) {
+__global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p, DecodeReqs inline_reqs) {
   const int r = blockIdx.x / p.n_layers;
   const int layer = blockIdx.x - r * p.n_layers;
-  const DecodeReq rq = p.reqs[r];
+  const DecodeReq rq = p.reqs ? p.reqs[r] : inline_reqs.req[r];
   const int L = rq.seq_len;
   int32_t* row = p.block_tables + (size_t)rq.table_row * p.max_blocks;
   int blk;
@@ -45,13 +45,13 @@ __global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p) {
   }
 }
 
-hipError_t launch_append(const DecodeParams& p, hipStream_t s) {
+hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
   if (p.n_req == 0) return hipSuccess;
   const unsigned grid = (unsigned)p.n_req * p.n_layers;
   if (p.head_dim == 128)
-    append_kernel<128><<<grid, kThreads, 0, s>>>(p);
+    append_kernel<128><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else if (p.head_dim == 64)
-    append_kernel<64><<<grid, kThreads, 0, s>>>(p);
+    append_kernel<64><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -71,14 +71,14 @@ hipError_t launch_append(const DecodeParams& p, hipStream_t s) {
 // the unit attends over the budget_r tokens of its kept list, read where they
 // lie in the uncompacted cache (every row its own 2*D contiguous bytes).
 template <int D, bool kIndexed>
-__global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p) {
+__global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, DecodeReqs inline_reqs) {
   constexpr int LPR = D / 8;        // lanes per row
   constexpr int RPI = 64 / LPR;     // rows per wavefront load instruction
   constexpr int IPB = 16 / RPI;     // load instructions per 16-token block
   constexpr int NG = kWaves * RPI;  // softmax states per workgroup
   const int n_lh = p.n_layers * p.n_heads;
   const int unit = blockIdx.x;
-  const DecodeReq rq = p.reqs[unit / n_lh];
+  const DecodeReq rq = p.reqs ? p.reqs[unit / n_lh] : inline_reqs.req[unit / n_lh];
   const int lh = unit - (unit / n_lh) * n_lh;
   const int layer = lh / p.n_heads;
   const int head = lh - layer * p.n_heads;
@@ -171,18 +171,18 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
   }
 }
 
-hipError_t launch_decode_attention(const DecodeParams& p, hipStream_t s) {
+hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
   if (p.n_req == 0) return hipSuccess;
   const unsigned grid = (unsigned)p.n_req * p.n_layers * p.n_heads;
   const bool indexed = p.kept != nullptr;
   if (p.head_dim == 128 && !indexed)
-    decode_attention_kernel<128, false><<<grid, kThreads, 0, s>>>(p);
+    decode_attention_kernel<128, false><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else if (p.head_dim == 128)
-    decode_attention_kernel<128, true><<<grid, kThreads, 0, s>>>(p);
+    decode_attention_kernel<128, true><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else if (p.head_dim == 64 && !indexed)
-    decode_attention_kernel<64, false><<<grid, kThreads, 0, s>>>(p);
+    decode_attention_kernel<64, false><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else if (p.head_dim == 64)
-    decode_attention_kernel<64, true><<<grid, kThreads, 0, s>>>(p);
+    decode_attention_kernel<64, true><<<grid, kThreads, 0, s>>>(p, inline_reqs);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -22,6 +22,14 @@ struct MlpParams {
   const float* b2[2];
 };
 
+// Requests of a decode step that travel as kernel arguments, up to kInline of them:
+// a copy through pinned memory costs the stream a copy kernel and 10 to 20 us of
+// idle time on either side, and the host has to wait until the last one is through.
+struct DecodeReqs {
+  static constexpr int kInline = 112;  // (3584 bytes of the 4 KB that arguments may take)
+  DecodeReq req[kInline];
+};
+
 struct DecodeParams {
   _Float16* kv;
   int32_t n_blocks, n_layers, n_heads, head_dim;
@@ -29,7 +37,7 @@ struct DecodeParams {
   int32_t top_before;
   int32_t* block_tables;
   int32_t max_blocks;
-  const DecodeReq* reqs;
+  const DecodeReq* reqs;  // NULL: the requests are in the DecodeReqs argument
   int32_t n_req;
   const _Float16* new_kv;  // append: [row][layer][2][head][d]
   const _Float16* q;       // attention: [row][layer][head][d]
@@ -84,9 +92,9 @@ struct BatchParams {
                                // 2 being released; NULL when the checks are off
 };
 
-// Descriptor bytes that travel as a kernel argument (allocation-free entry point).
+// Descriptor bytes that travel as a kernel argument.
 struct MetaChunk {
-  char bytes[3584];
+  alignas(16) char bytes[3584];
 };
 
 enum KernelSlot {
@@ -119,7 +127,9 @@ hipError_t launch_owner_check_ids(const int32_t* ids, int n, int n_blocks, int32
                                   int32_t* word, bool revert, hipStream_t s);
 hipError_t launch_owner_check_tables(const BatchParams& p, int32_t* word, bool revert,
                                      hipStream_t s);
-hipError_t launch_plan_alloc(const BatchParams& p, hipStream_t s);
+// inline_meta (nullable): the n_bytes of descriptors and lists that the kernel writes
+// to p.descs before anything else reads them
+hipError_t launch_plan_alloc(const BatchParams& p, const MetaChunk* inline_meta, int n_bytes, hipStream_t s);
 hipError_t launch_snapkv_score(const BatchParams& p, hipStream_t s);
 // a fill kernel (not a memset: calls may be captured into a graph)
 hipError_t launch_zero_ints(int32_t* p, int n, hipStream_t s);
@@ -147,8 +157,8 @@ hipError_t launch_reclaim(const BatchParams& p, hipStream_t s);
 hipError_t launch_meta_upload(const MetaChunk& c, char* dst, int n_bytes, hipStream_t s);
 hipError_t kernels_one_time_setup();
 // decode-side pool traffic (fc_decode.hip)
-hipError_t launch_append(const DecodeParams& p, hipStream_t s);
-hipError_t launch_decode_attention(const DecodeParams& p, hipStream_t s);
+hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s);
+hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s);
 // chunk-MLP compressor (fc_mlp.hip)
 hipError_t mlp_one_time_setup();
 size_t mlp_w1p_elems(int head_dim, int hidden, int k);

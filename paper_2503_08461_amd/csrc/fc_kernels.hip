@@ -103,15 +103,19 @@ __global__ void pool_push_kernel(int32_t* stack, int top, int n, const int32_t* 
 }
 
 // Writes descriptor bytes that came as a kernel argument to device memory.
+__device__ __forceinline__ void write_meta(const MetaChunk& c, char* dst, int n_bytes) {
+  // (dst and n_bytes are multiples of 16)
+  for (int i = threadIdx.x; i < n_bytes / 16; i += blockDim.x)
+    reinterpret_cast<uint4*>(dst)[i] = reinterpret_cast<const uint4*>(c.bytes)[i];
+}
 __global__ void meta_upload_kernel(MetaChunk c, char* dst, int n_bytes) {
-  for (int i = threadIdx.x; i < n_bytes; i += blockDim.x) dst[i] = c.bytes[i];
+  write_meta(c, dst, n_bytes);
 }
 
 // Pops the new blocks of every compressed request (batch order) and saves the
 // pre-compression ids.  One workgroup per request; offsets are exclusive
 // prefix sums computed by the host, which knows every count.
-__global__ __launch_bounds__(kThreads) void plan_alloc_kernel(BatchParams p) {
-  const ReqDesc rd = p.descs[blockIdx.x];
+__device__ __forceinline__ void plan_alloc_request(const BatchParams& p, const ReqDesc& rd) {
   const int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
   for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
     p.old_ids[rd.old_off + i] = row[i];
@@ -121,6 +125,18 @@ __global__ __launch_bounds__(kThreads) void plan_alloc_kernel(BatchParams p) {
       p.new_ids[rd.new_off + i] = id;
       owner_take(p.owner, id, p.n_blocks, p.error_flag);
     }
+}
+__global__ __launch_bounds__(kThreads) void plan_alloc_kernel(BatchParams p) {
+  plan_alloc_request(p, p.descs[blockIdx.x]);
+}
+// The same with the descriptors in its arguments, from where they go to device
+// memory for the kernels that follow: a small call has no copy of its own in the
+// stream (a copy through pinned memory left the GPU idle for 20 to 40 us, most of
+// it the host's wait for the staging buffer; a launch costs about 4.5 us).
+__global__ __launch_bounds__(kThreads) void plan_alloc_inline_kernel(BatchParams p, MetaChunk c, char* meta,
+                                                                     int n_bytes) {
+  plan_alloc_request(p, reinterpret_cast<const ReqDesc*>(c.bytes)[blockIdx.x]);
+  if (blockIdx.x == 0) write_meta(c, meta, n_bytes);
 }
 
 // Zombie reclaim: pushes the pre-compression blocks (batch order, table
@@ -379,8 +395,14 @@ hipError_t launch_meta_upload(const MetaChunk& c, char* dst, int n_bytes, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_plan_alloc(const BatchParams& p, hipStream_t s) {
-  plan_alloc_kernel<<<p.n_comp, kThreads, 0, s>>>(p);
+hipError_t launch_plan_alloc(const BatchParams& p, const MetaChunk* inline_meta, int n_bytes, hipStream_t s) {
+  if (inline_meta) {
+    if (n_bytes > (int)sizeof(MetaChunk)) return hipErrorInvalidValue;
+    plan_alloc_inline_kernel<<<p.n_comp, kThreads, 0, s>>>(
+        p, *inline_meta, const_cast<char*>(reinterpret_cast<const char*>(p.descs)), n_bytes);
+  } else {
+    plan_alloc_kernel<<<p.n_comp, kThreads, 0, s>>>(p);
+  }
   return hipGetLastError();
 }
 

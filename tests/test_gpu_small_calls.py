@@ -1,0 +1,52 @@
+"""Descriptors as kernel arguments: calls whose descriptors just fit one launch's
+arguments, just do not, need several launches, and go through pinned memory, one
+after the other on the same pool (each may only see its own)."""
+
+import numpy as np
+import pytest
+
+from oracle import decode_oracle as do
+from oracle import fastcache_oracle as fo
+from test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_req", [1, 34, 35, 36, 37, 142, 143, 144, 300])
+def test_compression(n_req):
+    """96 bytes a request and 4 per entry of a work list: 35 requests fill 3584 bytes, 143 four times as much."""
+    from parity_util import SideBySide
+    lens = [17 + (37 * i) % 90 for i in range(n_req)]
+    methods = [(fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING)[i % 3] for i in range(n_req)]
+    s = SideBySide(_custom(lens, [max(16, n // 2) for n in lens], methods, W=16, d=64, n_heads=1))
+    try:
+        s.compress_and_compare()
+        # again, with the shorter caches and fewer of them taking part
+        methods = np.array([m if i % 2 else fo.METHOD_NONE for i, m in enumerate(methods)], np.int32)
+        s.compress_and_compare(methods, np.full(n_req, 16, np.int32))
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("n_req", [1, 111, 112, 113, 460])
+def test_decode_step(n_req):
+    """32 bytes a request: 112 fill the arguments, 448 four launches'."""
+    import torch
+    from paper_2503_08461_amd import fastcache as fc
+    from test_gpu_decode import ATOL, RTOL, _setup
+    lens = [(29 * i) % 70 for i in range(n_req)]
+    s, wl = _setup(lens, d=64, n_heads=1, n_layers=1, spare=n_req)
+    try:
+        rng = np.random.default_rng(4)
+        for _ in range(2):
+            new = rng.standard_normal((n_req, 1, 2, 1, 64)).astype(np.float16)
+            fc.fc_append_batch(s.pool, s.bt_dev, s.lens_g, torch.from_numpy(new).to(s.dev))
+            q = rng.standard_normal((n_req, 1, 1, 64)).astype(np.float16)
+            got = fc.fc_decode_attention(s.pool, s.bt_dev, s.lens_g, torch.from_numpy(q).to(s.dev)).cpu().numpy()
+            assert do.append_batch(s.kv_host, s.stack, s.bt_host, s.lens_o, new, np.ones(n_req, np.int32)) is None
+            want = do.decode_attention(s.kv_host, s.bt_host, s.lens_o, q)
+            assert (np.abs(got - want) <= RTOL * np.abs(want) + ATOL).all()
+        torch.cuda.synchronize()
+        s.compare_state()
+    finally:
+        s.close()
