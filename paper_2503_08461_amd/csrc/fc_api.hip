@@ -152,6 +152,7 @@ struct fc_pool {
   bool meta_pending = false;
 
   int n_cu = 0;                   // compute units of the pool's device
+  float* decode_partial = nullptr;  // states of the segments of a split decode attention
   int32_t* error_flag = nullptr;  // device, one int, zero unless a kernel found something wrong
   int score_mode = FC_SCORE_AUTO;
   bool score_pruning = true;       // the fused kernel prunes the second pass of SnapKV units
@@ -248,6 +249,10 @@ int fc_pool_create(fc_pool** out, void* kv_base, size_t kv_bytes, int n_blocks, 
   if (e == hipSuccess) e = launch_stack_init(p->stack, n_blocks, nullptr);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->error_flag), sizeof(int32_t));
   if (e == hipSuccess) e = launch_zero_ints(p->error_flag, 1, nullptr);
+  // (a fixed size, here and not on demand: no decode step waits for an allocation)
+  if (e == hipSuccess)
+    e = hipMalloc(reinterpret_cast<void**>(&p->decode_partial),
+                  (size_t)kMaxDecodeSegments * DecodeParams::state_words(head_dim) * sizeof(float));
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->meta_event, hipEventDisableTiming);
   for (int c = 0; c < kProfRing && e == hipSuccess; ++c)
     for (int k = 0; k < K_COUNT && e == hipSuccess; ++k)
@@ -270,6 +275,7 @@ int fc_pool_destroy(fc_pool* p) {
   if (p->raw_scores) (void)hipFree(p->raw_scores);
   if (p->kept) (void)hipFree(p->kept);
   if (p->ids) (void)hipFree(p->ids);
+  if (p->decode_partial) (void)hipFree(p->decode_partial);
   if (p->error_flag) (void)hipFree(p->error_flag);
   for (int m = 0; m < 2; ++m) {
     if (p->mlp_w1p[m]) (void)hipFree(p->mlp_w1p[m]);  // w2p lies in the same allocation
@@ -1051,6 +1057,10 @@ int decode_attention_impl(fc_pool* p, const int32_t* dev_block_tables, int max_b
   dp.q = static_cast<const _Float16*>(dev_q);
   dp.out = dev_out;
   dp.kept = dev_kept;
+  plan_decode_segments(pool_view(p), p->n_cu, dev_kept != nullptr, &plan);
+  dp.seg_blocks = plan.seg_blocks;
+  dp.n_seg = plan.n_seg;
+  dp.partial = p->decode_partial;
   const float sc = (scale > 0.f) ? scale : 1.0f / sqrtf((float)p->head_dim);
   dp.scale_log2e = sc * 1.44269504088896340736f;
   FC_HIP(run_profiled(p, K_DECODE_ATTENTION, stream,

@@ -58,18 +58,41 @@ hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, h
 }
 
 // ---------------------------------------------------------------------------
-// attention of one decode step: workgroup = (request, layer, head), requests
-// in the order the host lists them (longest first).  A 16-token block of one
-// head is 32*D contiguous bytes for K and for V; a wavefront reads it with
+// attention of one decode step: workgroup = (request, layer, head) or a segment of
+// one, requests in the order the host lists them (longest first).  A 16-token block
+// of one head is 32*D contiguous bytes for K and for V; a wavefront reads it with
 // D/8 neighbouring lanes on one row (fully coalesced 16-byte loads), forms
-// q.k by a reduction inside that lane group, and keeps one online-softmax state
+// q.k by a DPP reduction inside that lane group, and keeps one online-softmax state
 // (running max, sum, and this lane's 8 output channels) per lane group.  The
 // 4 * (512 / D) states of the workgroup are merged through LDS at the end.
+//
+// What bounds it is HBM where the call has many heads to offer.  With few of them
+// the chip waits for the CU that has the longest one (one CU draws about 27 GB/s
+// whatever its wavefronts request), so such a call cuts every head into segments of
+// p.seg_blocks blocks: each leaves its state in p.partial, and a second launch merges
+// them.  (Merged by the workgroup that finishes a head last, the release and acquire
+// fences of all segments cost 170 to 300 us, against the 5 us of a launch.)
 // ---------------------------------------------------------------------------
 //
 // kIndexed: the counterfactual of a cache that was pruned WITHOUT compaction:
 // the unit attends over the budget_r tokens of its kept list, read where they
 // lie in the uncompacted cache (every row its own 2*D contiguous bytes).
+
+// sum over the LPR neighbouring lanes of a row, in every one of them
+template <int LPR>
+__device__ __forceinline__ float row_lanes_sum(float s) {
+  s += from_lane<0xB1>(s);   // the other lane of the pair,
+  s += from_lane<0x4E>(s);   // the other pair of the quad,
+  s += from_lane<0x141>(s);  // the other quad of the eight,
+  if constexpr (LPR == 16) s += from_lane<0x140>(s);  // the other eight of the sixteen
+  return s;
+}
+
+// segments of a head of L tokens
+__device__ __forceinline__ int decode_segments(int L, int seg_blocks) {
+  return (((L + 15) >> 4) + seg_blocks - 1) / seg_blocks;
+}
+
 template <int D, bool kIndexed>
 __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, DecodeReqs inline_reqs) {
   constexpr int LPR = D / 8;        // lanes per row
@@ -77,12 +100,18 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
   constexpr int IPB = 16 / RPI;     // load instructions per 16-token block
   constexpr int NG = kWaves * RPI;  // softmax states per workgroup
   const int n_lh = p.n_layers * p.n_heads;
-  const int unit = blockIdx.x;
-  const DecodeReq rq = p.reqs ? p.reqs[unit / n_lh] : inline_reqs.req[unit / n_lh];
-  const int lh = unit - (unit / n_lh) * n_lh;
+  // (request, segment, layer and head)
+  const int per_req = n_lh * p.n_seg;
+  const int slot = blockIdx.x / per_req;
+  const int seg = (blockIdx.x - slot * per_req) / n_lh;
+  const int lh = blockIdx.x - slot * per_req - seg * n_lh;
+  const DecodeReq rq = p.reqs ? p.reqs[slot] : inline_reqs.req[slot];
+  const int L = kIndexed ? rq.pop_index : rq.seq_len;  // indexed: pop_index holds the budget
+  const int nb = (L + 15) >> 4;
+  const int b0 = seg * p.seg_blocks, b1 = min(nb, b0 + p.seg_blocks);
+  if (seg > 0 && b0 >= nb) return;  // uniform: this request has fewer segments
   const int layer = lh / p.n_heads;
   const int head = lh - layer * p.n_heads;
-  const int L = kIndexed ? rq.pop_index : rq.seq_len;  // indexed: pop_index holds the budget
   const int32_t* kept =
       kIndexed ? p.kept + rq.kept_off + (size_t)lh * L : nullptr;  // ascending token indices
   const int lane = threadIdx.x & 63;
@@ -105,8 +134,7 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
                          (kIndexed ? 0 : (size_t)grp * D) + piece * 8;
 
   float m = -INFINITY, z = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int nb = (L + 15) >> 4;
-  for (int b = wave; b < nb; b += kWaves) {
+  for (int b = b0 + wave; b < b1; b += kWaves) {
     half8 k[IPB], v[IPB];
     if (kIndexed) {
       // 16 kept tokens at a time, each fetched from its own block and slot
@@ -132,8 +160,7 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) s += qf[e] * (float)k[i][e];
-#pragma unroll
-      for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o);
+      s = row_lanes_sum<LPR>(s);
       const int tok = b * 16 + i * RPI + grp;
       if (tok < L) {  // the whole lane group takes the same branch
         const float mn = fmaxf(m, s);
@@ -158,31 +185,82 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
 #pragma unroll
   for (int e = 0; e < 8; ++e) sm_acc[g][piece * 8 + e] = acc[e];
   __syncthreads();
+  float mm = -INFINITY, zz = 0.f, o = 0.f;
   if (threadIdx.x < D) {
-    float mm = -INFINITY;
     for (int i = 0; i < NG; ++i) mm = fmaxf(mm, sm_m[i]);
-    float zz = 0.f, o = 0.f;
     for (int i = 0; i < NG; ++i) {
-      const float f = sm_m[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm_m[i] - mm);
+      // (a sum of zero: no token; not a number stays not a number)
+      const float f = sm_z[i] == 0.f ? 0.f : __builtin_amdgcn_exp2f(sm_m[i] - mm);
       zz += sm_z[i] * f;
       o += sm_acc[i][threadIdx.x] * f;
     }
-    out[threadIdx.x] = L > 0 ? o / zz : 0.f;
   }
+  if (decode_segments(L, p.seg_blocks) <= 1) {  // uniform
+    if (threadIdx.x < D) out[threadIdx.x] = L > 0 ? o / zz : 0.f;
+    return;
+  }
+
+  // a segment's state: channel sums, max, sum
+  float* mine = p.partial + (((size_t)slot * n_lh + lh) * p.n_seg + seg) * DecodeParams::state_words(D);
+  if (threadIdx.x < D) mine[threadIdx.x] = o;
+  if (threadIdx.x == 0) {
+    mine[D] = mm;
+    mine[D + 1] = zz;
+  }
+}
+
+// segments of at least 16 blocks, of a head of at most 32768 tokens
+static constexpr int kMaxHeadSegments = kPlanMaxSeqLen / kPlanBlockSize / 16;
+
+// Heads that were cut: the output from the segments' states.  workgroup =
+// (request, layer, head), one thread per channel.
+template <int D, bool kIndexed>
+__global__ __launch_bounds__(D) void decode_merge_kernel(DecodeParams p, DecodeReqs inline_reqs) {
+  const int n_lh = p.n_layers * p.n_heads;
+  const int slot = blockIdx.x / n_lh;
+  const int lh = blockIdx.x - slot * n_lh;
+  const DecodeReq rq = p.reqs ? p.reqs[slot] : inline_reqs.req[slot];
+  const int L = kIndexed ? rq.pop_index : rq.seq_len;
+  const int n_seg = decode_segments(L, p.seg_blocks);
+  if (n_seg <= 1) return;  // written by the kernel above
+  constexpr int kWords = DecodeParams::state_words(D);
+  const float* states = p.partial + (size_t)blockIdx.x * p.n_seg * kWords;
+  __shared__ float sm_m[kMaxHeadSegments], sm_z[kMaxHeadSegments];
+  for (int i = threadIdx.x; i < n_seg; i += D) {  // (kMaxHeadSegments at most: checked by the launcher)
+    sm_m[i] = states[(size_t)i * kWords + D];
+    sm_z[i] = states[(size_t)i * kWords + D + 1];
+  }
+  __syncthreads();
+  float mm = -INFINITY, zz = 0.f, o = 0.f;
+  for (int i = 0; i < n_seg; ++i) mm = fmaxf(mm, sm_m[i]);
+#pragma unroll 8
+  for (int i = 0; i < n_seg; ++i) {
+    const float f = sm_z[i] == 0.f ? 0.f : __builtin_amdgcn_exp2f(sm_m[i] - mm);
+    zz += sm_z[i] * f;
+    o += states[(size_t)i * kWords + threadIdx.x] * f;
+  }
+  p.out[((size_t)rq.table_row * n_lh + lh) * D + threadIdx.x] = o / zz;
+}
+
+template <int D, bool kIndexed>
+static void launch_decode_one(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
+  const unsigned heads = (unsigned)p.n_req * p.n_layers * p.n_heads;
+  decode_attention_kernel<D, kIndexed><<<heads * p.n_seg, kThreads, 0, s>>>(p, inline_reqs);
+  if (p.n_seg > 1) decode_merge_kernel<D, kIndexed><<<heads, D, 0, s>>>(p, inline_reqs);
 }
 
 hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
   if (p.n_req == 0) return hipSuccess;
-  const unsigned grid = (unsigned)p.n_req * p.n_layers * p.n_heads;
+  if (p.n_seg < 1 || p.n_seg > kMaxHeadSegments || p.seg_blocks < 1) return hipErrorInvalidValue;
   const bool indexed = p.kept != nullptr;
   if (p.head_dim == 128 && !indexed)
-    decode_attention_kernel<128, false><<<grid, kThreads, 0, s>>>(p, inline_reqs);
+    launch_decode_one<128, false>(p, inline_reqs, s);
   else if (p.head_dim == 128)
-    decode_attention_kernel<128, true><<<grid, kThreads, 0, s>>>(p, inline_reqs);
+    launch_decode_one<128, true>(p, inline_reqs, s);
   else if (p.head_dim == 64 && !indexed)
-    decode_attention_kernel<64, false><<<grid, kThreads, 0, s>>>(p, inline_reqs);
+    launch_decode_one<64, false>(p, inline_reqs, s);
   else if (p.head_dim == 64)
-    decode_attention_kernel<64, true><<<grid, kThreads, 0, s>>>(p, inline_reqs);
+    launch_decode_one<64, true>(p, inline_reqs, s);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -5,7 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "fc_types.h"
+#include "fc_plan.h"
 
 namespace fc {
 
@@ -44,8 +44,12 @@ struct DecodeParams {
   float* out;              // attention: [row][layer][head][d]
   const int32_t* kept;     // attention over kept lists of an uncompacted cache, else NULL
   float scale_log2e;
+  // attention: blocks per segment of a head, segments of the longest one (1: no head is cut)
+  int32_t seg_blocks, n_seg;
+  float* partial;          // [n_req * layers * heads][n_seg][state_words] states of the segments
   int32_t* owner;          // ownership checks (debug mode), else NULL
   int32_t* error_flag;
+  static constexpr int state_words(int head_dim) { return head_dim + 4; }
 };
 
 // Everything a kernel of the stage needs.  Passed by value.

@@ -124,10 +124,16 @@ struct DecodePlan {
   std::vector<DecodeReq> reqs;
   int n_pop = 0;
   size_t kept_entries = 0;
+  int seg_blocks = 0, n_seg = 1;  // attention: blocks per segment of a head, segments of the longest one
 };
+// Attention: most segments of all heads of a call that is split (heads x n_seg), which
+// is what the pool's buffers for their states hold (8.7 MB at 128 channels).
+static constexpr int kMaxDecodeSegments = 16384;
 int plan_append(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,
                 const int32_t* enable, DecodePlan* plan);
 int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,
                           const int32_t* budget /* NULL: whole cache */, DecodePlan* plan);
+// Sets seg_blocks and n_seg of a planned attention (over_kept: of the kept lists).
+void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan);
 
 }  // namespace fc
