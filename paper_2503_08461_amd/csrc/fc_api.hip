@@ -893,7 +893,7 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
   if (n_req > 0 && !dev_block_tables) return fail(FC_EINVAL, "NULL argument");
   MlpPlan plan;
   if (plan_mlp(pool_view(p), n_req, max_blocks_per_req, host_seq_lens, host_img_begin,
-               host_img_end, host_enable, p->mlp_k, mlp_rows_per_tile(p->mlp_hidden),
+               host_img_end, host_enable, p->mlp_k, mlp_rows_per_tile(p->head_dim, p->mlp_hidden),
                &plan) != PLAN_OK)
     return fail(plan.code, "%s", plan.message);
   const int n_comp = (int)plan.descs.size();
@@ -935,7 +935,7 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
   mp.jobs = reinterpret_cast<const MlpJob*>(p->dev_meta + desc_bytes);
   mp.n_jobs = (int)plan.jobs.size();
   mp.n_tiles = (int)plan.n_tiles;
-  mp.max_grid = p->n_cu * mlp_workgroups_per_cu();
+  mp.max_grid = p->n_cu * mlp_workgroups_per_cu(p->head_dim, p->mlp_hidden);
   mp.k = p->mlp_k;
   mp.hidden = p->mlp_hidden;
   mp.activation = p->mlp_activation;

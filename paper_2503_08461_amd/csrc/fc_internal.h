@@ -167,8 +167,8 @@ hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs& inli
 hipError_t mlp_one_time_setup();
 size_t mlp_w1p_elems(int head_dim, int hidden, int k);
 size_t mlp_w2p_elems(int head_dim, int hidden);
-int mlp_rows_per_tile(int hidden);   // rows (units x chunks) one workgroup takes at a time
-int mlp_workgroups_per_cu();
+int mlp_rows_per_tile(int head_dim, int hidden);  // rows (units x chunks) one workgroup takes at a time
+int mlp_workgroups_per_cu(int head_dim, int hidden);
 hipError_t launch_mlp_permute_weights(const _Float16* w1, const _Float16* w2, _Float16* w1p,
                                       _Float16* w2p, int head_dim, int hidden, int k,
                                       hipStream_t s);

@@ -18,10 +18,17 @@
 //     order of the contraction index differs, and that is folded into the
 //     pre-permutation of W2.  The hidden activations therefore never leave
 //     registers.
-// A workgroup handles tiles of 256 rows (row = (layer, head, K|V) x chunk of
-// one request and one modality), NT column tiles of 32 rows per wavefront; the kernel
-// is persistent (one workgroup per CU walks the tile list) so that W2 is loaded
-// into LDS once per modality change rather than once per tile.
+// A workgroup handles tiles of 128 or 256 rows (row = (layer, head, K|V) x chunk of
+// one request and one modality), a column tile of 32 rows per wavefront; the kernel
+// is persistent (one to three workgroups per CU walk the tile list) so that W2 is
+// loaded into LDS once per modality change rather than once per tile.
+//
+// What bounds it: the latency of the scattered pool rows.  Loads complete in order,
+// so any load that is waited for waits for all rows requested before it; the tile
+// list and the requests are read by scalar loads, a tile's target block is looked up
+// before the next tile's rows are requested, and the store phase reloads nothing
+// (24 prompts of 1280-7040 tokens, 2 layers, d = 128, hidden 256: 1518 -> 1420 us,
+// 0.74 PFLOP/s; spilled registers 25 -> 8, none of them in the loops).
 
 #include "fc_device.h"
 
@@ -32,13 +39,36 @@ namespace fc {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
-static constexpr int kMlpRowsPerTile = 256;
 static constexpr uint32_t kNoRow = 0xffffffffu;  // "no such token" in the table of pool rows
-// threads of a workgroup when a wavefront takes NT column tiles of 32 chunks
-constexpr int mlp_threads(int nt) { return kMlpRowsPerTile / (32 * nt) * 64; }
 
-int mlp_rows_per_tile(int) { return kMlpRowsPerTile; }
-int mlp_workgroups_per_cu() { return 1; }
+// Wavefronts of a workgroup (32 rows of a tile each) and workgroups per CU.  Eight
+// wavefronts of up to 256 registers are what the accumulators and the operands in
+// flight allow; at 64 channels and 128 hidden units a wavefront needs 154 registers
+// and a workgroup 43 KB of LDS, so three workgroups of four fit, whose phases (first
+// product, activation, second product, store) then run side by side instead of in
+// step.  24 prompts of 1280-7040 tokens, 2 layers of 32 heads, k = 5: 743 -> 595 us
+// (one workgroup of four wavefronts with 64 rows each before).  At 128 channels and
+// 128 hidden units two workgroups of four would fit: 1049 -> 1075 us; at 64 and 256:
+// 833 both; not taken.
+template <int D, int HID>
+struct MlpShape {
+  static constexpr int kWaves = D == 64 && HID == 128 ? 4 : 8;
+  static constexpr int kPerCu = D == 64 && HID == 128 ? 3 : 1;
+  static constexpr int kRows = 32 * kWaves, kThreads = 64 * kWaves;
+  static constexpr int kWavesPerSimd = kWaves * kPerCu / 4;
+};
+
+template <typename F>
+static auto with_mlp_shape(int head_dim, int hidden, F f) {
+  if (head_dim == 128) return hidden == 256 ? f(MlpShape<128, 256>()) : f(MlpShape<128, 128>());
+  return hidden == 256 ? f(MlpShape<64, 256>()) : f(MlpShape<64, 128>());
+}
+int mlp_rows_per_tile(int head_dim, int hidden) {
+  return with_mlp_shape(head_dim, hidden, [](auto s) -> int { return s.kRows; });
+}
+int mlp_workgroups_per_cu(int head_dim, int hidden) {
+  return with_mlp_shape(head_dim, hidden, [](auto s) -> int { return s.kPerCu; });
+}
 
 // hidden unit that sits at contraction position (slab sl, lane half kh, element e)
 // of the second product, given how the first product leaves its result in
@@ -140,12 +170,32 @@ __device__ __forceinline__ float mlp_activation(float v) {
   return ACT == 0 ? gelu_erf(v) : gelu_tanh(v);
 }
 
+// Loads of what no lane of the launch writes, from a uniform address: scalar loads.
+// (Next to the kernel's own stores the compiler takes vector loads, and whatever
+// waits for one of those waits for all pool rows in flight.)
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+  typedef const __attribute__((address_space(4))) int32_t* ConstWords;
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  union {
+    T value;
+    int32_t words[sizeof(T) / 4];
+  } u;
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) u.words[i] = ((ConstWords)(uintptr_t)p)[i];
+  return u.value;
+}
+
 // what the lanes of a chunk read for the tokens its segment does not have
 __device__ __align__(256) _Float16 g_zero_row[128];
 
-template <int D, int HID, int NT, int ACT>
-__global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchParams p,
-                                                                      MlpParams mp) {
+template <int D, int HID, int ACT>
+__global__ __launch_bounds__((MlpShape<D, HID>::kThreads), (MlpShape<D, HID>::kWavesPerSimd))
+void mlp_compress_kernel(BatchParams p, MlpParams mp) {
+  // column tiles (32 chunks each) per wavefront: with two, one wavefront per SIMD is
+  // left, and nothing covers its stalls (slower at every width)
+  constexpr int NT = 1;
+  constexpr int kMlpRowsPerTile = MlpShape<D, HID>::kRows;
   constexpr int MT1 = HID / 32;               // 32-row tiles of hidden units
   constexpr int MT2 = D / 32;                 // 32-row tiles of output channels
   constexpr int S2 = HID / 16;                // K slabs of the second product
@@ -153,10 +203,10 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
   constexpr int GPT = 4;                      // W1 groups per token
   constexpr int GS = SPT / GPT;               // K slabs per group
   constexpr int GO = GS * MT1;                // A operands (W1 tiles) per group
-  constexpr int kMlpThreads = mlp_threads(NT);  // NT column tiles (32 chunks each) per wavefront
+  constexpr int kMlpThreads = MlpShape<D, HID>::kThreads;
   constexpr int PPG = GO * 64 / kMlpThreads;  // 16-byte pieces of a W1 group per thread
   constexpr int AR = 4;                       // A operands in flight from LDS
-  constexpr int XR = NT == 1 ? 2 : 1;         // tokens of B operands held in registers
+  constexpr int XR = 2;                       // tokens of B operands held in registers
   constexpr int WD = 2;                       // W1 groups in flight in registers (4 measured slower)
   constexpr int RT = 8 + XR;                  // rows of the per-lane token table
   static_assert(GO % AR == 0 && PPG >= 1, "tiling");
@@ -195,7 +245,7 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
     uint32_t base_row;     // pool row (units of D elements) of slot 0 of block 0 of its (layer, head, K|V)
   };
   auto find_job = [&](int tile, int& ji) {  // jobs are sorted by tile_start; ji only moves up
-    while (ji + 1 < mp.n_jobs && mp.jobs[ji + 1].tile_start <= tile) ++ji;
+    while (ji + 1 < mp.n_jobs && load_uniform(&mp.jobs[ji + 1].tile_start) <= tile) ++ji;
   };
   auto lane_of = [&](int tile, const MlpJob& job, const ReqDesc& rd, int nt) -> Lane {
     Lane ln;
@@ -263,8 +313,8 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
   int cur_m = -1;
   int ji = 0;
   find_job(blockIdx.x, ji);
-  MlpJob job = mp.jobs[ji];
-  ReqDesc rd = p.descs[job.desc];
+  MlpJob job = load_uniform(mp.jobs + ji);
+  ReqDesc rd = load_uniform(p.descs + job.desc);
   half8 xq[XR][NT][SPT];
   // the first tile's chain, not overlapped with anything
 #pragma unroll
@@ -290,8 +340,8 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
     const int tile_n = tile + (int)gridDim.x < mp.n_tiles ? tile + (int)gridDim.x : tile;
     int ji_n = ji;
     find_job(tile_n, ji_n);
-    const MlpJob job_n = mp.jobs[ji_n];
-    const ReqDesc rd_n = p.descs[job_n.desc];
+    const MlpJob job_n = load_uniform(mp.jobs + ji_n);
+    const ReqDesc rd_n = load_uniform(p.descs + job_n.desc);
 
     // weights of this modality: W2 and the biases stay in LDS across tiles and
     // are only reloaded when the modality changes
@@ -394,6 +444,19 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
       bid_n[nt][0] = ids[ln_n[nt].s0 >> 4];
       bid_n[nt][1] = ids[last >> 4];
     }
+    // ---- where this tile's rows go.  (Looked up here: behind the next tile's rows
+    // the block id would arrive only after all of them, loads complete in order.)
+    int out_row[NT], out_blk[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const long long row = (long long)(tile - job.tile_start) * kMlpRowsPerTile +
+                            wave * (32 * NT) + nt * 32 + col;
+      out_row[nt] = row < (long long)n_units * job.chunks ? (int)row : -1;
+      const int cl = max(out_row[nt], 0) % job.chunks;
+      const int o = (m == 1) ? rd.chunks_text0 + cl
+                             : (cl < rd.chunks_text0 ? cl : rd.chunks_image + cl);
+      out_blk[nt] = clamp_block(p.new_ids[rd.new_off + (o >> 4)], p.n_blocks);
+    }
 
     // ---- bias, gelu, fp16: each 32x32 result tile becomes two B operands of
     // the second product and stays in registers.  Half-way through, when half
@@ -418,7 +481,10 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
 #pragma unroll
     for (int mt = 0; mt < MT1 / 2; ++mt) gelu_tile(mt);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) write_rows(ln_n[nt], bid_n[nt], nt);
+    for (int nt = 0; nt < NT; ++nt) {
+      asm volatile("" : "+v"(out_blk[nt]));  // has arrived: the rows are requested behind it
+      write_rows(ln_n[nt], bid_n[nt], nt);
+    }
 #pragma unroll
     for (int u = 0; u < XR; ++u)
 #pragma unroll
@@ -451,21 +517,18 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
     // ---- bias, fp16, store the rows into the request's new blocks -------------
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      // (this tile's row again: cheaper than a register held across the loops)
-      const long long row_ll = (long long)(tile - job.tile_start) * kMlpRowsPerTile +
-                               wave * (32 * NT) + nt * 32 + col;
-      if (row_ll < (long long)n_units * job.chunks) {
-        const int row = (int)row_ll;
-        const int unit = row / job.chunks;
-        const int cl = row - unit * job.chunks;
+      if (out_row[nt] >= 0) {
+        const int unit = out_row[nt] / job.chunks;
+        const int cl = out_row[nt] - unit * job.chunks;
         const int o = (m == 1) ? rd.chunks_text0 + cl
                                : (cl < rd.chunks_text0 ? cl : rd.chunks_image + cl);
         const int lh = unit >> 1;
         const int layer = lh / p.n_heads;
-        const int nblk = clamp_block(p.new_ids[rd.new_off + (o >> 4)], p.n_blocks);
         _Float16* dst = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                        (size_t)nblk * blk_stride + (unit & 1) * v_off +
+                        (size_t)out_blk[nt] * blk_stride + (unit & 1) * v_off +
                         (size_t)(lh - layer * p.n_heads) * chunk_el + (size_t)(o & 15) * D;
+        int b2_at = 8 * kh;
+        asm volatile("" : "+v"(b2_at));  // one base and immediate offsets, not an address kept for every group
 #pragma unroll
         for (int ot = 0; ot < MT2; ++ot)
 #pragma unroll
@@ -475,7 +538,7 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
             const int c0 = 32 * ot + 16 * gp + 8 * kh;
             half8 y;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) y[r] = (_Float16)(acc2[ot][nt][8 * gp + r] + sm_b2[c0 + r]);
+            for (int r = 0; r < 8; ++r) y[r] = (_Float16)(acc2[ot][nt][8 * gp + r] + sm_b2[b2_at + 32 * ot + 16 * gp + r]);
             store_half8(dst + c0, y);
           }
       }
@@ -486,30 +549,20 @@ __global__ __launch_bounds__(mlp_threads(NT), 1) void mlp_compress_kernel(BatchP
   }
 }
 
-template <int D, int HID, int NT>
-static size_t mlp_lds_bytes() {
-  return (size_t)(HID / 16) * (D / 32) * 64 * 16 + (size_t)(D / 16) * (HID / 32) * 64 * 16 +
-         (size_t)(HID + D) * sizeof(float) + (size_t)(8 + 2) * NT * mlp_threads(NT) * sizeof(int);
-}
-
-// Column tiles per wavefront: with a hidden width of 256 one column tile
-// already needs 128 accumulator registers, so a wavefront takes one (eight
-// wavefronts, two per SIMD, 256 registers each); with 128 it takes two (four
-// wavefronts).  Two tiles at width 256 (four wavefronts with 512 registers)
-// measured slower: nothing covers the stalls of a lone wavefront on its SIMD.
 template <int D, int HID>
-constexpr int mlp_nt() { return (D / 64) * (HID / 32) * 64 >= 512 ? 1 : 2; }
+static constexpr size_t mlp_lds_bytes() {
+  return (size_t)(HID / 16) * (D / 32) * 64 * 16 + (size_t)(D / 16) * (HID / 32) * 64 * 16 +
+         (size_t)(HID + D) * sizeof(float) + (size_t)(8 + 2) * MlpShape<D, HID>::kThreads * sizeof(int);
+}
 
 template <int D, int HID>
 static hipError_t mlp_setup_one() {
-  constexpr int NT = mlp_nt<D, HID>();
-  hipError_t e = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(mlp_compress_kernel<D, HID, NT, 0>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlp_lds_bytes<D, HID, NT>());
+  static_assert(mlp_lds_bytes<D, HID>() * MlpShape<D, HID>::kPerCu <= 160 * 1024, "LDS of a CU");
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_compress_kernel<D, HID, 0>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlp_lds_bytes<D, HID>());
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_compress_kernel<D, HID, NT, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)mlp_lds_bytes<D, HID, NT>());
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_compress_kernel<D, HID, 1>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlp_lds_bytes<D, HID>());
   return e;
 }
 
@@ -523,14 +576,12 @@ hipError_t mlp_one_time_setup() {
 
 template <int D, int HID>
 static hipError_t mlp_launch_one(const BatchParams& p, const MlpParams& mp, hipStream_t s) {
-  constexpr int NT = mlp_nt<D, HID>();
+  constexpr int threads = MlpShape<D, HID>::kThreads;
   const unsigned grid = (unsigned)std::min(mp.n_tiles, mp.max_grid);
   if (mp.activation == 0)
-    mlp_compress_kernel<D, HID, NT, 0><<<grid, mlp_threads(NT), mlp_lds_bytes<D, HID, NT>(), s>>>(
-        p, mp);
+    mlp_compress_kernel<D, HID, 0><<<grid, threads, mlp_lds_bytes<D, HID>(), s>>>(p, mp);
   else
-    mlp_compress_kernel<D, HID, NT, 1><<<grid, mlp_threads(NT), mlp_lds_bytes<D, HID, NT>(), s>>>(
-        p, mp);
+    mlp_compress_kernel<D, HID, 1><<<grid, threads, mlp_lds_bytes<D, HID>(), s>>>(p, mp);
   return hipGetLastError();
 }
 
