@@ -43,8 +43,11 @@ def kernel_symbol(slot, wl, pruning):
     `slot` on workload wl (None where a slot covers several kernels)."""
     nt = 1 if wl.window <= 16 else (2 if wl.window <= 32 else 4)
     if slot == "fused_unit":
-        return "fc::%s<%d, %d>" % ("fused_bounded_kernel" if pruning else "fused_unit_kernel",
-                                   wl.head_dim, nt)
+        # wavefronts per workgroup: 4, or wide workgroups where a chip of 256 CUs gets at most two heads each
+        units = len(wl.seq_lens) * wl.n_layers * wl.n_heads
+        waves = 4 if units > 512 else (16 if nt <= 2 else 12)
+        return "fc::%s<%d, %d, %d>" % ("fused_bounded_kernel" if pruning else "fused_unit_kernel",
+                                       wl.head_dim, nt, waves)
     if slot == "snapkv_score":
         return "fc::snapkv_score_kernel<%d, %d>" % (wl.head_dim, nt)
     if slot in ("gather", "knorm_score"):

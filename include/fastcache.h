@@ -351,10 +351,10 @@ int fc_set_streaming_sinks(fc_pool* pool, int n_sink);
 
 /*
  * How fc_compress_batch schedules the scoring.
- *   FC_SCORE_AUTO (default): every (request, layer, head) of at most 8192
- *     tokens is handled by one fused kernel (two-pass score -> select -> gather
- *     inside the workgroup that owns the head; scores stay in LDS); longer
- *     heads go through the separate two-pass score, select and gather kernels.
+ *   FC_SCORE_AUTO (default): every (request, layer, head) is handled by one
+ *     fused kernel (two-pass score -> select -> gather inside the workgroup
+ *     that owns the head; scores stay in LDS), except in calls with so few and
+ *     long heads that each is split over several workgroups.
  *     (See fc_set_score_pruning for what the fused kernel does with the
  *     second pass when the call does not ask for the scores.)
  *   FC_SCORE_TWO_PASS: separate kernels for everything; SnapKV scoring streams
