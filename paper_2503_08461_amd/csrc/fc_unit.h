@@ -620,7 +620,7 @@ struct alignas(16) SelectShared {
   uint32_t wmin[WV], wmax[WV];
   int sel[2];
   int n_cand;
-  int cnt[WV][2];
+  int cnt[WV][2];  // keys above and keys not below the hinted range
 };
 
 // Selects the kept tokens of one (request, layer, head) and writes them, in
@@ -833,15 +833,19 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
         n_eq += __popcll(__ballot(k4[e] == thr));
       }
     });
+    // (not in sh.cnt: a narrowed range that is a single key comes here without a
+    // barrier, and slower wavefronts may still be reading the counts of step 1.  The
+    // histogram is read before a barrier, or was only cleared, before one as well)
+    int* const counts = hist;
     if (lane == 0) {
-      sh.cnt[wave][0] = n_gt;
-      sh.cnt[wave][1] = n_eq;
+      counts[2 * wave] = n_gt;
+      counts[2 * wave + 1] = n_eq;
     }
     __syncthreads();
     int gt_before = 0, eq_before = 0;
     for (int w = 0; w < wave; ++w) {
-      gt_before += sh.cnt[w][0];
-      eq_before += sh.cnt[w][1];
+      gt_before += counts[2 * w];
+      eq_before += counts[2 * w + 1];
     }
     t0 = gt_before + min(eq_before, need_eq);
     int eq_run = eq_before;

@@ -1,0 +1,116 @@
+"""The selection of a head (csrc/fc_unit.h: select_unit, bound_classify) run lane by
+lane on the CPU, wavefronts and lanes in every extreme order, against a plain
+statement of what it selects: the code as it is compiled for the GPU, no GPU."""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from conftest import ROOT
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
+
+ALL_KEYS = (0, 0xFFFFFFFF)
+ORDERS = range(4)  # bit 0: lanes, bit 1: wavefronts from the highest down
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("select") / "select_emulation")
+    subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1",
+                    os.path.join(ROOT, "tests", "select_emulation_driver.cpp"), "-o", exe], check=True)
+    return exe
+
+
+def score_keys(scores):
+    """uint32 in the order of the floats, -0 and +0 alike."""
+    u = (np.asarray(scores, np.float32) + np.float32(0)).view(np.uint32)
+    return np.where(u >> 31, ~u, u | 0x80000000)
+
+
+def pooled(scores, width):
+    """Max-pooled, what is not a number left out of a maximum with numbers."""
+    h = width // 2
+    p = np.concatenate([np.full(h, np.nan, np.float32), scores, np.full(h, np.nan, np.float32)])
+    return np.fmax.reduce([p[i:i + len(scores)] for i in range(width)])
+
+
+def kept_tokens(scores, k):
+    """The k best scores, ties to the lower index, in token order."""
+    order = np.argsort(-score_keys(scores).astype(np.int64), kind="stable")
+    return np.sort(order[:k])
+
+
+class Case:
+    def __init__(self, scores, k, width=7, snap=True, window=3, waves=4, hints=ALL_KEYS, order=0, bounds=None):
+        self.scores = np.asarray(scores, np.float32)
+        self.k, self.width, self.snap, self.window = k, width, snap, window if snap else 0
+        self.waves, self.hints, self.order, self.bounds = waves, hints, order, bounds
+
+    def text(self):
+        n = len(self.scores)
+        head = "%d %d %d %d %d %d %x %x %d %d" % (self.waves, self.snap, n, self.window, self.k, self.width,
+                                                  self.hints[0], self.hints[1], self.bounds is not None, self.order)
+        words = [] if self.bounds is None else [self.bounds]
+        return "\n".join([head] + [" ".join("%x" % w for w in x) for x in [self.scores.view(np.uint32)] + words])
+
+    def __repr__(self):
+        return "n %d k %d width %d snap %d waves %d order %d" % (len(self.scores), self.k, self.width, self.snap,
+                                                                 self.waves, self.order)
+
+
+def run(driver, cases):
+    """[(key_lo, key_hi, kept, scores, named)] of the cases."""
+    r = subprocess.run([driver], input="\n".join(c.text() for c in cases), capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, "%s (after %d cases)" % (r.stdout[-200:], r.stdout.count("\n") // 4)
+    lines = r.stdout.split("\n")
+    out = []
+    for i in range(len(cases)):
+        keys, kept, scores, named = (lines[4 * i + j].split() for j in range(4))
+        out.append((int(keys[0], 16), int(keys[1], 16), np.array(kept, np.int64),
+                    np.array([int(x, 16) for x in scores], np.uint32).view(np.float32), np.array(named, np.int64)))
+    return out
+
+
+def check(driver, cases):
+    for c, (_, _, kept, scores, _) in zip(cases, run(driver, cases)):
+        n = len(c.scores)
+        final = pooled(c.scores, c.width) if c.snap else c.scores
+        np.testing.assert_array_equal(scores[:n], final, str(c))
+        assert (scores[n:] == np.inf).all(), c
+        want = np.concatenate([kept_tokens(final, c.k), n + np.arange(c.window)])
+        np.testing.assert_array_equal(kept, want, str(c))
+
+
+@pytest.mark.parametrize("waves", [4, 12, 16])
+def test_selection(driver, waves):
+    """Counts at the edges of a lane's four tokens and of a chunk, every kind of
+    pooling width, values that tie, one candidate list and many."""
+    rng = np.random.default_rng(waves)
+    cases = []
+    for i, n in enumerate([1, 2, 5, 63, 255, 256, 257, 1023, 1025, 64 * waves * 4 + 3, 2048]):
+        for width in (1, 3, 7, 9, 17, 63):
+            kinds = [rng.random(n), rng.integers(0, 9, n) / 8.0, 1.0 + rng.random(n) * 1e-5,
+                     2.0 ** rng.integers(-60, 3, n)]
+            cases.append(Case(kinds[(i + width) % 4], int(rng.integers(0, n + 1)), width, waves=waves,
+                              order=int(rng.integers(0, 4))))
+        cases.append(Case(-rng.random(n), max(1, n // 2), snap=False, waves=waves, order=i % 4))
+    check(driver, cases)
+
+
+@pytest.mark.parametrize("order", ORDERS)
+def test_a_range_that_is_a_single_key(driver, order):
+    """The hinted range narrowed to one key that few tokens have: neither histogram nor candidate
+    list, nothing to wait for between the counts of one step and of the next."""
+    rng = np.random.default_rng(5)
+    for waves in (4, 16):
+        scores = np.ones(1500, np.float32)
+        places = rng.permutation(1500)
+        scores[places[:60]] = 3.0
+        scores[places[60:100]] = 2.0
+        key = int(score_keys([2.0])[0])
+        check(driver, [Case(scores, 80, 1, waves=waves, hints=(key, key), order=order)])
