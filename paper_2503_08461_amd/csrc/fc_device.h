@@ -20,6 +20,15 @@ __device__ __forceinline__ int clamp_block(int blk, int n_blocks) {
   return ((unsigned)blk < (unsigned)n_blocks) ? blk : 0;
 }
 
+// LDS accesses of a wavefront's lanes before and after this point stay in that order
+// across its lanes (the hardware executes them in program order; this binds the
+// compiler, and costs no instruction)
+__device__ __forceinline__ void wave_lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // the same register of another lane of the 16-lane row, by DPP control
 template <int CTRL>
 __device__ __forceinline__ float from_lane(float v) {

@@ -435,6 +435,7 @@ struct SegmentRewrite {
       const int c = base + lane4;
       uint32x4 v = {0u, 0u, 0u, 0u};
       if (c < j1) v = f(c);
+      wave_lds_barrier();  // (per lane the words read and written here never meet: nothing else keeps them in order)
       if (n == 0) {
         first = v;
       } else {

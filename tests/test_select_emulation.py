@@ -88,11 +88,11 @@ def check(driver, cases):
 
 @pytest.mark.parametrize("waves", [4, 12, 16])
 def test_selection(driver, waves):
-    """Counts at the edges of a lane's four tokens and of a chunk, every kind of
+    """Counts at the edges of a lane's four tokens, of a chunk and of a segment, every kind of
     pooling width, values that tie, one candidate list and many."""
     rng = np.random.default_rng(waves)
     cases = []
-    for i, n in enumerate([1, 2, 5, 63, 255, 256, 257, 1023, 1025, 64 * waves * 4 + 3, 2048]):
+    for i, n in enumerate([1, 2, 5, 63, 255, 256, 257, 1023, 1025, 64 * waves * 4 + 3, 2048, 2049, 3600]):
         for width in (1, 3, 7, 9, 17, 63):
             kinds = [rng.random(n), rng.integers(0, 9, n) / 8.0, 1.0 + rng.random(n) * 1e-5,
                      2.0 ** rng.integers(-60, 3, n)]
