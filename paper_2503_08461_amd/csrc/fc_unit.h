@@ -391,7 +391,8 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
 __device__ __forceinline__ uint32_t score_key(float s) {
   s += 0.0f;  // -0 and +0 compare equal, give them one key
   const uint32_t u = __float_as_uint(s);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  // (0 is the key of no token; what is not a number may have any bits, all of them too)
+  return (u & 0x80000000u) ? max(~u, 1u) : (u | 0x80000000u);
 }
 
 static constexpr int kBuckets = 2048;

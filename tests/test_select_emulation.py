@@ -114,3 +114,18 @@ def test_a_range_that_is_a_single_key(driver, order):
         scores[places[60:100]] = 2.0
         key = int(score_keys([2.0])[0])
         check(driver, [Case(scores, 80, 1, waves=waves, hints=(key, key), order=order)])
+
+
+def test_scores_that_are_not_numbers_still_fill_the_budget(driver):
+    """Scores with every bit set, as a buffer of log-sum-exps that was never written gives: the
+    lowest of all, the lowest indices first, and no key that stands for "no token"."""
+    ones = np.full(1, 0xFFFFFFFF, np.uint32).view(np.float32)[0]
+    cases = []
+    for snap in (True, False):
+        for n, k in ((40, 10), (700, 300), (2049, 2000)):
+            scores = np.full(n, ones, np.float32)
+            cases.append(Case(scores, k, 1, snap=snap))
+            scores = scores.copy()
+            scores[::5] = -np.arange(len(scores[::5])) if not snap else np.arange(len(scores[::5]))
+            cases.append(Case(scores, k, 1, snap=snap, order=1))
+    check(driver, cases)
