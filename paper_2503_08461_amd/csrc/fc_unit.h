@@ -401,8 +401,8 @@ static constexpr int kMaxCand = 2048;
 static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
 
 // LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
-// that the four-token reads of the pooling may touch (filled with the neutral
-// value), then one bit per token.
+// that the four-token reads of the pooling may touch (filled with what changes no
+// result), then one bit per token.
 static constexpr int kStageFront = 4;
 __host__ __device__ constexpr int stage_words(int len) { return kStageFront + ((len + 3) & ~3) + 8; }
 __host__ __device__ constexpr int need_words(int len) { return (len + kChunk - 1) / kChunk * (kChunk / 32); }
@@ -466,24 +466,27 @@ __device__ __forceinline__ uint32_t token_bits(const uint32_t* map, int base) {
   return (map[base / 32 + (lane >> 3)] >> (4 * (lane & 7))) & 0xFu;
 }
 
-// Writes `v` to the words around stage[0 .. n) that pooling reads.
-__device__ __forceinline__ void fill_stage_margins(uint32_t* stage, int n, uint32_t v) {
-  if (threadIdx.x < kStageFront) stage[(int)threadIdx.x - kStageFront] = v;
-  if (threadIdx.x < 8) stage[n + threadIdx.x] = v;  // n + 7 < the padded length + 8
+// Writes `front` and `back` to the words around stage[0 .. n) that pooling reads.
+__device__ __forceinline__ void fill_stage_margins(uint32_t* stage, int n, uint32_t front, uint32_t back) {
+  if (threadIdx.x < kStageFront) stage[(int)threadIdx.x - kStageFront] = front;
+  if (threadIdx.x < 8) stage[n + threadIdx.x] = back;  // n + 7 < the padded length + 8
 }
 
+struct PoolMaxScore {  // largest score; what is not a number is left out where there are numbers
+  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w; }
+  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }
+};
 struct PoolMaxWord {  // largest whole word (non-negative floats compare like their bits)
-  static constexpr uint32_t neutral = 0u;
   static __device__ __forceinline__ uint32_t get(uint32_t w) { return w; }
   static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
 };
 struct PoolMaxLow {  // largest low half
-  static constexpr uint32_t neutral = 0u;
   static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
   static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
 };
 struct PoolMinLow {  // smallest low half
-  static constexpr uint32_t neutral = 0xFFFFu;
   static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
   static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return min(a, b); }
 };
@@ -539,7 +542,7 @@ struct PoolWindow {
         }
         return;
       }
-      uint32_t shared = Op::neutral;
+      uint32_t shared = out[0];  // (in all four windows: h > 4)
       const int reach = (h + 3) >> 2;  // groups to either side
       for (int g = -reach; g <= reach; ++g) {
         const int at = c + 4 * g;
@@ -659,7 +662,8 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
   const int j1 = min(n_sel, j0 + seg);
 
   // ---- 1. final scores -> keys, min / max -------------------------------------
-  fill_stage_margins(stage, n_sel, 0u);
+  // (a window that reaches over an end holds the token there: its value again changes no maximum)
+  if (n_sel > 0) fill_stage_margins(stage, n_sel, stage[0], stage[n_sel - 1]);
   if (tid == 0) sh.n_cand = 0;
   for (int i = tid; i < kBuckets; i += 64 * WV) hist[i] = 0;
   __syncthreads();
@@ -670,7 +674,7 @@ __device__ __forceinline__ void select_unit_h(const BatchParams& p, const ReqDes
     const PoolWindow<kThree> pw(stage, c, rd.pool_kernel >> 1, n_sel);
     uint32_t v[4];
     if (snap) {
-      pw.template reduce<PoolMaxWord>(v);  // (sums of exponentials: none is negative)
+      pw.template reduce<PoolMaxScore>(v);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = pw.mid[e];
@@ -1357,7 +1361,7 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
   int* hist_lo = sh.hist;
   int* hist_hi = reinterpret_cast<int*>(sh.cand);
   static_assert(kMaxCand >= kBuckets, "the candidate list doubles as the second histogram");
-  fill_stage_margins(stage, n_sel, 0u);
+  fill_stage_margins(stage, n_sel, 0u, 0u);
   uint32_t vmax = 0u;
   for (int c = j0 + 4 * lane; c < j1; c += kChunk) {
     const uint32x4 w = lds_words4(stage + c);

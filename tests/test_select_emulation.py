@@ -35,7 +35,7 @@ def score_keys(scores):
 def pooled(scores, width):
     """Max-pooled, what is not a number left out of a maximum with numbers."""
     h = width // 2
-    p = np.concatenate([np.full(h, np.nan, np.float32), scores, np.full(h, np.nan, np.float32)])
+    p = np.pad(scores, h, mode="edge")  # (a window over an end holds the token there)
     return np.fmax.reduce([p[i:i + len(scores)] for i in range(width)])
 
 
@@ -128,4 +128,21 @@ def test_scores_that_are_not_numbers_still_fill_the_budget(driver):
             scores = scores.copy()
             scores[::5] = -np.arange(len(scores[::5])) if not snap else np.arange(len(scores[::5]))
             cases.append(Case(scores, k, 1, snap=snap, order=1))
+    check(driver, cases)
+
+
+@pytest.mark.parametrize("bits", [0x7FC00000, 0xFFC00000])
+def test_pooling_leaves_out_what_is_not_a_number(driver, bits):
+    """With the log-sum-exps handed in, a key row that is not a number spoils its own token's sum
+    only: the windows around it hold the largest of the others."""
+    nan = np.full(1, bits, np.uint32).view(np.float32)[0]
+    rng = np.random.default_rng(bits & 7)
+    cases = []
+    for n in (5, 64, 700, 2049):
+        for width in (1, 3, 5, 7, 9, 17, 63):
+            scores = rng.random(n).astype(np.float32)
+            scores[rng.random(n) < (0.1, 0.6)[width % 4 == 1]] = nan
+            if n == 700:
+                scores[:90] = scores[-90:] = nan     # whole windows, the ends among them
+            cases.append(Case(scores, max(1, n // 3), width, order=width % 4))
     check(driver, cases)
