@@ -175,19 +175,30 @@ struct fc_pool {
 namespace {
 
 template <typename T>
-int grow(T** buf, size_t* cap, size_t need) {
-  if (need <= *cap) return FC_OK;
+hipError_t try_grow(T** buf, size_t* cap, size_t need) {
+  if (need <= *cap) return hipSuccess;
   // the old buffer may still be in use by queued work
-  FC_HIP(hipDeviceSynchronize());
-  if (*buf) FC_HIP(hipFree(*buf));
+  hipError_t e = hipDeviceSynchronize();
+  if (e == hipSuccess && *buf) e = hipFree(*buf);
+  if (e != hipSuccess) return e;
   *buf = nullptr;
   *cap = 0;
   const size_t n = round_up(need + need / 8, 4096);
-  FC_HIP(hipMalloc(reinterpret_cast<void**>(buf), n * sizeof(T)));
+  e = hipMalloc(reinterpret_cast<void**>(buf), n * sizeof(T));
+  if (e != hipSuccess) {
+    *buf = nullptr;
+    (void)hipGetLastError();  // (a later launch must not report it)
+    return e;
+  }
   *cap = n;
-  return FC_OK;
+  return hipSuccess;
 }
 
+template <typename T>
+int grow(T** buf, size_t* cap, size_t need) {
+  FC_HIP(try_grow(buf, cap, need));
+  return FC_OK;
+}
 
 int grow_meta(fc_pool* p, size_t need) {
   if (need <= p->meta_cap) return FC_OK;
@@ -553,6 +564,11 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   // (room for any split on this chip: 128 heads of 32768 tokens)
   const size_t fixed_kept = dev_kept_out ? 0 : plan.kept_entries;
   if (no_alloc && fixed_kept + raw_floats > kNoAllocKeptInts) n_split = 0;
+  // no memory for what only split heads need (scores, kept lists): the fused kernels do without
+  if (n_split && !no_alloc &&
+      (try_grow(&p->raw_scores, &p->raw_cap, raw_floats) != hipSuccess ||
+       (!dev_kept_out && try_grow(&p->kept, &p->kept_cap, plan.kept_entries) != hipSuccess)))
+    n_split = 0;
   std::vector<FusedLaunch> fused;
   if (n_split == 0) fused = plan_fused_launches(pv, plan, p->n_cu);
   const bool separate = n_split == 0 && pv.score_mode != FC_SCORE_AUTO && !plan.lists[LIST_ALL].empty();
@@ -603,11 +619,10 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   } else {
     // (growth waits for the device and frees: it happens before anything is queued)
     // (the fused kernels keep their lists in LDS)
-    if (!dev_kept_out && (separate || n_split) &&
-        (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK)
+    if (!dev_kept_out && separate && (rc = grow(&p->kept, &p->kept_cap, plan.kept_entries)) != FC_OK)
       return rc;
     if ((rc = grow(&p->ids, &p->ids_cap, n_ids)) != FC_OK) return rc;
-    if ((separate || n_split) && (rc = grow(&p->raw_scores, &p->raw_cap, raw_floats)) != FC_OK) return rc;
+    if (separate && (rc = grow(&p->raw_scores, &p->raw_cap, raw_floats)) != FC_OK) return rc;
     if ((rc = grow_meta(p, meta_bytes)) != FC_OK) return rc;
     if (!kept_buf) kept_buf = p->kept;
     raw_buf = p->raw_scores;

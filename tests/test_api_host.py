@@ -1,0 +1,46 @@
+"""The host side of the library on the CPU (tests/api_host_driver.cpp): the C ABI over a
+HIP runtime that can be out of device memory, with launchers that only say their name."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("api")
+    exe, obj, plan = str(tmp / "api_host"), str(tmp / "api.o"), str(tmp / "plan.o")
+    subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-fPIC", "-c",
+                    os.path.join(ROOT, "tests", "api_host_driver.cpp"), "-o", obj], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-c", os.path.join(ROOT, "paper_2503_08461_amd", "csrc", "fc_plan.cpp"),
+                    "-o", plan], check=True)
+    subprocess.run(["g++", obj, plan, "-o", exe], check=True)  # (without the HIP runtime: the driver is it)
+    return exe
+
+
+def run(driver, scenario):
+    """{what: (return code, [launches])}, and the last line as it is."""
+    r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
+    lines = r.stdout.splitlines()
+    out = {ln.split()[0]: (int(ln.split()[1]), ln.split()[2:]) for ln in lines if not ln.startswith("error")}
+    return out, [ln for ln in lines if ln.startswith("error")]
+
+
+def test_a_call_that_cannot_have_split_scores_runs_in_the_fused_kernels(driver):
+    """Few long heads are split over workgroups, which takes score scratch.  Without memory for it
+    the call runs as it does with many heads; the pool stays usable and no error is left behind."""
+    out, errors = run(driver, "no_room_for_split_scores")
+    fused = [["plan_inline", "fused_wide", "reclaim"]]
+    assert out["in_place"] == (0, fused[0])
+    assert out["full"] == (0, fused[0])
+    assert out["full_kept_out"] == (0, fused[0])
+    assert errors == ["error []"]
+    assert out["room"] == (0, ["plan_inline", "split_scores", "select", "gather", "reclaim"])
