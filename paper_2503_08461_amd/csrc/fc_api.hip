@@ -260,10 +260,14 @@ int fc_pool_create(fc_pool** out, void* kv_base, size_t kv_bytes, int n_blocks, 
   if (e == hipSuccess) e = launch_stack_init(p->stack, n_blocks, nullptr);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->error_flag), sizeof(int32_t));
   if (e == hipSuccess) e = launch_zero_ints(p->error_flag, 1, nullptr);
-  // (a fixed size, here and not on demand: no decode step waits for an allocation)
-  if (e == hipSuccess)
-    e = hipMalloc(reinterpret_cast<void**>(&p->decode_partial),
-                  (size_t)kMaxDecodeSegments * DecodeParams::state_words(head_dim) * sizeof(float));
+  // (a fixed size, here and not on demand: no decode step waits for an allocation;
+  // without it no head is cut into segments)
+  if (e == hipSuccess &&
+      hipMalloc(reinterpret_cast<void**>(&p->decode_partial),
+                (size_t)kMaxDecodeSegments * DecodeParams::state_words(head_dim) * sizeof(float)) != hipSuccess) {
+    p->decode_partial = nullptr;
+    (void)hipGetLastError();  // (a later launch must not report it)
+  }
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->meta_event, hipEventDisableTiming);
   for (int c = 0; c < kProfRing && e == hipSuccess; ++c)
     for (int k = 0; k < K_COUNT && e == hipSuccess; ++k)
@@ -1072,7 +1076,8 @@ int decode_attention_impl(fc_pool* p, const int32_t* dev_block_tables, int max_b
   dp.q = static_cast<const _Float16*>(dev_q);
   dp.out = dev_out;
   dp.kept = dev_kept;
-  plan_decode_segments(pool_view(p), p->n_cu, dev_kept != nullptr, &plan);
+  plan_decode_segments(pool_view(p), p->n_cu, dev_kept != nullptr, &plan,
+                       p->decode_partial ? kMaxDecodeSegments : 0);
   dp.seg_blocks = plan.seg_blocks;
   dp.n_seg = plan.n_seg;
   dp.partial = p->decode_partial;

@@ -415,7 +415,7 @@ int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const
 // 256-1408 tokens 47.9 us whole, 35.7 in segments of 16 blocks, 37.9 of 8; 16 caches
 // of 130-16384 tokens 490 whole, 426 / 383 / 369 with a quarter / an eighth / a
 // sixteenth of the share; but 48 caches of 1280-7040 tokens, 2 layers, 985 / 986 / 993.
-void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan) {
+void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan, int max_segments) {
   if (plan->reqs.empty()) return;
   auto blocks = [&](const DecodeReq& q) { return blocks_for(over_kept ? q.pop_index : q.seq_len); };
   const int64_t n_lh = (int64_t)pool.n_layers * pool.n_heads;
@@ -425,7 +425,7 @@ void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, Decode
   const int longest = blocks(plan->reqs.front());  // (longest first)
   plan->seg_blocks = std::max(longest, 1);
   plan->n_seg = 1;
-  const int64_t room = kMaxDecodeSegments / units;  // segments per head
+  const int64_t room = max_segments / units;  // segments per head
   if (room < 2) return;
   const int64_t eighth = total / (8 * (int64_t)std::max(n_cu, 1));
   const int64_t seg = std::max<int64_t>({(eighth + 3) / 4 * 4, 16, (longest + room - 1) / room});

@@ -133,7 +133,9 @@ int plan_append(const PoolView& pool, int n_req, int max_blocks, const int32_t* 
                 const int32_t* enable, DecodePlan* plan);
 int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,
                           const int32_t* budget /* NULL: whole cache */, DecodePlan* plan);
-// Sets seg_blocks and n_seg of a planned attention (over_kept: of the kept lists).
-void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan);
+// Sets seg_blocks and n_seg of a planned attention (over_kept: of the kept lists);
+// max_segments: of all heads, kMaxDecodeSegments or 0 (a pool without the buffers).
+void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan,
+                          int max_segments = kMaxDecodeSegments);
 
 }  // namespace fc

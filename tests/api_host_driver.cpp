@@ -121,6 +121,19 @@ int main(int argc, char** argv) {
     printf("error [%s]\n", fc_last_error());
     g_largest = ~(size_t)0;
     compress("room", nullptr);
+  } else if (scenario == "no_room_for_decode_segments") {
+    const int32_t lens[2] = {8000, 30000};
+    auto attention = [&](const char* what) {
+      report(what, fc_decode_attention(pool, somewhere<int32_t>(), 2048, lens, somewhere<void>(), somewhere<float>(), 2,
+                                       0.f, nullptr));
+    };
+    g_largest = 1 << 20;
+    report("create", create());
+    attention("whole");
+    fc_pool_destroy(pool);
+    g_largest = ~(size_t)0;
+    report("create_with_room", create());
+    attention("cut");
   } else {
     return 2;
   }

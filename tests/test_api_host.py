@@ -44,3 +44,13 @@ def test_a_call_that_cannot_have_split_scores_runs_in_the_fused_kernels(driver):
     assert out["full_kept_out"] == (0, fused[0])
     assert errors == ["error []"]
     assert out["room"] == (0, ["plan_inline", "split_scores", "select", "gather", "reclaim"])
+
+
+def test_a_pool_without_room_for_decode_segments_attends_over_whole_heads(driver):
+    """A decode step over few long caches is cut into segments, whose states lie in memory of the
+    pool.  A pool that cannot have it is created all the same and cuts nothing."""
+    out, _ = run(driver, "no_room_for_decode_segments")
+    assert out["create"][0] == 0
+    assert out["whole"] == (0, ["attention_inline:1"])
+    assert out["create_with_room"][0] == 0
+    assert out["cut"][0] == 0 and int(out["cut"][1][0].split(":")[1]) > 1
