@@ -146,3 +146,25 @@ def test_pooling_leaves_out_what_is_not_a_number(driver, bits):
                 scores[:90] = scores[-90:] = nan     # whole windows, the ends among them
             cases.append(Case(scores, max(1, n // 3), width, order=width % 4))
     check(driver, cases)
+
+
+@pytest.mark.parametrize("within", [1, 63, 64, 65, 255, 256, 257, 900])
+def test_hinted_ranges(driver, within):
+    """A range known to hold the threshold, with as many keys as are listed at once, ranked at
+    once, and more; the threshold at either end of it and in the middle."""
+    rng = np.random.default_rng(within)
+    cases = []
+    for waves in (4, 16):
+        n, above = 1500, 200
+        for place, k in enumerate((above + 1, above + (within + 1) // 2, above + within)):
+            scores = np.empty(n, np.float32)
+            at = rng.permutation(n)
+            scores[at[:above]] = 4.0 + rng.random(above)
+            scores[at[above:above + within]] = 2.0 + rng.random(within)
+            scores[at[above + within:]] = rng.random(n - above - within)
+            cases.append(Case(scores, k, 1, waves=waves, order=place,
+                              hints=tuple(int(x) for x in score_keys([2.0, 3.0]))))
+            # (and with hints that turn out not to hold it: nothing is narrowed)
+            cases.append(Case(scores, above, 1, waves=waves, order=place,
+                              hints=tuple(int(x) for x in score_keys([2.0, 3.0]))))
+    check(driver, cases)
