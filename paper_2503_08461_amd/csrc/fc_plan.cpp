@@ -25,6 +25,34 @@ constexpr int kMixedQueryTiles = kPlanClasses;
 // Heads shorter than this are not worth the launches of the split path.
 constexpr int kSplitMinLen = 2048;
 
+// Whether a call of `units` heads of up to 8192 tokens is better off in wide
+// workgroups.  With at most one head per CU it is, from the length on at which a
+// head keeps their wavefronts busy; with up to two per CU, which narrow workgroups
+// run at once and wide ones one after the other, from a greater length on; with more
+// it is not.  All kernels of a call, narrow / wide in us, at 256 and at 512 heads:
+//   SnapKV, window 32, 128 channels       64 channels
+//     300 tokens   35.9 / 36.9    43.5 / 56.3     30.5 / 30.7    34.0 / 43.5
+//     512          53.9 / 42.3    62.9 / 66.7     48.2 / 33.1    54.3 / 49.0
+//    1300          91.7 / 65.1   106.2 / 112.3    83.6 / 44.2    94.1 / 69.3
+//    2300         132.1 / 92.4   158.5 / 154.9   120.1 / 73.3   137.8 / 126.8
+//    3200         168.2 / 110.2  210.4 / 199.5   169.1 / 90.5   171.8 / 152.5
+//   key-norm
+//     200          29.2 / 28.3    32.3 / 36.7     25.4 / 24.8    26.8 / 32.0
+//     640          46.4 / 34.9    52.9 / 53.7     33.5 / 27.7    38.8 / 41.2
+//     900          56.8 / 39.4    64.9 / 62.4     40.4 / 30.3    46.6 / 45.8
+//    1800          90.6 / 57.6   104.6 / 95.0     62.4 / 38.5    70.3 / 61.0
+// (SnapKV: 512 and 2048 are also where narrow and wide workgroups begin to prune.)
+bool wide_pays(const CompressPlan& plan, size_t units, int head_dim, int n_cu) {
+  if (units > 2 * (size_t)n_cu) return false;
+  const bool one_each = units <= (size_t)n_cu;
+  const int snap_from = one_each || head_dim == 64 ? 512 : 2048, other_from = one_each ? 256 : 768;
+  for (const ReqDesc& d : plan.descs) {
+    if (d.method != PLAN_METHOD_STREAMING && d.seq_len > kPlanFusedMaxLen) continue;  // (wide anyhow)
+    if (d.seq_len >= (d.method == PLAN_METHOD_SNAPKV ? snap_from : other_from)) return true;
+  }
+  return false;
+}
+
 int blocks_for(int tokens) { return (tokens + kPlanBlockSize - 1) / kPlanBlockSize; }
 
 template <typename Plan>
@@ -209,8 +237,9 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
   };
   size_t short_units = 0;
   for (int c = 0; c < kPlanClasses; ++c) short_units += plan.lists[LIST_FUSED + c].size() * n_lh;
+  const bool few = wide_pays(plan, short_units, pool.head_dim, n_cu);
   for (int c = 0; c < kPlanClasses; ++c) {
-    add(short_units <= 2 * (size_t)n_cu ? wide : narrow, plan.lists[LIST_FUSED + c]);
+    add(few ? wide : narrow, plan.lists[LIST_FUSED + c]);
     if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_SNAP + c]);
   }
   if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_KNORM]);
