@@ -4,16 +4,60 @@ path keeps.  Kept lists against the oracle (identical outside the threshold
 band), gathered bytes, block tables and free list bit-exact: on the reduced
 benchmark configurations, on the shapes that stress the bounds (first blocks
 without a reference, every pooling width, ties, clustered scores, logits that
-outrun the reference), and next to everything else a batch can hold."""
+outrun the reference), and next to everything else a batch can hold.
+
+Every test runs its batch three times: as it is (few heads: split over several
+workgroups where they are long, and not pruned), with fillers that bring it into
+wide workgroups (which prune heads of 2048 tokens and more) and into narrow ones
+(of 512 and more); the host planner says that it got there."""
 
 import numpy as np
 import pytest
 
+import launch_shapes
 from oracle import fastcache_oracle as fo
 from paper_2503_08461_amd import synth
-from test_gpu_parity import _custom, _mixed_window_batch
+from test_gpu_parity import _custom as _plain_custom, _mixed_window_batch
 
 pytestmark = pytest.mark.gpu
+
+_shape = None
+
+
+@pytest.fixture(params=["few", "wide", "narrow"], autouse=True)
+def shape(request):
+    global _shape
+    _shape = request.param
+    yield _shape
+    _shape = None
+
+
+def _in_shape(wl):
+    return launch_shapes.in_shape(wl, _shape)
+
+
+def _custom(*args, **kw):
+    return _in_shape(_plain_custom(*args, **kw))
+
+
+def _fill(wl, budgets, value=launch_shapes.FILLER_BUDGET):
+    """An array per request of the batch without its fillers -> with them."""
+    return launch_shapes.padded(budgets, wl.n_req - len(budgets), value)
+
+
+def _assert_prunes(wl, in_place=False, **kw):
+    """The requests that this shape prunes run in it."""
+    if _shape == "few":
+        return
+    lens = kw.get("lens", wl.seq_lens)
+    methods = kw.get("methods", wl.methods)
+    for r, got in enumerate(launch_shapes.planned(wl, in_place=in_place, **kw)):
+        if methods[r] != fo.METHOD_SNAPKV:
+            continue
+        if lens[r] > 8192 or (_shape == "wide" and lens[r] >= 2048):
+            assert got == "wide", (r, lens[r], got)
+        elif _shape == "narrow" and lens[r] >= 512:
+            assert got == "narrow", (r, lens[r], got)
 
 
 def _pruned(wl, **kw):
@@ -25,6 +69,7 @@ def _pruned(wl, **kw):
 
 
 def _run_pruned(wl, repeats=1, sbs_kw=None, **kw):
+    _assert_prunes(wl)
     s = _pruned(wl, **(sbs_kw or {}))
     try:
         out = [s.compress_and_compare(scores=False, **kw) for _ in range(repeats)]
@@ -50,13 +95,13 @@ def test_pruned_pass_keeps_what_two_passes_keep(L, W, d, pct):
 
 
 def test_reduced_benchmark_configurations():
-    _run_pruned(synth.make_workload(2, n_layers=2, n_heads=3))
-    _run_pruned(synth.make_workload(3, n_layers=1, n_heads=2, n_req=6))
-    _run_pruned(synth.make_workload(4, n_layers=1, n_heads=2, n_req=4))
-    _run_pruned(synth.make_workload(4, n_layers=2, n_heads=3, n_req=2))
+    _run_pruned(_in_shape(synth.make_workload(2, n_layers=2, n_heads=3)))
+    _run_pruned(_in_shape(synth.make_workload(3, n_layers=1, n_heads=2, n_req=6)))
+    _run_pruned(_in_shape(synth.make_workload(4, n_layers=1, n_heads=2, n_req=4)))
+    _run_pruned(_in_shape(synth.make_workload(4, n_layers=2, n_heads=3, n_req=2)))
 
 
-@pytest.mark.parametrize("pool_kernel", [1, 3, 7, 15, 63])
+@pytest.mark.parametrize("pool_kernel", [1, 3, 5, 7, 9, 15, 63])
 def test_pooling_widths(pool_kernel):
     _run_pruned(_custom([3000, 2600], [500, 700], [fo.METHOD_SNAPKV] * 2, W=32, d=128, n_heads=3),
                 pool_kernel=pool_kernel)
@@ -79,7 +124,7 @@ def test_all_scores_tie():
     """All-zero queries: every prefix token has the same score, and the kept
     prefix must be the lowest indices."""
     wl = _custom([2600, 2100], [600, 300], [fo.METHOD_SNAPKV] * 2, W=16, d=64)
-    q = np.zeros((2, 1, 2, 16, 64), dtype=np.float16)
+    q = np.zeros((wl.n_req, 1, 2, 16, 64), dtype=np.float16)
     out = _run_pruned(wl, sbs_kw={"q_host": q})
     assert out[0]["units_kept_identical"] == out[0]["units"]
 
@@ -116,15 +161,12 @@ def test_logits_that_outrun_the_reference_fall_back_to_two_passes():
     _run_pruned(wl, sbs_kw={"kv_host": kv, "q_host": q})
 
 
-@pytest.mark.parametrize("fillers", [0, 300])
-def test_rows_that_overflow_do_not_hide_behind_rows_that_do_not(fillers):
+def test_rows_that_overflow_do_not_hide_behind_rows_that_do_not():
     """The late large key is seen by every other window row only.  Those rows
     overflow in the middle of the head and give the other tokens nothing; the
-    rest of the rows, whose references stay fine, decide the selection.  (With
-    300 short key-norm requests next to them the heads run in small workgroups.)"""
+    rest of the rows, whose references stay fine, decide the selection."""
     from parity_util import SideBySide
-    wl = _custom([3000, 2500] + [9] * fillers, [600, 500] + [4] * fillers,
-                 [fo.METHOD_SNAPKV] * 2 + [fo.METHOD_KNORM] * fillers, W=32, d=128, n_heads=2)
+    wl = _custom([3000, 2500], [600, 500], [fo.METHOD_SNAPKV] * 2, W=32, d=128, n_heads=2)
     kv = synth.fill_pool_host(wl)
     s0 = SideBySide(wl)     # only to learn where the tokens live
     try:
@@ -195,39 +237,41 @@ def test_structured_attention_patterns(shape):
     _run_pruned(wl, sbs_kw={"kv_host": kv, "q_host": q.astype(np.float16)})
 
 
-def test_heads_beyond_the_fused_limit_share_a_call_with_pruned_ones():
-    """A request too long for the fused kernel goes through the separate score,
-    select and gather kernels; the other heads of the call are pruned."""
+def test_heads_beyond_the_narrow_limit_share_a_call_with_pruned_ones():
+    """A request too long for narrow workgroups runs in wide ones whatever the rest
+    of the call does; all of them are pruned."""
     wl = _custom([9000, 3000, 8200], [1500, 600, 4000], [fo.METHOD_SNAPKV] * 3, W=32, d=64, n_heads=2)
     _run_pruned(wl)
 
 
 def test_repeated_calls_and_in_place_compaction():
     wl = _custom([5000, 3000], [2500, 1200], [fo.METHOD_SNAPKV] * 2, W=64, d=128, n_heads=2)
-    s = _pruned(wl)
-    try:
-        s.compress_and_compare(scores=False)
-        s.compress_and_compare(scores=False, budgets=np.array([600, 400], np.int32))
-    finally:
-        s.close()
-    s = _pruned(wl, in_place=True)
-    try:
-        s.compress_and_compare(scores=False)
-        s.compress_and_compare(scores=False, budgets=np.array([2100, 300], np.int32))
-    finally:
-        s.close()
+    for in_place, second in ((False, [600, 400]), (True, [2100, 300])):
+        second = _fill(wl, second, 3)
+        _assert_prunes(wl, in_place)
+        _assert_prunes(wl, in_place, lens=wl.budgets, budgets=second)
+        s = _pruned(wl, in_place=in_place)
+        try:
+            s.compress_and_compare(scores=False)
+            s.compress_and_compare(scores=False, budgets=second)
+        finally:
+            s.close()
 
 
 def test_per_request_windows_and_pooling_widths():
     lens = [2700, 130, 3333, 2250, 4200, 96, 2064, 2513, 90, 8000]
     wl, methods, budgets, windows, pools, q_list = _mixed_window_batch(78, lens, d=128)
     budgets = np.minimum(budgets, np.maximum(windows, np.array(lens) // 4)).astype(np.int32)
+    wl = _in_shape(wl)
+    methods, budgets, windows, pools = wl.methods, _fill(wl, budgets), _fill(wl, windows, 1), _fill(wl, pools, 1)
+    q_list += [None] * (wl.n_req - len(q_list))
+    _assert_prunes(wl, methods=methods, budgets=budgets, windows=windows)
     s = _pruned(wl)
     try:
         stats = s.compress_and_compare(methods, budgets, windows, pools, q_list=q_list, scores=False)
     finally:
         s.close()
-    assert stats["units"] == len(lens) * wl.n_layers * wl.n_heads
+    assert stats["units"] == wl.n_req * wl.n_layers * wl.n_heads
 
 
 def test_asking_for_the_scores_takes_the_two_pass_path():
