@@ -26,9 +26,11 @@ struct MlpParams {
 // a copy through pinned memory costs the stream a copy kernel and 10 to 20 us of
 // idle time on either side, and the host has to wait until the last one is through.
 struct DecodeReqs {
-  static constexpr int kInline = 112;  // (3584 bytes of the 4 KB that arguments may take)
+  static constexpr int kInline = 112;  // (2688 bytes)
   DecodeReq req[kInline];
 };
+static_assert(sizeof(DecodeReq) == 24, "tests count on the sizes of descriptors and argument blocks");
+static constexpr size_t kMaxArgumentBytes = 4096;  // what the arguments of a kernel may take
 
 struct DecodeParams {
   _Float16* kv;
@@ -51,6 +53,7 @@ struct DecodeParams {
   int32_t* error_flag;
   static constexpr int state_words(int head_dim) { return head_dim + 4; }
 };
+static_assert(sizeof(DecodeParams) + sizeof(DecodeReqs) <= kMaxArgumentBytes, "decode kernels");
 
 // Everything a kernel of the stage needs.  Passed by value.
 struct BatchParams {
@@ -100,6 +103,7 @@ struct BatchParams {
 struct MetaChunk {
   alignas(16) char bytes[3584];
 };
+static_assert(sizeof(BatchParams) + sizeof(MetaChunk) + 32 <= kMaxArgumentBytes, "plan_alloc_inline_kernel");
 
 enum KernelSlot {
   K_PLAN_ALLOC = 0,

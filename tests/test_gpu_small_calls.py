@@ -28,9 +28,10 @@ def test_compression(n_req):
         s.close()
 
 
-@pytest.mark.parametrize("n_req", [1, 111, 112, 113, 460])
+@pytest.mark.parametrize("n_req", [1, 111, 112, 113, 149, 150, 460, 597, 598, 640])
 def test_decode_step(n_req):
-    """32 bytes a request: 112 fill the arguments, 448 four launches'."""
+    """24 bytes a request: up to 112 are arguments of the kernel itself, 149 fill one launch's
+    3584 bytes, 597 four launches', and more go through pinned memory."""
     import torch
     from paper_2503_08461_amd import fastcache as fc
     from test_gpu_decode import ATOL, RTOL, _setup
