@@ -1,11 +1,12 @@
 """The three ways a head is spread over the chip, against the oracle: narrow
-workgroups (a launch with more heads than fit the chip as wide workgroups), wide
-ones (fewer heads, or heads of more than 8192 tokens), heads split over several
-workgroups (very few heads); with the pruned second pass and with the scores
-asked for."""
+workgroups (a launch with more heads than fit the chip as wide workgroups, or short
+ones), wide ones (fewer heads, or heads of more than 8192 tokens), heads split over
+several workgroups (very few long heads); with the pruned second pass (narrow and
+wide) and with the scores asked for."""
 
 import pytest
 
+import launch_shapes
 from oracle import fastcache_oracle as fo
 from test_gpu_parity import _custom
 
@@ -19,12 +20,15 @@ SNAP, KNORM, STREAM = fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING
 WIDE, NARROW = 70, 300
 
 
-def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, **kw):
+def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, shape=None, **kw):
     from parity_util import SideBySide
     lens = list(lens) + [9] * fillers        # key-norm requests of nine tokens that only add heads
     budgets = list(budgets) + [4] * fillers
     methods = list(methods) + [KNORM] * fillers
-    s = SideBySide(_custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads), in_place=in_place)
+    wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads)
+    if shape:
+        assert set(launch_shapes.planned(wl)) == {shape}
+    s = SideBySide(wl, in_place=in_place)
     try:
         return s.compress_and_compare(scores=scores, **kw)
     finally:
@@ -38,7 +42,7 @@ SHAPES = [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 6
 @pytest.mark.parametrize("W,d", SHAPES)
 def test_narrow_workgroups(W, d, scores):
     lens = [W, 511, 512, 700, 2047, 2049, 4100, 8192]
-    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW)
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW, shape="narrow")
 
 
 @pytest.mark.parametrize("scores", [True, False])
@@ -47,7 +51,7 @@ def test_wide_workgroups(W, d, scores):
     # both sides of the pruning limit of wide workgroups, of the narrow ones' longest head, of the
     # longer epochs and of a wavefront's last chunk; the longest head of all
     lens = [W, 300, 2047, 2048 + W, 8192, 8193, 16384, 16385, 32768]
-    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1)
+    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1, shape="wide")
 
 
 @pytest.mark.parametrize("scores", [True, False])
@@ -55,7 +59,7 @@ def test_wide_workgroups(W, d, scores):
 def test_split_heads(W, d, scores):
     # segments that end inside the window, heads with fewer blocks than segments, empty prefixes
     lens = [W, W + 1, 100, 2047, 2048, 4097, 16384, 32768]
-    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, n_heads=1)
+    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, n_heads=1, shape="split")
 
 
 @pytest.mark.parametrize("fillers", [0, WIDE, NARROW])
