@@ -196,12 +196,14 @@ int fc_compress_batch(fc_pool* pool, int32_t* dev_block_tables, int max_blocks_p
  * nothing, on the device or in pinned host memory, and never waits for the
  * device.  Limits (FC_EINVAL beyond them, nothing touched):
  *   - at most FC_NOALLOC_MAX_REQUESTS compressed requests per call;
- *   - every compressed request has at most 8192 tokens and the pool uses the
- *     default scheduling (FC_SCORE_AUTO): nothing may need the library's
- *     un-pooled score scratch;
+ *   - every compressed request (but FC_METHOD_STREAMING ones) has at most 8192
+ *     tokens and the pool uses the default scheduling (FC_SCORE_AUTO);
  *   - sum over requests of budget * n_layers * n_heads <= 15 Mi entries,
  *     unless dev_kept_out is given (then the kept lists go there);
  *   - sum over requests of ceil(L/16) + ceil(budget/16) <= 256 Ki block ids.
+ * A call whose few long heads are split over workgroups (FC_SCORE_AUTO) keeps
+ * their scores behind the kept lists; where they do not fit there, it runs in the
+ * fused kernels instead.
  * All calls on one GPU share that GPU's array and it keeps the last call's
  * contents (nothing in it has to start at zero): two such calls that overlap
  * in time on one GPU, on any streams or pools, race.
@@ -354,7 +356,9 @@ int fc_set_streaming_sinks(fc_pool* pool, int n_sink);
  *   FC_SCORE_AUTO (default): every (request, layer, head) is handled by one
  *     fused kernel (two-pass score -> select -> gather inside the workgroup
  *     that owns the head; scores stay in LDS), except in calls with so few and
- *     long heads that each is split over several workgroups.
+ *     long heads that each is split over several workgroups (two full passes
+ *     over K, scores in library scratch; a call that cannot have that memory
+ *     runs in the fused kernels).
  *     (See fc_set_score_pruning for what the fused kernel does with the
  *     second pass when the call does not ask for the scores.)
  *   FC_SCORE_TWO_PASS: separate kernels for everything; SnapKV scoring streams
@@ -369,18 +373,19 @@ int fc_set_score_mode(fc_pool* pool, int mode);
 /*
  * Pruned second pass of the SnapKV-style score (Algorithm 1, "Batch
  * compression"; the selection only needs exact scores near its threshold).
- * On by default (enable == 0 turns it off): for heads of at least 512 tokens
- * the fused kernel of the default
+ * On by default (enable == 0 turns it off): the fused kernel of the default
  * scheduling bounds every column sum during its first pass over K and re-reads
- * only the key rows whose exact score can still decide the selection.  The kept
+ * only the key rows whose exact score can still decide the selection, for heads
+ * of at least 512 tokens, or of at least 2048 where it runs in large workgroups
+ * (heads of more than 8192 tokens, calls with few heads).  The kept
  * set is the exact top-budget set of the exactly evaluated scores, as on the
  * two-pass path (the two evaluate a column sum in different orders of
  * addition, so between scores that agree to fp32 rounding the choice may
  * differ); the compacted caches and the pool follow from it in the same way.
  * It applies to calls that do not ask for the scores (dev_scores_out == NULL)
- * and do not bring the row log-sum-exps; the separate-kernel modes never
- * prune.  The bounds live in the kernel's local memory: no device memory
- * beyond that of the two-pass path is used.
+ * and do not bring the row log-sum-exps; the separate kernels and calls with
+ * split heads never prune.  The bounds live in the kernel's local memory and
+ * take no device memory.
  */
 int fc_set_score_pruning(fc_pool* pool, int enable);
 
@@ -391,7 +396,8 @@ int fc_set_score_pruning(fc_pool* pool, int enable);
  * waits for those calls and writes, for each kernel, its elapsed milliseconds
  * averaged over the calls made since profiling was switched on (at most the
  * last 32; 0 if it was never launched) to host_ms[0..FC_N_KERNELS).
- * fc_kernel_name(i) names slot i.  fc_set_profiling(pool, 1) restarts the
+ * fc_kernel_name(i) names slot i (the score kernels of split heads, of every
+ * method, report as "snapkv_score").  fc_set_profiling(pool, 1) restarts the
  * average.
  */
 #define FC_N_KERNELS 11

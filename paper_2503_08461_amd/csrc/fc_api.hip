@@ -560,7 +560,8 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
 
   // ---- launches: the fused kernels, or (FC_SCORE_TWO_PASS) the separate ones ---
   // or, with few long heads, kernels that split them over workgroups
-  const bool beyond_narrow = plan.raw_floats > 0;  // (a unit that the default narrow workgroups cannot take)
+  // a head that narrow workgroups cannot take, or the separate kernels: not for the allocation-free call
+  const bool beyond_narrow = !plan.lists[LIST_ALL].empty();
   int n_split = plan_split(pv, p->n_cu, &plan);
   // score scratch; of split heads the row pairs of every segment behind the scores
   const size_t raw_floats = plan.raw_floats + (size_t)n_split * n_comp * p->n_layers * p->n_heads * 128;

@@ -28,7 +28,7 @@
 // list and the requests are read by scalar loads, a tile's target block is looked up
 // before the next tile's rows are requested, and the store phase reloads nothing
 // (24 prompts of 1280-7040 tokens, 2 layers, d = 128, hidden 256: 1518 -> 1420 us,
-// 0.74 PFLOP/s; spilled registers 25 -> 8, none of them in the loops).
+// 0.74 PFLOP/s; spilled registers 25 -> 7, read back once a tile).
 
 #include "fc_device.h"
 

@@ -162,12 +162,14 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
 
   // ---- work lists ------------------------------------------------------------------
   // Descriptor indices, heaviest first so that the tail of each launch is made
-  // of light units.  Heads short enough for the fused kernel (score -> select ->
-  // gather in one workgroup) are listed per window class (class c: SnapKV with
-  // ceil(window/16) == c, the number of 16-row query tiles the kernel is
-  // compiled for; class 0: no queries at all); the rest go through the
-  // separate kernels: SnapKV per class, key-norm, and one list of all of them
-  // for select and gather.
+  // of light units, per window class (class c: SnapKV with ceil(window/16) == c,
+  // the number of 16-row query tiles the kernels are compiled for; class 0: no
+  // queries at all).  Heads that narrow workgroups of the fused kernels (score ->
+  // select -> gather in one workgroup) can take are in the fused lists; the rest
+  // in those of the separate kernels: SnapKV per class, key-norm, and one list of
+  // all of them for select and gather.  In the default scheduling the rest are the
+  // longer heads, which plan_fused_launches puts into wide workgroups, and the
+  // separate kernels run only with PLAN_SCORE_TWO_PASS.
   std::vector<int> sorted(n_comp);
   std::iota(sorted.begin(), sorted.end(), 0);
   // bytes a unit moves (K once or twice, kept K/V read and written)
@@ -187,17 +189,6 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
     return d.method == PLAN_METHOD_STREAMING ||
            (allow_fused && d.seq_len <= kPlanFusedMaxLen);
   };
-  // Units without queries (key-norm, streaming) ride in the launch of the
-  // SnapKV class that has the most fused units, if there is one: one launch
-  // fills the chip better than two that each end in a tail.
-  int home_class = 0;
-  {
-    int count[kPlanClasses] = {};
-    for (int i = 0; i < n_comp; ++i)
-      if (descs[i].method == PLAN_METHOD_SNAPKV && fused(i)) ++count[(descs[i].window + 15) / 16];
-    for (int c = 1; c < kPlanClasses; ++c)
-      if (count[c] > count[home_class]) home_class = c;
-  }
   size_t raw_need = 0;
   for (int di : sorted) {
     ReqDesc& d = descs[di];
@@ -205,9 +196,9 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
     const int cls = snap ? (d.window + 15) / 16 : 0;
     int li;
     if (fused(di)) {
-      li = LIST_FUSED + (snap ? cls : home_class);
+      li = LIST_FUSED + cls;
     } else {
-      // scores of these units travel through the library's scratch
+      // (the separate kernels keep these units' scores in the library's scratch)
       d.raw_off = (int64_t)raw_need;
       raw_need += n_lh * (size_t)d.seq_len;
       li = snap ? LIST_SNAP + cls : LIST_KNORM;

@@ -23,7 +23,7 @@ static constexpr int kPlanBlockSize = 16;
 static constexpr int kPlanMaxWindow = 64;
 static constexpr int kPlanMaxSeqLen = 32768;
 static constexpr int kPlanMaxPoolKernel = 63;
-static constexpr int kPlanFusedMaxLen = 8192;   // longest head the fused kernel takes
+static constexpr int kPlanFusedMaxLen = 8192;   // longest head of narrow workgroups of the fused kernels
 static constexpr int kPlanClasses = 5;          // query-tile counts 0..4 (0: no queries)
 
 // What the pool contributes to a plan.
@@ -51,7 +51,9 @@ struct CompressArgs {
 
 // Work lists of a compress call (descriptor indices, heaviest first).
 enum {
-  LIST_FUSED = 0,                  // + class: units of the fused kernel, per query-tile count
+  // (in the default scheduling the lists after the first hold the heads that only wide
+  // workgroups of the fused kernels take, see plan_fused_launches)
+  LIST_FUSED = 0,                  // + class: units of the fused kernels, per query-tile count
   LIST_SNAP = kPlanClasses,        // + class: separate two-pass score kernel
   LIST_KNORM = 2 * kPlanClasses,   // separate key-norm score kernel
   LIST_ALL,                        // select and gather of the separate path
@@ -69,7 +71,7 @@ struct CompressPlan {
   int window_hi = 0;                          // largest window of a SnapKV request
   size_t kept_entries = 0;                    // ints of the kept buffer
   size_t score_entries = 0;                   // floats of a packed scores_out
-  size_t raw_floats = 0;                      // floats of un-pooled score scratch
+  size_t raw_floats = 0;                      // floats of un-pooled score scratch (separate or split kernels)
   int top_after = 0;                          // free blocks after the call
 };
 

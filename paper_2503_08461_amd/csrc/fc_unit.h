@@ -28,8 +28,8 @@ namespace fc {
 // queries in registers, so the sum over window queries is an in-lane add plus
 // two cross-lane adds.  Softmax uses exp2 with scale*log2(e) folded in.
 //
-// The un-pooled column sums of the prefix are written to raw_scores; pooling
-// and the forced window are applied by the select kernel.
+// The un-pooled column sums of the prefix go to store(): LDS in the fused kernels,
+// raw_scores in the others; pooling and the forced window are the selection's.
 
 // Wavefronts of a workgroup of the fused kernels.  Four, so that three or four
 // workgroups share a CU and the selection of one overlaps the streaming of the
@@ -367,7 +367,7 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
 // selects the budget-minus-window best of the prefix and appends the window.
 //
 //   1. the un-pooled scores lie in LDS; they are max-pooled and turned into
-//      order-preserving 32-bit keys, which stay in registers for the rest;
+//      order-preserving 32-bit keys, in the same words;
 //   2. the threshold (the k-th largest key) is found by a bucket select: 2048
 //      linear buckets over a range that holds it (so the histogram is spread
 //      even when every score shares its exponent), then the keys of the one
@@ -1622,10 +1622,11 @@ __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc
 // back to back in the workgroup that owns the (request, layer, head): the
 // column sums (or key norms) go straight into LDS, the selection works on
 // them in place and the copy follows.  The scores never travel through HBM,
-// the stage is one launch per method, and the LDS/ALU-bound selection of one
-// workgroup overlaps the HBM-bound streaming of the others on the same CU.
-// One launch serves both methods (the unit's descriptor says which); NT =
-// ceil(window / 16), or 0 when the launch holds no SnapKV unit.
+// the stage is one launch per workgroup shape, and the LDS/ALU-bound selection of
+// one workgroup overlaps the HBM-bound streaming of the others on the same CU.
+// One launch serves all methods (the unit's descriptor says which); NT =
+// ceil(window / 16), 0 when the launch holds no SnapKV unit, kMixedTiles when its
+// units differ.
 
 // f(the number of query tiles): NT itself, or (kMixedTiles: a launch whose SnapKV
 // units have windows of different classes) what the unit's window needs.
@@ -1686,7 +1687,9 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
 }
 
 // Wavefronts per SIMD that the registers must allow: what the kernel needs without
-// spilling in its loops.
+// spilling in its loops.  (At 128 channels the forms with one, four and mixed query
+// tiles spill 4 to 7 vector registers, stored and read back once a head, outside of
+// every loop.)
 __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
   return wv != kNarrow ? wv / 4 : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
 }
