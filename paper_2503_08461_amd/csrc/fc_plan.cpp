@@ -22,7 +22,20 @@ namespace {
 // FusedLaunch::query_tiles of a launch whose windows need different numbers of tiles.
 constexpr int kMixedQueryTiles = kPlanClasses;
 
-// Heads shorter than this are not worth the launches of the split path.
+// Heads shorter than this are not worth the launches of the split path, and with more
+// than one head per two CUs its second read of K and its extra launches cost more than
+// the idle CUs.  A call of one layer, window 32, 128 channels, fused / split in us:
+//             4 heads       32            64            128           160 heads
+//   SnapKV
+//     1500    48.3 / 40.8   49.3 / 42.0   51.3 / 46.5   54.6 / 52.8
+//     2048    56.8 / 40.6   61.5 / 41.7   63.8 / 49.0   67.6 / 60.7   69.3 / 67.7
+//     4000    83.0 / 43.0   89.2 / 55.2   93.4 / 63.7  101.7 / 91.3  102.3 / 105.4
+//     16000    244 / 75      255 / 109     277 / 163     297 / 299     326 / 370
+//   key-norm
+//     2048    37.1 / 38.5   36.5 / 37.7   38.8 / 36.6   41.6 / 47.9   43.2 / 55.7
+//     4000    47.9 / 38.0   54.5 / 39.7   59.3 / 49.6   65.3 / 72.2   69.5 / 86.4
+//     16000    161 / 44      178 / 83      194 / 129     225 / 250     242 / 314
+// (Calls of key-norm requests alone would be better off with a limit of 64 to 96 heads.)
 constexpr int kSplitMinLen = 2048;
 
 // Whether a call of `units` heads of up to 8192 tokens is better off in wide

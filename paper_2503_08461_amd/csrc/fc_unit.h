@@ -68,7 +68,16 @@ __host__ __device__ constexpr int bound_max_epochs() {
   return a > b ? a : b;
 }
 // Shorter heads take the two passes: the tokens of the first step have no bounds,
-// and a step of a wide workgroup is three to four times as many tokens.
+// and a step of a wide workgroup is three to four times as many tokens.  What the
+// line is worth depends on where the second pass would find K.  All kernels of a
+// call of one layer or four, whose K mostly stays in the memory-side cache, two
+// passes / pruned in us, window 32:
+//   narrow, 1024 heads, 128 channels   512 tokens  79.6 / 80.7   1024  145 / 128   2048  292 / 240
+//                        64 channels               51.2 / 65.5         83 / 94           146 / 153
+//   wide, 256 heads,    128 channels  1024 tokens  53.7 / 61.8   2048   84 / 86    3000  117 / 108
+//                        64 channels               39.5 / 50.3          52 / 68           67 / 83
+// With a pool of 32 layers, where it has to come from HBM again, 128 channels are
+// 2 % faster from 512 tokens on (32 prompts of 600-1200 tokens).
 template <int WV>
 static constexpr int kBoundMinLen = WV == kNarrow ? 512 : 2048;
 
