@@ -445,7 +445,11 @@ void mlp_compress_kernel(BatchParams p, MlpParams mp) {
       bid_n[nt][1] = ids[last >> 4];
     }
     // ---- where this tile's rows go.  (Looked up here: behind the next tile's rows
-    // the block id would arrive only after all of them, loads complete in order.)
+    // the block id would arrive only after all of them, loads complete in order.  At
+    // 64 channels and 256 hidden units, and at 128 and 128, the early wait costs more:
+    // 16 prompts of 3000 tokens, 4 layers, k = 2, 1250 -> 1204 and 1356 -> 1317 us
+    // with the lookup left to the store.)
+    constexpr bool kEarly = (D == 128) == (HID == 256);
     int out_row[NT], out_blk[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -455,7 +459,7 @@ void mlp_compress_kernel(BatchParams p, MlpParams mp) {
       const int cl = max(out_row[nt], 0) % job.chunks;
       const int o = (m == 1) ? rd.chunks_text0 + cl
                              : (cl < rd.chunks_text0 ? cl : rd.chunks_image + cl);
-      out_blk[nt] = clamp_block(p.new_ids[rd.new_off + (o >> 4)], p.n_blocks);
+      out_blk[nt] = kEarly ? clamp_block(p.new_ids[rd.new_off + (o >> 4)], p.n_blocks) : 0;
     }
 
     // ---- bias, gelu, fp16: each 32x32 result tile becomes two B operands of
@@ -482,7 +486,7 @@ void mlp_compress_kernel(BatchParams p, MlpParams mp) {
     for (int mt = 0; mt < MT1 / 2; ++mt) gelu_tile(mt);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      asm volatile("" : "+v"(out_blk[nt]));  // has arrived: the rows are requested behind it
+      if constexpr (kEarly) asm volatile("" : "+v"(out_blk[nt]));  // has arrived: the rows are requested behind it
       write_rows(ln_n[nt], bid_n[nt], nt);
     }
 #pragma unroll
@@ -524,6 +528,7 @@ void mlp_compress_kernel(BatchParams p, MlpParams mp) {
                                : (cl < rd.chunks_text0 ? cl : rd.chunks_image + cl);
         const int lh = unit >> 1;
         const int layer = lh / p.n_heads;
+        if constexpr (!kEarly) out_blk[nt] = clamp_block(p.new_ids[rd.new_off + (o >> 4)], p.n_blocks);
         _Float16* dst = p.kv + (size_t)layer * p.n_blocks * blk_stride +
                         (size_t)out_blk[nt] * blk_stride + (unit & 1) * v_off +
                         (size_t)(lh - layer * p.n_heads) * chunk_el + (size_t)(o & 15) * D;
