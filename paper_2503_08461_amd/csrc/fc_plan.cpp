@@ -41,8 +41,9 @@ constexpr int kSplitMinLen = 2048;
 // Whether a call of `units` heads of up to 8192 tokens is better off in wide
 // workgroups.  With at most one head per CU it is, from the length on at which a
 // head keeps their wavefronts busy; with up to two per CU, which narrow workgroups
-// run at once and wide ones one after the other, from a greater length on; with more
-// it is not.  All kernels of a call, narrow / wide in us, at 256 and at 512 heads:
+// run at once and wide ones one after the other, heaviest first, from there on as
+// well unless all heads are alike; with more it is not.  All kernels of a call,
+// narrow / wide in us, at 256 and at 512 heads:
 //   SnapKV, window 32, 128 channels       64 channels
 //     300 tokens   35.9 / 36.9    43.5 / 56.3     30.5 / 30.7    34.0 / 43.5
 //     512          53.9 / 42.3    62.9 / 66.7     48.2 / 33.1    54.3 / 49.0
@@ -54,11 +55,12 @@ constexpr int kSplitMinLen = 2048;
 //     640          46.4 / 34.9    52.9 / 53.7     33.5 / 27.7    38.8 / 41.2
 //     900          56.8 / 39.4    64.9 / 62.4     40.4 / 30.3    46.6 / 45.8
 //    1800          90.6 / 57.6   104.6 / 95.0     62.4 / 38.5    70.3 / 61.0
-// (SnapKV: 512 and 2048 are also where narrow and wide workgroups begin to prune.)
-bool wide_pays(const CompressPlan& plan, size_t units, int head_dim, int n_cu) {
+// and with lengths that differ (SnapKV, 128 channels, 300-900 tokens): 288 heads
+// 72.0 / 56.5, 384 heads 73.9 / 65.1, 512 heads 79.2 / 74.7.
+bool wide_pays(const CompressPlan& plan, size_t units, int n_cu) {
   if (units > 2 * (size_t)n_cu) return false;
   const bool one_each = units <= (size_t)n_cu;
-  const int snap_from = one_each || head_dim == 64 ? 512 : 2048, other_from = one_each ? 256 : 768;
+  const int snap_from = 512, other_from = one_each ? 256 : 768;
   for (const ReqDesc& d : plan.descs) {
     if (d.method != PLAN_METHOD_STREAMING && d.seq_len > kPlanFusedMaxLen) continue;  // (wide anyhow)
     if (d.seq_len >= (d.method == PLAN_METHOD_SNAPKV ? snap_from : other_from)) return true;
@@ -241,7 +243,7 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
   };
   size_t short_units = 0;
   for (int c = 0; c < kPlanClasses; ++c) short_units += plan.lists[LIST_FUSED + c].size() * n_lh;
-  const bool few = wide_pays(plan, short_units, pool.head_dim, n_cu);
+  const bool few = wide_pays(plan, short_units, n_cu);
   for (int c = 0; c < kPlanClasses; ++c) {
     add(few ? wide : narrow, plan.lists[LIST_FUSED + c]);
     if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_SNAP + c]);

@@ -50,14 +50,12 @@ def test_launch_plan(tmp_path):
         # one head per compute unit at most, and two: wide from the length on that keeps them busy
         (_case(1, 256, [(511, SNAP, 100, 32)]), "narrow"),
         (_case(1, 256, [(512, SNAP, 100, 32)]), "wide"),
-        (_case(1, 257, [(2047, SNAP, 100, 32)]), "narrow"),
-        (_case(1, 257, [(2048, SNAP, 100, 32)]), "wide"),
+        (_case(1, 512, [(511, SNAP, 100, 32)]), "narrow"),
+        (_case(1, 512, [(512, SNAP, 100, 32)]), "wide"),
         (_case(1, 256, [(255, KNORM, 100, 32)]), "narrow"),
         (_case(1, 256, [(256, KNORM, 100, 32)]), "wide"),
         (_case(1, 257, [(767, KNORM, 100, 32)]), "narrow"),
         (_case(1, 257, [(768, KNORM, 100, 32)]), "wide"),
-        (_case(1, 512, [(511, SNAP, 100, 32)], d=64), "narrow"),
-        (_case(1, 512, [(512, SNAP, 100, 32)], d=64), "wide"),
         (_case(1, 4, [(256, SNAP, 64, 16)]), "narrow"),
         (_case(1, 32, [(100, SNAP, 64, 16), (9, KNORM, 4, 16), (20000, STREAM, 4000, 16)]), "wide"),
     ]
