@@ -731,7 +731,10 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   int select_len = plan.max_len[LIST_ALL];
   if (n_split)
     for (const ReqDesc& d : plan.descs) select_len = std::max(select_len, d.seq_len);
-  FC_HIP_STAGE(p, run(K_SELECT, bp.n_unfused > 0, [&] { return launch_select(bp, select_len, stream); }));
+  const bool wide_select =
+      select_is_wide(select_len, (size_t)bp.n_unfused * p->n_layers * p->n_heads, p->n_cu);
+  FC_HIP_STAGE(p, run(K_SELECT, bp.n_unfused > 0,
+                      [&] { return launch_select(bp, select_len, wide_select, stream); }));
   FC_HIP_STAGE(p, run(K_GATHER, bp.n_unfused > 0, [&] { return launch_gather(bp, stream); }));
   FC_HIP_STAGE(p, run(K_FUSED, !fused.empty(), [&] {
     hipError_t e = hipSuccess;

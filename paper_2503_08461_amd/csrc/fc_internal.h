@@ -144,7 +144,8 @@ hipError_t launch_zero_ints(int32_t* p, int n, hipStream_t s);
 hipError_t launch_knorm_score(const BatchParams& p, hipStream_t s);
 // scores of heads split over workgroups (order_all; select and gather follow)
 hipError_t launch_split_scores(const BatchParams& p, hipStream_t s);
-hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s);
+// wide: workgroups for heads of more than kFusedMaxLen tokens and for few heads
+hipError_t launch_select(const BatchParams& p, int max_seq_len, bool wide, hipStream_t s);
 hipError_t launch_gather(const BatchParams& p, hipStream_t s);
 // score -> select -> gather of every unit of order_fused in one launch.
 // max_seq_len: longest head that is scored, at most kFusedMaxLen (kFusedWideMaxLen

@@ -292,12 +292,14 @@ __global__ __launch_bounds__(kThreads) void split_scores_kernel(BatchParams p) {
   snapkv_columns<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, fin, qreg, [&](int j, float v) { raw[j] = v; });
 }
 
-// Heads of up to 32768 tokens whose scores come from a kernel of their own: 16
-// wavefronts, so that a lane's share of the keys is that of a short head.
+// Heads whose scores come from a kernel of their own.  16 wavefronts for heads of up
+// to 32768 tokens and for launches with few heads, so that a lane's share of the keys
+// is that of a short head; 4, of which a CU holds several workgroups, for the rest.
 static constexpr int kSelectWaves = 16;
-__global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p) {
+template <int WV>
+__global__ __launch_bounds__(64 * WV) void select_kernel(BatchParams p) {
   extern __shared__ __align__(16) uint32_t lds[];
-  __shared__ SelectShared<kSelectWaves> sh;
+  __shared__ SelectShared<WV> sh;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
@@ -305,14 +307,14 @@ __global__ __launch_bounds__(64 * kSelectWaves) void select_kernel(BatchParams p
   uint32_t* stage = lds + kStageFront;
   int32_t* kept = p.kept + rd.kept_off + (size_t)lh * rd.budget;
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform (heads split over workgroups only)
-    streaming_unit<kSelectWaves>(p, rd, lh, kept);
+    streaming_unit<WV>(p, rd, lh, kept);
     return;
   }
   const float* raw = p.raw_scores + rd.raw_off + (size_t)lh * rd.seq_len;
   const int n_sel = rd.method == 1 /* FC_METHOD_SNAPKV */ ? rd.seq_len - rd.window : rd.seq_len;
-  for (int j = threadIdx.x; j < n_sel; j += 64 * kSelectWaves) stage[j] = __float_as_uint(raw[j]);
+  for (int j = threadIdx.x; j < n_sel; j += 64 * WV) stage[j] = __float_as_uint(raw[j]);
   __syncthreads();
-  select_unit<kSelectWaves>(p, rd, lh, stage, lds + stage_words(rd.seq_len), kept, sh);
+  select_unit<WV>(p, rd, lh, stage, lds + stage_words(rd.seq_len), kept, sh);
 }
 
 template <int D>
@@ -339,7 +341,7 @@ __global__ void zero_ints_kernel(int32_t* p, int n) {
 hipError_t kernels_one_time_setup() {
   // kernels that may need more than the default 64 KiB of dynamic LDS
   // (the narrow fused kernels never do)
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel<kSelectWaves>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (stage_words(32768) + need_words(32768)) * 4);
   if (e == hipSuccess) e = fused_wide_setup_64();
   if (e == hipSuccess) e = fused_wide_setup_128();
@@ -470,10 +472,15 @@ hipError_t launch_split_scores(const BatchParams& p, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_select(const BatchParams& p, int max_seq_len, hipStream_t s) {
+hipError_t launch_select(const BatchParams& p, int max_seq_len, bool wide, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_unfused * p.n_layers * p.n_heads;
   const size_t lds = (size_t)(stage_words(max_seq_len) + need_words(max_seq_len)) * sizeof(uint32_t);
-  select_kernel<<<grid, 64 * kSelectWaves, lds, s>>>(p);
+  if (wide)
+    select_kernel<kSelectWaves><<<grid, 64 * kSelectWaves, lds, s>>>(p);
+  else if (max_seq_len <= kFusedMaxLen)
+    select_kernel<kNarrow><<<grid, 64 * kNarrow, lds, s>>>(p);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

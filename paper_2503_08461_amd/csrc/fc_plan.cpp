@@ -285,6 +285,14 @@ int plan_split(const PoolView& pool, int n_cu, CompressPlan* plan) {
   return (int)std::min<size_t>(std::max<size_t>(2 * (size_t)n_cu / units, 2), longest / 256);
 }
 
+// All kernels of a key-norm call with the separate kernels, 4 / 16 wavefronts in us:
+// 256 heads of 300, 700, 1500 and 4000 tokens 41.9 / 42.4, 60.5 / 61.5, 96.6 / 94.4
+// and 209 / 203; 512 heads 50.4 / 54.8, 72.6 / 77.6, 119 / 123 and 300 / 300; 4096
+// heads of 300 and 700 tokens 160 / 224 and 369 / 434.
+bool select_is_wide(int max_len, size_t units, int n_cu) {
+  return max_len > kPlanFusedMaxLen || (units <= (size_t)n_cu && max_len >= 1024);
+}
+
 int plan_window_lse(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,
                     const int32_t* method, int window, LsePlan* plan) {
   *plan = LsePlan();

@@ -95,6 +95,9 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
 // plan->descs get their offsets in the score scratch, plan->raw_floats its size.
 int plan_split(const PoolView& pool, int n_cu, CompressPlan* plan);
 
+// Whether the select kernel of `units` heads of at most max_len tokens takes 16 wavefronts a head.
+bool select_is_wide(int max_len, size_t units, int n_cu);
+
 // fc_window_lse: one descriptor per SnapKV request (all if method is NULL),
 // longest first, queries packed as [n_req][...][window].
 struct LsePlan {

@@ -70,7 +70,7 @@ hipError_t launch_snapkv_score(const BatchParams&, hipStream_t) { return launche
 hipError_t launch_zero_ints(int32_t*, int, hipStream_t) { return launched("zero"); }
 hipError_t launch_knorm_score(const BatchParams&, hipStream_t) { return launched("knorm_score"); }
 hipError_t launch_split_scores(const BatchParams&, hipStream_t) { return launched("split_scores"); }
-hipError_t launch_select(const BatchParams&, int, hipStream_t) { return launched("select"); }
+hipError_t launch_select(const BatchParams&, int, bool, hipStream_t) { return launched("select"); }
 hipError_t launch_gather(const BatchParams&, hipStream_t) { return launched("gather"); }
 hipError_t launch_fused(BatchParams, int, int, int, bool wide, hipStream_t) { return launched(wide ? "fused_wide" : "fused_narrow"); }
 hipError_t launch_reclaim(const BatchParams&, hipStream_t) { return launched("reclaim"); }
