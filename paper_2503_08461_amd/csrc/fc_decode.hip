@@ -5,6 +5,8 @@
 // 4*d bytes per (request, layer, head), the attention reads every cached K and
 // V row once, 4*d bytes per token of a (layer, head).
 
+#include <type_traits>
+
 #include "fc_device.h"
 
 namespace fc {
@@ -15,11 +17,15 @@ namespace fc {
 // boundary takes the block that the host assigned it from the top of the free
 // stack (pops in batch order) and the layer-0 workgroup records it in the table.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p, DecodeReqs inline_reqs) {
+//
+// Reqs (here and below): DecodeReqs, the requests in the arguments, or DecodeReqList,
+// on the device.  Kernels of their own: 3.6 KB of arguments that nobody reads cost a
+// launch of small caches several us.
+template <int D, typename Reqs>
+__global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p, Reqs reqs) {
   const int r = blockIdx.x / p.n_layers;
   const int layer = blockIdx.x - r * p.n_layers;
-  const DecodeReq rq = p.reqs ? p.reqs[r] : inline_reqs.req[r];
+  const DecodeReq rq = reqs.req[r];
   const int L = rq.seq_len;
   int32_t* row = p.block_tables + (size_t)rq.table_row * p.max_blocks;
   int blk;
@@ -45,15 +51,26 @@ __global__ __launch_bounds__(kThreads) void append_kernel(DecodeParams p, Decode
   }
 }
 
+// f(the requests of p, wherever they are)
+template <typename F>
+static void with_reqs(const DecodeParams& p, const DecodeReqs& inline_reqs, F f) {
+  if (p.reqs)
+    f(DecodeReqList{p.reqs});
+  else
+    f(inline_reqs);
+}
+
 hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
   if (p.n_req == 0) return hipSuccess;
+  if (p.head_dim != 64 && p.head_dim != 128) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)p.n_req * p.n_layers;
-  if (p.head_dim == 128)
-    append_kernel<128><<<grid, kThreads, 0, s>>>(p, inline_reqs);
-  else if (p.head_dim == 64)
-    append_kernel<64><<<grid, kThreads, 0, s>>>(p, inline_reqs);
-  else
-    return hipErrorInvalidValue;
+  with_reqs(p, inline_reqs, [&](const auto& reqs) {
+    using Reqs = std::decay_t<decltype(reqs)>;
+    if (p.head_dim == 128)
+      append_kernel<128, Reqs><<<grid, kThreads, 0, s>>>(p, reqs);
+    else
+      append_kernel<64, Reqs><<<grid, kThreads, 0, s>>>(p, reqs);
+  });
   return hipGetLastError();
 }
 
@@ -93,8 +110,8 @@ __device__ __forceinline__ int decode_segments(int L, int seg_blocks) {
   return (((L + 15) >> 4) + seg_blocks - 1) / seg_blocks;
 }
 
-template <int D, bool kIndexed>
-__global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, DecodeReqs inline_reqs) {
+template <int D, bool kIndexed, typename Reqs>
+__global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, Reqs reqs) {
   constexpr int LPR = D / 8;        // lanes per row
   constexpr int RPI = 64 / LPR;     // rows per wavefront load instruction
   constexpr int IPB = 16 / RPI;     // load instructions per 16-token block
@@ -105,7 +122,7 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
   const int slot = blockIdx.x / per_req;
   const int seg = (blockIdx.x - slot * per_req) / n_lh;
   const int lh = blockIdx.x - slot * per_req - seg * n_lh;
-  const DecodeReq rq = p.reqs ? p.reqs[slot] : inline_reqs.req[slot];
+  const DecodeReq rq = reqs.req[slot];
   const int L = kIndexed ? rq.pop_index : rq.seq_len;  // indexed: pop_index holds the budget
   const int nb = (L + 15) >> 4;
   const int b0 = seg * p.seg_blocks, b1 = min(nb, b0 + p.seg_blocks);
@@ -214,12 +231,12 @@ static constexpr int kMaxHeadSegments = kPlanMaxSeqLen / kPlanBlockSize / 16;
 
 // Heads that were cut: the output from the segments' states.  workgroup =
 // (request, layer, head), one thread per channel.
-template <int D, bool kIndexed>
-__global__ __launch_bounds__(D) void decode_merge_kernel(DecodeParams p, DecodeReqs inline_reqs) {
+template <int D, bool kIndexed, typename Reqs>
+__global__ __launch_bounds__(D) void decode_merge_kernel(DecodeParams p, Reqs reqs) {
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
-  const DecodeReq rq = p.reqs ? p.reqs[slot] : inline_reqs.req[slot];
+  const DecodeReq rq = reqs.req[slot];
   const int L = kIndexed ? rq.pop_index : rq.seq_len;
   const int n_seg = decode_segments(L, p.seg_blocks);
   if (n_seg <= 1) return;  // written by the kernel above
@@ -245,8 +262,11 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecodeParams p, DecodeR
 template <int D, bool kIndexed>
 static void launch_decode_one(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {
   const unsigned heads = (unsigned)p.n_req * p.n_layers * p.n_heads;
-  decode_attention_kernel<D, kIndexed><<<heads * p.n_seg, kThreads, 0, s>>>(p, inline_reqs);
-  if (p.n_seg > 1) decode_merge_kernel<D, kIndexed><<<heads, D, 0, s>>>(p, inline_reqs);
+  with_reqs(p, inline_reqs, [&](const auto& reqs) {
+    using Reqs = std::decay_t<decltype(reqs)>;
+    decode_attention_kernel<D, kIndexed, Reqs><<<heads * p.n_seg, kThreads, 0, s>>>(p, reqs);
+    if (p.n_seg > 1) decode_merge_kernel<D, kIndexed, Reqs><<<heads, D, 0, s>>>(p, reqs);
+  });
 }
 
 hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs& inline_reqs, hipStream_t s) {

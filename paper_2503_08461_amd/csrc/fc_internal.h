@@ -26,8 +26,11 @@ struct MlpParams {
 // a copy through pinned memory costs the stream a copy kernel and 10 to 20 us of
 // idle time on either side, and the host has to wait until the last one is through.
 struct DecodeReqs {
-  static constexpr int kInline = 112;  // (2688 bytes)
+  static constexpr int kInline = 3584 / sizeof(DecodeReq);  // 149
   DecodeReq req[kInline];
+};
+struct DecodeReqList {  // requests on the device
+  const DecodeReq* req;
 };
 static_assert(sizeof(DecodeReq) == 24, "tests count on the sizes of descriptors and argument blocks");
 static constexpr size_t kMaxArgumentBytes = 4096;  // what the arguments of a kernel may take

@@ -14,6 +14,7 @@
 
 static hipError_t g_last = hipSuccess;
 static size_t g_largest = ~(size_t)0;  // largest device allocation that succeeds
+static bool g_capturing = false;
 static std::string g_launched;
 
 static hipError_t give(void** out, size_t size) {
@@ -37,6 +38,10 @@ hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t*) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t*, unsigned) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
@@ -134,6 +139,19 @@ int main(int argc, char** argv) {
     g_largest = ~(size_t)0;
     report("create_with_room", create());
     attention("cut");
+  } else if (scenario == "decode_requests") {
+    report("create", create());
+    for (int n : {149, 150}) {
+      std::vector<int32_t> lens(n, 20);
+      auto step = [&](const char* what) {
+        report(what, fc_decode_attention(pool, somewhere<int32_t>(), 2, lens.data(), somewhere<void>(),
+                                         somewhere<float>(), n, 0.f, nullptr));
+      };
+      step(n == 149 ? "few" : "many");
+      g_capturing = true;
+      step(n == 149 ? "few_captured" : "many_captured");
+      g_capturing = false;
+    }
   } else {
     return 2;
   }

@@ -54,3 +54,12 @@ def test_a_pool_without_room_for_decode_segments_attends_over_whole_heads(driver
     assert out["whole"] == (0, ["attention_inline:1"])
     assert out["create_with_room"][0] == 0
     assert out["cut"][0] == 0 and int(out["cut"][1][0].split(":")[1]) > 1
+
+
+def test_requests_of_a_decode_step(driver):
+    """As arguments of the kernel where they fit, else through pinned memory, but never that in a
+    captured call: a replay would read what the staging buffer holds by then."""
+    out, _ = run(driver, "decode_requests")
+    assert out["few"] == out["few_captured"] == (0, ["attention_inline:1"])
+    assert out["many"] == (0, ["copy", "attention:1"])
+    assert out["many_captured"] == (0, ["upload", "upload", "attention:1"])
