@@ -487,12 +487,13 @@ int release_verdict(fc_pool* p, hipStream_t stream, const char* what) {
               "nothing was changed");
 }
 
-// Descriptors and work lists to the device (bytes: a multiple of 16).  Up to four
+// Descriptors and work lists to the device (bytes: a multiple of 16).  Up to three
 // launches' worth go as kernel arguments, and whatever the allocation-free call
 // needs; more go through the pinned staging buffer and one asynchronous copy, whose
-// price (10 to 40 us of an idle GPU, see plan_alloc_inline_kernel) is that of four to
-// eight launches and does not grow with the size.
-constexpr size_t kMaxArgumentMeta = 4 * sizeof(MetaChunk);
+// price does not grow with the size.  Calls back to back, arguments / copy in us: 36
+// prompts of 40 tokens, 32 heads (two launches) 38.0 / 41.3, 100 (three) 57.1 / 59.3,
+// 143 (four) 74.7 / 72.2, with 8 heads 54.1 / 45.4.
+constexpr size_t kMaxArgumentMeta = 3 * sizeof(MetaChunk);
 int upload_meta_arguments(const char* image, size_t bytes, char* dev_dst, hipStream_t stream) {
   for (size_t off = 0; off < bytes; off += sizeof(MetaChunk)) {
     MetaChunk c;

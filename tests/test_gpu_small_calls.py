@@ -12,9 +12,9 @@ from test_gpu_parity import _custom
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_req", [1, 34, 35, 36, 37, 142, 143, 144, 300])
+@pytest.mark.parametrize("n_req", [1, 34, 35, 36, 37, 107, 108, 143, 144, 300])
 def test_compression(n_req):
-    """96 bytes a request and 4 per entry of a work list: 35 requests fill 3584 bytes, 143 four times as much."""
+    """96 bytes a request and 4 per entry of a work list: 35 requests fill 3584 bytes, 107 three times as much."""
     from parity_util import SideBySide
     lens = [17 + (37 * i) % 90 for i in range(n_req)]
     methods = [(fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING)[i % 3] for i in range(n_req)]
