@@ -357,8 +357,8 @@ int fc_set_streaming_sinks(fc_pool* pool, int n_sink);
  *     fused kernel (two-pass score -> select -> gather inside the workgroup
  *     that owns the head; scores stay in LDS), except in calls with so few and
  *     long heads that each is split over several workgroups (two full passes
- *     over K, scores in library scratch; a call that cannot have that memory
- *     runs in the fused kernels).
+ *     over K, scores in library scratch; a call that cannot have that memory,
+ *     or is captured into a graph before it was there, runs in the fused kernels).
  *     (See fc_set_score_pruning for what the fused kernel does with the
  *     second pass when the call does not ask for the scores.)
  *   FC_SCORE_TWO_PASS: separate kernels for everything; SnapKV scoring streams

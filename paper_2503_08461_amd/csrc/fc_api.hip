@@ -143,6 +143,7 @@ struct fc_pool {
   size_t raw_cap = 0;  // floats
   int32_t* kept = nullptr;
   size_t kept_cap = 0;  // ints
+  size_t split_refused = ~(size_t)0;  // least score scratch of split heads that could not be had
   int32_t* ids = nullptr;
   size_t ids_cap = 0;  // ints (old ids then new ids)
   char* dev_meta = nullptr;
@@ -538,6 +539,19 @@ bool fits_inline(const fc_pool* p, const char* image, size_t bytes, MetaChunk* c
   return true;
 }
 
+// Whether the scratch of split heads is there, or can be had now.  A captured call
+// allocates nothing, and a size that was refused is not asked for again: each attempt
+// waits for the device.
+bool have_split_scratch(fc_pool* p, size_t raw_floats, size_t kept_entries, hipStream_t stream) {
+  if (raw_floats <= p->raw_cap && kept_entries <= p->kept_cap) return true;
+  if (raw_floats >= p->split_refused || capturing(stream)) return false;
+  if (try_grow(&p->raw_scores, &p->raw_cap, raw_floats) == hipSuccess &&
+      try_grow(&p->kept, &p->kept_cap, kept_entries) == hipSuccess)
+    return true;
+  p->split_refused = raw_floats;
+  return false;
+}
+
 // All entry points of the pruning stage.  host_window / host_pool_kernel are
 // NULL for the calls that take one size for the whole batch.  no_alloc: every
 // scratch buffer lies in the file-scope device array and nothing is allocated.
@@ -584,9 +598,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   const size_t fixed_kept = dev_kept_out ? 0 : plan.kept_entries;
   if (no_alloc && fixed_kept + raw_floats > kNoAllocKeptInts) n_split = 0;
   // no memory for what only split heads need (scores, kept lists): the fused kernels do without
-  if (n_split && !no_alloc &&
-      (try_grow(&p->raw_scores, &p->raw_cap, raw_floats) != hipSuccess ||
-       (!dev_kept_out && try_grow(&p->kept, &p->kept_cap, plan.kept_entries) != hipSuccess)))
+  if (n_split && !no_alloc && !have_split_scratch(p, raw_floats, dev_kept_out ? 0 : plan.kept_entries, stream))
     n_split = 0;
   std::vector<FusedLaunch> fused;
   if (n_split == 0) fused = plan_fused_launches(pv, plan, p->n_cu);

@@ -14,6 +14,7 @@
 
 static hipError_t g_last = hipSuccess;
 static size_t g_largest = ~(size_t)0;  // largest device allocation that succeeds
+static int g_allocations = 0;  // device allocations and waits
 static bool g_capturing = false;
 static std::string g_launched;
 
@@ -23,7 +24,10 @@ static hipError_t give(void** out, size_t size) {
   return hipSuccess;
 }
 extern "C" {
-hipError_t hipMalloc(void** out, size_t size) { return give(out, size); }
+hipError_t hipMalloc(void** out, size_t size) {
+  ++g_allocations;
+  return give(out, size);
+}
 hipError_t hipHostMalloc(void** out, size_t size, unsigned) { *out = calloc(1, size); return hipSuccess; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
@@ -36,7 +40,10 @@ hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind, h
 hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
-hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+  ++g_allocations;
+  return hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
   *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -124,8 +131,24 @@ int main(int argc, char** argv) {
     compress("full", nullptr);
     compress("full_kept_out", somewhere<int32_t>());
     printf("error [%s]\n", fc_last_error());
+    g_allocations = 0;
+    compress("full_again", nullptr);
+    printf("error %d\n", g_allocations);
     g_largest = ~(size_t)0;
+    fc_pool_destroy(pool);
+    report("create_with_room", create());
+    fc_set_compaction_mode(pool, FC_COMPACT_IN_PLACE);
+    compress("in_place_again", nullptr);
+    fc_set_compaction_mode(pool, FC_COMPACT_FRESH);
+    g_capturing = true;
+    g_allocations = 0;
+    compress("captured", nullptr);
+    printf("error %d\n", g_allocations);
+    g_capturing = false;
     compress("room", nullptr);
+    g_capturing = true;
+    compress("captured_warm", nullptr);
+    g_capturing = false;
   } else if (scenario == "no_room_for_decode_segments") {
     const int32_t lens[2] = {8000, 30000};
     auto attention = [&](const char* what) {

@@ -36,14 +36,18 @@ def run(driver, scenario):
 
 def test_a_call_that_cannot_have_split_scores_runs_in_the_fused_kernels(driver):
     """Few long heads are split over workgroups, which takes score scratch.  Without memory for it
-    the call runs as it does with many heads; the pool stays usable and no error is left behind."""
+    the call runs as it does with many heads; the pool stays usable and no error is left behind.
+    What was refused is not asked for again (an attempt waits for the device), and a captured call
+    asks for nothing."""
     out, errors = run(driver, "no_room_for_split_scores")
     fused = [["plan_inline", "fused_wide", "reclaim"]]
     assert out["in_place"] == (0, fused[0])
     assert out["full"] == (0, fused[0])
     assert out["full_kept_out"] == (0, fused[0])
-    assert errors == ["error []"]
-    assert out["room"] == (0, ["plan_inline", "split_scores", "select", "gather", "reclaim"])
+    assert out["full_again"] == out["captured"] == (0, fused[0])
+    assert errors == ["error []", "error 0", "error 0"]
+    split = (0, ["plan_inline", "split_scores", "select", "gather", "reclaim"])
+    assert out["room"] == out["captured_warm"] == split
 
 
 def test_a_pool_without_room_for_decode_segments_attends_over_whole_heads(driver):
