@@ -263,6 +263,7 @@ __global__ __launch_bounds__(kThreads) void split_rows_kernel(BatchParams p) {
 template <int D, int NT>
 __global__ __launch_bounds__(kThreads) void split_scores_kernel(BatchParams p) {
   __shared__ float fin[64];
+  __shared__ KeyTiles<kWaves> tiles;
   __shared__ int32_t sm_ids[kSplitIds];
   const SplitUnit u = split_unit(p);
   if (u.rd.method != 1 /* FC_METHOD_SNAPKV */) return;  // uniform
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void split_scores_kernel(BatchParams p) {
   load_window_queries<D, NT>(p, u.rd, u.lh, qreg);
   __syncthreads();
   float* raw = p.raw_scores + u.rd.raw_off + (size_t)u.lh * u.rd.seq_len;
-  snapkv_columns<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, fin, qreg, [&](int j, float v) { raw[j] = v; });
+  snapkv_columns<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, fin, tiles, qreg, [&](int j, float v) { raw[j] = v; });
 }
 
 // Heads whose scores come from a kernel of their own.  16 wavefronts for heads of up

@@ -15,11 +15,10 @@ namespace fc {
 // ---------------------------------------------------------------------------
 //
 // One workgroup per (request, layer, head).  A wavefront takes pool blocks
-// (16 tokens) round-robin and feeds them to v_mfma_f32_16x16x32_f16 straight
-// from global memory: lane l holds 8 consecutive channels
-// [32*ks + 8*(l/16), +8) of token l%16, which is both the A-operand layout
-// (rows = tokens) and the B-operand layout (columns = tokens) of that
-// instruction, and 4 lanes cover 64 contiguous bytes of a token row.
+// (16 tokens) round-robin and feeds them to v_mfma_f32_16x16x32_f16: lane l holds
+// 8 consecutive channels [32*ks + 8*(l/16), +8) of token l%16, which is both the
+// A-operand layout (rows = tokens) and the B-operand layout (columns = tokens) of
+// that instruction (KeyBlocks: how they get there).
 //
 // Pass 1 (A = keys, B = queries): the 16x16 result has the window query on the
 // lane (l%16) and 4 tokens in the lane's registers, so every lane keeps an
@@ -81,6 +80,88 @@ __host__ __device__ constexpr int bound_max_epochs() {
 template <int WV>
 static constexpr int kBoundMinLen = WV == kNarrow ? 512 : 2048;
 
+// A block's keys of one (layer, head), from memory to the operand layout of the
+// products: k[ks] of lane (q4, c16) = channels [32 ks + 8 q4, +8) of token c16.
+// Loaded straight into that layout, 16 rows of 64 bytes an instruction, or (kLines)
+// eight rows of 128 bytes, whole cache lines, which arrange() then hands to the lanes
+// through 2 KB of LDS of the wavefront's own, 64 channels at a time.  Only with whole
+// lines does the non-temporal hint give anything: a plain pass over 2 GB of K blocks
+// reads 5.95 TB/s without it in either layout, with it 6.0 straight and 6.6 in lines.
+// So lines are for keys that are not wanted again (second pass of a call with scores,
+// 4096 heads of 3000 tokens, window 64: 1638 -> 1494 us; the single pass of a call with
+// the log-sum-exps), and passes that leave the keys to the caches load straight.  Wide
+// workgroups do in any case: their wavefronts wait longer for the LDS than lines save
+// (pruned heads of 10000 tokens, 1024 of them, 64 channels: 603 us straight, 653 in lines).
+static constexpr int kTilePieces = 128;  // 16-byte pieces of a wavefront's tile
+template <int WV>
+struct KeyTiles {
+  half8 piece[WV == kNarrow ? WV * kTilePieces : 1];
+};
+template <int D, int WV, bool kWanted>
+struct KeyBlocks {
+  static constexpr bool kLines = kWanted && WV == kNarrow;
+  const _Float16* base;
+  size_t stride;
+  int n_blocks;
+  half8* put;         // where this lane's piece of rows 0 .. 7 goes (a piece of row r lies at its index ^ (r & 7))
+  const half8* got0;  // its operand of the first 32 of 64 channels,
+  const half8* got1;  // of the second
+  __device__ __forceinline__ KeyBlocks(const BatchParams& p, int lh, KeyTiles<WV>& tiles) : n_blocks(p.n_blocks) {
+    const int layer = lh / p.n_heads, head = lh - layer * p.n_heads;
+    const int lane = threadIdx.x & 63;
+    const int row = lane >> 3, c16 = lane & 15, q4 = lane >> 4;
+    stride = (size_t)2 * p.n_heads * 16 * D;
+    base = p.kv + (size_t)layer * p.n_blocks * stride + (size_t)head * 16 * D + (kLines ? (lane & 7) * 8 : q4 * 8);
+    if constexpr (kLines) {
+      half8* const mine = tiles.piece + (threadIdx.x >> 6) * kTilePieces;
+      put = mine + row * 8 + ((lane & 7) ^ row);
+      got0 = mine + c16 * 8 + (q4 ^ (c16 & 7));
+      got1 = mine + c16 * 8 + ((4 + q4) ^ (c16 & 7));
+    }
+  }
+  __device__ __forceinline__ const _Float16* block(int id) const {
+    return base + (size_t)clamp_block(id, n_blocks) * stride;
+  }
+  template <bool kNonTemporal>
+  static __device__ __forceinline__ half8 piece(const _Float16* at) {
+    return kNonTemporal ? load_half8_nt(at) : load_half8(at);
+  }
+  template <bool kNonTemporal>
+  __device__ __forceinline__ void load(int id, half8 (&k)[D / 32]) const {
+    // (the block is the wavefront's: scalar address arithmetic)
+    const _Float16* kp = block(__builtin_amdgcn_readfirstlane(id));
+    kp += (kLines ? (threadIdx.x & 63) >> 3 : threadIdx.x & 15) * D;
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+      k[i] = piece<kNonTemporal>(kLines ? kp + (i & 1) * 8 * D + (i >> 1) * 64 : kp + i * 32);
+  }
+  // The same of sixteen tokens from anywhere in the head: lane % 16 names one in tok.
+  __device__ __forceinline__ void load_rows(int tok, const int32_t* ids, half8 (&k)[D / 32]) const {
+    const _Float16* at[2];
+#pragma unroll
+    for (int i = 0; i < (kLines ? 2 : 1); ++i) {
+      const int t = kLines ? __shfl(tok, ((threadIdx.x & 63) >> 3) + 8 * i) : tok;
+      at[i] = block(ids[t >> 4]) + (t & 15) * D;
+    }
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+      k[i] = piece<true>(kLines ? at[i & 1] + (i >> 1) * 64 : at[0] + i * 32);
+  }
+  __device__ __forceinline__ void arrange(half8 (&k)[D / 32]) const {
+    if constexpr (kLines) {
+#pragma unroll
+      for (int i = 0; i < D / 32; i += 2) {
+        put[0] = k[i];
+        put[64] = k[i + 1];
+        wave_lds_barrier();
+        k[i] = *got0;
+        k[i + 1] = *got1;
+        wave_lds_barrier();
+      }
+    }
+  }
+};
+
 template <int WV>
 struct ScoreShared {
   // partial (max, sum) pairs per wavefront and row: those of the four lane groups,
@@ -89,6 +170,7 @@ struct ScoreShared {
   float m[WV][kParts][64];
   float z[WV][kParts][64];
   float fin[64];
+  KeyTiles<WV> tiles;
 };
 
 // Scores one (request, layer, head); store(j, a_j) receives the un-pooled
@@ -116,31 +198,6 @@ __device__ __forceinline__ void load_window_queries(const BatchParams& p, const 
   }
 }
 
-// Where a lane finds its part of a block's keys of one (layer, head).
-template <int D>
-struct KeyBlocks {
-  const _Float16* base;
-  size_t stride;
-  int n_blocks;
-  __device__ __forceinline__ KeyBlocks(const BatchParams& p, int lh) : n_blocks(p.n_blocks) {
-    const int layer = lh / p.n_heads, head = lh - layer * p.n_heads;
-    const int lane = threadIdx.x & 63;
-    stride = (size_t)2 * p.n_heads * 16 * D;
-    base = p.kv + (size_t)layer * p.n_blocks * stride + (size_t)head * 16 * D + (size_t)(lane & 15) * D +
-           (lane >> 4) * 8;
-  }
-  __device__ __forceinline__ void load(int id, half8 (&k)[D / 32]) const {
-    const _Float16* kp = base + (size_t)clamp_block(id, n_blocks) * stride;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) k[ks] = load_half8(kp + ks * 32);
-  }
-  __device__ __forceinline__ void load_last_use(int id, half8 (&k)[D / 32]) const {
-    const _Float16* kp = base + (size_t)clamp_block(id, n_blocks) * stride;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
-  }
-};
-
 // Pass 1 over blocks [b0, b1): every lane's online (max, sum) of its query rows'
 // logits -> sh.m, sh.z.  ids: the block ids, indexed from block 0.
 template <int D, int NT, int WV>
@@ -154,7 +211,7 @@ __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc&
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D> keys(p, lh);
+  const KeyBlocks<D, WV, false> keys(p, lh, sh.tiles);
   const float c = p.scale_log2e;
   const int n_unmasked = (L - W) >> 4;  // blocks that lie wholly before the window
   float m[NT], z[NT];
@@ -166,9 +223,9 @@ __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc&
   {
     half8 kc[KS], kn[KS];
     int b = b0 + wave;
-    if (b < b1) keys.load(ids[b], kc);
+    if (b < b1) keys.template load<false>(ids[b], kc);
     for (; b < b1; b += WV) {
-      if (b + WV < b1) keys.load(ids[b + WV], kn);
+      if (b + WV < b1) keys.template load<false>(ids[b + WV], kn);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -235,14 +292,14 @@ __device__ __forceinline__ void merged_row(const ScoreShared<WV>& sh, int row, f
 // fin: log2 of every row's denominator.
 template <int D, int NT, int WV, typename Store>
 __device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDesc& rd, int lh,
-                                               const int32_t* ids, int b0, int b1, const float* fin,
+                                               const int32_t* ids, int b0, int b1, const float* fin, KeyTiles<WV>& tiles,
                                                const half8 (&qreg)[NT][D / 32], Store store) {
   constexpr int KS = D / 32;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D> keys(p, lh);
+  const KeyBlocks<D, WV, true> keys(p, lh, tiles);
   const float c = p.scale_log2e;
   const int n_prefix = rd.seq_len - rd.window;
   float mrow[NT][4];
@@ -254,9 +311,10 @@ __device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDe
   // last are the ones most likely to be still in a cache
   half8 kc[KS], kn[KS];
   int b = b1 - 1 - wave;
-  if (b >= b0) keys.load_last_use(ids[b], kc);
+  if (b >= b0) keys.template load<true>(ids[b], kc);
   for (; b >= b0; b -= WV) {
-    if (b - WV >= b0) keys.load_last_use(ids[b - WV], kn);
+    if (b - WV >= b0) keys.template load<true>(ids[b - WV], kn);
+    keys.arrange(kc);
     float colsum = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -312,7 +370,7 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
       p.lse_out[lse_offset<D>(rd, lh) + threadIdx.x] = sh.fin[threadIdx.x] * 0.69314718055994530942f;
     return;
   }
-  snapkv_columns<D, NT, WV>(p, rd, lh, old_ids, 0, (L - W + 15) >> 4, sh.fin, qreg, store);
+  snapkv_columns<D, NT, WV>(p, rd, lh, old_ids, 0, (L - W + 15) >> 4, sh.fin, sh.tiles, qreg, store);
 }
 
 template <int D, int NT, int WV, typename Store>
@@ -978,12 +1036,18 @@ struct BoundEpoch {  // the factors rho_i of one epoch over the window rows
   float p_dn[kBoundCentres];
 };
 
-template <int WV>
+// rows that hold anything, rounded up to what one lane each at a renewal covers
+template <int NT>
+static constexpr int kBoundRows = NT == 1 ? 16 : NT == 2 ? 32 : 64;
+template <int WV, int ROWS>
 struct BoundShared {
-  float fin[64];                   // log2 of every row's soft-max denominator
-  float pub[2][WV][64];        // the wavefronts' row sums at a renewal, absolute log2
-  float ref[bound_max_epochs<WV>()][64];  // the reference of every epoch
-  BoundEpoch stat[bound_max_epochs<WV>()];
+  float fin[64];                            // log2 of every row's soft-max denominator
+  float pub[2][WV][ROWS];                   // the wavefronts' row sums at a renewal, absolute log2
+  float ref[bound_max_epochs<WV>()][ROWS];  // the reference of every epoch
+  union {
+    KeyTiles<WV> tiles;                       // during the pass
+    BoundEpoch stat[bound_max_epochs<WV>()];  // after it
+  };
 };
 
 struct BoundKeep {  // what survives into the selection's LDS
@@ -1018,34 +1082,24 @@ __device__ __forceinline__ float lower_of(uint32_t w) { return __uint_as_float(w
 // First pass with bounds.  On return stage[j] holds the packed bounds of the
 // column sum of every prefix token j and bs.fin the rows' log-sum-exps.  All
 // threads of the workgroup call; ends with a barrier.
-template <int D, int NT, int WV>
+template <int D, int NT, int WV, int ROWS>
 __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              const int32_t* old_ids, BoundShared<WV>& bs,
+                                              const int32_t* old_ids, BoundShared<WV, ROWS>& bs,
                                               BoundKeep& keep, float* stage,
                                               half8 (&qreg)[NT][D / 32]) {
   constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
   const int L = rd.seq_len;
   const int W = rd.window;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
-                          (size_t)head * 16 * D + (size_t)c16 * D + q4 * 8;
+  const KeyBlocks<D, WV, false> keys(p, lh, bs.tiles);
   const float c = p.scale_log2e;
   const int nb = (L + 15) >> 4;
   const int n_prefix = L - W;
   const int n_unmasked = n_prefix >> 4;
-  auto load_block = [&](int b, half8 (&k)[KS]) {
-    // (the block is the wavefront's: scalar address arithmetic)
-    const int blk = __builtin_amdgcn_readfirstlane(old_ids[b]);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8(kp + ks * 32);
-  };
+  auto load_block = [&](int b, half8 (&k)[KS]) { keys.template load<false>(old_ids[b], k); };
 
   // Lane (q4, c16) holds the logits of token c16 of a block for the rows
   // 16 nt + 4 q4 + r: sums over the rows are in-lane adds, and row sums stay in
@@ -1201,9 +1255,12 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   __syncthreads();
   if (threadIdx.x < 64) {
     const int row = threadIdx.x;
-    const float lse = merged(buf, row);
-    bs.fin[row] = row < W ? lse : INFINITY;  // padded rows contribute exp2(-inf) = 0
-    if (row < W && !(fabsf(lse) < 3.0e38f)) keep.bad = 1;
+    float lse = INFINITY;  // padded rows contribute exp2(-inf) = 0
+    if (row < W) {
+      lse = merged(buf, row);
+      if (!(fabsf(lse) < 3.0e38f)) keep.bad = 1;
+    }
+    bs.fin[row] = lse;
   }
   __syncthreads();
   // the factors of every epoch, rho_i = 2^(ref_i - lse_i) over the window rows
@@ -1211,7 +1268,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   // deviation to either side of it the one-sided deviations
   for (int e = 1 + wave; e <= epoch; e += WV) {
     const bool ok = lane < W;
-    const float rho = ok ? __builtin_amdgcn_exp2f(bs.ref[e][lane] - bs.fin[lane]) : 0.f;
+    const float rho = ok ? __builtin_amdgcn_exp2f(bs.ref[e][lane % ROWS] - bs.fin[lane]) : 0.f;
     // (non-negative: their bits compare like the values; what is not a number makes
     // the head fall back, whatever comes out here)
     const float lo = __uint_as_float(wave_min(ok ? __float_as_uint(rho) : 0x7F800000u));
@@ -1274,21 +1331,21 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
 
 // Exact column sums of the tokens named by need[] (one bit per prefix token),
 // row by row -> stage[].  mrow: the rows' log-sum-exps as the second product
-// leaves the rows in registers.
+// leaves the rows in registers.  Rows of 256 bytes are fetched in whole lines unless
+// the registers of one query tile are short of it (8192 heads of 700 tokens: 606 -> 593
+// us with two tiles, 697 -> 681 with four, 576 -> 614 with one); rows of 128 bytes, one
+// line anyhow, are not (2048 heads of 6500 tokens, four tiles: 969 straight, 995 us).
 template <int D, int NT, int WV>
 __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDesc& rd, int lh,
                                                const int32_t* old_ids, const uint32_t* need,
-                                               float* stage, half8 (&qreg)[NT][D / 32],
+                                               float* stage, KeyTiles<WV>& tiles, half8 (&qreg)[NT][D / 32],
                                                const float (&mrow)[NT][4]) {
   constexpr int KS = D / 32;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
-  const _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * 16 * D + q4 * 8;
+  const KeyBlocks<D, WV, (D == 128 && NT > 1)> keys(p, lh, tiles);
   const float c = p.scale_log2e;
   const int n_prefix = rd.seq_len - rd.window;
   const int n_words = (n_prefix + 31) >> 5;
@@ -1317,11 +1374,7 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
   };
   auto load_rows = [&](int tok, half8 (&k)[KS]) {
     // (a lane without a token reads the head's first row and drops the result)
-    const int tk = max(tok, 0);
-    const int blk = clamp_block(old_ids[tk >> 4], p.n_blocks);
-    const _Float16* kp = base + (size_t)blk * blk_stride + (size_t)(tk & 15) * D;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = load_half8_nt(kp + ks * 32);
+    keys.load_rows(max(tok, 0), old_ids, k);
   };
   half8 kc[KS], kn[KS], kf[KS];
   int tok_c = -1, tok_n = -1, tok_f = -1;
@@ -1332,6 +1385,7 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
   while (have) {
     const bool have_f = have_n && next_tile(tok_f);
     if (have_f) load_rows(tok_f, kf);
+    keys.arrange(kc);
     float colsum = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -1719,7 +1773,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
   __shared__ union {
     ScoreShared<WV> score;
     SelectShared<WV> select;
-    BoundShared<WV> bound;
+    BoundShared<WV, kBoundRows<NT>> bound;
   } sh;
   __shared__ BoundKeep keep;
   const int n_lh = p.n_layers * p.n_heads;
@@ -1760,7 +1814,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
             for (int r = 0; r < 4; ++r) mrow[t][r] = sh.bound.fin[t * 16 + q4 * 4 + r];
           __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
           bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
-          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, qreg, mrow);
+          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, sh.bound.tiles, qreg, mrow);
         }
       });
     } else {
@@ -1821,7 +1875,7 @@ template <int D, int NT>
 static hipError_t wide_setup_one() {
   constexpr int WV = kWide<D, NT>;
   constexpr int most = fused_lds(kFusedWideMaxLen, kFusedWideMaxLen / 16, true).words * 4;
-  static_assert(most + (int)sizeof(BoundShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
+  static_assert(most + (int)sizeof(BoundShared<WV, kBoundRows<NT>>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(SelectShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(ScoreShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_unit_kernel<D, NT, WV>),

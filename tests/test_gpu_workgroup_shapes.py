@@ -76,3 +76,10 @@ def test_every_method_in_one_batch(fillers):
 def test_log_sum_exp_handed_in(fillers):
     lens = [2500, 9000, 700]
     _run(lens, [500, 1800, 300], [SNAP] * 3, 32, 128, True, fillers, lse="library")
+
+
+@pytest.mark.parametrize("W,d", SHAPES)
+def test_single_pass_of_narrow_workgroups(W, d):
+    # prefixes that end anywhere in a block, in a wavefront's first and later ones; the keys come in whole lines
+    lens = [W, W + 1, W + 15, W + 16, W + 17, W + 64, 500, 1037, 2050]
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, True, NARROW, shape="narrow", lse="library")
