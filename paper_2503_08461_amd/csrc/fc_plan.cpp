@@ -68,6 +68,15 @@ bool wide_pays(const CompressPlan& plan, size_t units, int n_cu) {
   return false;
 }
 
+// From what mean length of its SnapKV heads (each weighted by its own) on a launch of
+// narrow workgroups leaves only half of the keys to the caches in its first pass.  All
+// kernels of a pruned call, window 16 to 64, 128 channels, all / half:
+//   8192 heads of  700 tokens  580-681 / 607-692 us     4096 heads of 3000  1237-1324 / 1209-1274
+//   8192          1500         1259-1304 / 1300-1364    2048          4000  799-875 / 768-849
+//   6144          2400         1420-1441 / 1396-1452    2048          6500  1338-1382 / 1279-1338
+//   4096          2000         827-886 / 808-871         768          2500  210-228 / 194-216
+constexpr int kHalfReuseLen = 2304;
+
 int blocks_for(int tokens) { return (tokens + kPlanBlockSize - 1) / kPlanBlockSize; }
 
 template <typename Plan>
@@ -255,6 +264,7 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
     if (l->units.empty()) continue;
     std::stable_sort(l->units.begin(), l->units.end(),
                      [&](int x, int y) { return plan.weights[x] > plan.weights[y]; });
+    int64_t tokens = 0, weighted = 0;
     for (int i : l->units) {
       const ReqDesc& d = plan.descs[i];
       if (d.method != PLAN_METHOD_STREAMING) l->max_len = std::max(l->max_len, d.seq_len);
@@ -262,7 +272,10 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
       if (d.method != PLAN_METHOD_SNAPKV) continue;
       const int tiles = (d.window + 15) / 16;
       l->query_tiles = l->query_tiles == 0 || l->query_tiles == tiles ? tiles : kMixedQueryTiles;
+      tokens += d.seq_len;
+      weighted += (int64_t)d.seq_len * d.seq_len;
     }
+    l->half_reuse = !l->wide && tokens > 0 && weighted >= kHalfReuseLen * tokens;
     launches.push_back(std::move(*l));
   }
   return launches;

@@ -87,6 +87,7 @@ struct FusedLaunch {
   bool wide = false;           // wide workgroups, one per CU
   int max_len = 0;             // longest head that is scored
   int max_blocks = 0;          // most blocks of a unit
+  bool half_reuse = false;     // long heads: a pruned first pass leaves only half of the keys to the caches
 };
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu);
 

@@ -1079,10 +1079,20 @@ __device__ __forceinline__ float upper_of(uint32_t w) { return __uint_as_float(w
 __device__ __forceinline__ float lower_of(uint32_t w) { return __uint_as_float(w << 16); }
 
 
+// kHalf (128 channels, narrow workgroups): every other block of a wavefront is read in
+// whole lines with the hint that it is not wanted again.  Of long heads in a full chip
+// little of what this pass reads is still in the memory-side cache when rows are read
+// again; that half leaves the cache to the other one, and streams faster.  Where heads
+// are short enough to be found there whole it costs (plan_fused_launches has the line).
+// (A wavefront's branch on the block's number instead, to keep the end of a head, gains
+// no more and costs 2 % where nothing is gained.)
+template <int D, int WV>
+static constexpr bool kHasHalfReuse = D == 128 && WV == kNarrow;
+
 // First pass with bounds.  On return stage[j] holds the packed bounds of the
 // column sum of every prefix token j and bs.fin the rows' log-sum-exps.  All
 // threads of the workgroup call; ends with a barrier.
-template <int D, int NT, int WV, int ROWS>
+template <int D, int NT, int WV, bool kHalf, int ROWS>
 __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDesc& rd, int lh,
                                               const int32_t* old_ids, BoundShared<WV, ROWS>& bs,
                                               BoundKeep& keep, float* stage,
@@ -1094,12 +1104,13 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, false> keys(p, lh, bs.tiles);
+  const KeyBlocks<D, WV, kHalf> keys(p, lh, bs.tiles);
   const float c = p.scale_log2e;
   const int nb = (L + 15) >> 4;
   const int n_prefix = L - W;
   const int n_unmasked = n_prefix >> 4;
-  auto load_block = [&](int b, half8 (&k)[KS]) { keys.template load<false>(old_ids[b], k); };
+  auto load_even = [&](int b, half8 (&k)[KS]) { keys.template load<false>(old_ids[b], k); };
+  auto load_odd = [&](int b, half8 (&k)[KS]) { keys.template load<kHalf>(old_ids[b], k); };
 
   // Lane (q4, c16) holds the logits of token c16 of a block for the rows
   // 16 nt + 4 q4 + r: sums over the rows are in-lane adds, and row sums stay in
@@ -1221,9 +1232,10 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     if (q4 == 0 && tok < n_prefix) reinterpret_cast<uint32_t*>(stage)[tok] = pack_sums(cs, ss);
   };
   // one step: kc holds this wavefront's block b, kn takes the next one
-  auto step = [&](int t, const half8 (&kc)[KS], half8 (&kn)[KS]) {
+  auto step = [&](int t, half8 (&kc)[KS], half8 (&kn)[KS], auto load_next) {
     const int b = wave + WV * t;
-    if (b + WV < nb) load_block(b + WV, kn);
+    if (b + WV < nb) load_next(b + WV, kn);
+    keys.arrange(kc);
     if (bound_renews_before(t, seg)) {  // uniform over the workgroup
       if (t == 1) my_ref = bs.pub[buf][wave][my_row];
       publish(buf);
@@ -1244,12 +1256,13 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   };
   static_assert(kBoundMinLen<WV> - 64 >= 16 * WV, "the first step lies before the window");
   half8 ka[KS], kb[KS];
-  load_block(wave, ka);
-  if (wave + WV < nb) load_block(wave + WV, kb);
+  load_even(wave, ka);
+  if (wave + WV < nb) load_odd(wave + WV, kb);
+  keys.arrange(ka);
   numerators(std::integral_constant<int, 0>{}, wave, ka);
   for (int t = 1; t < T; t += 2) {
-    step(t, kb, ka);
-    if (t + 1 < T) step(t + 1, ka, kb);
+    step(t, kb, ka, load_even);
+    if (t + 1 < T) step(t + 1, ka, kb, load_odd);
   }
   publish(buf);
   __syncthreads();
@@ -1767,7 +1780,7 @@ __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
 // snapkv_bounds); key-norm and streaming units that ride in the launch run as in
 // fused_unit_kernel.  Dynamic LDS: the scores, then one bit per token, then the
 // block ids.
-template <int D, int NT, int WV>
+template <int D, int NT, int WV, bool kHalf>
 __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_bounded_kernel(BatchParams p) {
   extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
@@ -1803,7 +1816,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
         half8 qreg[N][KS];
         load_window_queries<D, N>(p, rd, lh, qreg);
         const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
-        if (prune) snapkv_bounds<D, N, WV>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
+        if (prune) snapkv_bounds<D, N, WV, kHalf>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
         if (!prune || keep.bad) {  // bad: not representable against a running reference
           snapkv_unit_q<D, N, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
         } else {
@@ -1850,7 +1863,13 @@ static void launch_fused_one(const BatchParams& p, size_t lds, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_fused * p.n_layers * p.n_heads;
   if constexpr (NT > 0) {
     if (p.bounded) {
-      fused_bounded_kernel<D, NT, WV><<<grid, 64 * WV, lds, s>>>(p);
+      if constexpr (kHasHalfReuse<D, WV>) {
+        if (p.half_reuse) {
+          fused_bounded_kernel<D, NT, WV, true><<<grid, 64 * WV, lds, s>>>(p);
+          return;
+        }
+      }
+      fused_bounded_kernel<D, NT, WV, false><<<grid, 64 * WV, lds, s>>>(p);
       return;
     }
   }
@@ -1882,7 +1901,7 @@ static hipError_t wide_setup_one() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, most);
   if constexpr (NT > 0)
     if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_bounded_kernel<D, NT, WV>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_bounded_kernel<D, NT, WV, false>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
   return e;
 }

@@ -83,3 +83,11 @@ def test_single_pass_of_narrow_workgroups(W, d):
     # prefixes that end anywhere in a block, in a wavefront's first and later ones; the keys come in whole lines
     lens = [W, W + 1, W + 15, W + 16, W + 17, W + 64, 500, 1037, 2050]
     _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, True, NARROW, shape="narrow", lse="library")
+
+
+@pytest.mark.parametrize("W", [16, 32, 64])
+@pytest.mark.parametrize("lens", [[513, 640, 2303, 2303, 2303],      # mean (weighted) below 2304: all keys cached
+                                  [600, 2500, 2519, 2593, 2400],      # above: half of them
+                                  [2304 + 17, 527, 528, 4097 + 63]])
+def test_narrow_pruned_first_pass(W, lens):
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, 128, False, NARROW, shape="narrow")
