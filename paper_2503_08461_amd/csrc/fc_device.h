@@ -20,6 +20,30 @@ __device__ __forceinline__ int clamp_block(int blk, int n_blocks) {
   return ((unsigned)blk < (unsigned)n_blocks) ? blk : 0;
 }
 
+// Zombie reclaim of one request: pushes the pre-compression blocks (batch order, table
+// order) above the stack top left by plan_alloc and rewrites the table row.  From
+// plan_alloc on all kernels of the stage read the saved copies of the ids, nobody the
+// table or the stack, so one workgroup of a request may do this at any time after it.
+__device__ __forceinline__ void reclaim_request(const BatchParams& p, const ReqDesc& rd) {
+  const int tid = threadIdx.x, n_threads = blockDim.x;
+  int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
+  if (p.in_place) {
+    // the request keeps its first n_new blocks; the rest are released
+    for (int i = tid; i < rd.n_old - rd.n_new; i += n_threads)
+      p.stack[p.top_before + rd.new_off + i] = p.old_ids[rd.old_off + rd.n_new + i];
+    for (int i = rd.n_new + tid; i < p.max_blocks; i += n_threads) row[i] = -1;
+    if (p.owner)  // (ids checked before the stage: in range, claimed)
+      for (int i = tid; i < rd.n_old; i += n_threads) p.owner[p.old_ids[rd.old_off + i]] = i < rd.n_new ? 1 : 0;
+    return;
+  }
+  const int base = p.top_before - p.total_new;
+  for (int i = tid; i < rd.n_old; i += n_threads) {
+    p.stack[base + rd.old_off + i] = p.old_ids[rd.old_off + i];
+    if (p.owner) p.owner[p.old_ids[rd.old_off + i]] = 0;  // (checked before the stage)
+  }
+  for (int i = tid; i < p.max_blocks; i += n_threads) row[i] = (i < rd.n_new) ? p.new_ids[rd.new_off + i] : -1;
+}
+
 // LDS accesses of a wavefront's lanes before and after this point stay in that order
 // across its lanes (the hardware executes them in program order; this binds the
 // compiler, and costs no instruction)

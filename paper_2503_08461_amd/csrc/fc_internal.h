@@ -97,6 +97,7 @@ struct BatchParams {
                                // separate kernels)
   float* split_part;           // ... [unit][segment][2][64]: the segments' row (max, sum) pairs
   int32_t ids_at, ids_room;    // fused kernels: where the block ids lie in LDS (words), room for how many
+  int32_t main_reclaims;       // 1: the last kernel of the stage does what reclaim_kernel would
   int32_t bounded;             // 1: the fused kernel prunes the second pass of its SnapKV units
   int32_t half_reuse;          // ... and leaves only half of the keys that it reads first to the caches
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,

@@ -139,29 +139,7 @@ __global__ __launch_bounds__(kThreads) void plan_alloc_inline_kernel(BatchParams
   if (blockIdx.x == 0) write_meta(c, meta, n_bytes);
 }
 
-// Zombie reclaim: pushes the pre-compression blocks (batch order, table
-// order) above the stack top left by plan_alloc and rewrites the table rows.
-__global__ __launch_bounds__(kThreads) void reclaim_kernel(BatchParams p) {
-  const ReqDesc rd = p.descs[blockIdx.x];
-  int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
-  if (p.in_place) {
-    // the request keeps its first n_new blocks; the rest are released
-    for (int i = threadIdx.x; i < rd.n_old - rd.n_new; i += kThreads)
-      p.stack[p.top_before + rd.new_off + i] = p.old_ids[rd.old_off + rd.n_new + i];
-    for (int i = rd.n_new + threadIdx.x; i < p.max_blocks; i += kThreads) row[i] = -1;
-    if (p.owner)  // (ids checked before the stage: in range, claimed)
-      for (int i = threadIdx.x; i < rd.n_old; i += kThreads)
-        p.owner[p.old_ids[rd.old_off + i]] = i < rd.n_new ? 1 : 0;
-    return;
-  }
-  const int base = p.top_before - p.total_new;
-  for (int i = threadIdx.x; i < rd.n_old; i += kThreads) {
-    p.stack[base + rd.old_off + i] = p.old_ids[rd.old_off + i];
-    if (p.owner) p.owner[p.old_ids[rd.old_off + i]] = 0;  // (checked before the stage)
-  }
-  for (int i = threadIdx.x; i < p.max_blocks; i += kThreads)
-    row[i] = (i < rd.n_new) ? p.new_ids[rd.new_off + i] : -1;
-}
+__global__ __launch_bounds__(kThreads) void reclaim_kernel(BatchParams p) { reclaim_request(p, p.descs[blockIdx.x]); }
 
 // ---------------------------------------------------------------------------
 // separate kernels (FC_SCORE_TWO_PASS, fc_window_lse): scores through HBM
@@ -321,6 +299,7 @@ __global__ __launch_bounds__(64 * WV) void select_kernel(BatchParams p) {
 template <int D>
 __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const SplitUnit u = split_unit(p);
+  if (p.main_reclaims && u.lh == 0 && u.seg == 0) reclaim_request(p, u.rd);
   const int32_t* kept = p.kept + u.rd.kept_off + (size_t)u.lh * u.rd.budget;
   int nb0, nb1;
   split_range(p, u.seg, u.rd.n_new, nb0, nb1);
@@ -410,6 +389,7 @@ hipError_t launch_plan_alloc(const BatchParams& p, const MetaChunk* inline_meta,
 }
 
 hipError_t launch_reclaim(const BatchParams& p, hipStream_t s) {
+  if (p.main_reclaims) return hipSuccess;  // done by the kernel before
   reclaim_kernel<<<p.n_comp, kThreads, 0, s>>>(p);
   return hipGetLastError();
 }

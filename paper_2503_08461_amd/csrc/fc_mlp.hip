@@ -592,6 +592,9 @@ void mlp_compress_kernel(BatchParams p, MlpParams mp) {
     rd = rd_n;
     ji = ji_n;
   }
+  // (the last workgroups: they have a tile less, if any have)
+  if (p.main_reclaims)
+    for (int r = (int)gridDim.x - 1 - (int)blockIdx.x; r < p.n_comp; r += gridDim.x) reclaim_request(p, p.descs[r]);
   wait_loads<0>();  // nothing may arrive in the LDS of a workgroup that has ended
 }
 

@@ -1744,6 +1744,7 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
   // the request's block ids, read once per workgroup (every later use is an LDS read)
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
+  if (p.main_reclaims && lh == 0) reclaim_request(p, rd);
   const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
   if (ids_in_lds)
     for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV)
@@ -1798,6 +1799,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
   uint32_t* map = lds + stage_words(rd.seq_len);  // one bit per token
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
+  if (p.main_reclaims && lh == 0) reclaim_request(p, rd);
   const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
   if (ids_in_lds)
     for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV)

@@ -113,6 +113,24 @@ def test_shapes_and_factors(d, hidden, k, activation):
              n_layers=2, n_heads=3, seed=5, activation=activation)
 
 
+@pytest.mark.parametrize("d,hidden,k", [(128, 256, 1), (128, 256, 2), (64, 256, 1), (64, 128, 2), (128, 128, 1)])
+def test_workgroups_with_several_tiles(d, hidden, k):
+    """More tiles than workgroups (three to a CU at 64 channels and 128 hidden units), the
+    modality changing under way, segments that end inside a chunk and a tile."""
+    n = 68 if (d, hidden) == (64, 128) else 45
+    run_case([n * k, (n - 12) * k + 1, (n - 4) * k - 1, 16], [5, 0, 23 * k, 7],
+             [(n - 9) * k, (n - 12) * k + 1, 35 * k, 7], [1, 1, 1, 1],
+             d=d, k=k, hidden=hidden, n_layers=8, n_heads=40, seed=13)
+
+
+@pytest.mark.parametrize("n_req", [20, 40])
+def test_many_short_requests(n_req):
+    """The pool's blocks taken back by the kernel itself (few requests) and by a launch of its own."""
+    lens = [1 + (13 * i) % 40 for i in range(n_req)]
+    run_case(lens, [n // 3 for n in lens], [n - n // 4 for n in lens], [i % 5 != 3 for i in range(n_req)],
+             d=64, k=3, hidden=128, n_layers=1, n_heads=1, seed=17)
+
+
 def test_large_pre_activations_both_signs():
     """Rows scaled so that the pre-activations reach far into both tails of the
     activation (|v| up to about 12), where the erf form is v * (a tiny number)
