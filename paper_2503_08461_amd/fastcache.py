@@ -36,6 +36,7 @@ EXPORTS = [
 ]
 
 _lib = None
+_raw_stream = None  # (device index) -> the current stream's handle, without the stream object
 
 
 class MlpWeights(ctypes.Structure):
@@ -63,19 +64,21 @@ def _hip_runtimes_loaded():
 def load_library():
     """Loads libfastcache.so once.  torch is imported first so that the HIP
     runtime torch ships is the one the library binds to (same soname)."""
-    global _lib
+    global _lib, _raw_stream
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise FileNotFoundError(
             "%s is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`"
             % LIB_PATH)
-    import torch  # noqa: F401  (loads libamdhip64 before the library asks for it)
+    import torch  # (loads libamdhip64 before the library asks for it)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     lib = ctypes.CDLL(LIB_PATH)
     runtimes = _hip_runtimes_loaded()
     if len(runtimes) > 1:
         raise RuntimeError("two HIP runtimes in one process: %s" % runtimes)
-    vp, i32p, i = ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32), ctypes.c_int
+    # (host arrays go as addresses: a pointer object costs ten times as much to make)
+    vp, i32p, i = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int
     lib.fc_pool_create.argtypes = [ctypes.POINTER(vp), vp, ctypes.c_size_t, i, i, i, i, i, i]
     lib.fc_pool_destroy.argtypes = [vp]
     lib.fc_pool_alloc.argtypes = [vp, i, vp, vp]
@@ -131,6 +134,9 @@ def _check(rc):
     return rc
 
 
+# Addresses, as plain ints (None: NULL).  A call on a small batch takes the library 5 to
+# 8 us; with pointer objects, stream objects and array sums around it the marshalling took
+# 13 (one prompt of 256 tokens).
 def _dev_ptr(t, dtype=None):
     if t is None:
         return None
@@ -138,20 +144,36 @@ def _dev_ptr(t, dtype=None):
         raise ValueError("expected a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError("expected dtype %s, got %s" % (dtype, t.dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    import torch
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+_INT32 = np.dtype(np.int32)
+_first_byte = ctypes.c_char.from_buffer
 
 
 def _host_i32(a):
-    if not (isinstance(a, np.ndarray) and a.dtype == np.int32 and a.flags.c_contiguous):
+    if not (isinstance(a, np.ndarray) and a.dtype == _INT32 and a.flags.c_contiguous):
         raise ValueError("expected a contiguous int32 numpy array")
-    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+    try:
+        return ctypes.addressof(_first_byte(a))
+    except (TypeError, ValueError):  # read-only, empty
+        return a.ctypes.data
+
+
+def _entries(per_request, method):
+    """Sum of per_request over the requests that are compressed."""
+    if method.shape[0] > 16 or method.ndim != 1 or per_request.ndim != 1:
+        return int(per_request[method != FC_METHOD_NONE].astype(np.int64).sum())
+    return sum([n for n, m in zip(per_request.tolist(), method.tolist()) if m != FC_METHOD_NONE])
 
 
 class PoolHandle:
@@ -259,15 +281,12 @@ def fc_compress_batch(pool, block_tables, seq_lens, q_window, window, method, bu
         want = (n_req, pool.n_layers, pool.n_heads, window, pool.head_dim)
         if tuple(q_window.shape) != want:
             raise ValueError("q_window must have shape %s" % (want,))
-    comp = method != FC_METHOD_NONE
-    if scores_out is not None:
-        need = int((seq_lens[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if scores_out.numel() < need:
-            raise ValueError("scores_out too small")
-    if kept_out is not None:
-        need = int((budget[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if kept_out.numel() < need:
-            raise ValueError("kept_out too small")
+    if scores_out is not None and \
+            scores_out.numel() < _entries(seq_lens, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("scores_out too small")
+    if kept_out is not None and \
+            kept_out.numel() < _entries(budget, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("kept_out too small")
     _check(getattr(lib, _entry)(
         pool.ptr, _dev_ptr(block_tables, torch.int32), int(block_tables.shape[1]),
         _host_i32(seq_lens), _dev_ptr(q_window, torch.float16), int(window),
@@ -295,15 +314,12 @@ def fc_compress_batch_lse(pool, block_tables, seq_lens, q_window, lse_window, wi
     if lse_window is not None and tuple(lse_window.shape) != (n_req, pool.n_layers, pool.n_heads,
                                                               window):
         raise ValueError("lse_window must be [n_req][n_layers][n_heads][window]")
-    comp = method != FC_METHOD_NONE
-    if scores_out is not None:
-        need = int((seq_lens[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if scores_out.numel() < need:
-            raise ValueError("scores_out too small")
-    if kept_out is not None:
-        need = int((budget[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if kept_out.numel() < need:
-            raise ValueError("kept_out too small")
+    if scores_out is not None and \
+            scores_out.numel() < _entries(seq_lens, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("scores_out too small")
+    if kept_out is not None and \
+            kept_out.numel() < _entries(budget, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("kept_out too small")
     _check(lib.fc_compress_batch_lse(
         pool.ptr, _dev_ptr(block_tables, torch.int32), int(block_tables.shape[1]),
         _host_i32(seq_lens), _dev_ptr(q_window, torch.float16),
@@ -353,15 +369,12 @@ def fc_compress_batch_var(pool, block_tables, seq_lens, q_window, window, method
         pool.n_heads * pool.head_dim
     if need_q > 0 and (q_window is None or q_window.numel() < need_q):
         raise ValueError("q_window holds fewer than %d elements" % need_q)
-    comp = method != FC_METHOD_NONE
-    if scores_out is not None:
-        need = int((seq_lens[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if scores_out.numel() < need:
-            raise ValueError("scores_out too small")
-    if kept_out is not None:
-        need = int((budget[comp].astype(np.int64)).sum()) * pool.n_layers * pool.n_heads
-        if kept_out.numel() < need:
-            raise ValueError("kept_out too small")
+    if scores_out is not None and \
+            scores_out.numel() < _entries(seq_lens, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("scores_out too small")
+    if kept_out is not None and \
+            kept_out.numel() < _entries(budget, method) * pool.n_layers * pool.n_heads:
+        raise ValueError("kept_out too small")
     _check(lib.fc_compress_batch_var(
         pool.ptr, _dev_ptr(block_tables, torch.int32), int(block_tables.shape[1]),
         _host_i32(seq_lens), _dev_ptr(q_window, torch.float16), _host_i32(window),
@@ -449,10 +462,10 @@ def fc_mlp_set_weights(pool, k, w1, b1, w2, b2, activation=FC_ACT_GELU_ERF, stre
     w = MlpWeights()
     w.k, w.hidden, w.activation = int(k), hidden, int(activation)
     for m in range(2):
-        w.w1[m] = _dev_ptr(w1[m], torch.float16).value
-        w.b1[m] = _dev_ptr(b1[m], torch.float32).value
-        w.w2[m] = _dev_ptr(w2[m], torch.float16).value
-        w.b2[m] = _dev_ptr(b2[m], torch.float32).value
+        w.w1[m] = _dev_ptr(w1[m], torch.float16)
+        w.b1[m] = _dev_ptr(b1[m], torch.float32)
+        w.w2[m] = _dev_ptr(w2[m], torch.float16)
+        w.b2[m] = _dev_ptr(b2[m], torch.float32)
     _check(lib.fc_mlp_set_weights(pool.ptr, ctypes.byref(w), _stream_ptr(stream)))
 
 
