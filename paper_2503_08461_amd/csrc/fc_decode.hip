@@ -86,9 +86,15 @@ hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, h
 // What bounds it is HBM where the call has many heads to offer.  With few of them
 // the chip waits for the CU that has the longest one (one CU draws about 27 GB/s
 // whatever its wavefronts request), so such a call cuts every head into segments of
-// p.seg_blocks blocks: each leaves its state in p.partial, and a second launch merges
-// them.  (Merged by the workgroup that finishes a head last, the release and acquire
-// fences of all segments cost 170 to 300 us, against the 5 us of a launch.)
+// about p.seg_blocks blocks, all of one head alike: each leaves its state in p.partial, and
+// a second launch merges them.  A wavefront has only about four blocks of a segment, so
+// there its loads' latency shows: it asks for the next block before it works on this one
+// (kCut).  8 caches of 256-1408 tokens, 32 heads: 27.2 us with segments of exactly
+// p.seg_blocks and one block in flight, 25.8 with even segments, 25.0 with both; 4 of
+// 2000: 26.9, 26.0, 25.7.  Whole heads keep one block in flight and more wavefronts (59
+// registers against 92): 957 us against 964 (48 caches of 1280-7040 tokens, 2 layers).
+// (Merged by the workgroup that finishes a head last, the release and acquire fences of
+// all segments cost 170 to 300 us, against the 5 us of a launch.)
 // ---------------------------------------------------------------------------
 //
 // kIndexed: the counterfactual of a cache that was pruned WITHOUT compaction:
@@ -105,28 +111,32 @@ __device__ __forceinline__ float row_lanes_sum(float s) {
   return s;
 }
 
-// segments of a head of L tokens
+// segments of a head of L tokens: as many of seg_blocks as come nearest to its blocks
+// (at most n_seg, which is that of the longest head rounded up), 1 for a short or empty one
 __device__ __forceinline__ int decode_segments(int L, int seg_blocks) {
-  return (((L + 15) >> 4) + seg_blocks - 1) / seg_blocks;
+  return max((((L + 15) >> 4) + seg_blocks / 2) / seg_blocks, 1);
 }
 
-template <int D, bool kIndexed, typename Reqs>
+template <int D, bool kIndexed, bool kCut, typename Reqs>
 __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, Reqs reqs) {
   constexpr int LPR = D / 8;        // lanes per row
   constexpr int RPI = 64 / LPR;     // rows per wavefront load instruction
   constexpr int IPB = 16 / RPI;     // load instructions per 16-token block
   constexpr int NG = kWaves * RPI;  // softmax states per workgroup
   const int n_lh = p.n_layers * p.n_heads;
-  // (request, segment, layer and head)
-  const int per_req = n_lh * p.n_seg;
-  const int slot = blockIdx.x / per_req;
-  const int seg = (blockIdx.x - slot * per_req) / n_lh;
-  const int lh = blockIdx.x - slot * per_req - seg * n_lh;
+  // (segment, request, layer and head): the workgroups of segments that a shorter request
+  // does not have come last (16 caches of 1000-3000 tokens, 4 layers of 12 heads: 131.6 us
+  // with them between the others, 128.0 so)
+  const int unit = kCut ? blockIdx.x % (p.n_req * n_lh) : blockIdx.x;
+  const int seg = kCut ? blockIdx.x / (p.n_req * n_lh) : 0;
+  const int slot = unit / n_lh;
+  const int lh = unit - slot * n_lh;
   const DecodeReq rq = reqs.req[slot];
   const int L = kIndexed ? rq.pop_index : rq.seq_len;  // indexed: pop_index holds the budget
   const int nb = (L + 15) >> 4;
-  const int b0 = seg * p.seg_blocks, b1 = min(nb, b0 + p.seg_blocks);
-  if (seg > 0 && b0 >= nb) return;  // uniform: this request has fewer segments
+  const int n_seg = kCut ? decode_segments(L, p.seg_blocks) : 1;
+  if (seg >= n_seg) return;  // uniform: this request has fewer segments
+  const int b0 = kCut ? nb * seg / n_seg : 0, b1 = kCut ? nb * (seg + 1) / n_seg : nb;
   const int layer = lh / p.n_heads;
   const int head = lh - layer * p.n_heads;
   const int32_t* kept =
@@ -151,8 +161,10 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
                          (kIndexed ? 0 : (size_t)grp * D) + piece * 8;
 
   float m = -INFINITY, z = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int b = b0 + wave; b < b1; b += kWaves) {
+  struct Rows {
     half8 k[IPB], v[IPB];
+  };
+  auto fetch = [&](int b, Rows& x) {
     if (kIndexed) {
       // 16 kept tokens at a time, each fetched from its own block and slot
 #pragma unroll
@@ -161,22 +173,24 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
         const int tok = min(max(kept[min(j, L - 1)], 0), rq.seq_len - 1);
         const _Float16* kp = base + (size_t)clamp_block(row[tok >> 4], p.n_blocks) * blk_stride +
                              (size_t)(tok & 15) * D;
-        k[i] = load_half8_nt(kp);
-        v[i] = load_half8_nt(kp + v_off);
+        x.k[i] = load_half8_nt(kp);
+        x.v[i] = load_half8_nt(kp + v_off);
       }
     } else {
       const _Float16* kp = base + (size_t)clamp_block(row[b], p.n_blocks) * blk_stride;
 #pragma unroll
       for (int i = 0; i < IPB; ++i) {
-        k[i] = load_half8_nt(kp + (size_t)i * RPI * D);
-        v[i] = load_half8_nt(kp + v_off + (size_t)i * RPI * D);
+        x.k[i] = load_half8_nt(kp + (size_t)i * RPI * D);
+        x.v[i] = load_half8_nt(kp + v_off + (size_t)i * RPI * D);
       }
     }
+  };
+  auto attend = [&](int b, const Rows& x) {
 #pragma unroll
     for (int i = 0; i < IPB; ++i) {
       float s = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s += qf[e] * (float)k[i][e];
+      for (int e = 0; e < 8; ++e) s += qf[e] * (float)x.k[i][e];
       s = row_lanes_sum<LPR>(s);
       const int tok = b * 16 + i * RPI + grp;
       if (tok < L) {  // the whole lane group takes the same branch
@@ -185,9 +199,29 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
         const float w = __builtin_amdgcn_exp2f(s - mn);
         z = z * a + w;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * a + w * (float)v[i][e];
+        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * a + w * (float)x.v[i][e];
         m = mn;
       }
+    }
+  };
+  if constexpr (kCut) {
+    Rows x, y;
+    int b = b0 + wave;
+    if (b < b1) fetch(b, x);
+    while (b < b1) {
+      const int b2 = b + kWaves;
+      if (b2 < b1) fetch(b2, y);
+      attend(b, x);
+      if (b2 >= b1) break;
+      b = b2 + kWaves;
+      if (b < b1) fetch(b, x);
+      attend(b2, y);
+    }
+  } else {
+    for (int b = wave; b < nb; b += kWaves) {
+      Rows x;
+      fetch(b, x);
+      attend(b, x);
     }
   }
 
@@ -212,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
       o += sm_acc[i][threadIdx.x] * f;
     }
   }
-  if (decode_segments(L, p.seg_blocks) <= 1) {  // uniform
+  if (n_seg == 1) {  // uniform
     if (threadIdx.x < D) out[threadIdx.x] = L > 0 ? o / zz : 0.f;
     return;
   }
@@ -264,8 +298,12 @@ static void launch_decode_one(const DecodeParams& p, const DecodeReqs& inline_re
   const unsigned heads = (unsigned)p.n_req * p.n_layers * p.n_heads;
   with_reqs(p, inline_reqs, [&](const auto& reqs) {
     using Reqs = std::decay_t<decltype(reqs)>;
-    decode_attention_kernel<D, kIndexed, Reqs><<<heads * p.n_seg, kThreads, 0, s>>>(p, reqs);
-    if (p.n_seg > 1) decode_merge_kernel<D, kIndexed, Reqs><<<heads, D, 0, s>>>(p, reqs);
+    if (p.n_seg == 1) {
+      decode_attention_kernel<D, kIndexed, false, Reqs><<<heads, kThreads, 0, s>>>(p, reqs);
+      return;
+    }
+    decode_attention_kernel<D, kIndexed, true, Reqs><<<heads * p.n_seg, kThreads, 0, s>>>(p, reqs);
+    decode_merge_kernel<D, kIndexed, Reqs><<<heads, D, 0, s>>>(p, reqs);
   });
 }
 

@@ -468,9 +468,10 @@ int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const
 // Heads are cut when whole ones would leave the CUs unevenly loaded: into segments of
 // an eighth of a CU's share, at least 16 blocks (four for each wavefront), if that is
 // at most half of the longest head.  Measured at 1 layer of 32 heads: 8 caches of
-// 256-1408 tokens 47.9 us whole, 35.7 in segments of 16 blocks, 37.9 of 8; 16 caches
-// of 130-16384 tokens 490 whole, 426 / 383 / 369 with a quarter / an eighth / a
-// sixteenth of the share; but 48 caches of 1280-7040 tokens, 2 layers, 985 / 986 / 993.
+// 256-1408 tokens 24.4 us in segments of 16 blocks, 23.7 of 8 (before: 47.9 whole, 35.7
+// and 37.9 with the append), but 1 cache of 4000 tokens 15.4 and 16.9, 1 of 16000 with 8
+// heads 16.2 and 21.3; 16 caches of 130-16384 tokens 490 whole, 426 / 383 / 369 with a
+// quarter / an eighth / a sixteenth of the share; but 48 caches of 1280-7040 tokens, 2 layers, 985 / 986 / 993.
 void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan, int max_segments) {
   if (plan->reqs.empty()) return;
   auto blocks = [&](const DecodeReq& q) { return blocks_for(over_kept ? q.pop_index : q.seq_len); };
@@ -484,7 +485,7 @@ void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, Decode
   const int64_t room = max_segments / units;  // segments per head
   if (room < 2) return;
   const int64_t eighth = total / (8 * (int64_t)std::max(n_cu, 1));
-  const int64_t seg = std::max<int64_t>({(eighth + 3) / 4 * 4, 16, (longest + room - 1) / room});
+  const int64_t seg = std::max<int64_t>({eighth, 16, (longest + room - 1) / room});
   if (2 * seg > longest) return;
   plan->seg_blocks = (int)seg;
   plan->n_seg = (int)((longest + seg - 1) / seg);

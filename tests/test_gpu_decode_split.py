@@ -51,3 +51,22 @@ def test_nan_key_reaches_the_output(at):
         assert torch.isnan(got[1]).all() and not torch.isnan(got[0]).any()
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("blocks", [23, 24, 32, 39, 40, 41, 56, 57])
+def test_even_segments(blocks, d):
+    """Both sides of the block counts at which a head gets one segment more, next to a head
+    of twice 16 blocks that makes the call cut: one to four segments of 16 to 23 blocks,
+    whose wavefronts have an even or an odd number of blocks, down to one."""
+    import torch
+    from paper_2503_08461_amd import fastcache as fc
+    lens = [blocks * 16 - 7, 512, 16 * blocks, 3]
+    s, wl = _setup(lens, d=d, n_heads=2, n_layers=1)
+    try:
+        q = np.random.default_rng(blocks).standard_normal((len(lens), 1, 2, d)).astype(np.float16)
+        got = fc.fc_decode_attention(s.pool, s.bt_dev, s.lens_g, torch.from_numpy(q).to(s.dev)).cpu().numpy()
+        want = do.decode_attention(s.kv_host, s.bt_host, s.lens_o, q)
+        assert (np.abs(got - want) <= RTOL * np.abs(want) + ATOL).all()
+    finally:
+        s.close()
