@@ -100,7 +100,8 @@ struct KeyTiles {
 template <int D, int WV, bool kWanted>
 struct KeyBlocks {
   static constexpr bool kLines = kWanted && WV == kNarrow;
-  const _Float16* base;
+  const _Float16* base;      // this lane's channels of token 0 of block 0
+  const _Float16* row_base;  // of the first token it loads of a block
   size_t stride;
   int n_blocks;
   half8* put;         // where this lane's piece of rows 0 .. 7 goes (a piece of row r lies at its index ^ (r & 7))
@@ -112,6 +113,7 @@ struct KeyBlocks {
     const int row = lane >> 3, c16 = lane & 15, q4 = lane >> 4;
     stride = (size_t)2 * p.n_heads * 16 * D;
     base = p.kv + (size_t)layer * p.n_blocks * stride + (size_t)head * 16 * D + (kLines ? (lane & 7) * 8 : q4 * 8);
+    row_base = base + (kLines ? row : c16) * D;
     if constexpr (kLines) {
       half8* const mine = tiles.piece + (threadIdx.x >> 6) * kTilePieces;
       put = mine + row * 8 + ((lane & 7) ^ row);
@@ -119,9 +121,7 @@ struct KeyBlocks {
       got1 = mine + c16 * 8 + ((4 + q4) ^ (c16 & 7));
     }
   }
-  __device__ __forceinline__ const _Float16* block(int id) const {
-    return base + (size_t)clamp_block(id, n_blocks) * stride;
-  }
+  __device__ __forceinline__ size_t block(int id) const { return (size_t)clamp_block(id, n_blocks) * stride; }
   template <bool kNonTemporal>
   static __device__ __forceinline__ half8 piece(const _Float16* at) {
     return kNonTemporal ? load_half8_nt(at) : load_half8(at);
@@ -129,8 +129,7 @@ struct KeyBlocks {
   template <bool kNonTemporal>
   __device__ __forceinline__ void load(int id, half8 (&k)[D / 32]) const {
     // (the block is the wavefront's: scalar address arithmetic)
-    const _Float16* kp = block(__builtin_amdgcn_readfirstlane(id));
-    kp += (kLines ? (threadIdx.x & 63) >> 3 : threadIdx.x & 15) * D;
+    const _Float16* kp = row_base + block(__builtin_amdgcn_readfirstlane(id));
 #pragma unroll
     for (int i = 0; i < D / 32; ++i)
       k[i] = piece<kNonTemporal>(kLines ? kp + (i & 1) * 8 * D + (i >> 1) * 64 : kp + i * 32);
@@ -141,7 +140,7 @@ struct KeyBlocks {
 #pragma unroll
     for (int i = 0; i < (kLines ? 2 : 1); ++i) {
       const int t = kLines ? __shfl(tok, ((threadIdx.x & 63) >> 3) + 8 * i) : tok;
-      at[i] = block(ids[t >> 4]) + (t & 15) * D;
+      at[i] = base + block(ids[t >> 4]) + (t & 15) * D;
     }
 #pragma unroll
     for (int i = 0; i < D / 32; ++i)
