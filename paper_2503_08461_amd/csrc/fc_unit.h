@@ -166,10 +166,18 @@ struct ScoreShared {
   // partial (max, sum) pairs per wavefront and row: those of the four lane groups,
   // or (wide workgroups, whose LDS is short) already merged within the wavefront
   static constexpr int kParts = WV == kNarrow ? 4 : 1;
-  float m[WV][kParts][64];
-  float z[WV][kParts][64];
+  struct Pairs {
+    float m[WV][kParts][64];
+    float z[WV][kParts][64];
+  };
   float fin[64];
-  KeyTiles<WV> tiles;
+  // (one place: side by side they would exceed what the selection needs, which is what
+  // says how many workgroups a CU takes: scores of 2048 heads of 4700-5600 tokens, 64
+  // channels, window 32, 702 us with them apart, 640 so)
+  union {
+    Pairs rows;          // until fin is known
+    KeyTiles<WV> tiles;  // from there on
+  };
 };
 
 // Scores one (request, layer, head); store(j, a_j) receives the un-pooled
@@ -268,8 +276,8 @@ __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc&
       }
     }
     if (q4 < kParts) {
-      sh.m[wave][q4 % kParts][nt * 16 + c16] = m[nt];
-      sh.z[wave][q4 % kParts][nt * 16 + c16] = z[nt];
+      sh.rows.m[wave][q4 % kParts][nt * 16 + c16] = m[nt];
+      sh.rows.z[wave][q4 % kParts][nt * 16 + c16] = z[nt];
     }
   }
 }
@@ -280,11 +288,11 @@ __device__ __forceinline__ void merged_row(const ScoreShared<WV>& sh, int row, f
   constexpr int kParts = ScoreShared<WV>::kParts;
   mm = -3.0e38f;
   for (int w = 0; w < WV; ++w)
-    for (int q = 0; q < kParts; ++q) mm = fmaxf(mm, sh.m[w][q][row]);
+    for (int q = 0; q < kParts; ++q) mm = fmaxf(mm, sh.rows.m[w][q][row]);
   zz = 0.f;
   for (int w = 0; w < WV; ++w)
     for (int q = 0; q < kParts; ++q)
-      zz += sh.z[w][q][row] * __builtin_amdgcn_exp2f(sh.m[w][q][row] - mm);
+      zz += sh.rows.z[w][q][row] * __builtin_amdgcn_exp2f(sh.rows.m[w][q][row] - mm);
 }
 
 // Pass 2 over blocks [b0, b1) of the prefix: column sums of the soft-maxed rows;
