@@ -75,7 +75,8 @@ static_assert(PLAN_SCORE_AUTO == FC_SCORE_AUTO && PLAN_SCORE_TWO_PASS == FC_SCOR
 static_assert(K_COUNT == FC_N_KERNELS, "timing slots");
 static_assert(kPlanBlockSize == FC_BLOCK_SIZE && kPlanMaxWindow == FC_MAX_WINDOW &&
               kPlanMaxSeqLen == FC_MAX_SEQ_LEN && kPlanMaxPoolKernel == FC_MAX_POOL_KERNEL &&
-              kPlanFusedMaxLen == kFusedMaxLen && kPlanClasses == FC_MAX_WINDOW / 16 + 1,
+              kPlanFusedMaxLen == kFusedMaxLen && kPlanMaxSeqLen == kFusedWideMaxLen &&
+              kPlanClasses == FC_MAX_WINDOW / 16 + 1,
               "limits");
 
 // ---- scratch of the allocation-free entry point --------------------------------

@@ -75,6 +75,12 @@ bool wide_pays(const CompressPlan& plan, size_t units, int n_cu) {
 //   8192          1500         1259-1304 / 1300-1364    2048          4000  799-875 / 768-849
 //   6144          2400         1420-1441 / 1396-1452    2048          6500  1338-1382 / 1279-1338
 //   4096          2000         827-886 / 808-871         768          2500  210-228 / 194-216
+// With three and more query tiles that kernel takes 3 KB more of LDS, so where a head of
+// more than 7820 tokens is in the launch (kPlanHalfReuseWords) two workgroups of it fit a
+// CU, not three, and the plain one is the faster.  1536 heads of 7900-8190 tokens, window
+// 48 half 1200, all 1180, window 64 1210 and 1167; of 6000-8192 1065 and 1043, 1086 and
+// 1052; but of 7700-7800 1052 and 1105, 1070 and 1117, and with window 32, where both fit
+// alike, of 6000-8192 987 and 1036.
 constexpr int kHalfReuseLen = 2304;
 
 int blocks_for(int tokens) { return (tokens + kPlanBlockSize - 1) / kPlanBlockSize; }
@@ -275,7 +281,8 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
       tokens += d.seq_len;
       weighted += (int64_t)d.seq_len * d.seq_len;
     }
-    l->half_reuse = !l->wide && tokens > 0 && weighted >= kHalfReuseLen * tokens;
+    l->half_reuse = pool.head_dim == 128 && !l->wide && tokens > 0 && weighted >= kHalfReuseLen * tokens &&
+                    (l->query_tiles <= 2 || fused_lds(l->max_len, l->max_blocks, false).words <= kPlanHalfReuseWords);
     launches.push_back(std::move(*l));
   }
   return launches;

@@ -26,6 +26,30 @@ static constexpr int kPlanMaxPoolKernel = 63;
 static constexpr int kPlanFusedMaxLen = 8192;   // longest head of narrow workgroups of the fused kernels
 static constexpr int kPlanClasses = 5;          // query-tile counts 0..4 (0: no queries)
 
+// LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
+// that the four-token reads of the pooling may touch (filled with what changes no
+// result), then one bit per token.
+static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
+static constexpr int kStageFront = 4;
+constexpr int stage_words(int len) { return kStageFront + ((len + 3) & ~3) + 8; }
+constexpr int need_words(int len) { return (len + kChunk - 1) / kChunk * (kChunk / 32); }
+
+// LDS words of a fused launch: scores, then one bit per token, then the block ids.
+struct FusedLds {
+  int ids_at, ids_room, words;
+};
+constexpr FusedLds fused_lds(int max_len, int max_blocks, bool wide) {
+  FusedLds f = {};
+  f.ids_at = stage_words(max_len) + need_words(max_len);
+  const int most = (wide ? kPlanMaxSeqLen : kPlanFusedMaxLen) / kPlanBlockSize;
+  f.ids_room = max_blocks < most ? max_blocks : most;
+  f.words = f.ids_at + ((f.ids_room + 3) & ~3);
+  return f;
+}
+// Of narrow workgroups, three and more query tiles: the words up to which a CU takes as
+// many of the kernel that leaves half of the keys to the caches as of the plain one.
+static constexpr int kPlanHalfReuseWords = 8572;
+
 // What the pool contributes to a plan.
 struct PoolView {
   int n_layers = 0, n_heads = 0, head_dim = 0;

@@ -93,9 +93,9 @@ static constexpr int kBoundMinLen = WV == kNarrow ? 512 : 2048;
 // workgroups do in any case: their wavefronts wait longer for the LDS than lines save
 // (pruned heads of 10000 tokens, 1024 of them, 64 channels: 603 us straight, 653 in lines).
 static constexpr int kTilePieces = 128;  // 16-byte pieces of a wavefront's tile
-template <int WV>
+template <int WV, bool kUsed = true>
 struct KeyTiles {
-  half8 piece[WV == kNarrow ? WV * kTilePieces : 1];
+  half8 piece[kUsed && WV == kNarrow ? WV * kTilePieces : 1];
 };
 template <int D, int WV, bool kWanted>
 struct KeyBlocks {
@@ -107,7 +107,8 @@ struct KeyBlocks {
   half8* put;         // where this lane's piece of rows 0 .. 7 goes (a piece of row r lies at its index ^ (r & 7))
   const half8* got0;  // its operand of the first 32 of 64 channels,
   const half8* got1;  // of the second
-  __device__ __forceinline__ KeyBlocks(const BatchParams& p, int lh, KeyTiles<WV>& tiles) : n_blocks(p.n_blocks) {
+  // tiles: of the workgroup (nullptr: no lines)
+  __device__ __forceinline__ KeyBlocks(const BatchParams& p, int lh, half8* tiles) : n_blocks(p.n_blocks) {
     const int layer = lh / p.n_heads, head = lh - layer * p.n_heads;
     const int lane = threadIdx.x & 63;
     const int row = lane >> 3, c16 = lane & 15, q4 = lane >> 4;
@@ -115,7 +116,7 @@ struct KeyBlocks {
     base = p.kv + (size_t)layer * p.n_blocks * stride + (size_t)head * 16 * D + (kLines ? (lane & 7) * 8 : q4 * 8);
     row_base = base + (kLines ? row : c16) * D;
     if constexpr (kLines) {
-      half8* const mine = tiles.piece + (threadIdx.x >> 6) * kTilePieces;
+      half8* const mine = tiles + (threadIdx.x >> 6) * kTilePieces;
       put = mine + row * 8 + ((lane & 7) ^ row);
       got0 = mine + c16 * 8 + (q4 ^ (c16 & 7));
       got1 = mine + c16 * 8 + ((4 + q4) ^ (c16 & 7));
@@ -218,7 +219,7 @@ __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc&
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, false> keys(p, lh, sh.tiles);
+  const KeyBlocks<D, WV, false> keys(p, lh, nullptr);
   const float c = p.scale_log2e;
   const int n_unmasked = (L - W) >> 4;  // blocks that lie wholly before the window
   float m[NT], z[NT];
@@ -306,7 +307,7 @@ __device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDe
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, true> keys(p, lh, tiles);
+  const KeyBlocks<D, WV, true> keys(p, lh, tiles.piece);
   const float c = p.scale_log2e;
   const int n_prefix = rd.seq_len - rd.window;
   float mrow[NT][4];
@@ -472,14 +473,6 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 static constexpr int kBuckets = 2048;
 static constexpr int kBucketBits = 11;
 static constexpr int kMaxCand = 2048;
-static constexpr int kChunk = 256;  // tokens a wavefront takes at a time (4 per lane)
-
-// LDS of a head's per-token words: stage[0 .. n) plus room in front and behind
-// that the four-token reads of the pooling may touch (filled with what changes no
-// result), then one bit per token.
-static constexpr int kStageFront = 4;
-__host__ __device__ constexpr int stage_words(int len) { return kStageFront + ((len + 3) & ~3) + 8; }
-__host__ __device__ constexpr int need_words(int len) { return (len + kChunk - 1) / kChunk * (kChunk / 32); }
 
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
@@ -1043,16 +1036,22 @@ struct BoundEpoch {  // the factors rho_i of one epoch over the window rows
   float p_dn[kBoundCentres];
 };
 
+// The selection needs most LDS of what a workgroup does, and how many of them a CU takes
+// hangs on it; so what comes before it stays below that: no tiles where the pass loads
+// straight, and those of the rescoring lie over all this, which is done with by then.
+// (With tiles for both in here, and three or four query tiles, 3 KB above it: 64 channels,
+// 2048 heads of 5000-5500 tokens, window 64, 745 us with three workgroups per CU, 626 with
+// four.)
 // rows that hold anything, rounded up to what one lane each at a renewal covers
 template <int NT>
 static constexpr int kBoundRows = NT == 1 ? 16 : NT == 2 ? 32 : 64;
-template <int WV, int ROWS>
+template <int WV, int ROWS, bool kHalf>
 struct BoundShared {
   float fin[64];                            // log2 of every row's soft-max denominator
   float pub[2][WV][ROWS];                   // the wavefronts' row sums at a renewal, absolute log2
   float ref[bound_max_epochs<WV>()][ROWS];  // the reference of every epoch
   union {
-    KeyTiles<WV> tiles;                       // during the pass
+    KeyTiles<WV, kHalf> tiles;                // during the pass
     BoundEpoch stat[bound_max_epochs<WV>()];  // after it
   };
 };
@@ -1095,13 +1094,18 @@ __device__ __forceinline__ float lower_of(uint32_t w) { return __uint_as_float(w
 // no more and costs 2 % where nothing is gained.)
 template <int D, int WV>
 static constexpr bool kHasHalfReuse = D == 128 && WV == kNarrow;
+// With three and more query tiles its LDS is 3 KB above what the selection needs (the tiles
+// lie next to the rows' references): it pays up to the length where a CU still takes as
+// many workgroups of it (kPlanHalfReuseWords).
+template <int NT, bool kHalf>
+static constexpr bool kTilesCost = kHalf && NT > 2;
 
 // First pass with bounds.  On return stage[j] holds the packed bounds of the
 // column sum of every prefix token j and bs.fin the rows' log-sum-exps.  All
 // threads of the workgroup call; ends with a barrier.
 template <int D, int NT, int WV, bool kHalf, int ROWS>
 __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDesc& rd, int lh,
-                                              const int32_t* old_ids, BoundShared<WV, ROWS>& bs,
+                                              const int32_t* old_ids, BoundShared<WV, ROWS, kHalf>& bs,
                                               BoundKeep& keep, float* stage,
                                               half8 (&qreg)[NT][D / 32]) {
   constexpr int KS = D / 32;
@@ -1111,7 +1115,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, kHalf> keys(p, lh, bs.tiles);
+  const KeyBlocks<D, WV, kHalf> keys(p, lh, bs.tiles.piece);
   const float c = p.scale_log2e;
   const int nb = (L + 15) >> 4;
   const int n_prefix = L - W;
@@ -1355,17 +1359,19 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
 // the registers of one query tile are short of it (8192 heads of 700 tokens: 606 -> 593
 // us with two tiles, 697 -> 681 with four, 576 -> 614 with one); rows of 128 bytes, one
 // line anyhow, are not (2048 heads of 6500 tokens, four tiles: 969 straight, 995 us).
+template <int D, int NT>
+static constexpr bool kRescoreLines = D == 128 && NT > 1;
 template <int D, int NT, int WV>
 __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDesc& rd, int lh,
                                                const int32_t* old_ids, const uint32_t* need,
-                                               float* stage, KeyTiles<WV>& tiles, half8 (&qreg)[NT][D / 32],
+                                               float* stage, half8* tiles, half8 (&qreg)[NT][D / 32],
                                                const float (&mrow)[NT][4]) {
   constexpr int KS = D / 32;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, (D == 128 && NT > 1)> keys(p, lh, tiles);
+  const KeyBlocks<D, WV, kRescoreLines<D, NT>> keys(p, lh, tiles);
   const float c = p.scale_log2e;
   const int n_prefix = rd.seq_len - rd.window;
   const int n_words = (n_prefix + 31) >> 5;
@@ -1794,8 +1800,11 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
   __shared__ union {
     ScoreShared<WV> score;
     SelectShared<WV> select;
-    BoundShared<WV, kBoundRows<NT>> bound;
+    BoundShared<WV, kBoundRows<NT>, kHalf> bound;
+    KeyTiles<WV, kRescoreLines<D, NT>> rescore;  // (the bounds and the classification are done with theirs)
   } sh;
+  static_assert(WV != kNarrow || kTilesCost<NT, kHalf> || sizeof(sh) <= sizeof(SelectShared<WV>),
+                "the selection sets how many workgroups a CU takes");
   __shared__ BoundKeep keep;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
@@ -1836,7 +1845,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
             for (int r = 0; r < 4; ++r) mrow[t][r] = sh.bound.fin[t * 16 + q4 * 4 + r];
           __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
           bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
-          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, sh.bound.tiles, qreg, mrow);
+          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, sh.rescore.piece, qreg, mrow);
         }
       });
     } else {
@@ -1849,21 +1858,21 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
   gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
 }
 
-// LDS words of a fused launch: scores, then one bit per token, then the block ids.
-struct FusedLds {
-  int ids_at, ids_room, words;
-};
-static constexpr FusedLds fused_lds(int max_len, int max_blocks, bool wide) {
-  FusedLds f = {};
-  f.ids_at = stage_words(max_len) + need_words(max_len);
-  const int most = (wide ? kFusedWideMaxLen : kFusedMaxLen) / 16;
-  f.ids_room = max_blocks < most ? max_blocks : most;
-  f.words = f.ids_at + ((f.ids_room + 3) & ~3);
-  return f;
-}
-
 // what a wide workgroup may ask for next to its static LDS
 static constexpr int kLdsPerCu = 160 * 1024;
+
+// Narrow workgroups of the pruned kernel that fit the LDS of a CU (which is given out in
+// pieces of 1280 bytes) next to `words` each.
+template <int NT, bool kHalf>
+static constexpr int narrow_per_cu(int words) {
+  constexpr int bound = (int)sizeof(BoundShared<kNarrow, kBoundRows<NT>, kHalf>), rest = (int)sizeof(SelectShared<kNarrow>);
+  return kLdsPerCu / (((bound > rest ? bound : rest) + 16 + 4 * words + 1279) / 1280 * 1280);
+}
+static constexpr int kMostNarrowWords = fused_lds(kFusedMaxLen, kFusedMaxLen / 16, false).words;
+static_assert(narrow_per_cu<2, true>(kMostNarrowWords) == narrow_per_cu<2, false>(kMostNarrowWords) &&
+                  narrow_per_cu<4, true>(kPlanHalfReuseWords) == narrow_per_cu<4, false>(kMostNarrowWords) &&
+                  narrow_per_cu<4, true>(kPlanHalfReuseWords + 4) < narrow_per_cu<4, false>(kMostNarrowWords),
+              "plan_fused_launches");
 
 // One fused launch of workgroups of narrow or wide shape.
 template <int D, int NT, bool kWideShape>
@@ -1903,7 +1912,7 @@ template <int D, int NT>
 static hipError_t wide_setup_one() {
   constexpr int WV = kWide<D, NT>;
   constexpr int most = fused_lds(kFusedWideMaxLen, kFusedWideMaxLen / 16, true).words * 4;
-  static_assert(most + (int)sizeof(BoundShared<WV, kBoundRows<NT>>) + 64 <= kLdsPerCu, "LDS of the longest head");
+  static_assert(most + (int)sizeof(BoundShared<WV, kBoundRows<NT>, false>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(SelectShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   static_assert(most + (int)sizeof(ScoreShared<WV>) + 64 <= kLdsPerCu, "LDS of the longest head");
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_unit_kernel<D, NT, WV>),

@@ -37,7 +37,7 @@ int main() {
     for (const ReqDesc& d : plan.descs) printf(" %lld", (long long)d.raw_off);
     printf("\n");
     for (const FusedLaunch& l : plan_fused_launches(pv, plan, n_cu)) {
-      printf("F %d %d %d %d", l.wide ? 1 : 0, l.query_tiles, l.max_len, l.max_blocks);
+      printf("F %d %d %d %d %d", l.wide ? 1 : 0, l.query_tiles, l.max_len, l.max_blocks, l.half_reuse ? 1 : 0);
       for (int32_t i : l.units) printf(" %d", i);
       printf("\n");
     }

@@ -47,7 +47,7 @@ def planned(wl, methods=None, budgets=None, windows=None, lens=None, in_place=Fa
         return got
     for line in out[1:]:
         row = [int(x) for x in line.split()[1:]]
-        for i in row[4:]:
+        for i in row[5:]:
             got[idx[i]] = "wide" if row[0] else "narrow"
     return got
 

@@ -87,7 +87,7 @@ def test_launch_plan(tmp_path):
                 at += units * L
             assert raw_floats == at and 2 <= split <= max(L for L, m, *_ in reqs if m != STREAM) // 256
         seen = []
-        for wide, tiles, max_len, max_blocks, *members in launches:
+        for wide, tiles, max_len, max_blocks, _, *members in launches:
             seen += members
             lens = [reqs[i][0] for i in members]
             scored = [reqs[i][0] for i in members if reqs[i][1] != STREAM]

@@ -3,18 +3,21 @@ selection needs allows, at every length that the host planner puts into such a l
 Static LDS is what the built library's kernels declare; no GPU."""
 
 import os
+import shutil
 import struct
 import subprocess
 
 import pytest
 
+from launch_shapes import _driver
 from paper_2503_08461_amd import fastcache
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
-pytestmark = pytest.mark.skipif(not os.path.exists(READELF), reason="no toolchain")
+pytestmark = pytest.mark.skipif(not os.path.exists(READELF) or shutil.which("g++") is None, reason="no toolchain")
 
 LDS, PIECE = 160 * 1024, 1280
 VGPRS = 512  # of a SIMD; a narrow workgroup has one wavefront on each
+KEEP = 16  # of the pruned kernel, next to what it shares with the selection
 
 
 def kernels(tmp_path):
@@ -56,3 +59,26 @@ def test_kernels_that_score_in_full(tmp_path):
             lds, vgprs = built["_ZN2fc17fused_unit_kernelILi%dELi%dELi4EEEvNS_11BatchParamsE" % (d, tiles)]
             for L in range(16, 8193, 16):
                 assert per_cu(lds, vgprs, L, L // 16) == per_cu(select, vgprs, L, L // 16), (d, tiles, L)
+
+
+def test_pruned_kernels(tmp_path):
+    built = kernels(tmp_path)
+    select = built["_ZN2fc13select_kernelILi4EEEvNS_11BatchParamsE"][0]
+    # the pruned form that the planner takes, for each number of query tiles (5: they differ)
+    cases = [(d, tiles, L) for d in (64, 128) for tiles in (1, 2, 3, 4, 5) for L in range(512, 8193, 16)]
+    text = ""
+    for d, tiles, L in cases:
+        more = "%d 1 %d 16\n" % (L, L // 5) if tiles == 5 else ""
+        text += "1 600 %d 0 0 256 %d\n%d 1 %d %d\n%s" % (d, 2 if more else 1, L, L // 5, 16 * min(tiles, 4), more)
+    out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    launches = [[int(x) for x in line.split()[1:]] for line in out if line[0] == "F"]
+    assert len(launches) == len(cases)
+    for (wide, got_tiles, max_len, max_blocks, half, *_), (d, tiles, L) in zip(launches, cases):
+        assert not wide and got_tiles == tiles and max_len == L
+        name = "_ZN2fc20fused_bounded_kernelILi%dELi%dELi4ELb%dEEEvNS_11BatchParamsE"
+        vgprs = built[name % (d, tiles, 0)][1]
+        assert per_cu(*built[name % (d, tiles, half)], max_len, max_blocks) \
+            == per_cu(select + KEEP, vgprs, max_len, max_blocks), (d, tiles, L, half)
+        if d == 128 and L >= 2304:  # half of the keys are left to the caches wherever that costs no workgroup
+            half_lds = built[name % (d, tiles, 1)][0]
+            assert half == (per_cu(half_lds, vgprs, max_len, max_blocks) == per_cu(select + KEEP, vgprs, max_len, max_blocks))
