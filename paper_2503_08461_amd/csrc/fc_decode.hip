@@ -111,12 +111,6 @@ __device__ __forceinline__ float row_lanes_sum(float s) {
   return s;
 }
 
-// segments of a head of L tokens: as many of seg_blocks as come nearest to its blocks
-// (at most n_seg, which is that of the longest head rounded up), 1 for a short or empty one
-__device__ __forceinline__ int decode_segments(int L, int seg_blocks) {
-  return max((((L + 15) >> 4) + seg_blocks / 2) / seg_blocks, 1);
-}
-
 template <int D, bool kIndexed, bool kCut, typename Reqs>
 __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams p, Reqs reqs) {
   constexpr int LPR = D / 8;        // lanes per row
@@ -134,9 +128,10 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
   const DecodeReq rq = reqs.req[slot];
   const int L = kIndexed ? rq.pop_index : rq.seq_len;  // indexed: pop_index holds the budget
   const int nb = (L + 15) >> 4;
-  const int n_seg = kCut ? decode_segments(L, p.seg_blocks) : 1;
+  const int n_seg = kCut ? decode_segments(nb, p.seg_blocks) : 1;
   if (seg >= n_seg) return;  // uniform: this request has fewer segments
-  const int b0 = kCut ? nb * seg / n_seg : 0, b1 = kCut ? nb * (seg + 1) / n_seg : nb;
+  const int b0 = kCut ? decode_segment_begin(nb, n_seg, seg) : 0;
+  const int b1 = kCut ? decode_segment_begin(nb, n_seg, seg + 1) : nb;
   const int layer = lh / p.n_heads;
   const int head = lh - layer * p.n_heads;
   const int32_t* kept =
@@ -272,7 +267,7 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecodeParams p, Reqs re
   const int lh = blockIdx.x - slot * n_lh;
   const DecodeReq rq = reqs.req[slot];
   const int L = kIndexed ? rq.pop_index : rq.seq_len;
-  const int n_seg = decode_segments(L, p.seg_blocks);
+  const int n_seg = decode_segments((L + 15) >> 4, p.seg_blocks);
   if (n_seg <= 1) return;  // written by the kernel above
   constexpr int kWords = DecodeParams::state_words(D);
   const float* states = p.partial + (size_t)blockIdx.x * p.n_seg * kWords;

@@ -495,7 +495,7 @@ void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, Decode
   const int64_t seg = std::max<int64_t>({eighth, 16, (longest + room - 1) / room});
   if (2 * seg > longest) return;
   plan->seg_blocks = (int)seg;
-  plan->n_seg = (int)((longest + seg - 1) / seg);
+  plan->n_seg = decode_segments(longest, plan->seg_blocks);  // (a head with fewer blocks has no more)
 }
 
 }  // namespace fc

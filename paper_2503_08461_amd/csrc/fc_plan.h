@@ -154,11 +154,19 @@ struct DecodePlan {
   std::vector<DecodeReq> reqs;
   int n_pop = 0;
   size_t kept_entries = 0;
-  int seg_blocks = 0, n_seg = 1;  // attention: blocks per segment of a head, segments of the longest one
+  int seg_blocks = 0, n_seg = 1;  // attention: blocks per segment of a head, segments of the longest one, which no head exceeds
 };
 // Attention: most segments of all heads of a call that is split (heads x n_seg), which
-// is what the pool's buffers for their states hold (8.7 MB at 128 channels).
+// is what the pool's buffers for their states hold (10.5 MB at 128 channels).
 static constexpr int kMaxDecodeSegments = 16384;
+// Segments of a head of `blocks` blocks in a call that cuts its heads: as many of
+// seg_blocks as come nearest (1 for a short or empty head), all alike in size; segment s
+// begins at block decode_segment_begin(blocks, n, s) and ends where the next one does.
+constexpr int decode_segments(int blocks, int seg_blocks) {
+  const int n = (blocks + seg_blocks / 2) / seg_blocks;
+  return n > 1 ? n : 1;
+}
+constexpr int decode_segment_begin(int blocks, int n, int s) { return blocks * s / n; }
 int plan_append(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,
                 const int32_t* enable, DecodePlan* plan);
 int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const int32_t* seq_lens,

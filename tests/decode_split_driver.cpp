@@ -1,6 +1,7 @@
 // Prints how a decode attention cuts its heads (csrc/fc_plan.cpp: plan_decode_segments).
 // Built, fed and checked by test_decode_split_plan.py.
 // Input, one case per line (all integers): nl nh n_cu over_kept n_req, then the lengths.
+// Output, a line per case: blocks of a segment, segments of the launch, then every head's.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -22,7 +23,15 @@ int main() {
                               over_kept ? lens.data() : nullptr, &plan) != PLAN_OK)
       return 3;
     plan_decode_segments(pv, n_cu, over_kept != 0, &plan);
-    printf("%d %d\n", plan.seg_blocks, plan.n_seg);
+    printf("%d %d", plan.seg_blocks, plan.n_seg);
+    // every head's segments, as the kernels cut it: their number, then where each begins, then the end
+    for (int len : lens) {
+      const int blocks = (len + kPlanBlockSize - 1) / kPlanBlockSize;
+      const int n = plan.n_seg > 1 ? decode_segments(blocks, plan.seg_blocks) : 1;
+      printf(" %d", n);
+      for (int seg = 0; seg <= n; ++seg) printf(" %d", decode_segment_begin(blocks, n, seg));
+    }
+    printf("\n");
   }
   return 0;
 }

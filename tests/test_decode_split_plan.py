@@ -22,9 +22,10 @@ def test_decode_segments(tmp_path):
                     "-static-libasan", "-static-libubsan", os.path.join(ROOT, "tests", "decode_split_driver.cpp"),
                     os.path.join(ROOT, "paper_2503_08461_amd", "csrc", "fc_plan.cpp"), "-o", exe], check=True)
     rng = random.Random(3)
-    # both sides of twice the smallest segment; no tokens at all; no room for two segments per
-    # head, and more than enough heads to load every compute unit alike
-    cases = [(1, 4, 256, 0, [496]), (1, 4, 256, 0, [512]), (1, 4, 256, 1, [0, 0]), (32, 257, 256, 0, [32768]),
+    # both sides of twice the smallest segment, and nearer to two than to three of them; no tokens at all; no room
+    # for two segments per head, and more than enough heads to load every compute unit alike
+    cases = [(1, 4, 256, 0, [496]), (1, 4, 256, 0, [512]), (1, 4, 256, 0, [16 * 39, 5]), (1, 4, 256, 1, [0, 0]),
+             (32, 257, 256, 0, [32768]),
              (32, 256, 256, 0, [32768])]
     for _ in range(400):
         nl, nh = rng.choice([(1, 4), (1, 32), (2, 12), (32, 32), (80, 64)])
@@ -34,10 +35,23 @@ def test_decode_segments(tmp_path):
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
     got = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
     assert len(got) == len(cases)
-    assert [n for _, n in got[:5]] == [1, 2, 1, 1, 1]
-    for (seg, n), (nl, nh, _, _, lens) in zip(got, cases):
+    assert [row[1] for row in got[:6]] == [1, 2, 2, 1, 1, 1]
+    for (seg, n, *rest), (nl, nh, _, _, lens) in zip(got, cases):
         longest = (max(lens) + 15) // 16
-        assert seg >= 1 and n == max(1, -(-longest // seg))
+        counts = []
+        for L in lens:
+            blocks, count, at = (L + 15) // 16, rest[0], rest[1:rest[0] + 2]
+            rest = rest[count + 2:]
+            counts.append(count)
+            # one behind the other, none empty unless the head is, alike in size and near to seg
+            assert at[0] == 0 and at[-1] == blocks and at == sorted(at)
+            sizes = [b - a for a, b in zip(at, at[1:])]
+            assert max(sizes) - min(sizes) <= 1
+            if n > 1:
+                assert min(sizes) > 0 or blocks == 0
+                assert max(sizes) < 1.5 * seg + 1 and (count == 1 or min(sizes) >= 2 * seg // 3)
+        assert not rest
+        assert seg >= 1 and n == max(counts)  # no workgroups that no head has a segment for
         if n > 1:
             assert 16 <= seg <= longest // 2 and n <= MAX_PER_HEAD and n * len(lens) * nl * nh <= MAX_SEGMENTS
-    assert sum(n > 1 for _, n in got) > 50
+    assert sum(row[1] > 1 for row in got) > 50
