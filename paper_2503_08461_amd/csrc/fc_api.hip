@@ -780,7 +780,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     }
     return e;
   }));
-  FC_HIP_STAGE(p, run(K_RECLAIM, true, [&] { return launch_reclaim(bp, stream); }));
+  FC_HIP_STAGE(p, run(K_RECLAIM, !bp.main_reclaims, [&] { return launch_reclaim(bp, stream); }));
 
   // ---- host mirrors ------------------------------------------------------------
   p->top = plan.top_after;
@@ -1030,7 +1030,7 @@ int fc_compress_batch_mlp(fc_pool* p, int32_t* dev_block_tables, int max_blocks_
     return launch_plan_alloc(bp, meta_inline ? &inline_meta : nullptr, (int)image.size(), stream);
   }));
   FC_HIP_STAGE(p, run(K_MLP, [&] { return launch_mlp_compress(bp, mp, stream); }));
-  FC_HIP_STAGE(p, run(K_RECLAIM, [&] { return launch_reclaim(bp, stream); }));
+  if (!bp.main_reclaims) FC_HIP_STAGE(p, run(K_RECLAIM, [&] { return launch_reclaim(bp, stream); }));
 
   p->top = plan.top_after;
   for (const ReqDesc& d : plan.descs) host_seq_lens[d.table_row] = d.budget;

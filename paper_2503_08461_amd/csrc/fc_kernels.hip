@@ -389,7 +389,6 @@ hipError_t launch_plan_alloc(const BatchParams& p, const MetaChunk* inline_meta,
 }
 
 hipError_t launch_reclaim(const BatchParams& p, hipStream_t s) {
-  if (p.main_reclaims) return hipSuccess;  // done by the kernel before
   reclaim_kernel<<<p.n_comp, kThreads, 0, s>>>(p);
   return hipGetLastError();
 }

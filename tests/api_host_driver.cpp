@@ -54,7 +54,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t*, unsigned) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** out, const void* symbol) { *out = const_cast<void*>(symbol); return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
 }
@@ -83,8 +83,12 @@ hipError_t launch_zero_ints(int32_t*, int, hipStream_t) { return launched("zero"
 hipError_t launch_knorm_score(const BatchParams&, hipStream_t) { return launched("knorm_score"); }
 hipError_t launch_split_scores(const BatchParams&, hipStream_t) { return launched("split_scores"); }
 hipError_t launch_select(const BatchParams&, int, bool, hipStream_t) { return launched("select"); }
-hipError_t launch_gather(const BatchParams&, hipStream_t) { return launched("gather"); }
-hipError_t launch_fused(BatchParams, int, int, int, bool wide, hipStream_t) { return launched(wide ? "fused_wide" : "fused_narrow"); }
+// (+reclaim: told to take the old blocks back in passing)
+static hipError_t launched_main(const BatchParams& p, const char* name) {
+  return launched((std::string(name) + (p.main_reclaims ? "+reclaim" : "")).c_str());
+}
+hipError_t launch_gather(const BatchParams& p, hipStream_t) { return launched_main(p, "gather"); }
+hipError_t launch_fused(BatchParams p, int, int, int, bool wide, hipStream_t) { return launched_main(p, wide ? "fused_wide" : "fused_narrow"); }
 hipError_t launch_reclaim(const BatchParams&, hipStream_t) { return launched("reclaim"); }
 hipError_t launch_meta_upload(const MetaChunk&, char*, int, hipStream_t) { return launched("upload"); }
 hipError_t launch_append(const DecodeParams& p, const DecodeReqs&, hipStream_t) { return launched(p.reqs ? "append" : "append_inline"); }
@@ -92,7 +96,7 @@ hipError_t launch_decode_attention(const DecodeParams& p, const DecodeReqs&, hip
   return launched((std::string(p.reqs ? "attention" : "attention_inline") + ":" + std::to_string(p.n_seg)).c_str());
 }
 hipError_t launch_mlp_permute_weights(const _Float16*, const _Float16*, _Float16*, _Float16*, int, int, int, hipStream_t) { return launched("permute"); }
-hipError_t launch_mlp_compress(const BatchParams&, const MlpParams&, hipStream_t) { return launched("mlp"); }
+hipError_t launch_mlp_compress(const BatchParams& p, const MlpParams&, hipStream_t) { return launched_main(p, "mlp"); }
 }  // namespace fc
 
 static void report(const char* what, int rc) {
@@ -174,6 +178,37 @@ int main(int argc, char** argv) {
       g_capturing = true;
       step(n == 149 ? "few_captured" : "many_captured");
       g_capturing = false;
+    }
+  } else if (scenario == "reclaim") {
+    report("create", create());
+    const _Float16 w1[256 * 128] = {}, w2[128 * 256] = {};
+    const float b1[256] = {}, b2[128] = {};
+    const fc_mlp_weights weights = {1, 256, FC_ACT_GELU_ERF, {w1, w1}, {b1, b1}, {w2, w2}, {b2, b2}};
+    report("weights", fc_mlp_set_weights(pool, &weights, nullptr));
+    fc_set_profiling(pool, 1);
+    // few requests (descriptors as an argument of plan_alloc), many, few with ownership checks
+    for (const char* how : {"few", "many", "checked"}) {
+      const int n = std::string(how) == "many" ? 60 : 2;
+      fc_set_debug_checks(pool, std::string(how) == "checked");
+      // a head in one workgroup, heads split over workgroups, the separate kernels next to a streaming request, the MLP
+      for (const char* what : {"fused", "split", "separate", "mlp"}) {
+        const std::string name = what;
+        std::vector<int32_t> lens(n, name == "split" ? 4000 : 500), budgets(n, 100), methods(n, FC_METHOD_KNORM), zeros(n, 0);
+        if (name == "split" && n == 60) continue;  // (more heads than are split)
+        if (name == "separate") methods[0] = FC_METHOD_STREAMING;
+        fc_set_score_mode(pool, name == "separate" ? FC_SCORE_TWO_PASS : FC_SCORE_AUTO);
+        fc_pool_import_state_dev(pool, somewhere<int32_t>(), 4096, nullptr);
+        g_launched.clear();
+        const int rc = name == "mlp" ? fc_compress_batch_mlp(pool, somewhere<int32_t>(), 512, lens.data(), zeros.data(),
+                                                             lens.data(), nullptr, n, nullptr)
+                                     : fc_compress_batch(pool, somewhere<int32_t>(), 512, lens.data(), nullptr, 32,
+                                                         methods.data(), budgets.data(), n, 7, 0.f, nullptr, nullptr, nullptr);
+        report((name + "_" + how).c_str(), rc);
+        float ms[FC_N_KERNELS];
+        fc_get_kernel_times(pool, ms);
+        report((name + "_" + how + "_timed").c_str(), (int)ms[K_RECLAIM]);
+        fc_set_profiling(pool, 1);  // (counts from here)
+      }
     }
   } else {
     return 2;

@@ -40,13 +40,13 @@ def test_a_call_that_cannot_have_split_scores_runs_in_the_fused_kernels(driver):
     What was refused is not asked for again (an attempt waits for the device), and a captured call
     asks for nothing."""
     out, errors = run(driver, "no_room_for_split_scores")
-    fused = [["plan_inline", "fused_wide", "reclaim"]]
+    fused = [["plan_inline", "fused_wide+reclaim"]]
     assert out["in_place"] == (0, fused[0])
     assert out["full"] == (0, fused[0])
     assert out["full_kept_out"] == (0, fused[0])
     assert out["full_again"] == out["captured"] == (0, fused[0])
     assert errors == ["error []", "error 0", "error 0"]
-    split = (0, ["plan_inline", "split_scores", "select", "gather", "reclaim"])
+    split = (0, ["plan_inline", "split_scores", "select", "gather+reclaim"])
     assert out["room"] == out["captured_warm"] == split
 
 
@@ -67,3 +67,26 @@ def test_requests_of_a_decode_step(driver):
     assert out["few"] == out["few_captured"] == (0, ["attention_inline:1"])
     assert out["many"] == (0, ["copy", "attention:1"])
     assert out["many_captured"] == (0, ["upload", "upload", "attention:1"])
+
+
+def test_old_blocks_are_taken_back_exactly_once(driver):
+    """By a launch of its own, or in passing by the last kernel of a call whose descriptors are
+    plan_alloc's argument; only a launch is timed."""
+    out, _ = run(driver, "reclaim")
+    assert out["create"][0] == out["weights"][0] == 0
+    main = {"fused": ["fused"], "split": ["split_scores", "select", "gather"],
+            "separate": ["knorm_score", "select", "gather", "fused"], "mlp": ["mlp"]}
+    before = {"few": ["plan_inline"], "many": ["upload", "upload", "plan"],
+              "checked": ["upload", "zero", "check_tables", "plan"]}
+    for what, kernels in main.items():
+        for how, first in before.items():
+            if what + "_" + how == "split_many":
+                continue  # (more heads than are split)
+            rc, launches = out[what + "_" + how]
+            launches = [x.replace("fused_wide", "fused").replace("fused_narrow", "fused") for x in launches]
+            if how == "few":
+                in_passing = [k + "+reclaim" if k in ("fused", "gather", "mlp") else k for k in kernels]
+                assert (rc, launches) == (0, first + in_passing)
+            else:
+                assert (rc, launches) == (0, first + kernels + ["reclaim"])
+            assert out[what + "_" + how + "_timed"][0] == (how != "few")
