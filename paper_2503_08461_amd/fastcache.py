@@ -171,7 +171,8 @@ def _host_i32(a):
 
 def _entries(per_request, method):
     """Sum of per_request over the requests that are compressed."""
-    if method.shape[0] > 16 or method.ndim != 1 or per_request.ndim != 1:
+    # (as lists 0.2 us for one request, 1.1 for 32, 1.6 for 48; as arrays 1.45 to 1.5)
+    if method.shape[0] > 32 or method.ndim != 1 or per_request.ndim != 1:
         return int(per_request[method != FC_METHOD_NONE].astype(np.int64).sum())
     return sum([n for n, m in zip(per_request.tolist(), method.tolist()) if m != FC_METHOD_NONE])
 
