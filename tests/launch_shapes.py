@@ -30,8 +30,8 @@ def compute_units():
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
-def planned(wl, methods=None, budgets=None, windows=None, lens=None, in_place=False):
-    """"split", "wide" or "narrow" for every request of a call (None: not compressed)."""
+def _plan(wl, methods=None, budgets=None, windows=None, lens=None, in_place=False):
+    """(requests of a call that are compressed, the driver's output)"""
     methods = wl.methods if methods is None else methods
     budgets = wl.budgets if budgets is None else budgets
     windows = [wl.window] * wl.n_req if windows is None else windows
@@ -39,7 +39,12 @@ def planned(wl, methods=None, budgets=None, windows=None, lens=None, in_place=Fa
     idx = [r for r in range(wl.n_req) if methods[r] != fo.METHOD_NONE]
     text = "%d %d %d 0 %d %d %d\n" % (wl.n_layers, wl.n_heads, wl.head_dim, in_place, compute_units(), len(idx))
     text += "".join("%d %d %d %d\n" % (lens[r], methods[r], budgets[r], windows[r]) for r in idx)
-    out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    return idx, subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+
+
+def planned(wl, **call):
+    """"split", "wide" or "narrow" for every request of a call (None: not compressed)."""
+    idx, out = _plan(wl, **call)
     got = [None] * wl.n_req
     if int(out[0].split()[1]):
         for r in idx:
@@ -50,6 +55,11 @@ def planned(wl, methods=None, budgets=None, windows=None, lens=None, in_place=Fa
         for i in row[5:]:
             got[idx[i]] = "wide" if row[0] else "narrow"
     return got
+
+
+def leaves_half(wl):
+    """Whether the narrow launch of a call leaves half of the keys to the caches in a pruned first pass."""
+    return [bool(int(line.split()[5])) for line in _plan(wl)[1] if line.startswith("F 0")] == [True]
 
 
 def in_shape(wl, shape):

@@ -20,7 +20,7 @@ SNAP, KNORM, STREAM = fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING
 WIDE, NARROW = 70, 300
 
 
-def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, shape=None, **kw):
+def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, shape=None, half=None, **kw):
     from parity_util import SideBySide
     lens = list(lens) + [9] * fillers        # key-norm requests of nine tokens that only add heads
     budgets = list(budgets) + [4] * fillers
@@ -28,6 +28,8 @@ def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=Fa
     wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads)
     if shape:
         assert set(launch_shapes.planned(wl)) == {shape}
+    if half is not None:
+        assert launch_shapes.leaves_half(wl) == half
     s = SideBySide(wl, in_place=in_place)
     try:
         return s.compress_and_compare(scores=scores, **kw)
@@ -85,9 +87,11 @@ def test_single_pass_of_narrow_workgroups(W, d):
     _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, True, NARROW, shape="narrow", lse="library")
 
 
-@pytest.mark.parametrize("W", [16, 32, 64])
-@pytest.mark.parametrize("lens", [[513, 640, 2303, 2303, 2303],      # mean (weighted) below 2304: all keys cached
-                                  [600, 2500, 2519, 2593, 2400],      # above: half of them
-                                  [2304 + 17, 527, 528, 4097 + 63]])
-def test_narrow_pruned_first_pass(W, lens):
-    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, 128, False, NARROW, shape="narrow")
+@pytest.mark.parametrize("W", [16, 32, 48, 64])
+@pytest.mark.parametrize("lens,half", [([513, 640, 2303, 2303, 2303], False),  # mean (weighted) below 2304: all keys cached
+                                       ([600, 2500, 2519, 2593, 2400], True),   # above: half of them
+                                       ([2304 + 17, 527, 528, 4097 + 63], True),
+                                       ([7820, 2321], True), ([7821, 2321], None)])  # three workgroups per CU, with W up to 32
+def test_narrow_pruned_first_pass(W, lens, half):
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, 128, False, NARROW, shape="narrow",
+         half=W <= 32 if half is None else half)

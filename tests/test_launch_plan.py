@@ -102,3 +102,38 @@ def test_launch_plan(tmp_path):
         assert sorted(seen) == [i for i, r in enumerate(reqs) if mode == 0 or r[1] == STREAM]
         assert len(launches) <= 2
     assert n_split > 5
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_which_launches_leave_half_of_the_keys_to_the_caches():
+    """Narrow workgroups at 128 channels from a mean length of their SnapKV heads (weighted by
+    itself) on, unless the kernel that does it would cost a CU a workgroup."""
+    from launch_shapes import _driver
+
+    def snap(*lens, w=32):
+        return [(L, SNAP, max(w, L // 5), w) for L in lens]
+    fillers = [(9, KNORM, 4, 32)] * 600
+    cases = [
+        (_case(1, 600, snap(2303)), 0),
+        (_case(1, 600, snap(2304)), 1),
+        (_case(1, 512, snap(8000)), 0),                      # wide
+        (_case(1, 600, snap(8000), d=64), 0),
+        (_case(1, 1, snap(2303, 2303) + fillers), 0),        # other methods do not count
+        (_case(1, 1, snap(2304, 2304) + fillers), 1),
+        (_case(1, 600, [(8000, KNORM, 400, 32)] + snap(2303)), 0),
+        (_case(1, 600, snap(1000, 3000)), 1),                # (1000^2 + 3000^2) / 4000 = 2500
+        (_case(1, 600, snap(1000, 1000, 3000)), 0),          # 2200
+        (_case(1, 600, snap(8192)), 1),
+        (_case(1, 600, snap(7820, w=48)), 1),
+        (_case(1, 600, snap(7821, w=48)), 0),
+        (_case(1, 600, snap(7821, w=32) + snap(3000, w=16)), 0),   # two classes of windows
+        (_case(1, 600, snap(7820, w=32) + snap(3000, w=16)), 1),
+        (_case(1, 600, [(7821, KNORM, 400, 32)] + snap(3000, w=64)), 0),
+        (_case(1, 600, [(20000, STREAM, 400, 32)] + snap(7800, w=64)), 1),  # a longer table of block ids
+        (_case(1, 600, [(20000, STREAM, 400, 32)] + snap(7801, w=64)), 0),
+    ]
+    text = "".join("%d %d %d %d %d %d %d\n%s\n" % (c[:6] + (len(c[6]), "\n".join("%d %d %d %d" % r for r in c[6])))
+                   for c, _ in cases)
+    out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    got = [[int(x) for x in line.split()[1:]] for line in out if line[0] == "F"]
+    assert [launch[4] for launch in got] == [want for _, want in cases]
