@@ -474,11 +474,20 @@ int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const
 
 // Heads are cut when whole ones would leave the CUs unevenly loaded: into segments of
 // an eighth of a CU's share, at least 16 blocks (four for each wavefront), if that is
-// at most half of the longest head.  Measured at 1 layer of 32 heads: 8 caches of
-// 256-1408 tokens 24.4 us in segments of 16 blocks, 23.7 of 8 (before: 47.9 whole, 35.7
-// and 37.9 with the append), but 1 cache of 4000 tokens 15.4 and 16.9, 1 of 16000 with 8
-// heads 16.2 and 21.3; 16 caches of 130-16384 tokens 490 whole, 426 / 383 / 369 with a
-// quarter / an eighth / a sixteenth of the share; but 48 caches of 1280-7040 tokens, 2 layers, 985 / 986 / 993.
+// at most half of the longest head, or two fifths of it where it is the share that sets
+// the size: then a CU has more than three heads anyhow, and two segments a head gain less
+// than their states cost (59 caches of 249-747 tokens, 24 heads of 64 channels, 31.7 us
+// cut, 29.8 whole; 36 of 358-1074, 40 heads, 87.9 and 83.9; 44 of 496-744, 24 heads, 56.6
+// and 57.2).  The attention alone, 32 heads, us:
+//   segments at least of     8      16      24      whole
+//   8 caches of 256-1408    23.7    24.2    24.2    32.5
+//   1 of 4000               17.9    15.5    17.1    82.4
+//   a share's            quarter  eighth  sixteenth
+//   16 of 130-16384        377     353     358      417
+//   12 of 4000-16000 (2 layers)  664  648  643      666
+//   48 of 1280-7040 (2 layers)   960  960  984      959
+// (a ninth, a tenth and a twelfth are equal to an eighth over 60 calls of 1 to 48 caches
+// of 600-32000 tokens, 3 % either way in single ones).
 void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan, int max_segments) {
   if (plan->reqs.empty()) return;
   auto blocks = [&](const DecodeReq& q) { return blocks_for(over_kept ? q.pop_index : q.seq_len); };
@@ -493,9 +502,9 @@ void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, Decode
   if (room < 2) return;
   const int64_t eighth = total / (8 * (int64_t)std::max(n_cu, 1));
   const int64_t seg = std::max<int64_t>({eighth, 16, (longest + room - 1) / room});
-  if (2 * seg > longest) return;
+  if (2 * seg > longest || (seg == eighth && 5 * seg > 2 * (int64_t)longest)) return;
   plan->seg_blocks = (int)seg;
-  plan->n_seg = decode_segments(longest, plan->seg_blocks);  // (a head with fewer blocks has no more)
+  plan->n_seg = decode_segments(longest, plan->seg_blocks);
 }
 
 }  // namespace fc

@@ -154,7 +154,8 @@ struct DecodePlan {
   std::vector<DecodeReq> reqs;
   int n_pop = 0;
   size_t kept_entries = 0;
-  int seg_blocks = 0, n_seg = 1;  // attention: blocks per segment of a head, segments of the longest one, which no head exceeds
+  // attention: blocks per segment of a head, segments of the longest one (no head has more)
+  int seg_blocks = 0, n_seg = 1;
 };
 // Attention: most segments of all heads of a call that is split (heads x n_seg), which
 // is what the pool's buffers for their states hold (10.5 MB at 128 channels).

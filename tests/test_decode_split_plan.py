@@ -27,6 +27,8 @@ def test_decode_segments(tmp_path):
     cases = [(1, 4, 256, 0, [496]), (1, 4, 256, 0, [512]), (1, 4, 256, 0, [16 * 39, 5]), (1, 4, 256, 1, [0, 0]),
              (32, 257, 256, 0, [32768]),
              (32, 256, 256, 0, [32768])]
+    # a CU's share of an eighth is 21 blocks, the longest head has 47: whole; 22 and 55: cut
+    cases += [(1, 24, 256, 0, [16 * n] * 20 + [16 * 22] * 39) for n in (47, 55)]
     for _ in range(400):
         nl, nh = rng.choice([(1, 4), (1, 32), (2, 12), (32, 32), (80, 64)])
         cases.append((nl, nh, rng.choice([64, 256, 304]), rng.randrange(2),
@@ -35,7 +37,7 @@ def test_decode_segments(tmp_path):
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
     got = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
     assert len(got) == len(cases)
-    assert [row[1] for row in got[:6]] == [1, 2, 2, 1, 1, 1]
+    assert [row[1] for row in got[:8]] == [1, 2, 2, 1, 1, 1, 1, 3]
     for (seg, n, *rest), (nl, nh, _, _, lens) in zip(got, cases):
         longest = (max(lens) + 15) // 16
         counts = []
