@@ -46,8 +46,13 @@ def kernel_symbol(slot, wl, pruning):
         # wavefronts per workgroup: 4, or wide workgroups where a chip of 256 CUs gets at most two heads each
         units = len(wl.seq_lens) * wl.n_layers * wl.n_heads
         waves = 4 if units > 512 else (16 if nt <= 2 else 12)
-        return "fc::%s<%d, %d, %d>" % ("fused_bounded_kernel" if pruning else "fused_unit_kernel",
-                                       wl.head_dim, nt, waves)
+        if not pruning:
+            return "fc::fused_unit_kernel<%d, %d, %d>" % (wl.head_dim, nt, waves)
+        # long heads of narrow workgroups leave half of the keys to the caches in their first pass
+        lens = wl.seq_lens[wl.methods == 1].astype(int)
+        half = waves == 4 and wl.head_dim == 128 and lens.size > 0 and (lens ** 2).sum() >= 2304 * lens.sum() \
+            and (nt <= 2 or wl.seq_lens.max() <= 7820)
+        return "fc::fused_bounded_kernel<%d, %d, %d, %s>" % (wl.head_dim, nt, waves, "true" if half else "false")
     if slot == "snapkv_score":
         return "fc::snapkv_score_kernel<%d, %d>" % (wl.head_dim, nt)
     if slot in ("gather", "knorm_score"):

@@ -82,3 +82,23 @@ def test_pruned_kernels(tmp_path):
         if d == 128 and L >= 2304:  # half of the keys are left to the caches wherever that costs no workgroup
             half_lds = built[name % (d, tiles, 1)][0]
             assert half == (per_cu(half_lds, vgprs, max_len, max_blocks) == per_cu(select + KEEP, vgprs, max_len, max_blocks))
+
+
+def test_kernel_names_of_the_benchmark(tmp_path):
+    """The names that the benchmark prints are kernels of the library, the one with half of the
+    keys left to the caches where the planner takes it."""
+    import re
+    import bench
+    from paper_2503_08461_amd import synth
+    built = kernels(tmp_path)
+    for config, pruning in [(1, True), (2, True), (2, False), (3, True), (4, True), (4, False), (5, True)]:
+        wl = synth.make_workload(config)
+        name = bench.kernel_symbol("fused_unit", wl, pruning)
+        kernel, args = re.fullmatch(r"fc::(\w+)<(.*)>", name).groups()
+        args = ["Lb%d" % (a == "true") if a in ("true", "false") else "Li" + a for a in args.split(", ")]
+        assert "_ZN2fc%d%sI%sEEvNS_11BatchParamsE" % (len(kernel), kernel, "E".join(args) + "E") in built, name
+        if pruning:
+            text = "%d %d %d 0 0 256 %d\n" % (wl.n_layers, wl.n_heads, wl.head_dim, wl.n_req) + "".join(
+                "%d %d %d %d\n" % r for r in zip(wl.seq_lens, wl.methods, wl.budgets, [wl.window] * wl.n_req))
+            out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+            assert any(int(line.split()[5]) for line in out if line[0] == "F") == name.endswith("true>"), name
