@@ -534,10 +534,11 @@ int upload_meta(fc_pool* p, const char* image, size_t bytes, char* dev_dst, bool
 
 // Whether plan_alloc can take the descriptors as its own argument: they fit, and no
 // ownership check reads them first.  The last kernel of such a call, of up to about 35
-// prompts, then reclaims in passing: where the host is what bounds it, a launch less is
-// 3 us of about 33 (one prompt of 256 tokens, 4 heads: 34.5 -> 31.6), and on the GPU it
-// is 1 to 2 us (two prompts of 7000-8000 tokens, 32 heads: 93.3 -> 91.7).  In larger
-// calls that is nothing, and their heaviest heads run first.
+// prompts, then reclaims in passing.  A launch less is 2 to 3 us: two prompts of 7000-8000
+// tokens, 32 heads, 94.3 -> 91.8, one of 640 tokens, 1024 heads, 86.2 -> 84.2; where the
+// host is what bounds it, the chunk MLP over five prompts 30.8-32.8 -> 29.3, one prompt of
+// 256 tokens, 4 heads, 22.4-27.2 -> 22.6.  In larger calls that is nothing, and their
+// heaviest heads run first.
 bool fits_inline(const fc_pool* p, const char* image, size_t bytes, MetaChunk* c) {
   if (p->debug_checks || bytes > sizeof(MetaChunk)) return false;
   memcpy(c->bytes, image, bytes);

@@ -22,12 +22,15 @@
 // one request and one modality), two column tiles of 16 rows per wavefront; the kernel
 // is persistent (one to three workgroups per CU walk the tile list).
 //
-// What bounds it: at d = 128, hidden 256 the power that the card allows.  The clock
-// falls to 1.7 GHz, and with rows of zeros the same instructions take two thirds of
-// the time, every phase alike.  A loop of nothing but MFMAs on random values shows the
-// same: 32x32x16 1.56-1.65 PFLOP/s, 16x16x32 1.92; with an operand read from LDS every
-// 32 cycles 1.43 and 1.62.  So the smaller tiles are used although both need as many
-// operands (24 prompts of 1280-7040 tokens, 2 layers of 32 heads, k = 5: 1383 -> 1294 us;
+// What bounds it: at d = 128, hidden 256 the instructions of a tile at the clock that the
+// card's power allows.  The clock falls to 1.7 GHz, and with rows of zeros the same
+// instructions take two thirds of the time, every phase alike.  That is no ceiling: the
+// matrix pipes are busy for 46 % of those cycles, and next to a product stand 0.68 LDS
+// instructions (an operand of W1 serves two products) and 2.5 vector instructions, most of
+// them the activation's, which take cycles and power alike.  A loop of nothing but MFMAs
+// on random values: 32x32x16 1.56-1.65 PFLOP/s, 16x16x32 1.92; with an operand read from
+// LDS every 32 cycles 1.43 and 1.62.  So the smaller tiles are used although both need as
+// many operands (24 prompts of 1280-7040 tokens, 2 layers of 32 heads, k = 5: 1383 -> 1294 us;
 // with weights from memory to LDS past the registers, rows read 64 bytes at a time and
 // target rows looked up by one lane each 1403 -> 1383).  Loads complete in order, so any
 // load that is waited for waits for all rows requested before it: weights are requested

@@ -1784,7 +1784,7 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
 
 // Wavefronts per SIMD that the registers must allow: what the kernel needs without
 // spilling in its loops.  (At 128 channels the forms with one, four and mixed query
-// tiles spill 4 to 7 vector registers, stored and read back once a head, outside of
+// tiles spill 1 to 6 vector registers, stored and read back once a head, outside of
 // every loop.)
 __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
   return wv != kNarrow ? wv / 4 : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
