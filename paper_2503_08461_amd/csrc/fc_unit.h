@@ -1036,15 +1036,15 @@ struct BoundEpoch {  // the factors rho_i of one epoch over the window rows
   float p_dn[kBoundCentres];
 };
 
+// rows that hold anything, rounded up to what one lane each at a renewal covers
+template <int NT>
+static constexpr int kBoundRows = NT == 1 ? 16 : NT == 2 ? 32 : 64;
 // The selection needs most LDS of what a workgroup does, and how many of them a CU takes
 // hangs on it; so what comes before it stays below that: no tiles where the pass loads
 // straight, and those of the rescoring lie over all this, which is done with by then.
 // (With tiles for both in here, and three or four query tiles, 3 KB above it: 64 channels,
 // 2048 heads of 5000-5500 tokens, window 64, 745 us with three workgroups per CU, 626 with
 // four.)
-// rows that hold anything, rounded up to what one lane each at a renewal covers
-template <int NT>
-static constexpr int kBoundRows = NT == 1 ? 16 : NT == 2 ? 32 : 64;
 template <int WV, int ROWS, bool kHalf>
 struct BoundShared {
   float fin[64];                            // log2 of every row's soft-max denominator
