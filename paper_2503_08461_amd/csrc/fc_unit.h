@@ -558,11 +558,6 @@ struct PoolMaxLow {  // largest low half
   static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
   static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return max(a, b); }
 };
-struct PoolMinLow {  // smallest low half
-  static __device__ __forceinline__ uint32_t begin(uint32_t) { return 0xFFFFu; }
-  static __device__ __forceinline__ uint32_t get(uint32_t w) { return w & 0xFFFFu; }
-  static __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return min(a, b); }
-};
 
 // The pooling windows [c + e - h, c + e + h] of the four tokens c + e (c a
 // multiple of 4) over stage[0 .. n) and its margins: three 16-byte reads up to
@@ -1010,15 +1005,13 @@ __device__ __forceinline__ void select_unit(const BatchParams& p, const ReqDesc&
 // c_j min_i rho_i <= a_j <= c_j max_i rho_i.  Both numbers of a token
 // share its word of the LDS score array until the pass ends (c_j in the leading
 // 20 bits, s_j / c_j <= 1 in the other 12), so the bounds cost no memory traffic.
-// After the pass: bounds of the max-pooled scores, a lower and an upper bound of
-// the selection threshold from two histograms, and the tokens whose pooled
-// interval contains neither are decided without a second look.  For the others
-// the tokens of their pooling window that can carry the maximum are re-scored
-// exactly, row by row (256 bytes each), and everything else keeps its upper
-// bound: the plain selection that follows then returns exactly the set it
-// would return from exact scores (a decided-out token stays below the
-// threshold, a decided-in one above it, an undecided one carries its exact
-// pooled score; ties can only occur among those).
+// After the pass two histograms of the pooled bounds give T_lo <= T <= T_hi for the
+// selection's threshold T.  Only a token whose own interval reaches into
+// [T_lo, T_hi] is re-scored exactly, row by row (256 bytes each); every other one
+// keeps its upper bound.  The plain selection that follows then returns exactly the
+// set it would return from exact scores: a window that holds an unread token with a
+// lower bound above T_hi is above T either way, and in every other window the unread
+// tokens are below T_lo, so its maximum is exact or, like the exact one, below T_lo.
 //
 // The scores themselves are not produced (callers that ask for them take the
 // two-pass path).  A reference can be overtaken by more than the fp32 exponent
@@ -1439,10 +1432,18 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
 // Between the two: which prefix tokens need their exact column sum.  stage[]
 // holds the packed bounds; need[] is set (one bit per token), stage[j] of every
 // token becomes its upper bound.  Tokens are owned and pooled as in select_unit_h;
-// a sweep reads three 16-byte words per four tokens.  Which tokens are named is
-// found from the token's side: j is needed if some undecided token of its pooling
-// window has a pooled lower bound that j's upper bound reaches, i.e. if j's upper
-// bound is at least the least such lower bound of its window.
+// the histograms' sweep reads three 16-byte words per four tokens.
+//
+// What is named is read again, so the rule decides how much of K that is.  A token is
+// named if its own interval meets [T_lo, T_hi]: 9 % of the prefix rows of heads of 4096
+// tokens, window 64, a fifth kept, and 30 % at 900 tokens, half kept (fp64 model on
+// N(0,1) keys with four channels scaled by 8).  Naming whatever can carry the maximum of
+// an undecided window, also where that maximum lies below T_lo, named 16 and 44 %, and
+// took two sweeps over the windows more: 64 prompts of 1280-7040 tokens, 4 layers of 32
+// heads, 3154 -> 3066 us; one of 640 tokens, 32 layers, 83.3 -> 79.3.  A second histogram
+// after half of them are re-scored, and then the few that are still open, would name 5
+// and 19 %, but the further sweep, its barriers and the second wait for rows cost more
+// (3103 and 88 us).
 //
 // The selection's threshold is returned between two keys.
 template <bool kThree, int WV>
@@ -1533,49 +1534,33 @@ __device__ __forceinline__ void bound_classify_h(const ReqDesc& rd, uint32_t* st
     const uint32_t t_hi = kmin + (((uint32_t)bkt.y + 1u) << shift) - 1u;         // >= the threshold
     key_lo = t_lo | 0x80000000u;  // (score_key of a non-negative value)
     key_hi = t_hi | 0x80000000u;
-    // the low half of every undecided token's word becomes its pooled lower bound,
-    // of every other token's 0xFFFF
-    SegmentRewrite words;
-    words.run(stage, j0, j1, [&](int c) {
-      const PoolWindow<kThree> pw(stage, c, h, n_sel);
-      uint32_t hi[4], lo[4];
-      pw.template reduce<PoolMaxWord>(hi);
-      pw.template reduce<PoolMaxLow>(lo);
-      uint32x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (c + e >= j1 || (hi[e] & 0xFFFF0000u) < t_lo || (lo[e] << 16) > t_hi) lo[e] = 0xFFFFu;
-        w[e] = (pw.mid[e] & 0xFFFF0000u) | lo[e];
-      }
-      return w;
-    });
-    __syncthreads();  // the lower bounds have been read by everyone
-    words.finish(stage, j0, j1);
-    if (tid < kStageFront) stage[tid - kStageFront] = 0xFFFFu;
-    if (tid < 4) stage[((n_sel + 3) & ~3) + tid] = 0xFFFFu;  // (the last group's own words are set above)
-    __syncthreads();
+    // (own words only; the histograms' readers of a neighbour's have passed a barrier since)
     for (int base = j0; base < j1; base += kChunk) {  // uniform over the wavefront
       const int c = base + 4 * lane;
       uint32_t named = 0u;
       if (c < j1) {
-        const PoolWindow<kThree> pw(stage, c, h, n_sel);
-        uint32_t least[4];
-        pw.template reduce<PoolMinLow>(least);
+        uint32x4 w = lds_words4(stage + c);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e < j1 && (pw.mid[e] >> 16) >= least[e]) named |= 1u << e;
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t hi = w[e] & 0xFFFF0000u, lo = w[e] << 16;
+          if (c + e < j1 && hi >= t_lo && lo <= t_hi) named |= 1u << e;
+          w[e] = hi;
+        }
+        set_lds_words4(stage + c, w);
       }
       set_token_bits(need, base, named);
     }
-    __syncthreads();  // (the low halves are about to go)
   } else {
-    for (int base = j0; base < j1; base += kChunk) set_token_bits(need, base, 0u);
-  }
-  for (int c = j0 + 4 * lane; c < j1; c += kChunk) {
-    uint32x4 w = lds_words4(stage + c);
+    for (int base = j0; base < j1; base += kChunk) {
+      const int c = base + 4 * lane;
+      if (c < j1) {
+        uint32x4 w = lds_words4(stage + c);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
-    set_lds_words4(stage + c, w);
+        for (int e = 0; e < 4; ++e) w[e] &= 0xFFFF0000u;
+        set_lds_words4(stage + c, w);
+      }
+      set_token_bits(need, base, 0u);
+    }
   }
   __syncthreads();
 }

@@ -168,3 +168,37 @@ def test_hinted_ranges(driver, within):
             cases.append(Case(scores, above, 1, waves=waves, order=place,
                               hints=tuple(int(x) for x in score_keys([2.0, 3.0]))))
     check(driver, cases)
+
+
+def packed(lo, hi):
+    """Upper bounds rounded up, lower bounds down to their leading 16 bits, one word each."""
+    up = (np.asarray(hi, np.float32).view(np.uint32).astype(np.uint64) + 0xFFFF) >> 16
+    return (up << 16 | np.asarray(lo, np.float32).view(np.uint32) >> 16).astype(np.uint32)
+
+
+@pytest.mark.parametrize("waves", [4, 12, 16])
+@pytest.mark.parametrize("width", [1, 7, 9, 63])
+def test_selection_through_bounds(driver, waves, width):
+    """Bounds that are tight, loose, skewed or trivial, values that tie or span 2^60: with the named
+    tokens re-scored and upper bounds elsewhere, what is kept is what exact scores would keep, the
+    hinted keys enclose the threshold, and a token decided by its own bounds is not named."""
+    rng = np.random.default_rng(100 * waves + width)
+    cases, share = [], []
+    for i, n in enumerate([3, 40, 255, 256, 257, 600, 1025, 2049, 3600] * 3):
+        kinds = [np.exp(rng.normal(0, 1.5, n)), rng.integers(1, 9, n) / 8.0, 1.0 + rng.random(n) * 1e-5,
+                 2.0 ** rng.integers(-60, 3, n), np.ones(n), np.where(rng.random(n) < 0.01, 3.0, 1e-20 * rng.random(n))]
+        x = kinds[i % 6].astype(np.float32)
+        slack, skew = rng.random(n) * (0.0, 0.01, 0.3, 1.0)[i % 4], (0.05, 0.5, 0.95)[i % 3]
+        trivial = rng.random(n) < (0.0, 0.05, 0.0, 1.0)[(i + 1) % 4]
+        lo = np.minimum(np.where(trivial, 0.0, x * (1.0 - slack * skew)).astype(np.float32), x)
+        hi = np.maximum(np.where(trivial, 64.0, x * (1.0 + 3.0 * slack * (1.0 - skew))).astype(np.float32), x)
+        cases.append(Case(x, int(rng.integers(1, n)), width, waves=waves, order=i % 4, bounds=packed(lo, hi)))
+    for c, (key_lo, key_hi, kept, _, named) in zip(cases, run(driver, cases)):
+        final = pooled(c.scores, c.width)
+        np.testing.assert_array_equal(kept, np.concatenate([kept_tokens(final, c.k), len(final) + np.arange(c.window)]), str(c))
+        threshold = np.sort(score_keys(final))[-c.k]
+        assert key_lo <= threshold <= key_hi, c
+        up, low = score_keys((c.bounds & 0xFFFF0000).view(np.float32)), score_keys((c.bounds << 16).view(np.float32))
+        np.testing.assert_array_equal(named, (up >= key_lo) & (low <= key_hi), str(c))
+        share.append(named.mean())
+    assert min(share) < 0.1 and max(share) == 1.0
