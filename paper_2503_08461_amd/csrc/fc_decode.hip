@@ -200,18 +200,9 @@ __global__ __launch_bounds__(kThreads) void decode_attention_kernel(DecodeParams
     }
   };
   if constexpr (kCut) {
-    Rows x, y;
-    int b = b0 + wave;
-    if (b < b1) fetch(b, x);
-    while (b < b1) {
-      const int b2 = b + kWaves;
-      if (b2 < b1) fetch(b2, y);
-      attend(b, x);
-      if (b2 >= b1) break;
-      b = b2 + kWaves;
-      if (b < b1) fetch(b, x);
-      attend(b2, y);
-    }
+    stream_tiles<Rows>(
+        own_tiles(b1 - b0, wave, kWaves), [&](int i, Rows& x) { fetch(b0 + wave + kWaves * i, x); },
+        [&](int i, const Rows& x) { attend(b0 + wave + kWaves * i, x); });
   } else {
     for (int b = wave; b < nb; b += kWaves) {
       Rows x;

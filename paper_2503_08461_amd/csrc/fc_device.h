@@ -53,6 +53,16 @@ __device__ __forceinline__ void wave_lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The same value, made at this point: what is computed from it isn't kept from before a loop.
+__device__ __forceinline__ int made_here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// What stands before this point is issued before what follows (binds the compiler, which
+// would put requests for what comes next behind the wait for what is used now)
+__device__ __forceinline__ void requests_first() { __builtin_amdgcn_sched_barrier(0); }
+
 // the same register of another lane of the 16-lane row, by DPP control
 template <int CTRL>
 __device__ __forceinline__ float from_lane(float v) {
@@ -128,5 +138,38 @@ __device__ __forceinline__ void store_half8_nt(_Float16* p, half8 v) {
 __device__ __forceinline__ void store_half8(_Float16* p, half8 v) {
   *reinterpret_cast<half8*>(p) = v;
 }
+
+// Walks n tiles: load(i, tile) requests the i-th, use(i, tile) works on it
+// with the next one on its way.  The loop has no branch around a load and no copy between
+// the two buffers: after a branch the compiler waits for as few loads as either side left
+// in flight, and a copy waits for what it copies, so that with either of them a wavefront
+// waited for the tile that it had just asked for before it worked on the one it had.
+// The whole of a call, with that wait and without: one prompt of 640 tokens, 32 layers of 32
+// heads, 79.5 -> 70 us (5.9 us a head less in the first pass, 7 in the copy); 1024 heads of
+// 7000 tokens 813 -> 700; 2048 of 1500, 64 channels, 184 -> 155; 24 prompts of 500-6000
+// tokens with scores, 2 layers, 671 -> 635; 32 of 600-1200, 8 layers, 1037 -> 1009.
+template <typename Tile, typename Load, typename Use>
+__device__ __forceinline__ void stream_tiles(int n, Load load, Use use) {
+  if (n <= 0) return;  // uniform over the wavefront, as all conditions here
+  Tile a, b;
+  auto request = [&](int i, Tile& tile) {
+    load(i, tile);
+    requests_first();
+  };
+  load(0, a);
+  int i = 0;
+  for (; i + 2 < n; i += 2) {
+    request(i + 1, b);
+    use(i, a);
+    request(i + 2, a);
+    use(i + 1, b);
+  }
+  const bool two = i + 1 < n;
+  if (two) request(i + 1, b);
+  use(i, a);
+  if (two) use(i + 1, b);
+}
+// how many of n tiles a wavefront has, every `step`-th from its own on
+__device__ __forceinline__ int own_tiles(int n, int wave, int step) { return (n - wave + step - 1) / step; }
 
 }  // namespace fc

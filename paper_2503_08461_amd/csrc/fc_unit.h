@@ -228,42 +228,38 @@ __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc&
     m[nt] = -3.0e38f;
     z[nt] = 0.f;
   }
-  {
-    half8 kc[KS], kn[KS];
-    int b = b0 + wave;
-    if (b < b1) keys.template load<false>(ids[b], kc);
-    for (; b < b1; b += WV) {
-      if (b + WV < b1) keys.template load<false>(ids[b + WV], kn);
+  stream_tiles<half8[KS]>(
+      own_tiles(b1 - b0, wave, WV),
+      [&](int i, half8(&k)[KS]) { keys.template load<false>(ids[b0 + wave + WV * i], k); },
+      [&](int i, const half8(&kc)[KS]) {
+        const int b = b0 + wave + WV * i;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < NT; ++nt) {
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kc[ks], qreg[nt][ks], acc, 0, 0, 0);
-        float t[4];
+          for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kc[ks], qreg[nt][ks], acc, 0, 0, 0);
+          float t[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[r] = acc[r] * c;
-        if (b >= n_unmasked) {
-          // query i at position L-W+i sees tokens <= its own position
-          const int limit = L - W + nt * 16 + c16;
+          for (int r = 0; r < 4; ++r) t[r] = acc[r] * c;
+          if (b >= n_unmasked) {
+            // query i at position L-W+i sees tokens <= its own position
+            const int limit = L - W + nt * 16 + c16;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int tok = b * 16 + q4 * 4 + r;
-            if (tok > limit) t[r] = -INFINITY;
+            for (int r = 0; r < 4; ++r) {
+              const int tok = b * 16 + q4 * 4 + r;
+              if (tok > limit) t[r] = -INFINITY;
+            }
           }
+          const float bm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
+          const float mn = fmaxf(m[nt], bm);
+          float zz = z[nt] * __builtin_amdgcn_exp2f(m[nt] - mn);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) zz += __builtin_amdgcn_exp2f(t[r] - mn);
+          z[nt] = zz;
+          m[nt] = mn;
         }
-        const float bm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-        const float mn = fmaxf(m[nt], bm);
-        float zz = z[nt] * __builtin_amdgcn_exp2f(m[nt] - mn);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) zz += __builtin_amdgcn_exp2f(t[r] - mn);
-        z[nt] = zz;
-        m[nt] = mn;
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
-    }
-  }
+      });
   constexpr int kParts = ScoreShared<WV>::kParts;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -317,29 +313,26 @@ __device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDe
     for (int r = 0; r < 4; ++r) mrow[nt][r] = fin[nt * 16 + q4 * 4 + r];
   // from the end of the prefix backwards: the blocks that the first pass read
   // last are the ones most likely to be still in a cache
-  half8 kc[KS], kn[KS];
-  int b = b1 - 1 - wave;
-  if (b >= b0) keys.template load<true>(ids[b], kc);
-  for (; b >= b0; b -= WV) {
-    if (b - WV >= b0) keys.template load<true>(ids[b - WV], kn);
-    keys.arrange(kc);
-    float colsum = 0.f;
+  stream_tiles<half8[KS]>(
+      own_tiles(b1 - b0, wave, WV),
+      [&](int i, half8(&k)[KS]) { keys.template load<true>(ids[b1 - 1 - wave - WV * i], k); },
+      [&](int i, half8(&kc)[KS]) {
+        keys.arrange(kc);
+        float colsum = 0.f;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < NT; ++nt) {
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
+          for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
-    }
-    colsum = quarter_sum(colsum);
-    const int tok = b * 16 + c16;
-    if (q4 == 0 && tok < n_prefix) store(tok, colsum);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kc[ks] = kn[ks];
-  }
+          for (int r = 0; r < 4; ++r)
+            colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
+        }
+        colsum = quarter_sum(colsum);
+        const int tok = (b1 - 1 - wave - WV * i) * 16 + c16;
+        if (q4 == 0 && tok < n_prefix) store(tok, colsum);
+      });
 }
 
 // where a unit's window rows begin in the packed log-sum-exps
@@ -411,26 +404,31 @@ __device__ __forceinline__ void knorm_unit(const BatchParams& p, const ReqDesc& 
   const size_t blk_stride = (size_t)2 * p.n_heads * 16 * D;
   const _Float16* kbase = p.kv + (size_t)layer * p.n_blocks * blk_stride +
                           (size_t)head * 16 * D + lane * 8;
-  for (int b = b0 + wave; b < b1; b += WV) {
-    const int blk = clamp_block(old_ids[b], p.n_blocks);
-    const _Float16* kp = kbase + (size_t)blk * blk_stride;
-    half8 v[NI];
+  stream_tiles<half8[NI]>(
+      own_tiles(b1 - b0, wave, WV),
+      [&](int i, half8(&v)[NI]) {
+        const int blk = clamp_block(__builtin_amdgcn_readfirstlane(old_ids[b0 + wave + WV * i]), p.n_blocks);
+        const _Float16* kp = kbase + (size_t)blk * blk_stride;
 #pragma unroll
-    for (int k = 0; k < NI; ++k) v[k] = load_half8(kp + k * 512);
+        for (int k = 0; k < NI; ++k) v[k] = load_half8(kp + k * 512);
+      },
+      [&](int i, const half8(&v)[NI]) {
+        const int b = b0 + wave + WV * i;
 #pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      float s = 0.f;
+        for (int k = 0; k < NI; ++k) {
+          float s = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = (float)v[k][e];
-        s += x * x;
-      }
+          for (int e = 0; e < 8; ++e) {
+            const float x = (float)v[k][e];
+            s += x * x;
+          }
 #pragma unroll
-      for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o);
-      const int tok = b * 16 + k * RPI + lane / LPR;
-      if ((lane % LPR) == 0 && tok < L) store(tok, -sqrtf(s));
-    }
-  }
+          for (int o = 1; o < LPR; o <<= 1)  // (sums so far are equal in the lanes that a mirror exchanges)
+            s += o == 1 ? from_lane<0xB1>(s) : o == 2 ? from_lane<0x4E>(s) : o == 4 ? from_lane<0x141>(s) : from_lane<0x140>(s);
+          const int tok = b * 16 + k * RPI + lane / LPR;
+          if ((lane % LPR) == 0 && tok < L) store(tok, -sqrtf(s));
+        }
+      });
 }
 
 // ---------------------------------------------------------------------------
@@ -1113,8 +1111,9 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   const int nb = (L + 15) >> 4;
   const int n_prefix = L - W;
   const int n_unmasked = n_prefix >> 4;
-  auto load_even = [&](int b, half8 (&k)[KS]) { keys.template load<false>(old_ids[b], k); };
-  auto load_odd = [&](int b, half8 (&k)[KS]) { keys.template load<kHalf>(old_ids[b], k); };
+  // (past the end the last block again, so that no step branches around its request: stream_tiles)
+  auto load_even = [&](int b, half8 (&k)[KS]) { keys.template load<false>(old_ids[min(b, nb - 1)], k); };
+  auto load_odd = [&](int b, half8 (&k)[KS]) { keys.template load<kHalf>(old_ids[min(b, nb - 1)], k); };
 
   // Lane (q4, c16) holds the logits of token c16 of a block for the rows
   // 16 nt + 4 q4 + r: sums over the rows are in-lane adds, and row sums stay in
@@ -1125,12 +1124,16 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) z[nt][r] = 0.f;
-  // One row per lane at renewals: the row 16 nt + 4 q4 + r belongs to the lanes
+  // One row (my_row) per lane at renewals: the row 16 nt + 4 q4 + r belongs to the lanes
   // with c16 = 4 nt + r (modulo kRows), which is where the reduction below leaves
   // its sum.
   constexpr int kRows = NT == 1 ? 4 : NT == 2 ? 8 : 16;
-  const int my_slot = c16 & (kRows - 1);
-  const int my_row = (my_slot >> 2) * 16 + q4 * 4 + (my_slot & 3);
+  // (made anew at each renewal: kept through the loop, addresses of it were spilled, and a
+  // reload waits for all keys on their way)
+  auto row_of_lane = [&] {
+    const int l = made_here(lane), slot = l & (kRows - 1);
+    return (slot >> 2) * 16 + (l >> 4) * 4 + (slot & 3);
+  };
   float my_ref = 0.f, my_share = -INFINITY;  // its reference; log2 of this wavefront's sum so far
   // sums of z[][] over the 16 lanes of a DPP row: plain additions while there are
   // fewer values than lanes, then halving exchanges
@@ -1161,7 +1164,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     return (b0 ? v[1] : v[0]) + from_lane<0xB1>(b0 ? v[0] : v[1]);           // quad_perm [1,0,3,2]
   };
   // this wavefront's row sums so far, absolute log2 -> pub[buf]; starts new ones
-  auto publish = [&](int buf) {
+  auto publish = [&](int buf, int my_row) {
     const float zs = row_sums();
     // (a sum that is not a number stays one: see merged)
     const float l = zs == 0.f ? -INFINITY : my_ref + log2f(zs);
@@ -1236,13 +1239,15 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     if (q4 == 0 && tok < n_prefix) reinterpret_cast<uint32_t*>(stage)[tok] = pack_sums(cs, ss);
   };
   // one step: kc holds this wavefront's block b, kn takes the next one
-  auto step = [&](int t, half8 (&kc)[KS], half8 (&kn)[KS], auto load_next) {
+  auto step = [&](int t, half8 (&kc)[KS], auto load_next) {
     const int b = wave + WV * t;
-    if (b + WV < nb) load_next(b + WV, kn);
+    load_next(b + WV);
+    requests_first();
     keys.arrange(kc);
     if (bound_renews_before(t, seg)) {  // uniform over the workgroup
+      const int my_row = row_of_lane();
       if (t == 1) my_ref = bs.pub[buf][wave][my_row];
-      publish(buf);
+      publish(buf, my_row);
       __syncthreads();
       ++epoch;
       const float nr = merged(buf, my_row);
@@ -1255,20 +1260,22 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     }
     if (b < n_unmasked)  // uniform per wavefront
       numerators(std::integral_constant<int, 1>{}, b, kc);
-    else if (b < nb)
+    else  // (a block past the end is masked whole)
       numerators(std::integral_constant<int, 2>{}, b, kc);
   };
   static_assert(kBoundMinLen<WV> - 64 >= 16 * WV, "the first step lies before the window");
   half8 ka[KS], kb[KS];
   load_even(wave, ka);
-  if (wave + WV < nb) load_odd(wave + WV, kb);
+  load_odd(wave + WV, kb);
   keys.arrange(ka);
   numerators(std::integral_constant<int, 0>{}, wave, ka);
-  for (int t = 1; t < T; t += 2) {
-    step(t, kb, ka, load_even);
-    if (t + 1 < T) step(t + 1, ka, kb, load_odd);
+  int t = 1;
+  for (; t + 1 < T; t += 2) {
+    step(t, kb, [&](int b) { load_even(b, ka); });
+    step(t + 1, ka, [&](int b) { load_odd(b, kb); });
   }
-  publish(buf);
+  if (t < T) step(t, kb, [](int) {});
+  publish(buf, row_of_lane());
   __syncthreads();
   if (threadIdx.x < 64) {
     const int row = threadIdx.x;
@@ -1354,78 +1361,63 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
 // line anyhow, are not (2048 heads of 6500 tokens, four tiles: 969 straight, 995 us).
 template <int D, int NT>
 static constexpr bool kRescoreLines = D == 128 && NT > 1;
+// The tokens that a wavefront re-scores, taken from kWords words of the map at a time.
+template <int WV>
+struct RescoreLists {
+  static constexpr int kWords = WV == kNarrow ? 32 : 16;
+  uint16_t token[WV][kWords * 32];
+};
+template <int D, int NT, int WV>
+struct RescoreShared {
+  KeyTiles<WV, kRescoreLines<D, NT>> tiles;
+  RescoreLists<WV> lists;
+};
 template <int D, int NT, int WV>
 __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDesc& rd, int lh,
-                                               const int32_t* old_ids, const uint32_t* need,
-                                               float* stage, half8* tiles, half8 (&qreg)[NT][D / 32],
+                                               const int32_t* old_ids, const uint32_t* need, float* stage,
+                                               half8* tiles, RescoreLists<WV>& lists, half8 (&qreg)[NT][D / 32],
                                                const float (&mrow)[NT][4]) {
   constexpr int KS = D / 32;
+  constexpr int kWords = RescoreLists<WV>::kWords;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
   const KeyBlocks<D, WV, kRescoreLines<D, NT>> keys(p, lh, tiles);
   const float c = p.scale_log2e;
-  const int n_prefix = rd.seq_len - rd.window;
-  const int n_words = (n_prefix + 31) >> 5;
-  // Tiles of 16 named tokens (a wavefront walks its words of the bit map and
-  // fills a tile across them), the rows of the next tile requested before this
-  // one is multiplied.
-  int w = wave - WV;
-  uint32_t bits = 0u;
-  auto next_tile = [&](int& tok) -> bool {  // uniform over the wavefront
-    tok = -1;
-    int filled = 0;
-    while (filled < 16) {
-      while (bits == 0u) {
-        w += WV;
-        if (w >= n_words) return filled > 0;
-        bits = __builtin_amdgcn_readfirstlane(need[w]);
-      }
-#pragma unroll 1
-      for (; filled < 16 && bits; ++filled) {
-        const int pos = __ffs(bits) - 1;
-        bits &= bits - 1;
-        tok = c16 == filled ? (w << 5) + pos : tok;
-      }
-    }
-    return true;
-  };
-  auto load_rows = [&](int tok, half8 (&k)[KS]) {
-    // (a lane without a token reads the head's first row and drops the result)
-    keys.load_rows(max(tok, 0), old_ids, k);
-  };
-  half8 kc[KS], kn[KS], kf[KS];
-  int tok_c = -1, tok_n = -1, tok_f = -1;
-  bool have = next_tile(tok_c);
-  if (have) load_rows(tok_c, kc);
-  bool have_n = have && next_tile(tok_n);
-  if (have_n) load_rows(tok_n, kn);
-  while (have) {
-    const bool have_f = have_n && next_tile(tok_f);
-    if (have_f) load_rows(tok_f, kf);
-    keys.arrange(kc);
-    float colsum = 0.f;
+  const int n_words = (rd.seq_len - rd.window + 31) >> 5;
+  uint16_t* const list = lists.token[wave];
+  // A wavefront walks its words of the bit map, a lane each, lists the tokens they name in
+  // LDS and takes those sixteen at a time (found one after the other by scalar code, with
+  // their rows waited for as stream_tiles says, they took twice as long: 10.6 us of the 79
+  // that a head of 640 tokens spent, four heads on each CU, now 5.4).
+  for (int w0 = wave; w0 < n_words; w0 += WV * kWords) {  // uniform over the wavefront
+    const int w = w0 + WV * lane;
+    uint32_t bits = lane < kWords && w < n_words ? need[w] : 0u;
+    const int own = __popc(bits), upto = wave_scan_add(own);
+    const int n = __builtin_amdgcn_readlane(upto, 63);
+    for (int at = upto - own; bits; bits &= bits - 1, ++at) list[at] = (uint16_t)(w * 32 + __ffs(bits) - 1);
+    wave_lds_barrier();
+    // (the last tile's lanes without a token read the last row again and drop the result)
+    auto token = [&](int i) { return (int)list[min(16 * i + c16, n - 1)]; };
+    stream_tiles<half8[KS]>(
+        (n + 15) >> 4, [&](int i, half8(&k)[KS]) { keys.load_rows(token(i), old_ids, k); },
+        [&](int i, half8(&kc)[KS]) {
+          keys.arrange(kc);
+          float colsum = 0.f;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+          for (int nt = 0; nt < NT; ++nt) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
+            for (int ks = 0; ks < KS; ++ks)
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[nt][ks], kc[ks], acc, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
-    }
-    colsum = quarter_sum(colsum);
-    if (q4 == 0 && tok_c >= 0) stage[tok_c] = colsum;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kc[ks] = kn[ks];
-      kn[ks] = kf[ks];
-    }
-    tok_c = tok_n;
-    tok_n = tok_f;
-    have = have_n;
-    have_n = have_f;
+            for (int r = 0; r < 4; ++r) colsum += __builtin_amdgcn_exp2f(acc[r] * c - mrow[nt][r]);
+          }
+          colsum = quarter_sum(colsum);
+          if (q4 == 0 && 16 * i + c16 < n) stage[token(i)] = colsum;
+        });
+    wave_lds_barrier();
   }
 }
 
@@ -1628,7 +1620,7 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
   _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * chunk +
                    (lane % LPR) * 8;
   const int row_in_instr = lane / LPR;
-  auto load = [&](int nbk, half8 (&kk)[NI], half8 (&vv)[NI]) {
+  auto load = [&](int nbk, half8 (&kv)[2 * NI]) {  // keys, then values
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       // (slots past the budget load the last kept row again and drop it)
@@ -1636,11 +1628,11 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
       const int idx = min(max(kept_at(t), 0), rd.seq_len - 1);
       const int sblk = clamp_block(block_at(idx >> 4), p.n_blocks);
       const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
-      kk[k] = load_half8_nt(src);
-      vv[k] = load_half8_nt(src + v_off);
+      kv[k] = load_half8_nt(src);
+      kv[NI + k] = load_half8_nt(src + v_off);
     }
   };
-  auto store = [&](int nbk, const half8 (&kk)[NI], const half8 (&vv)[NI]) {
+  auto store = [&](int nbk, const half8 (&kv)[2 * NI]) {
     // freshly popped blocks, or the request's own first ones
     const int dblk = clamp_block(p.in_place ? block_at(nbk) : p.new_ids[rd.new_off + nbk], p.n_blocks);
     _Float16* dst = base + (size_t)dblk * blk_stride;
@@ -1648,13 +1640,13 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
     for (int k = 0; k < NI; ++k) {
       const int row = k * RPI + row_in_instr;
       if (nbk * 16 + row < B) {
-        store_half8_nt(dst + (size_t)row * D, kk[k]);
-        store_half8_nt(dst + (size_t)row * D + v_off, vv[k]);
+        store_half8_nt(dst + (size_t)row * D, kv[k]);
+        store_half8_nt(dst + (size_t)row * D + v_off, kv[NI + k]);
       }
     }
   };
-  half8 kc[NI], vc[NI];
   if (p.in_place) {
+    half8 kv[2 * NI];
     // Output t overwrites slot t while kept[t] >= t: a chunk of WV*16
     // outputs only reads slots at or after its own start, so reading the whole
     // chunk, a barrier, then writing it never destroys a row that is still
@@ -1662,24 +1654,15 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
     // (one workgroup then copies all blocks of a head)
     for (int c0 = nb0; c0 < nb1; c0 += WV) {
       const int nbk = c0 + wave;
-      if (nbk < nb1) load(nbk, kc, vc);
+      if (nbk < nb1) load(nbk, kv);
       __syncthreads();  // uniform: c0 and in_place are the same for all threads
-      if (nbk < nb1) store(nbk, kc, vc);
+      if (nbk < nb1) store(nbk, kv);
     }
     return;
   }
-  half8 kn[NI], vn[NI];
-  int nbk = nb0 + wave;
-  if (nbk < nb1) load(nbk, kc, vc);
-  for (; nbk < nb1; nbk += WV) {
-    if (nbk + WV < nb1) load(nbk + WV, kn, vn);
-    store(nbk, kc, vc);
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      kc[k] = kn[k];
-      vc[k] = vn[k];
-    }
-  }
+  stream_tiles<half8[2 * NI]>(
+      own_tiles(nb1 - nb0, wave, WV), [&](int i, half8(&kv)[2 * NI]) { load(nb0 + wave + WV * i, kv); },
+      [&](int i, const half8(&kv)[2 * NI]) { store(nb0 + wave + WV * i, kv); });
 }
 
 // The copy at the end of a fused kernel: the kept list is where the selection
@@ -1690,8 +1673,15 @@ __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc
                                              const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds) {
   const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
   const bool streaming = rd.method == 3 /* FC_METHOD_STREAMING */;  // uniform
-  gather_unit<D, WV>(p, rd, lh, 0, rd.n_new, [&](int i) { return ids_in_lds ? sm_ids[i] : p.old_ids[rd.old_off + i]; },
-                     [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
+  auto copy = [&](auto block_at) {
+    gather_unit<D, WV>(p, rd, lh, 0, rd.n_new, block_at,
+                       [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
+  };
+  // (a form for each place: an id from either of two comes by a load that waits for all others)
+  if (ids_in_lds)
+    copy([&](int i) { return sm_ids[i]; });
+  else
+    copy([&](int i) { return p.old_ids[rd.old_off + i]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -1786,7 +1776,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
     ScoreShared<WV> score;
     SelectShared<WV> select;
     BoundShared<WV, kBoundRows<NT>, kHalf> bound;
-    KeyTiles<WV, kRescoreLines<D, NT>> rescore;  // (the bounds and the classification are done with theirs)
+    RescoreShared<D, NT, WV> rescore;  // (the bounds and the classification are done with theirs)
   } sh;
   static_assert(WV != kNarrow || kTilesCost<NT, kHalf> || sizeof(sh) <= sizeof(SelectShared<WV>),
                 "the selection sets how many workgroups a CU takes");
@@ -1830,7 +1820,7 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
             for (int r = 0; r < 4; ++r) mrow[t][r] = sh.bound.fin[t * 16 + q4 * 4 + r];
           __syncthreads();  // the log-sum-exps are in registers: the selection's LDS may take over
           bound_classify<WV>(rd, words, map, sh.select, key_lo, key_hi);
-          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, sh.rescore.piece, qreg, mrow);
+          snapkv_rescore<D, N, WV>(p, rd, lh, sm_ids, map, stage, sh.rescore.tiles.piece, sh.rescore.lists, qreg, mrow);
         }
       });
     } else {
