@@ -156,6 +156,7 @@ struct fc_pool {
   int n_cu = 0;                   // compute units of the pool's device
   float* decode_partial = nullptr;  // states of the segments of a split decode attention
   int32_t* error_flag = nullptr;  // device, one int, zero unless a kernel found something wrong
+  int32_t* arrivals = nullptr;    // device, the int after it: zero between calls (BatchParams)
   int score_mode = FC_SCORE_AUTO;
   bool score_pruning = true;       // the fused kernel prunes the second pass of SnapKV units
   int n_sink = 4;
@@ -260,8 +261,9 @@ int fc_pool_create(fc_pool** out, void* kv_base, size_t kv_bytes, int n_blocks, 
   p->top = n_blocks;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->stack), (size_t)n_blocks * sizeof(int32_t));
   if (e == hipSuccess) e = launch_stack_init(p->stack, n_blocks, nullptr);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->error_flag), sizeof(int32_t));
-  if (e == hipSuccess) e = launch_zero_ints(p->error_flag, 1, nullptr);
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->error_flag), 2 * sizeof(int32_t));
+  if (e == hipSuccess) e = launch_zero_ints(p->error_flag, 2, nullptr);
+  p->arrivals = p->error_flag ? p->error_flag + 1 : nullptr;
   // (a fixed size, here and not on demand: no decode step waits for an allocation;
   // without it no head is cut into segments)
   if (e == hipSuccess &&
@@ -545,6 +547,19 @@ bool fits_inline(const fc_pool* p, const char* image, size_t bytes, MetaChunk* c
   return true;
 }
 
+// Whether a call of one request in one fused launch goes without plan_alloc (a call that is
+// timed kernel by kernel does not).  All kernels, with / without it in us: 4 heads of 256
+// tokens 22.3 / 17.6, 32 of 700 30.8 / 29.3, 256 of 1500 63.2 / 61.5 (key norms 45.4 / 44.0),
+// 1024 of 640 67.3 / 66.4; but 1024 of 2000 228.7 / 231.6 and of 7000 697 / 699, where the
+// taking back at the very end shows and the launch at the beginning does not, and streaming,
+// whose workgroups all come to their copy at once and queue at the counter, 25.2 / 25.9.
+// (Calls with scores, log-sum-exps or without pruning gain as little and have no kernels for it.)
+constexpr long long kOnlyMaxTokens = 1 << 20;  // of all heads
+bool needs_no_plan(const fc_pool* p, const ReqDesc& d) {
+  return !p->profiling && d.method != FC_METHOD_STREAMING &&
+         (long long)d.seq_len * p->n_layers * p->n_heads <= kOnlyMaxTokens;
+}
+
 // Whether the scratch of split heads is there, or can be had now.  A captured call
 // allocates nothing, and a size that was refused is not asked for again: each attempt
 // waits for the device.
@@ -671,6 +686,8 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   memcpy(image.data() + desc_bytes, lists.data(), lists.size() * sizeof(int32_t));
   MetaChunk inline_meta;
   const bool meta_inline = fits_inline(p, image.data(), meta_bytes, &inline_meta);
+  const bool only = meta_inline && n_comp == 1 && fused.size() == 1 && !separate && n_ids <= (size_t)kOnlyMaxIds &&
+                    (pruned_call || plan.descs[0].method == FC_METHOD_KNORM) && needs_no_plan(p, plan.descs[0]);
   if (!meta_inline && (rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK)
     return rc;
 
@@ -713,6 +730,11 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   bp.error_flag = p->error_flag;
   bp.owner = p->debug_checks ? p->owner : nullptr;
   bp.bounded = pruned_call ? 1 : 0;
+  if (only) {
+    bp.arrivals = p->arrivals;
+    const ReqDesc& d = plan.descs[0];
+    bp.only = {d.seq_len, d.budget, d.method, d.table_row, d.n_old, d.n_new, d.window, d.pool_kernel, d.q_off};
+  }
 
   if (p->debug_checks) {
     // the table rows that the stage will release: every id in range, handed out, named once
@@ -744,7 +766,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
     return e;
   };
   bp.main_reclaims = meta_inline ? 1 : 0;
-  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, true, [&] {
+  FC_HIP_STAGE(p, run(K_PLAN_ALLOC, !only, [&] {
     return launch_plan_alloc(bp, meta_inline ? &inline_meta : nullptr, (int)meta_bytes, stream);
   }));
   FC_HIP_STAGE(p, run(K_SNAPKV_SCORE, ns > 0, [&] {

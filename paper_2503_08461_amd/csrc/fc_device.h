@@ -21,27 +21,47 @@ __device__ __forceinline__ int clamp_block(int blk, int n_blocks) {
 }
 
 // Zombie reclaim of one request: pushes the pre-compression blocks (batch order, table
-// order) above the stack top left by plan_alloc and rewrites the table row.  From
-// plan_alloc on all kernels of the stage read the saved copies of the ids, nobody the
-// table or the stack, so one workgroup of a request may do this at any time after it.
-__device__ __forceinline__ void reclaim_request(const BatchParams& p, const ReqDesc& rd) {
-  const int tid = threadIdx.x, n_threads = blockDim.x;
+// order) above the stack top that the new blocks leave and rewrites the table row; old_ids
+// and new_ids: copies of what table and stack held.  With copies that plan_alloc made
+// nobody reads the table or the stack any more, so one workgroup of a request may do this
+// at any time after it.
+__device__ __forceinline__ void reclaim_request(const BatchParams& p, const ReqDesc& rd, const int32_t* old_ids,
+                                                const int32_t* new_ids, int tid, int n_threads) {
   int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
   if (p.in_place) {
     // the request keeps its first n_new blocks; the rest are released
     for (int i = tid; i < rd.n_old - rd.n_new; i += n_threads)
-      p.stack[p.top_before + rd.new_off + i] = p.old_ids[rd.old_off + rd.n_new + i];
+      p.stack[p.top_before + rd.new_off + i] = old_ids[rd.n_new + i];
     for (int i = rd.n_new + tid; i < p.max_blocks; i += n_threads) row[i] = -1;
     if (p.owner)  // (ids checked before the stage: in range, claimed)
-      for (int i = tid; i < rd.n_old; i += n_threads) p.owner[p.old_ids[rd.old_off + i]] = i < rd.n_new ? 1 : 0;
+      for (int i = tid; i < rd.n_old; i += n_threads) p.owner[old_ids[i]] = i < rd.n_new ? 1 : 0;
     return;
   }
   const int base = p.top_before - p.total_new;
   for (int i = tid; i < rd.n_old; i += n_threads) {
-    p.stack[base + rd.old_off + i] = p.old_ids[rd.old_off + i];
-    if (p.owner) p.owner[p.old_ids[rd.old_off + i]] = 0;  // (checked before the stage)
+    p.stack[base + rd.old_off + i] = old_ids[i];
+    if (p.owner) p.owner[old_ids[i]] = 0;  // (checked before the stage)
   }
-  for (int i = tid; i < p.max_blocks; i += n_threads) row[i] = (i < rd.n_new) ? p.new_ids[rd.new_off + i] : -1;
+  for (int i = tid; i < p.max_blocks; i += n_threads) row[i] = (i < rd.n_new) ? new_ids[i] : -1;
+}
+__device__ __forceinline__ void reclaim_request(const BatchParams& p, const ReqDesc& rd) {
+  reclaim_request(p, rd, p.old_ids + rd.old_off, p.new_ids + rd.new_off, threadIdx.x, blockDim.x);
+}
+
+// Loads of what no lane of the launch writes, from a uniform address: scalar loads.
+// (Next to the kernel's own stores the compiler takes vector loads, and whatever
+// waits for one of those waits for all pool rows in flight.)
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+  typedef const __attribute__((address_space(4))) int32_t* ConstWords;
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  union {
+    T value;
+    int32_t words[sizeof(T) / 4];
+  } u;
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) u.words[i] = ((ConstWords)(uintptr_t)p)[i];
+  return u.value;
 }
 
 // LDS accesses of a wavefront's lanes before and after this point stay in that order

@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   int nb0, nb1;
   split_range(p, u.seg, u.rd.n_new, nb0, nb1);
   gather_unit<D, kWaves>(p, u.rd, u.lh, nb0, nb1, [&](int i) { return p.old_ids[u.rd.old_off + i]; },
-                         [&](int t) { return kept[t]; });
+                         [&](int i) { return p.new_ids[u.rd.new_off + i]; }, [&](int t) { return kept[t]; });
 }
 
 // a fill kernel for small device arrays (flags, verdict words): calls may be
@@ -471,7 +471,8 @@ hipError_t launch_fused(BatchParams p, int query_tiles, int max_seq_len, int max
   const FusedLds f = fused_lds(max_seq_len, max_blocks, wide);
   p.ids_at = f.ids_at;
   p.ids_room = f.ids_room;
-  const size_t lds = (size_t)f.words * sizeof(uint32_t);
+  p.new_ids_at = f.words;  // (a call of one request without plan_alloc)
+  const size_t lds = (size_t)(f.words + (p.arrivals ? (p.only.n_new + 3) & ~3 : 0)) * sizeof(uint32_t);
   if (p.head_dim == 128)
     return wide ? launch_fused_wide_128(p, query_tiles, lds, s) : launch_fused_narrow_128(p, query_tiles, lds, s);
   if (p.head_dim == 64)

@@ -171,22 +171,6 @@ __device__ __forceinline__ float mlp_activation(float v) {
   return ACT == 0 ? gelu_erf(v) : gelu_tanh(v);
 }
 
-// Loads of what no lane of the launch writes, from a uniform address: scalar loads.
-// (Next to the kernel's own stores the compiler takes vector loads, and whatever
-// waits for one of those waits for all pool rows in flight.)
-template <typename T>
-__device__ __forceinline__ T load_uniform(const T* p) {
-  typedef const __attribute__((address_space(4))) int32_t* ConstWords;
-  static_assert(sizeof(T) % 4 == 0, "whole words");
-  union {
-    T value;
-    int32_t words[sizeof(T) / 4];
-  } u;
-#pragma unroll
-  for (size_t i = 0; i < sizeof(T) / 4; ++i) u.words[i] = ((ConstWords)(uintptr_t)p)[i];
-  return u.value;
-}
-
 // 16 bytes a lane from memory to LDS: `to` is the wavefront's, lane l's piece goes to
 // to[l].  (A buffer load: of a global one the compiler assumes that it may touch LDS
 // out of order, and waits for everything at the next use of any load.)

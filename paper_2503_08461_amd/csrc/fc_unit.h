@@ -1597,15 +1597,16 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 // (16 output slots) at a time for K and V.  D/8 lanes move one row with
 // 128-bit accesses, so a wavefront instruction moves 64/(D/8) rows; the
 // destination chunk is contiguous.  kept_at(t) is the token that goes to slot t;
-// the workgroup fills the new blocks [nb0, nb1).
+// block_at(i) and new_at(i) are the request's i-th old and new block; the workgroup fills
+// the new blocks [nb0, nb1).
 //
 // Bound by HBM when the chip is full and by the latency of one block's chain
 // (kept index, block id, row) when it is not; the rows of a wavefront's next
 // block are therefore requested before those of this one are stored.
 
-template <int D, int WV, typename BlockAt, typename KeptAt>
+template <int D, int WV, typename BlockAt, typename NewAt, typename KeptAt>
 __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            int nb0, int nb1, BlockAt block_at, KeptAt kept_at) {
+                                            int nb0, int nb1, BlockAt block_at, NewAt new_at, KeptAt kept_at) {
   constexpr int LPR = D / 8;
   constexpr int RPI = 64 / LPR;
   constexpr int NI = 16 / RPI;
@@ -1634,7 +1635,7 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
   };
   auto store = [&](int nbk, const half8 (&kv)[2 * NI]) {
     // freshly popped blocks, or the request's own first ones
-    const int dblk = clamp_block(p.in_place ? block_at(nbk) : p.new_ids[rd.new_off + nbk], p.n_blocks);
+    const int dblk = clamp_block(p.in_place ? block_at(nbk) : new_at(nbk), p.n_blocks);
     _Float16* dst = base + (size_t)dblk * blk_stride;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
@@ -1668,13 +1669,18 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
 // The copy at the end of a fused kernel: the kept list is where the selection
 // left it in LDS, streaming units compute theirs; ids_in_lds: sm_ids holds the
 // block ids (streaming units may have more blocks than fit).
-template <int D, int WV>
+template <int D, int WV, bool kOnly>
 __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc& rd, int lh,
-                                             const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds) {
+                                             const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds,
+                                             const int32_t* sm_new) {
   const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
   const bool streaming = rd.method == 3 /* FC_METHOD_STREAMING */;  // uniform
   auto copy = [&](auto block_at) {
     gather_unit<D, WV>(p, rd, lh, 0, rd.n_new, block_at,
+                       [&](int i) {
+                         if constexpr (kOnly) return sm_new[i];
+                         else return p.new_ids[rd.new_off + i];
+                       },
                        [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
   };
   // (a form for each place: an id from either of two comes by a load that waits for all others)
@@ -1715,28 +1721,94 @@ __device__ __forceinline__ void for_query_tiles(int window, F f) {
   }
 }
 
-template <int D, int NT, int WV>
-__global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
+// kOnly: a call of one request whose only launch this is, without plan_alloc and without a
+// reclaim launch.  Its workgroups read the table and the stack themselves, and the last one
+// that says so (behind a barrier after which nothing of either is left to read; the count
+// only orders those reads before the writes, no data passes through it) writes them anew
+// when its own copy is under way.  A launch is 2.5 to 3 us of the host's time, and
+// plan_alloc, which the main kernel waited for, about 2 of the GPU's (needs_no_plan has
+// what that gives and where it stops).  Counted when the ids have been read instead, so
+// that not the last one writes, the counts of all workgroups come at once and stand before
+// their keys: one prompt of 640 tokens, 1024 heads, 66.4 -> 73.7 us.  Kernels of their own:
+// as a branch in those of all calls it cost these up to 3 % (registers).
+template <bool kOnly>
+__device__ __forceinline__ ReqDesc fused_request(const BatchParams& p, int slot) {
+  if constexpr (kOnly) {
+    ReqDesc rd = {};
+    rd.seq_len = p.only.seq_len;
+    rd.budget = p.only.budget;
+    rd.method = p.only.method;
+    rd.table_row = p.only.table_row;
+    rd.n_old = p.only.n_old;
+    rd.n_new = p.only.n_new;
+    rd.q_off = p.only.q_off;
+    rd.window = p.only.window;
+    rd.pool_kernel = p.only.pool_kernel;
+    return rd;
+  } else {
+    return p.descs[p.order_fused[slot]];
+  }
+}
+// The request's block ids to LDS; false: they stay where plan_alloc left them.
+template <int WV, bool kOnly>
+__device__ __forceinline__ bool stage_block_ids(const BatchParams& p, const ReqDesc& rd, int lh, int32_t* sm_ids,
+                                                int32_t* sm_new) {
+  if constexpr (kOnly) {
+    const int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
+    if (!p.in_place)
+      for (int i = threadIdx.x; i < rd.n_new; i += 64 * WV) sm_new[i] = p.stack[p.top_before - 1 - i];
+    for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV) sm_ids[i] = clamp_block(row[i], p.n_blocks);
+    return true;  // (kOnlyMaxIds: there is room)
+  } else {
+    if (p.main_reclaims && lh == 0) reclaim_request(p, rd);
+    const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
+    if (ids_in_lds)
+      for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV)
+        sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
+    return ids_in_lds;
+  }
+}
+// How many workgroups came here before (the first wavefront's).
+__device__ __forceinline__ int arrive(const BatchParams& p) {
+  int before = -1;
+  if (threadIdx.x < 64) {
+    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(p.arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = __builtin_amdgcn_readfirstlane(before);
+  }
+  return before;
+}
+// (one wavefront; ids: room for all of them, nobody else's any more)
+__device__ __forceinline__ void reclaim_only(const BatchParams& p, const ReqDesc& rd, int32_t* ids) {
+  const int lane = threadIdx.x;
+  const int32_t* row = p.block_tables + (size_t)rd.table_row * p.max_blocks;
+  for (int i = lane; i < rd.n_old; i += 64) ids[i] = row[i];
+  if (!p.in_place)
+    for (int i = lane; i < rd.n_new; i += 64) ids[rd.n_old + i] = p.stack[p.top_before - 1 - i];
+  wave_lds_barrier();
+  reclaim_request(p, rd, ids, ids + rd.n_old, lane, 64);
+  if (lane == 0) __hip_atomic_store(p.arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int D, int NT, int WV, bool kOnly>
+__device__ __forceinline__ void fused_unit(const BatchParams& p) {
   extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
     ScoreShared<WV> score;
     SelectShared<WV> select;
+    int32_t ids[kOnlyMaxIds];
   } sh;
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
-  const ReqDesc rd = p.descs[p.order_fused[slot]];
+  const ReqDesc rd = fused_request<kOnly>(p, slot);
   uint32_t* words = lds + kStageFront;
   float* stage = reinterpret_cast<float*>(words);
   uint32_t* map = lds + stage_words(rd.seq_len);  // one bit per token
   // the request's block ids, read once per workgroup (every later use is an LDS read)
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
-  if (p.main_reclaims && lh == 0) reclaim_request(p, rd);
-  const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
-  if (ids_in_lds)
-    for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV)
-      sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
+  int32_t* sm_new = reinterpret_cast<int32_t*>(lds + p.new_ids_at);
+  const bool ids_in_lds = stage_block_ids<WV, kOnly>(p, rd, lh, sm_ids, sm_new);
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
     streaming_unit<WV>(p, rd, lh, kept);
@@ -1754,7 +1826,21 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
     select_unit<WV>(p, rd, lh, words, map, kept, sh.select);
   }
   __syncthreads();  // the kept list is complete
-  gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
+  if constexpr (kOnly) {
+    const int arrived = arrive(p);
+    gather_fused<D, WV, true>(p, rd, lh, words, sm_ids, true, sm_new);
+    if (arrived == (int)gridDim.x - 1) reclaim_only(p, rd, sh.ids);
+  } else {
+    gather_fused<D, WV, false>(p, rd, lh, words, sm_ids, ids_in_lds, sm_new);
+  }
+}
+template <int D, int NT, int WV>
+__global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
+  fused_unit<D, NT, WV, false>(p);
+}
+template <int D, int WV>  // (of a scored request, key norms: the others are pruned)
+__global__ __launch_bounds__(64 * WV) void fused_unit_only_kernel(BatchParams p) {
+  fused_unit<D, 0, WV, true>(p);
 }
 
 // Wavefronts per SIMD that the registers must allow: what the kernel needs without
@@ -1769,14 +1855,15 @@ __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
 // snapkv_bounds); key-norm and streaming units that ride in the launch run as in
 // fused_unit_kernel.  Dynamic LDS: the scores, then one bit per token, then the
 // block ids.
-template <int D, int NT, int WV, bool kHalf>
-__global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_bounded_kernel(BatchParams p) {
+template <int D, int NT, int WV, bool kHalf, bool kOnly>
+__device__ __forceinline__ void fused_bounded(const BatchParams& p) {
   extern __shared__ __align__(16) uint32_t lds[];
   __shared__ union {
     ScoreShared<WV> score;
     SelectShared<WV> select;
     BoundShared<WV, kBoundRows<NT>, kHalf> bound;
     RescoreShared<D, NT, WV> rescore;  // (the bounds and the classification are done with theirs)
+    int32_t ids[kOnlyMaxIds];
   } sh;
   static_assert(WV != kNarrow || kTilesCost<NT, kHalf> || sizeof(sh) <= sizeof(SelectShared<WV>),
                 "the selection sets how many workgroups a CU takes");
@@ -1784,17 +1871,14 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
   const int n_lh = p.n_layers * p.n_heads;
   const int slot = blockIdx.x / n_lh;
   const int lh = blockIdx.x - slot * n_lh;
-  const ReqDesc rd = p.descs[p.order_fused[slot]];
+  const ReqDesc rd = fused_request<kOnly>(p, slot);
   uint32_t* words = lds + kStageFront;  // per token: its bounds, then its score
   float* stage = reinterpret_cast<float*>(words);
   uint32_t* map = lds + stage_words(rd.seq_len);  // one bit per token
   int32_t* sm_ids = reinterpret_cast<int32_t*>(lds + p.ids_at);
   int32_t* kept = p.kept_out ? p.kept_out + rd.kept_off + (size_t)lh * rd.budget : nullptr;
-  if (p.main_reclaims && lh == 0) reclaim_request(p, rd);
-  const bool ids_in_lds = rd.n_old <= p.ids_room;  // streaming units may be longer
-  if (ids_in_lds)
-    for (int i = threadIdx.x; i < rd.n_old; i += 64 * WV)
-      sm_ids[i] = clamp_block(p.old_ids[rd.old_off + i], p.n_blocks);
+  int32_t* sm_new = reinterpret_cast<int32_t*>(lds + p.new_ids_at);
+  const bool ids_in_lds = stage_block_ids<WV, kOnly>(p, rd, lh, sm_ids, sm_new);
   if (threadIdx.x == 0) keep.bad = 0;
   __syncthreads();
   if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
@@ -1830,7 +1914,21 @@ __global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_b
     select_unit<WV>(p, rd, lh, words, map, kept, sh.select, key_lo, key_hi);
   }
   __syncthreads();  // the kept list is complete
-  gather_fused<D, WV>(p, rd, lh, words, sm_ids, ids_in_lds);
+  if constexpr (kOnly) {
+    const int arrived = arrive(p);
+    gather_fused<D, WV, true>(p, rd, lh, words, sm_ids, true, sm_new);
+    if (arrived == (int)gridDim.x - 1) reclaim_only(p, rd, sh.ids);
+  } else {
+    gather_fused<D, WV, false>(p, rd, lh, words, sm_ids, ids_in_lds, sm_new);
+  }
+}
+template <int D, int NT, int WV, bool kHalf>
+__global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_bounded_kernel(BatchParams p) {
+  fused_bounded<D, NT, WV, kHalf, false>(p);
+}
+template <int D, int NT, int WV>
+__global__ __launch_bounds__(64 * WV, bounded_occupancy(D, NT, WV)) void fused_bounded_only_kernel(BatchParams p) {
+  fused_bounded<D, NT, WV, false, true>(p);
 }
 
 // what a wide workgroup may ask for next to its static LDS
@@ -1854,6 +1952,13 @@ template <int D, int NT, bool kWideShape>
 static void launch_fused_one(const BatchParams& p, size_t lds, hipStream_t s) {
   constexpr int WV = kWideShape ? kWide<D, NT> : kNarrow;
   const unsigned grid = (unsigned)p.n_fused * p.n_layers * p.n_heads;
+  if (p.arrivals) {
+    if constexpr (NT == 0)
+      fused_unit_only_kernel<D, WV><<<grid, 64 * WV, lds, s>>>(p);
+    else if constexpr (NT < kMixedTiles)
+      fused_bounded_only_kernel<D, NT, WV><<<grid, 64 * WV, lds, s>>>(p);
+    return;
+  }
   if constexpr (NT > 0) {
     if (p.bounded) {
       if constexpr (kHasHalfReuse<D, WV>) {
@@ -1896,6 +2001,11 @@ static hipError_t wide_setup_one() {
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_bounded_kernel<D, NT, WV, false>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  // (the kernels without plan_alloc stay below the 64 KB that need no setting: kOnlyMaxIds)
+  static_assert(4 * (fused_lds(kOnlyMaxIds * kPlanBlockSize, kOnlyMaxIds, true).words + kOnlyMaxIds) +
+                        (int)sizeof(BoundShared<WV, kBoundRows<NT>, false>) + 64 <= 64 * 1024 &&
+                    4 * (fused_lds(kOnlyMaxIds * kPlanBlockSize, kOnlyMaxIds, true).words + kOnlyMaxIds) +
+                        (int)sizeof(SelectShared<WV>) + 64 <= 64 * 1024, "LDS of a request without plan_alloc");
   return e;
 }
 

@@ -78,3 +78,31 @@ def test_captured_decode_step(n_req):
             assert torch.equal(out, want)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("L,B,method,n_heads", [
+    (16, 16, fo.METHOD_SNAPKV, 1),       # everything kept, one block
+    (300, 77, fo.METHOD_SNAPKV, 4),      # narrow workgroups, two passes
+    (700, 300, fo.METHOD_SNAPKV, 300),   # more than one head a CU
+    (700, 300, fo.METHOD_KNORM, 5),      # wide
+    (1500, 400, fo.METHOD_SNAPKV, 140),  # wide
+    (6000, 2176, fo.METHOD_SNAPKV, 136),  # 375 + 136 ids: fits
+    (6000, 2192, fo.METHOD_SNAPKV, 136),  # 512 ids: just
+    (6000, 2193, fo.METHOD_SNAPKV, 136),  # 513: has a plan_alloc
+    (700, 300, fo.METHOD_STREAMING, 3),  # has one
+])
+def test_one_request(L, B, method, n_heads, in_place):
+    """A call of one request reads table and stack itself and writes both at its end, whichever row
+    of the table it has; call after call on one pool, also between calls of several requests."""
+    from parity_util import SideBySide
+    lens = [40, L, 33]
+    s = SideBySide(_custom(lens, [20, B, 20], [method] * 3, W=16, d=64, n_heads=n_heads), in_place=in_place)
+    try:
+        for only in (1, 1, None, 0, 2):
+            methods = np.full(3, fo.METHOD_NONE, np.int32)
+            methods[slice(None) if only is None else only] = method
+            budgets = np.maximum(16, np.minimum(s.lens_o, [20, B, 20]) - (only is None)).astype(np.int32)
+            s.compress_and_compare(methods, budgets)
+    finally:
+        s.close()
