@@ -66,19 +66,20 @@ __host__ __device__ constexpr int bound_max_epochs() {
   const int b = 1 + bound_epoch_of_step((full / 16 + WV - 1) / WV, bound_seg<WV>(full));
   return a > b ? a : b;
 }
-// Shorter heads take the two passes: the tokens of the first step have no bounds,
-// and a step of a wide workgroup is three to four times as many tokens.  What the
-// line is worth depends on where the second pass would find K.  All kernels of a
-// call of one layer or four, whose K mostly stays in the memory-side cache, two
-// passes / pruned in us, window 32:
-//   narrow, 1024 heads, 128 channels   512 tokens  79.6 / 80.7   1024  145 / 128   2048  292 / 240
-//                        64 channels               51.2 / 65.5         83 / 94           146 / 153
-//   wide, 256 heads,    128 channels  1024 tokens  53.7 / 61.8   2048   84 / 86    3000  117 / 108
-//                        64 channels               39.5 / 50.3          52 / 68           67 / 83
-// With a pool of 32 layers, where it has to come from HBM again, 32 prompts of
-// 600-1200 tokens take 3.6 to 4.0 ms pruned and 3.7 to 4.2 unpruned, by process.
-template <int WV>
-static constexpr int kBoundMinLen = WV == kNarrow ? 512 : 2048;
+// Shorter heads take the two passes: the tokens of the first step have no bounds, and a
+// step of a wide workgroup is three to four times as many tokens; bounding costs the same
+// next to rows of 128 bytes as next to rows of 256.  All kernels of a call, window 32, two
+// passes / pruned in us; the heads are of a few prompts, whose K mostly stays in the
+// memory-side cache, but for those of 16 prompts, 32 layers, whose K does not:
+//   narrow, 1024 heads, 128 channels  400 tokens 52.7 / 54.1   512   64.9 / 59.4   640   79.5 / 68.2
+//                        64 channels  512        38.5 / 44.7   700   48.0 / 51.6  1024   66.6 / 62.8
+//           16384 heads, 64 channels  512         414 / 429    700    560 / 551   1024    832 / 769
+//   wide, 256 heads,    128 channels 1024        46.5 / 48.6  1400   58.1 / 58.0  1500   61.2 / 59.3
+//                        64 channels 2048        45.2 / 48.6  3000   58.8 / 61.1  4500   86.3 / 83.9
+//   wide, 512 heads, window 64: 128 channels 1400 115.1 / 114.5, 1800 125.1 / 122.7 (384 heads);
+//                               64 channels 4500 163.3 / 169.7; narrow, 16384 heads 700 613 / 657
+template <int D, int WV>
+static constexpr int kBoundMinLen = WV == kNarrow ? (D == 128 ? 512 : 800) : (D == 128 ? 1408 : 4096);
 
 // A block's keys of one (layer, head), from memory to the operand layout of the
 // products: k[ks] of lane (q4, c16) = channels [32 ks + 8 q4, +8) of token c16.
@@ -1263,7 +1264,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     else  // (a block past the end is masked whole)
       numerators(std::integral_constant<int, 2>{}, b, kc);
   };
-  static_assert(kBoundMinLen<WV> - 64 >= 16 * WV, "the first step lies before the window");
+  static_assert(kBoundMinLen<D, WV> - 64 >= 16 * WV, "the first step lies before the window");
   half8 ka[KS], kb[KS];
   load_even(wave, ka);
   load_odd(wave + WV, kb);
@@ -1355,21 +1356,21 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
 
 // Exact column sums of the tokens named by need[] (one bit per prefix token),
 // row by row -> stage[].  mrow: the rows' log-sum-exps as the second product
-// leaves the rows in registers.  Rows of 256 bytes are fetched in whole lines unless
-// the registers of one query tile are short of it (8192 heads of 700 tokens: 606 -> 593
-// us with two tiles, 697 -> 681 with four, 576 -> 614 with one); rows of 128 bytes, one
-// line anyhow, are not (2048 heads of 6500 tokens, four tiles: 969 straight, 995 us).
-template <int D, int NT>
-static constexpr bool kRescoreLines = D == 128 && NT > 1;
+// leaves the rows in registers.  Rows of 256 bytes are fetched in whole lines (8192 heads of
+// 700 tokens: 606 -> 593 us with two query tiles, 697 -> 681 with four, 563 -> 560 with one);
+// rows of 128 bytes, one line anyhow, are not (2048 heads of 6500 tokens, four tiles: 969
+// straight, 995 us).
+template <int D>
+static constexpr bool kRescoreLines = D == 128;
 // The tokens that a wavefront re-scores, taken from kWords words of the map at a time.
 template <int WV>
 struct RescoreLists {
   static constexpr int kWords = WV == kNarrow ? 32 : 16;
   uint16_t token[WV][kWords * 32];
 };
-template <int D, int NT, int WV>
+template <int D, int WV>
 struct RescoreShared {
-  KeyTiles<WV, kRescoreLines<D, NT>> tiles;
+  KeyTiles<WV, kRescoreLines<D>> tiles;
   RescoreLists<WV> lists;
 };
 template <int D, int NT, int WV>
@@ -1383,7 +1384,7 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
-  const KeyBlocks<D, WV, kRescoreLines<D, NT>> keys(p, lh, tiles);
+  const KeyBlocks<D, WV, kRescoreLines<D>> keys(p, lh, tiles);
   const float c = p.scale_log2e;
   const int n_words = (rd.seq_len - rd.window + 31) >> 5;
   uint16_t* const list = lists.token[wave];
@@ -1862,7 +1863,7 @@ __device__ __forceinline__ void fused_bounded(const BatchParams& p) {
     ScoreShared<WV> score;
     SelectShared<WV> select;
     BoundShared<WV, kBoundRows<NT>, kHalf> bound;
-    RescoreShared<D, NT, WV> rescore;  // (the bounds and the classification are done with theirs)
+    RescoreShared<D, WV> rescore;  // (the bounds and the classification are done with theirs)
     int32_t ids[kOnlyMaxIds];
   } sh;
   static_assert(WV != kNarrow || kTilesCost<NT, kHalf> || sizeof(sh) <= sizeof(SelectShared<WV>),
@@ -1892,7 +1893,7 @@ __device__ __forceinline__ void fused_bounded(const BatchParams& p) {
         const int q4 = (threadIdx.x & 63) >> 4;
         half8 qreg[N][KS];
         load_window_queries<D, N>(p, rd, lh, qreg);
-        const bool prune = rd.seq_len >= kBoundMinLen<WV>;  // uniform
+        const bool prune = rd.seq_len >= kBoundMinLen<D, WV>;  // uniform
         if (prune) snapkv_bounds<D, N, WV, kHalf>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
         if (!prune || keep.bad) {  // bad: not representable against a running reference
           snapkv_unit_q<D, N, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });

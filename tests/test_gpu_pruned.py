@@ -301,3 +301,17 @@ def test_random_long_batches(seed):
     wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=int(rng.integers(1, 3)), seed=300 + seed)
     print("seed", seed, lens, budgets, methods, W, d, flush=True)
     _run_pruned(wl, pool_kernel=int(rng.choice([1, 5, 7, 9])))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [895, 4095, 4096, 4097, 8160, 8193, 16385])
+def test_every_row_is_read_again(n, d):
+    """Scores that are all alike: every prefix token is named.  Prefixes around what a wavefront
+    lists at a time (32 words of the bit map, 16 in wide workgroups, every 4th to 16th its own),
+    last tiles of 1 and of 16 tokens."""
+    if d == 128 and n > 8200:
+        n += 15  # (a last tile of another size)
+    wl = _custom([n + 32], [n // 5 + 32], [fo.METHOD_SNAPKV], W=32, d=d, n_heads=1)
+    q = np.zeros((wl.n_req, 1, 1, 32, d), dtype=np.float16)
+    out = _run_pruned(wl, sbs_kw={"q_host": q})
+    assert out[0]["units_kept_identical"] == out[0]["units"]
