@@ -17,6 +17,12 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # no packed-fp32 instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # Small arrays (operands of the matrix products, rows in flight) become registers of their own,
+    # not one wide value that moves as a whole: as <48 x half> the window's operands of three query
+    # tiles, 64 channels, took 132 registers where four tiles take 112, now 92.  16 prompts of
+    # 200-480 tokens, 4 layers of 32 heads, window 48, with scores 60.4 -> 52.2 us; log-sum-exps
+    # alone, 600-1300 tokens, 49.9 -> 45.8; without scores, windows 1-64, 128 channels 103.9 -> 93.0.
+    "-mllvm", "-disable-promote-alloca-to-vector",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

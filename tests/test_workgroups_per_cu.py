@@ -84,6 +84,17 @@ def test_pruned_kernels(tmp_path):
             assert half == (per_cu(half_lds, vgprs, max_len, max_blocks) == per_cu(select + KEEP, vgprs, max_len, max_blocks))
 
 
+def test_registers_grow_with_the_query_tiles(tmp_path):
+    """A kernel for fewer query tiles needs no more registers than the next one (as it does where the
+    compiler keeps an array of operands as one wide value)."""
+    built = kernels(tmp_path)
+    for family in ("17fused_unit_kernelILi%dELi%dELi4E", "19snapkv_score_kernelILi%dELi%dE",
+                   "17split_rows_kernelILi%dELi%dE", "19split_scores_kernelILi%dELi%dE"):
+        for d in (64, 128):
+            vgprs = [built["_ZN2fc" + family % (d, tiles) + "EEvNS_11BatchParamsE"][1] for tiles in (1, 2, 3, 4)]
+            assert vgprs == sorted(vgprs), (family, d, vgprs)
+
+
 def test_kernel_names_of_the_benchmark(tmp_path):
     """The names that the benchmark prints are kernels of the library, the one with half of the
     keys left to the caches where the planner takes it."""
