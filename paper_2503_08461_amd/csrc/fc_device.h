@@ -79,6 +79,19 @@ __device__ __forceinline__ int made_here(int v) {
   return v;
 }
 
+// A thread's lane.  kAnew: made at this point.  The phases of the fused kernels each take it
+// anew: what they compute from it (a token's number in a block, a row's, a mask's limit) was
+// else computed once, for all phases and all numbers of query tiles, kept while the registers
+// hold four tiles of queries, that is, spilled, and read back in the loops.  (In the kernels of
+// one phase there is nothing to keep, and 600-1300 tokens, 64 channels, window 32, take 47.6 us
+// for their log-sum-exps with it and 43.2 without.)
+template <bool kAnew>
+__device__ __forceinline__ int lane_number() {
+  const int lane = threadIdx.x & 63;
+  if constexpr (kAnew) return made_here(lane);
+  return lane;
+}
+
 // What stands before this point is issued before what follows (binds the compiler, which
 // would put requests for what comes next behind the wait for what is used now)
 __device__ __forceinline__ void requests_first() { __builtin_amdgcn_sched_barrier(0); }

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kThreads) void snapkv_score_kernel(BatchParams p) {
   // the denominators-only call runs outside a compression: no saved ids, the table row itself
   const int32_t* ids = p.lse_out != nullptr ? p.block_tables + (size_t)rd.table_row * p.max_blocks
                                             : p.old_ids + rd.old_off;
-  snapkv_unit<D, NT, kWaves>(p, rd, lh, ids, sh, [&](int j, float v) { raw[j] = v; });
+  snapkv_unit<D, NT, kWaves, false>(p, rd, lh, ids, sh, [&](int j, float v) { raw[j] = v; });
 }
 
 template <int D>
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void split_rows_kernel(BatchParams p) {
     if constexpr (NT > 0) {
       half8 qreg[NT][D / 32];
       load_window_queries<D, NT>(p, u.rd, u.lh, qreg);
-      snapkv_rows<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, sh, qreg);
+      snapkv_rows<D, NT, kWaves, false>(p, u.rd, u.lh, sm_ids, b0, b1, sh, qreg);
       __syncthreads();
       if (threadIdx.x < 16 * NT) {
         float mm, zz;
@@ -268,7 +268,8 @@ __global__ __launch_bounds__(kThreads) void split_scores_kernel(BatchParams p) {
   load_window_queries<D, NT>(p, u.rd, u.lh, qreg);
   __syncthreads();
   float* raw = p.raw_scores + u.rd.raw_off + (size_t)u.lh * u.rd.seq_len;
-  snapkv_columns<D, NT, kWaves>(p, u.rd, u.lh, sm_ids, b0, b1, fin, tiles, qreg, [&](int j, float v) { raw[j] = v; });
+  snapkv_columns<D, NT, kWaves, false>(p, u.rd, u.lh, sm_ids, b0, b1, fin, tiles, qreg,
+                                       [&](int j, float v) { raw[j] = v; });
 }
 
 // Heads whose scores come from a kernel of their own.  16 wavefronts for heads of up

@@ -209,14 +209,14 @@ __device__ __forceinline__ void load_window_queries(const BatchParams& p, const 
 
 // Pass 1 over blocks [b0, b1): every lane's online (max, sum) of its query rows'
 // logits -> sh.m, sh.z.  ids: the block ids, indexed from block 0.
-template <int D, int NT, int WV>
+template <int D, int NT, int WV, bool kLaneAnew>
 __device__ __forceinline__ void snapkv_rows(const BatchParams& p, const ReqDesc& rd, int lh,
                                             const int32_t* ids, int b0, int b1, ScoreShared<WV>& sh,
                                             const half8 (&qreg)[NT][D / 32]) {
   constexpr int KS = D / 32;
   const int L = rd.seq_len;
   const int W = rd.window;  // <= 16 NT; the rows past it are padding
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_number<kLaneAnew>();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
@@ -295,12 +295,12 @@ __device__ __forceinline__ void merged_row(const ScoreShared<WV>& sh, int row, f
 
 // Pass 2 over blocks [b0, b1) of the prefix: column sums of the soft-maxed rows;
 // fin: log2 of every row's denominator.
-template <int D, int NT, int WV, typename Store>
+template <int D, int NT, int WV, bool kLaneAnew, typename Store>
 __device__ __forceinline__ void snapkv_columns(const BatchParams& p, const ReqDesc& rd, int lh,
                                                const int32_t* ids, int b0, int b1, const float* fin, KeyTiles<WV>& tiles,
                                                const half8 (&qreg)[NT][D / 32], Store store) {
   constexpr int KS = D / 32;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_number<kLaneAnew>();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
@@ -342,7 +342,7 @@ __device__ __forceinline__ size_t lse_offset(const ReqDesc& rd, int lh) {
   return (size_t)(rd.q_off / D) + (size_t)lh * rd.window;
 }
 
-template <int D, int NT, int WV, typename Store>
+template <int D, int NT, int WV, bool kLaneAnew, typename Store>
 __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDesc& rd, int lh,
                                               const int32_t* old_ids, ScoreShared<WV>& sh,
                                               half8 (&qreg)[NT][D / 32], Store store) {
@@ -357,7 +357,7 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
                                 : INFINITY;  // padded rows contribute exp2(-inf) = 0
     __syncthreads();
   } else {
-    snapkv_rows<D, NT, WV>(p, rd, lh, old_ids, 0, (L + 15) >> 4, sh, qreg);
+    snapkv_rows<D, NT, WV, kLaneAnew>(p, rd, lh, old_ids, 0, (L + 15) >> 4, sh, qreg);
     __syncthreads();
     if (threadIdx.x < 64) {
       float mm, zz;
@@ -372,15 +372,15 @@ __device__ __forceinline__ void snapkv_unit_q(const BatchParams& p, const ReqDes
       p.lse_out[lse_offset<D>(rd, lh) + threadIdx.x] = sh.fin[threadIdx.x] * 0.69314718055994530942f;
     return;
   }
-  snapkv_columns<D, NT, WV>(p, rd, lh, old_ids, 0, (L - W + 15) >> 4, sh.fin, sh.tiles, qreg, store);
+  snapkv_columns<D, NT, WV, kLaneAnew>(p, rd, lh, old_ids, 0, (L - W + 15) >> 4, sh.fin, sh.tiles, qreg, store);
 }
 
-template <int D, int NT, int WV, typename Store>
+template <int D, int NT, int WV, bool kLaneAnew, typename Store>
 __device__ __forceinline__ void snapkv_unit(const BatchParams& p, const ReqDesc& rd, int lh,
                                             const int32_t* old_ids, ScoreShared<WV>& sh, Store store) {
   half8 qreg[NT][D / 32];
   load_window_queries<D, NT>(p, rd, lh, qreg);
-  snapkv_unit_q<D, NT, WV>(p, rd, lh, old_ids, sh, qreg, store);
+  snapkv_unit_q<D, NT, WV, kLaneAnew>(p, rd, lh, old_ids, sh, qreg, store);
 }
 
 // ---------------------------------------------------------------------------
@@ -1103,7 +1103,7 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
   constexpr int KS = D / 32;
   const int L = rd.seq_len;
   const int W = rd.window;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_number<true>();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
@@ -1380,7 +1380,7 @@ __device__ __forceinline__ void snapkv_rescore(const BatchParams& p, const ReqDe
                                                const float (&mrow)[NT][4]) {
   constexpr int KS = D / 32;
   constexpr int kWords = RescoreLists<WV>::kWords;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_number<true>();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15;
   const int q4 = lane >> 4;
@@ -1818,7 +1818,8 @@ __device__ __forceinline__ void fused_unit(const BatchParams& p) {
     if constexpr (NT > 0) snap = rd.method == 1 /* FC_METHOD_SNAPKV */;
     if (snap) {
       for_query_tiles<NT>(rd.window, [&](auto nt) {
-        snapkv_unit<D, decltype(nt)::value, WV>(p, rd, lh, sm_ids, sh.score, [&](int j, float v) { stage[j] = v; });
+        snapkv_unit<D, decltype(nt)::value, WV, true>(p, rd, lh, sm_ids, sh.score,
+                                                      [&](int j, float v) { stage[j] = v; });
       });
     } else {
       knorm_unit<D, WV>(p, rd, lh, sm_ids, 0, rd.n_old, [&](int j, float v) { stage[j] = v; });
@@ -1845,9 +1846,8 @@ __global__ __launch_bounds__(64 * WV) void fused_unit_only_kernel(BatchParams p)
 }
 
 // Wavefronts per SIMD that the registers must allow: what the kernel needs without
-// spilling in its loops.  (At 128 channels the forms with one, four and mixed query
-// tiles spill 1 to 6 vector registers, stored and read back once a head, outside of
-// every loop.)
+// spilling in its loops.  (At 128 channels the forms with four and mixed query tiles spill
+// 3 to 9 vector registers, at 64 the narrow one of mixed tiles 2, outside of the streaming loops.)
 __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
   return wv != kNarrow ? wv / 4 : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
 }
@@ -1896,7 +1896,7 @@ __device__ __forceinline__ void fused_bounded(const BatchParams& p) {
         const bool prune = rd.seq_len >= kBoundMinLen<D, WV>;  // uniform
         if (prune) snapkv_bounds<D, N, WV, kHalf>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
         if (!prune || keep.bad) {  // bad: not representable against a running reference
-          snapkv_unit_q<D, N, WV>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
+          snapkv_unit_q<D, N, WV, true>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });
         } else {
           float mrow[N][4];
 #pragma unroll

@@ -20,8 +20,9 @@ VGPRS = 512  # of a SIMD; a narrow workgroup has one wavefront on each
 KEEP = 16  # of the pruned kernel, next to what it shares with the selection
 
 
-def kernels(tmp_path):
-    """{mangled kernel name: (static LDS in bytes, vector registers)} of every kernel in the library."""
+def kernels(tmp_path, spills=None):
+    """{mangled kernel name: (static LDS in bytes, vector registers)} of every kernel in the library;
+    spills: takes how many of these go through memory."""
     lib = open(fastcache.LIB_PATH, "rb").read()
     out, at = {}, lib.find(b"\x7fELF", 4)
     while at >= 0:
@@ -41,6 +42,8 @@ def kernels(tmp_path):
                     name = value.strip().removesuffix(".kd")
                 elif key == ".vgpr_count":
                     out[name] = lds, int(value)
+                elif key == ".vgpr_spill_count" and spills is not None:
+                    spills[name] = int(value)
         at = lib.find(b"\x7fELF", at + 4)
     return out
 
@@ -93,6 +96,16 @@ def test_registers_grow_with_the_query_tiles(tmp_path):
         for d in (64, 128):
             vgprs = [built["_ZN2fc" + family % (d, tiles) + "EEvNS_11BatchParamsE"][1] for tiles in (1, 2, 3, 4)]
             assert vgprs == sorted(vgprs), (family, d, vgprs)
+
+
+def test_vector_spills(tmp_path):
+    """The pruned kernels of four and of mixed query tiles, which fill the registers, spill no more
+    than a head writes and reads back a few times; no other kernel of the scores spills at all."""
+    spills = {}
+    kernels(tmp_path, spills)
+    spilling = {name: n for name, n in spills.items() if n and "mlp" not in name}
+    assert all("fused_bounded" in name and ("ELi4ELi" in name or "ELi5ELi" in name) for name in spilling), spilling
+    assert max(spilling.values()) <= 9, spilling
 
 
 def test_kernel_names_of_the_benchmark(tmp_path):
