@@ -1790,6 +1790,16 @@ __device__ __forceinline__ void reclaim_only(const BatchParams& p, const ReqDesc
   if (lane == 0) __hip_atomic_store(p.arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Wavefronts per SIMD that the registers must allow (1: as many as they come to), where that
+// takes no vector spills.  16 prompts of 200-480 tokens, 4 layers of 32 heads, with scores,
+// free / bounded: 128 channels, window 48 (3 and 4 wavefronts) 80.8 / 75.7 us; 64 channels,
+// window 16 (7, by the scalar registers, and 8) 50.4 / 43.1, key norms 39.0 / 33.6; wide ones at 64
+// channels, of which a CU takes two only if all eight fit, 512 heads of 900-1000 tokens 47.0 /
+// 39.2.  Two and four tiles would spill: 73.8 / 94.3 at 128 channels, window 32, and 52.7 / 68.7
+// at 64, window 64.
+__host__ __device__ constexpr int scored_occupancy(int d, int nt, int wv) {
+  return d == 64 && nt <= 1 ? 8 : wv != kNarrow ? wv / 4 : nt == 3 ? (d == 64 ? 5 : 4) : 1;
+}
 template <int D, int NT, int WV, bool kOnly>
 __device__ __forceinline__ void fused_unit(const BatchParams& p) {
   extern __shared__ __align__(16) uint32_t lds[];
@@ -1837,19 +1847,21 @@ __device__ __forceinline__ void fused_unit(const BatchParams& p) {
   }
 }
 template <int D, int NT, int WV>
-__global__ __launch_bounds__(64 * WV) void fused_unit_kernel(BatchParams p) {
+__global__ __launch_bounds__(64 * WV, scored_occupancy(D, NT, WV)) void fused_unit_kernel(BatchParams p) {
   fused_unit<D, NT, WV, false>(p);
 }
 template <int D, int WV>  // (of a scored request, key norms: the others are pruned)
-__global__ __launch_bounds__(64 * WV) void fused_unit_only_kernel(BatchParams p) {
+__global__ __launch_bounds__(64 * WV, scored_occupancy(D, 0, WV)) void fused_unit_only_kernel(BatchParams p) {
   fused_unit<D, 0, WV, true>(p);
 }
 
 // Wavefronts per SIMD that the registers must allow: what the kernel needs without
 // spilling in its loops.  (At 128 channels the forms with four and mixed query tiles spill
-// 3 to 9 vector registers, at 64 the narrow one of mixed tiles 2, outside of the streaming loops.)
+// 3 to 9 vector registers, at 64 the narrow one of mixed tiles 2, outside of the streaming loops.)  The wide one of one
+// tile at 64 channels must leave room for a second workgroup: 512 heads of 900-1000 tokens
+// 46.0 -> 39.8 us, of 4900-5100 141.9 -> 129.8.
 __host__ __device__ constexpr int bounded_occupancy(int d, int nt, int wv) {
-  return wv != kNarrow ? wv / 4 : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
+  return wv != kNarrow ? (d == 64 && nt == 1 ? 8 : wv / 4) : d == 64 ? (nt <= 2 ? 5 : 4) : nt == 1 ? 5 : nt == 2 ? 4 : 3;
 }
 
 // The fused kernel with the pruned second pass for its SnapKV units (see

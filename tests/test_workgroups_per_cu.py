@@ -20,9 +20,9 @@ VGPRS = 512  # of a SIMD; a narrow workgroup has one wavefront on each
 KEEP = 16  # of the pruned kernel, next to what it shares with the selection
 
 
-def kernels(tmp_path, spills=None):
+def kernels(tmp_path, details=None):
     """{mangled kernel name: (static LDS in bytes, vector registers)} of every kernel in the library;
-    spills: takes how many of these go through memory."""
+    details: takes what else their descriptions say, {name: {key: count}}."""
     lib = open(fastcache.LIB_PATH, "rb").read()
     out, at = {}, lib.find(b"\x7fELF", 4)
     while at >= 0:
@@ -33,17 +33,19 @@ def kernels(tmp_path, spills=None):
             path = tmp_path / "code"
             path.write_bytes(lib[at:end])
             text = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
-            lds = None
+            lds, more = None, {}
             for line in text.splitlines():
                 key, _, value = line.strip().partition(":")
                 if key == ".group_segment_fixed_size":
-                    lds = int(value)
+                    lds, more = int(value), {}
                 elif key == ".symbol":
                     name = value.strip().removesuffix(".kd")
                 elif key == ".vgpr_count":
                     out[name] = lds, int(value)
-                elif key == ".vgpr_spill_count" and spills is not None:
-                    spills[name] = int(value)
+                if key in (".sgpr_count", ".vgpr_count", ".vgpr_spill_count") and details is not None:
+                    more[key] = int(value)
+                    if key == ".vgpr_spill_count":  # (the last)
+                        details[name] = more
         at = lib.find(b"\x7fELF", at + 4)
     return out
 
@@ -101,11 +103,30 @@ def test_registers_grow_with_the_query_tiles(tmp_path):
 def test_vector_spills(tmp_path):
     """The pruned kernels of four and of mixed query tiles, which fill the registers, spill no more
     than a head writes and reads back a few times; no other kernel of the scores spills at all."""
-    spills = {}
-    kernels(tmp_path, spills)
-    spilling = {name: n for name, n in spills.items() if n and "mlp" not in name}
+    details = {}
+    kernels(tmp_path, details)
+    spilling = {name: x[".vgpr_spill_count"] for name, x in details.items() if x[".vgpr_spill_count"] and "mlp" not in name}
     assert all("fused_bounded" in name and ("ELi4ELi" in name or "ELi5ELi" in name) for name in spilling), spilling
     assert max(spilling.values()) <= 9, spilling
+
+
+def test_wavefronts_per_simd(tmp_path):
+    """Heads so short that LDS does not limit them: what the registers of the kernels that score in
+    full allow, and two wide workgroups a CU at 64 channels with at most one query tile."""
+    details = {}
+    kernels(tmp_path, details)
+
+    def wavefronts(name):
+        x = details["_ZN2fc%sEEvNS_11BatchParamsE" % name]
+        # (a SIMD has 800 scalar registers; 16 of each wavefront are the trap handler's)
+        return min(VGPRS // (-(-x[".vgpr_count"] // 8) * 8), 800 // (-(-(x[".sgpr_count"] + 16) // 16) * 16))
+    least = {(128, 0): 5, (128, 1): 5, (128, 2): 4, (128, 3): 4, (128, 4): 3, (128, 5): 3,
+             (64, 0): 8, (64, 1): 8, (64, 2): 7, (64, 3): 5, (64, 4): 4, (64, 5): 4}
+    for (d, tiles), n in least.items():
+        assert wavefronts("17fused_unit_kernelILi%dELi%dELi4E" % (d, tiles)) >= n, (d, tiles)
+    for name in ("17fused_unit_kernelILi64ELi0ELi16E", "17fused_unit_kernelILi64ELi1ELi16E", "22fused_unit_only_kernelILi64ELi16E",
+                 "20fused_bounded_kernelILi64ELi1ELi16ELb0E", "25fused_bounded_only_kernelILi64ELi1ELi16E"):
+        assert wavefronts(name) == 8, name
 
 
 def test_kernel_names_of_the_benchmark(tmp_path):
