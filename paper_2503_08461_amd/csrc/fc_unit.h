@@ -1791,14 +1791,15 @@ __device__ __forceinline__ void reclaim_only(const BatchParams& p, const ReqDesc
 }
 
 // Wavefronts per SIMD that the registers must allow (1: as many as they come to), where that
-// takes no vector spills.  16 prompts of 200-480 tokens, 4 layers of 32 heads, with scores,
-// free / bounded: 128 channels, window 48 (3 and 4 wavefronts) 80.8 / 75.7 us; 64 channels,
-// window 16 (7, by the scalar registers, and 8) 50.4 / 43.1, key norms 39.0 / 33.6; wide ones at 64
-// channels, of which a CU takes two only if all eight fit, 512 heads of 900-1000 tokens 47.0 /
-// 39.2.  Two and four tiles would spill: 73.8 / 94.3 at 128 channels, window 32, and 52.7 / 68.7
-// at 64, window 64.
+// takes no vector spills and pays.  16 prompts of 200-480 tokens, 4 layers of 32 heads, with
+// scores, free / bounded: 128 channels, window 48 (3 and 4 wavefronts) 80.8 / 75.7 us; 64
+// channels, window 16 (7, by the scalar registers, and 8) 50.4 / 43.1; wide ones at 64 channels,
+// of which a CU takes two only if all eight fit, 512 heads of 900-1000 tokens 47.0 / 39.2.
+// Two and four tiles would spill: 73.8 / 94.3 at 128 channels, window 32, and 52.7 / 68.7 at 64,
+// window 64.  Without SnapKV units key norms gain (39.0 / 33.6), but streaming, which HBM bounds,
+// loses (755 / 769).
 __host__ __device__ constexpr int scored_occupancy(int d, int nt, int wv) {
-  return d == 64 && nt <= 1 ? 8 : wv != kNarrow ? wv / 4 : nt == 3 ? (d == 64 ? 5 : 4) : 1;
+  return d == 64 && (nt == 1 || (nt == 0 && wv != kNarrow)) ? 8 : wv != kNarrow ? wv / 4 : nt == 3 ? (d == 64 ? 5 : 4) : 1;
 }
 template <int D, int NT, int WV, bool kOnly>
 __device__ __forceinline__ void fused_unit(const BatchParams& p) {
