@@ -547,19 +547,6 @@ bool fits_inline(const fc_pool* p, const char* image, size_t bytes, MetaChunk* c
   return true;
 }
 
-// Whether a call of one request in one fused launch goes without plan_alloc (a call that is
-// timed kernel by kernel does not).  All kernels, with / without it in us: 4 heads of 256
-// tokens 22.3 / 17.6, 32 of 700 30.8 / 29.3, 256 of 1500 63.2 / 61.5 (key norms 45.4 / 44.0),
-// 1024 of 640 67.3 / 66.4; but 1024 of 2000 228.7 / 231.6 and of 7000 697 / 699, where the
-// taking back at the very end shows and the launch at the beginning does not, and streaming,
-// whose workgroups all come to their copy at once and queue at the counter, 25.2 / 25.9.
-// (Calls with scores, log-sum-exps or without pruning gain as little and have no kernels for it.)
-constexpr long long kOnlyMaxTokens = 1 << 20;  // of all heads
-bool needs_no_plan(const fc_pool* p, const ReqDesc& d) {
-  return !p->profiling && d.method != FC_METHOD_STREAMING &&
-         (long long)d.seq_len * p->n_layers * p->n_heads <= kOnlyMaxTokens;
-}
-
 // Whether the scratch of split heads is there, or can be had now.  A captured call
 // allocates nothing, and a size that was refused is not asked for again: each attempt
 // waits for the device.
@@ -686,8 +673,8 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   memcpy(image.data() + desc_bytes, lists.data(), lists.size() * sizeof(int32_t));
   MetaChunk inline_meta;
   const bool meta_inline = fits_inline(p, image.data(), meta_bytes, &inline_meta);
-  const bool only = meta_inline && n_comp == 1 && fused.size() == 1 && !separate && n_ids <= (size_t)kOnlyMaxIds &&
-                    (pruned_call || plan.descs[0].method == FC_METHOD_KNORM) && needs_no_plan(p, plan.descs[0]);
+  // (a call that is timed kernel by kernel has its plan_alloc)
+  const bool only = meta_inline && !p->profiling && n_split == 0 && plan_one_launch(pv, plan, fused.size(), pruned_call);
   if (!meta_inline && (rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK)
     return rc;
 

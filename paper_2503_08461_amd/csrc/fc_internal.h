@@ -105,7 +105,7 @@ struct BatchParams {
   int32_t half_reuse;          // ... and leaves only half of the keys that it reads first to the caches
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,
                                // 2 being released; NULL when the checks are off
-  // A call of one request whose only launch is a fused one (needs_no_plan): its descriptor;
+  // A call of one request whose only launch is a fused one (plan_one_launch): its descriptor;
   // `arrivals` counts the workgroups that are done with the table and the stack, and is
   // zero between calls.  NULL: plan_alloc has run, descriptors and ids are in the buffers above.
   int32_t* arrivals;
@@ -115,9 +115,7 @@ struct BatchParams {
     int64_t q_off;
   } only;
 };
-// most block ids, old and new, of a request that needs no plan_alloc: the wavefront that
-// takes its old blocks back keeps them in LDS
-static constexpr int kOnlyMaxIds = 512;
+static constexpr int kOnlyMaxIds = kPlanOnlyMaxIds;
 
 // Descriptor bytes that travel as a kernel argument.
 struct MetaChunk {

@@ -288,6 +288,33 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
   return launches;
 }
 
+// All kernels of a call, with plan_alloc / without in us (32 heads and fewer: a launch less is
+// 2 to 4.5 of the host's).  Without it every workgroup counts itself out before its copy, one
+// after the other (some 6 ns each); where there are many short heads they all come at once:
+//   128 channels, tokens   128          256          400          700          1000
+//    256 heads  SnapKV   21.7 / 19.0  22.0 / 21.6  27.3 / 26.7  38.7 / 38.3  48.7 / 47.6
+//    512        SnapKV   22.1 / 23.0  28.8 / 29.2  37.0 / 36.5  67.2 / 66.4  86.9 / 84.7
+//               key-norm 20.4 / 20.2  23.7 / 25.4  31.1 / 31.3  43.6 / 41.5  63.4 / 61.4
+//    1024       SnapKV   29.1 / 33.3  38.7 / 39.7  56.7 / 55.0  79.8 / 77.9  105.0 / 102.8
+//    2048       key-norm 35.2 / 44.5  52.8 / 57.5  83.6 / 83.7
+//   64 channels
+//    512        key-norm 20.4 / 19.3  20.4 / 19.7  21.8 / 23.0  28.7 / 30.2  34.0 / 32.6
+//    1024       SnapKV   22.2 / 28.4  27.5 / 32.5  34.6 / 37.9  51.3 / 50.9  66.2 / 64.4
+//               key-norm 20.1 / 24.8  22.8 / 29.9  30.5 / 34.9  42.7 / 43.6  55.4 / 54.4
+// From a million tokens of all heads on the taking back at the very end shows and the launch
+// at the beginning does not (1024 heads of 2000 tokens 228.7 / 231.6, of 7000 697 / 699).
+// Streaming requests all come to their copy at once (25.2 / 25.9); calls with scores,
+// log-sum-exps or without pruning gain as little and have no kernels for it.
+bool plan_one_launch(const PoolView& pool, const CompressPlan& plan, size_t n_launches, bool pruned) {
+  if (pool.score_mode != PLAN_SCORE_AUTO || plan.descs.size() != 1 || n_launches != 1) return false;
+  const ReqDesc& d = plan.descs[0];
+  if (d.method != PLAN_METHOD_KNORM && !(d.method == PLAN_METHOD_SNAPKV && pruned)) return false;
+  if (plan.total_old + plan.total_new > kPlanOnlyMaxIds) return false;
+  const long long heads = (long long)pool.n_layers * pool.n_heads;
+  if (heads * d.seq_len > 1 << 20) return false;
+  return heads <= 256 || d.seq_len * pool.head_dim >= 400 * 128;
+}
+
 int plan_split(const PoolView& pool, int n_cu, CompressPlan* plan) {
   if (pool.score_mode != PLAN_SCORE_AUTO || pool.in_place || plan->descs.empty()) return 0;
   const size_t units = (size_t)pool.n_layers * pool.n_heads * plan->descs.size();

@@ -115,6 +115,14 @@ struct FusedLaunch {
 };
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu);
 
+// Whether a call in the default scheduling that is not split needs no plan_alloc: one request
+// in one launch whose kernels read the table and the stack themselves (pruned: the call asks
+// for no scores and gives no log-sum-exps).
+bool plan_one_launch(const PoolView& pool, const CompressPlan& plan, size_t n_launches, bool pruned);
+// Most block ids, old and new, of such a request: the wavefront that takes its old blocks
+// back keeps them in LDS.
+static constexpr int kPlanOnlyMaxIds = 512;
+
 // A call with so few heads that they are better split over workgroups: segments
 // per head, or 0 (not split).  Otherwise all requests of the call run that way;
 // plan->descs get their offsets in the score scratch, plan->raw_floats its size.

@@ -1727,7 +1727,7 @@ __device__ __forceinline__ void for_query_tiles(int window, F f) {
 // that says so (behind a barrier after which nothing of either is left to read; the count
 // only orders those reads before the writes, no data passes through it) writes them anew
 // when its own copy is under way.  A launch is 2.5 to 3 us of the host's time, and
-// plan_alloc, which the main kernel waited for, about 2 of the GPU's (needs_no_plan has
+// plan_alloc, which the main kernel waited for, about 2 of the GPU's (plan_one_launch has
 // what that gives and where it stops).  Counted when the ids have been read instead, so
 // that not the last one writes, the counts of all workgroups come at once and stand before
 // their keys: one prompt of 640 tokens, 1024 heads, 66.4 -> 73.7 us.  Kernels of their own:

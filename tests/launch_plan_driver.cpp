@@ -2,6 +2,8 @@
 // plan_split, plan_fused_launches).  Built, fed and checked by test_launch_plan.py.
 // Input, one case per line (all integers):
 //   nl nh d mode in_place n_cu n_req, then n_req times: length method budget window
+// With any argument: one line per case, whether it goes without plan_alloc (plan_one_launch),
+// as a pruned call and as one that is not.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -10,7 +12,7 @@
 
 using namespace fc;
 
-int main() {
+int main(int argc, char**) {
   PoolView pv;
   int mode, in_place, n_cu, n_req;
   while (scanf("%d %d %d %d %d %d %d", &pv.n_layers, &pv.n_heads, &pv.head_dim, &mode, &in_place,
@@ -33,6 +35,11 @@ int main() {
     CompressPlan plan;
     if (plan_compress(pv, a, &plan) != PLAN_OK) return 3;
     const int split = plan_split(pv, n_cu, &plan);
+    if (argc > 1) {
+      const size_t n = split ? 0 : plan_fused_launches(pv, plan, n_cu).size();
+      printf("O %d %d\n", plan_one_launch(pv, plan, n, true), plan_one_launch(pv, plan, n, false));
+      continue;
+    }
     printf("C %d %zu", split, plan.raw_floats);
     for (const ReqDesc& d : plan.descs) printf(" %lld", (long long)d.raw_off);
     printf("\n");

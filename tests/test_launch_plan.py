@@ -137,3 +137,41 @@ def test_which_launches_leave_half_of_the_keys_to_the_caches():
     out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
     got = [[int(x) for x in line.split()[1:]] for line in out if line[0] == "F"]
     assert [launch[4] for launch in got] == [want for _, want in cases]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_which_calls_go_without_plan_alloc():
+    """One request in one fused launch, as a pruned call and as one that is not: up to 512 block
+    ids and a million tokens of all heads; many heads only where they are long enough not to
+    come to the counter all at once."""
+    from launch_shapes import _driver
+    cases = [
+        (_case(1, 4, [(256, SNAP, 64, 16)], d=64), (1, 0)),
+        (_case(1, 4, [(256, KNORM, 64, 16)], d=64), (1, 1)),
+        (_case(1, 4, [(256, STREAM, 64, 16)], d=64), (0, 0)),
+        (_case(1, 4, [(256, SNAP, 64, 16)], mode=1), (0, 0)),
+        (_case(1, 4, [(256, KNORM, 64, 16)], mode=1), (0, 0)),
+        (_case(1, 4, [(256, STREAM, 64, 16)], mode=1), (0, 0)),
+        (_case(1, 4, [(256, SNAP, 64, 16)] * 2), (0, 0)),
+        (_case(1, 128, [(2047, SNAP, 400, 32)]), (1, 0)),
+        (_case(1, 128, [(2048, SNAP, 400, 32)]), (0, 0)),            # split
+        (_case(1, 128, [(2048, SNAP, 400, 32)], in_place=1), (1, 0)),
+        (_case(1, 136, [(6000, SNAP, 2192, 16)], d=64), (1, 0)),     # 375 + 137 ids
+        (_case(1, 136, [(6000, SNAP, 2193, 16)], d=64), (0, 0)),
+        (_case(1, 136, [(6000, SNAP, 6000, 16)], d=64, in_place=1), (1, 0)),  # (no new ones)
+        (_case(32, 32, [(1024, SNAP, 200, 32)]), (1, 0)),            # 1 << 20 tokens
+        (_case(32, 32, [(1025, SNAP, 200, 32)]), (0, 0)),
+        # more than 256 heads: from 400 tokens of 128 channels on
+        (_case(8, 32, [(20, KNORM, 9, 32)]), (1, 1)),
+        (_case(1, 257, [(399, KNORM, 100, 32)]), (0, 0)),
+        (_case(1, 257, [(400, KNORM, 100, 32)]), (1, 1)),
+        (_case(1, 257, [(799, SNAP, 100, 32)], d=64), (0, 0)),
+        (_case(1, 257, [(800, SNAP, 100, 32)], d=64), (1, 0)),
+        (_case(32, 32, [(300, KNORM, 90, 32)], d=64), (0, 0)),
+    ]
+    text = "".join("%d %d %d %d %d %d %d\n%s\n" % (c[:6] + (len(c[6]), "\n".join("%d %d %d %d" % r for r in c[6])))
+                   for c, _ in cases)
+    out = subprocess.run([_driver(), "one"], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    for (case, want), line in zip(cases, out):
+        assert tuple(int(x) for x in line.split()[1:]) == want, (case, line)
+    assert len(out) == len(cases)
