@@ -6,6 +6,8 @@
 // so one (layer, block, kv, head) chunk is 16*d contiguous halves (4 KiB at
 // d = 128) and one token row is d contiguous halves.
 
+#include <algorithm>
+
 #include "fc_unit.h"
 
 namespace fc {
@@ -297,15 +299,58 @@ __global__ __launch_bounds__(64 * WV) void select_kernel(BatchParams p) {
   select_unit<WV>(p, rd, lh, stage, lds + stage_words(rd.seq_len), kept, sh);
 }
 
+// The copy of heads whose selection was a kernel of its own.  A wavefront takes its blocks
+// four at a time, a lane for each of their rows: what goes there, then where that lies; of
+// the next four both are on their way before the rows of these are asked for, and no load
+// stands between the rows asked for and those that are stored.  (Each id and kept token
+// loaded where it was used, 18 loads a block, all of them waited for with the rows: 64 heads
+// of 4000 tokens 58.5 -> 57.0 us, the whole call; the split kernels' loops alone 58.3; 64
+// channels 45.4 -> 44.0; 3072 heads whole, 1000-3000 tokens, 923 -> 917 and 459 -> 464.)
 template <int D>
 __global__ __launch_bounds__(kThreads) void gather_kernel(BatchParams p) {
   const SplitUnit u = split_unit(p);
   if (p.main_reclaims && u.lh == 0 && u.seg == 0) reclaim_request(p, u.rd);
   const int32_t* kept = p.kept + u.rd.kept_off + (size_t)u.lh * u.rd.budget;
+  const int32_t* old_ids = p.old_ids + u.rd.old_off;
+  const int32_t* new_ids = p.new_ids + u.rd.new_off;
+  if (p.in_place) {  // (a head is not split then)
+    gather_unit<D, kWaves, false>(
+        p, u.rd, u.lh, [&](int i) { return old_ids[i]; }, [&](int i) { return new_ids[i]; }, [&](int t) { return kept[t]; });
+    return;
+  }
   int nb0, nb1;
   split_range(p, u.seg, u.rd.n_new, nb0, nb1);
-  gather_unit<D, kWaves>(p, u.rd, u.lh, nb0, nb1, [&](int i) { return p.old_ids[u.rd.old_off + i]; },
-                         [&](int i) { return p.new_ids[u.rd.new_off + i]; }, [&](int t) { return kept[t]; });
+  const RowCopy<D, kWaves> c(p, u.rd, u.lh, nb0);
+  typedef typename RowCopy<D, kWaves>::Rows Rows;
+  const int n = own_tiles(nb1 - nb0, c.wave, kWaves);
+  if (n <= 0) return;
+  const int lane = threadIdx.x & 63;
+  auto target_of = [&](int i) { return new_ids[min(c.block(i + lane), nb1 - 1)]; };  // lane l: of block i + l
+  auto kept_of = [&](int i) { return kept[min(c.block(i + (lane >> 4)) * 16 + (lane & 15), u.rd.budget - 1)]; };
+  auto row_of = [&](int token) {
+    const int idx = min(max(token, 0), u.rd.seq_len - 1);
+    return clamp_block(old_ids[idx >> 4], p.n_blocks) * 16 + (idx & 15);
+  };
+  int targets = target_of(0);
+  int from = row_of(kept_of(0)), token = kept_of(4);
+  for (int i0 = 0; i0 < n; i0 += 4) {  // uniform over the wavefront
+    if (i0 > 0 && (i0 & 63) == 0) targets = target_of(i0);
+    const int rows = made_here(from);
+    targets = made_here(targets);
+    if (i0 + 4 < n) {
+      from = row_of(token);
+      token = kept_of(i0 + 8);
+    }
+    stream_tiles<Rows>(
+        min(n - i0, 4),
+        [&](int i, Rows& kv) {
+          c.template load<false>(kv, [&](int row) {
+            const int at = __shfl(rows, 16 * i + row);
+            return int2{at >> 4, at & 15};
+          });
+        },
+        [&](int i, const Rows& kv) { c.store(c.block(i0 + i), __builtin_amdgcn_readlane(targets, (i0 + i) & 63), kv); });
+  }
 }
 
 // a fill kernel for small device arrays (flags, verdict words): calls may be
@@ -473,7 +518,15 @@ hipError_t launch_fused(BatchParams p, int query_tiles, int max_seq_len, int max
   p.ids_at = f.ids_at;
   p.ids_room = f.ids_room;
   p.new_ids_at = f.words;  // (a call of one request without plan_alloc)
-  const size_t lds = (size_t)(f.words + (p.arrivals ? (p.only.n_new + 3) & ~3 : 0)) * sizeof(uint32_t);
+  size_t lds = (size_t)(f.words + (p.arrivals ? (p.only.n_new + 3) & ~3 : 0)) * sizeof(uint32_t);
+  // A launch of nothing but copies is faster with fewer of them at a time: it asks for LDS that
+  // it doesn't use.  64 channels, one wide workgroup a CU, not two: 512 heads of 3000-6000
+  // tokens 83.0 -> 77.3 us; two narrow ones, not eight, from eight heads a CU on: 3840 heads of
+  // 1400-4300 341 -> 328, in place 357 -> 329 (128 channels 835 -> 817, 832 -> 820); but 1024
+  // of 640 tokens 25.8 -> 27.8.
+  const bool copies = query_tiles == 0 && max_seq_len == 0;  // (LDS for no score)
+  if (copies && wide && p.head_dim == 64) lds = std::max<size_t>(lds, 68 * 1024);
+  if (copies && !wide && p.n_fused * p.n_layers * p.n_heads >= 8 * 256) lds = std::max<size_t>(lds, 39 * 1024);
   if (p.head_dim == 128)
     return wide ? launch_fused_wide_128(p, query_tiles, lds, s) : launch_fused_narrow_128(p, query_tiles, lds, s);
   if (p.head_dim == 64)

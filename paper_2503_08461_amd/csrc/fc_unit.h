@@ -1597,74 +1597,122 @@ __device__ __forceinline__ void streaming_unit(const BatchParams& p, const ReqDe
 // One workgroup per (request, layer, head); a wavefront fills one new block
 // (16 output slots) at a time for K and V.  D/8 lanes move one row with
 // 128-bit accesses, so a wavefront instruction moves 64/(D/8) rows; the
-// destination chunk is contiguous.  kept_at(t) is the token that goes to slot t;
-// block_at(i) and new_at(i) are the request's i-th old and new block; the workgroup fills
-// the new blocks [nb0, nb1).
+// destination chunk is contiguous.
 //
 // Bound by HBM when the chip is full and by the latency of one block's chain
 // (kept index, block id, row) when it is not; the rows of a wavefront's next
-// block are therefore requested before those of this one are stored.
+// block are therefore requested before those of this one are stored.  (Where the
+// ids of the new blocks are vector loads, as in the fused kernels of several requests,
+// the wait for such an id is one for the rows just asked for as well; kept in registers
+// instead, they took the copy to fewer wavefronts a SIMD, and 24 requests of 1000-3000
+// tokens 726-821 -> 735-822 us at 128 channels, 344-411 -> 349-413 at 64.)
 
-template <int D, int WV, typename BlockAt, typename NewAt, typename KeptAt>
-__device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh,
-                                            int nb0, int nb1, BlockAt block_at, NewAt new_at, KeptAt kept_at) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = 64 / LPR;
-  constexpr int NI = 16 / RPI;
-  const int layer = lh / p.n_heads;
-  const int head = lh - layer * p.n_heads;
-  const int B = rd.budget;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const size_t chunk = (size_t)16 * D;               // one (block, kv, head)
-  const size_t v_off = (size_t)p.n_heads * chunk;    // K chunk -> V chunk of a block
-  const size_t blk_stride = 2 * v_off;
-  _Float16* base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * chunk +
-                   (lane % LPR) * 8;
-  const int row_in_instr = lane / LPR;
-  auto load = [&](int nbk, half8 (&kv)[2 * NI]) {  // keys, then values
+template <int D, int WV>
+struct RowCopy {
+  static constexpr int LPR = D / 8;
+  static constexpr int RPI = 64 / LPR;
+  static constexpr int NI = 16 / RPI;
+  typedef half8 Rows[2 * NI];  // of one block: keys, then values
+  const BatchParams& p;
+  const int nb0, n_kept, wave, row_in_instr;
+  size_t v_off, blk_stride;  // K chunk -> V chunk of a block; block -> block
+  _Float16* base;
+
+  // of the new blocks from nb0 on
+  __device__ __forceinline__ RowCopy(const BatchParams& p_, const ReqDesc& rd, int lh, int nb0_)
+      : p(p_), nb0(nb0_), n_kept(rd.budget), wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)),
+        row_in_instr((threadIdx.x & 63) / LPR) {
+    const int layer = lh / p.n_heads, head = lh - layer * p.n_heads;
+    const size_t chunk = (size_t)16 * D;  // one (block, kv, head)
+    v_off = (size_t)p.n_heads * chunk;
+    blk_stride = 2 * v_off;
+    base = p.kv + (size_t)layer * p.n_blocks * blk_stride + (size_t)head * chunk + (threadIdx.x % LPR) * 8;
+  }
+  __device__ __forceinline__ int block(int i) const { return nb0 + wave + WV * i; }  // the wavefront's i-th
+  // source(row of the block, 0..15) -> {block id, slot}.  kInOrder: where the second row lies is
+  // looked up when the first is asked for, and so on, which takes fewer registers (all at once,
+  // kernels of 128 channels and one query tile lost a wavefront a SIMD, or spilled).
+  template <bool kInOrder, typename Source>
+  __device__ __forceinline__ void load(Rows& kv, Source source) const {
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
-      // (slots past the budget load the last kept row again and drop it)
-      const int t = min(nbk * 16 + k * RPI + row_in_instr, B - 1);
-      const int idx = min(max(kept_at(t), 0), rd.seq_len - 1);
-      const int sblk = clamp_block(block_at(idx >> 4), p.n_blocks);
-      const _Float16* src = base + (size_t)sblk * blk_stride + (size_t)(idx & 15) * D;
+      const int2 from = source(k * RPI + row_in_instr);
+      const _Float16* src = base + (size_t)clamp_block(from.x, p.n_blocks) * blk_stride + (size_t)from.y * D;
       kv[k] = load_half8_nt(src);
       kv[NI + k] = load_half8_nt(src + v_off);
+      if constexpr (kInOrder) requests_first();
     }
-  };
-  auto store = [&](int nbk, const half8 (&kv)[2 * NI]) {
-    // freshly popped blocks, or the request's own first ones
-    const int dblk = clamp_block(p.in_place ? block_at(nbk) : new_at(nbk), p.n_blocks);
-    _Float16* dst = base + (size_t)dblk * blk_stride;
+  }
+  // (slots past the budget are not written)
+  __device__ __forceinline__ void store(int nbk, int id, const Rows& kv) const {
+    _Float16* dst = base + (size_t)clamp_block(id, p.n_blocks) * blk_stride;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       const int row = k * RPI + row_in_instr;
-      if (nbk * 16 + row < B) {
+      if (nbk * 16 + row < n_kept) {
         store_half8_nt(dst + (size_t)row * D, kv[k]);
         store_half8_nt(dst + (size_t)row * D + v_off, kv[NI + k]);
       }
     }
+  }
+};
+
+// block_at(i) and new_at(i): the request's i-th old and new block; kept_at(t): the token that
+// goes to slot t.  kStreaming: nothing was scored, all workgroups do nothing but copy, and more
+// requests in flight only make the chip change between reading and writing more often.  Wide
+// workgroups ask for their rows in order, and as their ids may be in either of two places
+// (gather_fused), each row waits for the one before; all at once / in order, half of the tokens
+// kept, 128 channels: 256 heads of 900-1000 tokens 29.0 / 26.9 us, 512 of 3000-6000 252 / 248,
+// of 9000-16000, a third kept, 533 / 520; 64 channels: 256 of 2000-4000 35.4 / 33.8, 512 of
+// 9000-16000 254 / 251.  In place, and narrow ones (see launch_fused), all at once: 256 heads of
+// 2000-4000 in place 63.5 / 66.5, 3840 of 1400-4300, 64 channels, 328 / 354.
+template <int D, int WV, bool kStreaming, typename BlockAt, typename NewAt, typename KeptAt>
+__device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh, BlockAt block_at,
+                                            NewAt new_at, KeptAt kept_at) {
+  const int nb = rd.n_new;
+  const RowCopy<D, WV> c(p, rd, lh, 0);
+  typedef typename RowCopy<D, WV>::Rows Rows;
+  auto source = [&](int nbk, int row) {
+    // (slots past the budget load the last kept row again and drop it)
+    const int idx = min(max(kept_at(min(nbk * 16 + row, rd.budget - 1)), 0), rd.seq_len - 1);
+    return int2{block_at(idx >> 4), idx & 15};
   };
   if (p.in_place) {
-    half8 kv[2 * NI];
+    Rows kv;
     // Output t overwrites slot t while kept[t] >= t: a chunk of WV*16
     // outputs only reads slots at or after its own start, so reading the whole
     // chunk, a barrier, then writing it never destroys a row that is still
     // needed (later chunks read strictly later slots).
-    // (one workgroup then copies all blocks of a head)
-    for (int c0 = nb0; c0 < nb1; c0 += WV) {
-      const int nbk = c0 + wave;
-      if (nbk < nb1) load(nbk, kv);
+    for (int c0 = 0; c0 < nb; c0 += WV) {
+      const int nbk = c0 + c.wave;
+      if (nbk < nb) c.template load<!kStreaming>(kv, [&](int row) { return source(nbk, row); });
       __syncthreads();  // uniform: c0 and in_place are the same for all threads
-      if (nbk < nb1) store(nbk, kv);
+      if (nbk < nb) c.store(nbk, block_at(nbk), kv);  // (the request's own first blocks)
     }
     return;
   }
-  stream_tiles<half8[2 * NI]>(
-      own_tiles(nb1 - nb0, wave, WV), [&](int i, half8(&kv)[2 * NI]) { load(nb0 + wave + WV * i, kv); },
-      [&](int i, const half8(&kv)[2 * NI]) { store(nb0 + wave + WV * i, kv); });
+  if constexpr (kStreaming && WV != kNarrow) {
+    Rows kc, kn;
+    int nbk = c.wave;
+    if (nbk < nb) c.template load<true>(kc, [&](int row) { return source(nbk, row); });
+    for (; nbk < nb; nbk += WV) {
+      if (nbk + WV < nb) c.template load<true>(kn, [&](int row) { return source(nbk + WV, row); });
+      c.store(nbk, new_at(nbk), kc);
+#pragma unroll
+      for (int k = 0; k < 2 * c.NI; ++k) kc[k] = kn[k];
+    }
+  } else {
+    stream_tiles<Rows>(
+        own_tiles(nb, c.wave, WV),
+        [&](int i, Rows& kv) { c.template load<!kStreaming>(kv, [&](int row) { return source(c.block(i), row); }); },
+        [&](int i, const Rows& kv) { c.store(c.block(i), new_at(c.block(i)), kv); });
+  }
+}
+
+// (of requests without plan_alloc none is)
+template <bool kOnly>
+__device__ __forceinline__ bool is_streaming(const ReqDesc& rd) {
+  return !kOnly && rd.method == 3 /* FC_METHOD_STREAMING */;
 }
 
 // The copy at the end of a fused kernel: the kept list is where the selection
@@ -1675,20 +1723,17 @@ __device__ __forceinline__ void gather_fused(const BatchParams& p, const ReqDesc
                                              const uint32_t* words, const int32_t* sm_ids, bool ids_in_lds,
                                              const int32_t* sm_new) {
   const uint16_t* kept16 = reinterpret_cast<const uint16_t*>(words);
-  const bool streaming = rd.method == 3 /* FC_METHOD_STREAMING */;  // uniform
-  auto copy = [&](auto block_at) {
-    gather_unit<D, WV>(p, rd, lh, 0, rd.n_new, block_at,
-                       [&](int i) {
-                         if constexpr (kOnly) return sm_new[i];
-                         else return p.new_ids[rd.new_off + i];
-                       },
-                       [&](int t) { return streaming ? streaming_token(rd, p.n_sink, t) : (int)kept16[t]; });
+  auto new_at = [&](int i) {
+    if constexpr (kOnly) return sm_new[i];
+    else return p.new_ids[rd.new_off + i];
   };
-  // (a form for each place: an id from either of two comes by a load that waits for all others)
-  if (ids_in_lds)
-    copy([&](int i) { return sm_ids[i]; });
-  else
-    copy([&](int i) { return p.old_ids[rd.old_off + i]; });
+  if (is_streaming<kOnly>(rd))  // uniform
+    gather_unit<D, WV, true>(
+        p, rd, lh, [&](int i) { return ids_in_lds ? sm_ids[i] : p.old_ids[rd.old_off + i]; }, new_at,
+        [&](int t) { return streaming_token(rd, p.n_sink, t); });
+  else  // (what is scored has its ids in LDS: one from either place comes by a load that waits for all others)
+    gather_unit<D, WV, false>(
+        p, rd, lh, [&](int i) { return sm_ids[i]; }, new_at, [&](int t) { return (int)kept16[t]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -1799,7 +1844,11 @@ __device__ __forceinline__ void reclaim_only(const BatchParams& p, const ReqDesc
 // window 64.  Without SnapKV units key norms gain (39.0 / 33.6), but streaming, which HBM bounds,
 // loses (755 / 769).
 __host__ __device__ constexpr int scored_occupancy(int d, int nt, int wv) {
-  return d == 64 && (nt == 1 || (nt == 0 && wv != kNarrow)) ? 8 : wv != kNarrow ? wv / 4 : nt == 3 ? (d == 64 ? 5 : 4) : 1;
+  return d == 64 && (nt == 1 || (nt == 0 && wv != kNarrow)) ? 8
+         : wv != kNarrow                                    ? wv / 4
+         : nt == 3                                          ? (d == 64 ? 5 : 4)
+         : nt == 1                                          ? 5
+                                                            : 1;
 }
 template <int D, int NT, int WV, bool kOnly>
 __device__ __forceinline__ void fused_unit(const BatchParams& p) {
@@ -1822,7 +1871,7 @@ __device__ __forceinline__ void fused_unit(const BatchParams& p) {
   int32_t* sm_new = reinterpret_cast<int32_t*>(lds + p.new_ids_at);
   const bool ids_in_lds = stage_block_ids<WV, kOnly>(p, rd, lh, sm_ids, sm_new);
   __syncthreads();
-  if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
+  if (is_streaming<kOnly>(rd)) {  // uniform per workgroup
     streaming_unit<WV>(p, rd, lh, kept);
   } else {
     bool snap = false;
@@ -1895,7 +1944,7 @@ __device__ __forceinline__ void fused_bounded(const BatchParams& p) {
   const bool ids_in_lds = stage_block_ids<WV, kOnly>(p, rd, lh, sm_ids, sm_new);
   if (threadIdx.x == 0) keep.bad = 0;
   __syncthreads();
-  if (rd.method == 3 /* FC_METHOD_STREAMING */) {  // uniform per workgroup
+  if (is_streaming<kOnly>(rd)) {  // uniform per workgroup
     streaming_unit<WV>(p, rd, lh, kept);
   } else {
     uint32_t key_lo = 0u, key_hi = 0xFFFFFFFFu;  // what is known of the selection's threshold
