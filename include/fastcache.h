@@ -376,8 +376,8 @@ int fc_set_score_mode(fc_pool* pool, int mode);
  * On by default (enable == 0 turns it off): the fused kernel of the default
  * scheduling bounds every column sum during its first pass over K and re-reads
  * only the key rows whose exact score can still decide the selection, for heads
- * of at least 512 tokens, or of at least 2048 where it runs in large workgroups
- * (heads of more than 8192 tokens, calls with few heads).  The kept
+ * that are long enough for that to pay (a few hundred to a few thousand tokens, by
+ * head_dim and by how many heads the call has).  The kept
  * set is the exact top-budget set of the exactly evaluated scores, as on the
  * two-pass path (the two evaluate a column sum in different orders of
  * addition, so between scores that agree to fp32 rounding the choice may

@@ -66,20 +66,8 @@ __host__ __device__ constexpr int bound_max_epochs() {
   const int b = 1 + bound_epoch_of_step((full / 16 + WV - 1) / WV, bound_seg<WV>(full));
   return a > b ? a : b;
 }
-// Shorter heads take the two passes: the tokens of the first step have no bounds, and a
-// step of a wide workgroup is three to four times as many tokens; bounding costs the same
-// next to rows of 128 bytes as next to rows of 256.  All kernels of a call, window 32, two
-// passes / pruned in us; the heads are of a few prompts, whose K mostly stays in the
-// memory-side cache, but for those of 16 prompts, 32 layers, whose K does not:
-//   narrow, 1024 heads, 128 channels  400 tokens 52.7 / 54.1   512   64.9 / 59.4   640   79.5 / 68.2
-//                        64 channels  512        38.5 / 44.7   700   48.0 / 51.6  1024   66.6 / 62.8
-//           16384 heads, 64 channels  512         414 / 429    700    560 / 551   1024    832 / 769
-//   wide, 256 heads,    128 channels 1024        46.5 / 48.6  1400   58.1 / 58.0  1500   61.2 / 59.3
-//                        64 channels 2048        45.2 / 48.6  3000   58.8 / 61.1  4500   86.3 / 83.9
-//   wide, 512 heads, window 64: 128 channels 1400 115.1 / 114.5, 1800 125.1 / 122.7 (384 heads);
-//                               64 channels 4500 163.3 / 169.7; narrow, 16384 heads 700 613 / 657
 template <int D, int WV>
-static constexpr int kBoundMinLen = WV == kNarrow ? (D == 128 ? 512 : 800) : (D == 128 ? 1408 : 4096);
+static constexpr int kBoundMinLen = plan_prune_from(D, WV != kNarrow);
 
 // A block's keys of one (layer, head), from memory to the operand layout of the
 // products: k[ks] of lane (q4, c16) = channels [32 ks + 8 q4, +8) of token c16.

@@ -30,7 +30,7 @@ def compute_units():
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
-def _plan(wl, methods=None, budgets=None, windows=None, lens=None, in_place=False):
+def _plan(wl, methods=None, budgets=None, windows=None, lens=None, in_place=False, args=()):
     """(requests of a call that are compressed, the driver's output)"""
     methods = wl.methods if methods is None else methods
     budgets = wl.budgets if budgets is None else budgets
@@ -39,7 +39,7 @@ def _plan(wl, methods=None, budgets=None, windows=None, lens=None, in_place=Fals
     idx = [r for r in range(wl.n_req) if methods[r] != fo.METHOD_NONE]
     text = "%d %d %d 0 %d %d %d\n" % (wl.n_layers, wl.n_heads, wl.head_dim, in_place, compute_units(), len(idx))
     text += "".join("%d %d %d %d\n" % (lens[r], methods[r], budgets[r], windows[r]) for r in idx)
-    return idx, subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    return idx, subprocess.run([_driver(), *args], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
 
 
 def planned(wl, **call):
@@ -55,6 +55,23 @@ def planned(wl, **call):
         for i in row[5:]:
             got[idx[i]] = "wide" if row[0] else "narrow"
     return got
+
+
+@functools.lru_cache(None)
+def _prune_limits():
+    out = subprocess.run([_driver(), "limits"], input="", capture_output=True, text=True, check=True).stdout
+    return [int(x) for x in out.split()[1:]]
+
+
+def prunes_from(head_dim, shape):
+    """The length from which heads are pruned in workgroups of a shape, "narrow" or "wide"."""
+    return _prune_limits()[2 * (64, 128).index(head_dim) + ("narrow", "wide").index(shape)]
+
+
+def without_plan_alloc(wl, scores, **call):
+    """Whether a call (of the default scheduling; scores: it asks for them) is one launch that reads
+    the table and the stack itself."""
+    return bool(int(_plan(wl, args=["one"], **call)[1][1].split()[2 if scores else 1]))
 
 
 def leaves_half(wl):

@@ -8,8 +8,8 @@ outrun the reference), and next to everything else a batch can hold.
 
 Every test runs its batch three times: as it is (few heads: split over several
 workgroups where they are long, and not pruned), with fillers that bring it into
-wide workgroups (which prune heads of 2048 tokens and more) and into narrow ones
-(of 512 and more); the host planner says that it got there."""
+wide workgroups and into narrow ones, each of which prunes from a length of its
+own on; the host planner says that it got there, and that a request is pruned."""
 
 import numpy as np
 import pytest
@@ -45,19 +45,22 @@ def _fill(wl, budgets, value=launch_shapes.FILLER_BUDGET):
     return launch_shapes.padded(budgets, wl.n_req - len(budgets), value)
 
 
-def _assert_prunes(wl, in_place=False, **kw):
-    """The requests that this shape prunes run in it."""
+def _assert_prunes(wl, in_place=False, least=1, **kw):
+    """The requests run in this shape (the longest in wide workgroups whatever it is), and at least
+    so many of them are pruned there."""
     if _shape == "few":
         return
     lens = kw.get("lens", wl.seq_lens)
     methods = kw.get("methods", wl.methods)
+    pruned = 0
     for r, got in enumerate(launch_shapes.planned(wl, in_place=in_place, **kw)):
         if methods[r] != fo.METHOD_SNAPKV:
             continue
-        if lens[r] > 8192 or (_shape == "wide" and lens[r] >= 2048):
-            assert got == "wide", (r, lens[r], got)
-        elif _shape == "narrow" and lens[r] >= 512:
-            assert got == "narrow", (r, lens[r], got)
+        want = "wide" if lens[r] > 8192 else _shape
+        if lens[r] >= launch_shapes.prunes_from(wl.head_dim, want):
+            assert got == want, (r, lens[r], got)
+            pruned += got == _shape or lens[r] > 8192
+    assert pruned >= least, (list(lens), pruned)
 
 
 def _pruned(wl, **kw):
@@ -68,8 +71,8 @@ def _pruned(wl, **kw):
     return s
 
 
-def _run_pruned(wl, repeats=1, sbs_kw=None, **kw):
-    _assert_prunes(wl)
+def _run_pruned(wl, repeats=1, sbs_kw=None, least=1, **kw):
+    _assert_prunes(wl, least=least)
     s = _pruned(wl, **(sbs_kw or {}))
     try:
         out = [s.compress_and_compare(scores=False, **kw) for _ in range(repeats)]
@@ -84,19 +87,22 @@ def _run_pruned(wl, repeats=1, sbs_kw=None, **kw):
                                        (2049, 33, 64, 35), (2500, 1, 128, 5), (5000, 17, 64, 3),
                                        (2111, 64, 128, 45), (4097, 64, 64, 99), (512, 32, 128, 50),
                                        (511, 64, 64, 30), (700, 64, 128, 80), (1200, 48, 64, 60),
-                                       (1031, 16, 128, 10)])
+                                       (1031, 16, 128, 10), (799, 32, 64, 40), (800, 32, 64, 40),
+                                       (1407, 16, 128, 30), (1408, 64, 128, 30), (4095, 48, 64, 20),
+                                       (4096, 16, 64, 20), (4500, 64, 64, 20)])
 def test_pruned_pass_keeps_what_two_passes_keep(L, W, d, pct):
-    """Heads on both sides of the length limit of the pruned path (the second
+    """Heads on both sides of the length limits of the pruned path (the second
     request of a case has half the length of the first), small and large
     budgets, every number of query tiles, ragged last blocks."""
     B = max(W, L * pct // 100)
+    pruned = _shape != "few" and L >= launch_shapes.prunes_from(d, _shape)
     _run_pruned(_custom([L, L // 2 + 9], [B, max(W, (L // 2 + 9) * pct // 100)],
-                        [fo.METHOD_SNAPKV] * 2, W=W, d=d, n_heads=4))
+                        [fo.METHOD_SNAPKV] * 2, W=W, d=d, n_heads=4), least=int(pruned))
 
 
 def test_reduced_benchmark_configurations():
-    _run_pruned(_in_shape(synth.make_workload(2, n_layers=2, n_heads=3)))
-    _run_pruned(_in_shape(synth.make_workload(3, n_layers=1, n_heads=2, n_req=6)))
+    for wl in (synth.make_workload(2, n_layers=2, n_heads=3), synth.make_workload(3, n_layers=1, n_heads=2, n_req=6)):
+        _run_pruned(_in_shape(wl), least=int(_shape == "narrow"))  # (up to 1200 tokens: short ones of wide workgroups)
     _run_pruned(_in_shape(synth.make_workload(4, n_layers=1, n_heads=2, n_req=4)))
     _run_pruned(_in_shape(synth.make_workload(4, n_layers=2, n_heads=3, n_req=2)))
 
@@ -120,20 +126,22 @@ def test_mixed_methods_and_pass_through_in_one_batch():
     _run_pruned(wl)
 
 
-def test_all_scores_tie():
+@pytest.mark.parametrize("lens,d", [([2600, 2100], 128), ([4600, 4100], 64)])
+def test_all_scores_tie(lens, d):
     """All-zero queries: every prefix token has the same score, and the kept
     prefix must be the lowest indices."""
-    wl = _custom([2600, 2100], [600, 300], [fo.METHOD_SNAPKV] * 2, W=16, d=64)
-    q = np.zeros((wl.n_req, 1, 2, 16, 64), dtype=np.float16)
+    wl = _custom(lens, [600, 300], [fo.METHOD_SNAPKV] * 2, W=16, d=d)
+    q = np.zeros((wl.n_req, 1, 2, 16, d), dtype=np.float16)
     out = _run_pruned(wl, sbs_kw={"q_host": q})
     assert out[0]["units_kept_identical"] == out[0]["units"]
 
 
-def test_scores_clustered_around_the_threshold():
+@pytest.mark.parametrize("L,d", [(3000, 128), (4300, 64)])
+def test_scores_clustered_around_the_threshold(L, d):
     """Keys that are all nearly alike: every column sum lies within a fraction
     of a per cent of the others, so the bounds decide nothing and the exact
     re-scoring carries the selection."""
-    wl = _custom([3000], [600], [fo.METHOD_SNAPKV], W=32, d=64, n_heads=2)
+    wl = _custom([L], [600], [fo.METHOD_SNAPKV], W=32, d=d, n_heads=2)
     kv = synth.fill_pool_host(wl)
     rng = np.random.default_rng(3)
     kv[:, :, 0] = (0.25 + rng.integers(0, 3, size=kv[:, :, 0].shape) / 1024.0).astype(np.float16)
@@ -199,8 +207,9 @@ def _keys_by_token(wl, make_key):
     return kv
 
 
-@pytest.mark.parametrize("shape", ["ramp", "sinks", "late_and_uneven", "giant_sinks", "late_giants"])
-def test_structured_attention_patterns(shape):
+@pytest.mark.parametrize("lens,d", [([3200, 2300], 128), ([4700, 4200], 64)])
+@pytest.mark.parametrize("pattern", ["ramp", "sinks", "late_and_uneven", "giant_sinks", "late_giants"])
+def test_structured_attention_patterns(pattern, lens, d):
     """Inputs on which the factor between a row's running sum and its final sum
     behaves in the three extreme ways: it keeps shrinking along the whole head
     (logits that rise with the position), it is one from the start (a few
@@ -210,23 +219,23 @@ def test_structured_attention_patterns(shape):
     selection is decided 60 nats below the largest score: a few first tokens
     that take all the mass, and a few late ones (every reference before them is
     overtaken by 2^86: the squares of the numerators leave the fp32 range)."""
-    d, W = 64, 32
-    wl = _custom([3200, 2300], [640, 300], [fo.METHOD_SNAPKV] * 2, W=W, d=d, n_heads=2)
+    W = 32
+    wl = _custom(lens, [640, 300], [fo.METHOD_SNAPKV] * 2, W=W, d=d, n_heads=2)
     rng = np.random.default_rng(17)
     u = np.zeros(d, np.float32)
-    u[:8] = 1.0
+    u[:8] = (d / 64.0) ** 0.5   # (the same logits at either channel count)
     noise = lambda: 0.3 * rng.standard_normal(d).astype(np.float32)
     q = synth.fill_q_window_host(wl).astype(np.float32) * 0.3
-    if shape == "ramp":
-        key = lambda r, tok: (noise() + u * (6.0 * tok / 3200.0)).astype(np.float16)
+    if pattern == "ramp":
+        key = lambda r, tok: (noise() + u * (6.0 * tok / lens[0])).astype(np.float16)
         q[..., :8] += 2.0
-    elif shape == "sinks":
+    elif pattern == "sinks":
         key = lambda r, tok: (noise() + (u * 8.0 if tok < 4 else 0.0)).astype(np.float16)
         q[..., :8] += 2.0
-    elif shape == "late_and_uneven":
+    elif pattern == "late_and_uneven":
         key = lambda r, tok: (noise() + (u * 5.0 if tok >= int(wl.seq_lens[r]) - 200 else 0.0)).astype(np.float16)
         q[:, :, :, ::2, :8] += 2.5          # every other query row leans on the late keys
-    elif shape == "giant_sinks":
+    elif pattern == "giant_sinks":
         key = lambda r, tok: (noise() + (u * 30.0 if tok < 4 else 0.0)).astype(np.float16)
         q[..., :8] += 2.0
     else:
@@ -240,8 +249,8 @@ def test_structured_attention_patterns(shape):
 def test_heads_beyond_the_narrow_limit_share_a_call_with_pruned_ones():
     """A request too long for narrow workgroups runs in wide ones whatever the rest
     of the call does; all of them are pruned."""
-    wl = _custom([9000, 3000, 8200], [1500, 600, 4000], [fo.METHOD_SNAPKV] * 3, W=32, d=64, n_heads=2)
-    _run_pruned(wl)
+    wl = _custom([9000, 4100, 8200], [1500, 600, 4000], [fo.METHOD_SNAPKV] * 3, W=32, d=64, n_heads=2)
+    _run_pruned(wl, least=3)
 
 
 def test_repeated_calls_and_in_place_compaction():
@@ -300,7 +309,9 @@ def test_random_long_batches(seed):
         lens.append(L); methods.append(m); budgets.append(B)
     wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=int(rng.integers(1, 3)), seed=300 + seed)
     print("seed", seed, lens, budgets, methods, W, d, flush=True)
-    _run_pruned(wl, pool_kernel=int(rng.choice([1, 5, 7, 9])))
+    limit = 1 << 30 if _shape == "few" else launch_shapes.prunes_from(d, _shape)
+    pruned = sum(m == fo.METHOD_SNAPKV and L >= limit for L, m in zip(lens, methods))
+    _run_pruned(wl, least=pruned, pool_kernel=int(rng.choice([1, 5, 7, 9])))
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -313,5 +324,5 @@ def test_every_row_is_read_again(n, d):
         n += 15  # (a last tile of another size)
     wl = _custom([n + 32], [n // 5 + 32], [fo.METHOD_SNAPKV], W=32, d=d, n_heads=1)
     q = np.zeros((wl.n_req, 1, 1, 32, d), dtype=np.float16)
-    out = _run_pruned(wl, sbs_kw={"q_host": q})
+    out = _run_pruned(wl, sbs_kw={"q_host": q}, least=int(_shape == "narrow" or n >= 4095))
     assert out[0]["units_kept_identical"] == out[0]["units"]

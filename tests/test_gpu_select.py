@@ -17,17 +17,20 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("width", [1, 3, 5, 7, 9, 11, 17, 63])
 @pytest.mark.parametrize("scores,shape", [(True, "few"), (False, "few"), (False, "wide"), (False, "narrow")])
 def test_token_counts_at_layout_edges(width, scores, shape):
-    """(Without the scores, classification: heads of 512 tokens and more in narrow workgroups,
-    2048 and more in wide ones.)"""
+    """(Without the scores, classification of the heads that are long enough to be pruned.)"""
     from parity_util import SideBySide
     W = 16
     # competing tokens: 1..5, around 256 (one chunk), 1024 (a segment per wavefront), 2048
     n_sel = [1, 2, 3, 4, 5, 31, 63, 255, 256, 257, 511, 513, 1023, 1024, 1025, 1027, 2047, 2049]
+    if shape == "wide":  # a segment per wavefront of sixteen
+        n_sel += [1407, 1535, 1537, 4095, 4096, 4097]
     lens = [n + W for n in n_sel]
     budgets = [W + max(1, n // 3) for n in n_sel]
-    wl = launch_shapes.in_shape(_custom(lens, budgets, [fo.METHOD_SNAPKV] * len(lens), W=W, d=64, n_heads=2), shape)
+    d = 64 if scores else 128
+    wl = launch_shapes.in_shape(_custom(lens, budgets, [fo.METHOD_SNAPKV] * len(lens), W=W, d=d, n_heads=2), shape)
     if shape != "few":
         assert launch_shapes.planned(wl) == [shape] * wl.n_req
+        assert sum(n >= launch_shapes.prunes_from(d, shape) for n in lens) >= 7
     s = SideBySide(wl)
     try:
         s.compress_and_compare(scores=scores, pool_kernel=width)

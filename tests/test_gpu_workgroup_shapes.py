@@ -43,7 +43,8 @@ SHAPES = [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 6
 @pytest.mark.parametrize("scores", [True, False])
 @pytest.mark.parametrize("W,d", SHAPES)
 def test_narrow_workgroups(W, d, scores):
-    lens = [W, 511, 512, 700, 2047, 2049, 4100, 8192]
+    limit = launch_shapes.prunes_from(d, "narrow")
+    lens = [W, limit - 1, limit, 700, 2047, 2049, 4100, 8192]
     _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW, shape="narrow")
 
 
@@ -52,7 +53,8 @@ def test_narrow_workgroups(W, d, scores):
 def test_wide_workgroups(W, d, scores):
     # both sides of the pruning limit of wide workgroups, of the narrow ones' longest head, of the
     # longer epochs and of a wavefront's last chunk; the longest head of all
-    lens = [W, 300, 2047, 2048 + W, 8192, 8193, 16384, 16385, 32768]
+    limit = launch_shapes.prunes_from(d, "wide")
+    lens = [W, 300, limit - 1, limit, limit + W, 8192, 8193, 16384, 16385, 32768]
     _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1, shape="wide")
 
 
