@@ -45,13 +45,19 @@ def kernel_symbol(slot, wl, pruning):
     if slot == "fused_unit":
         # wavefronts per workgroup: 4, or wide workgroups where a chip of 256 CUs gets at most two heads each
         units = len(wl.seq_lens) * wl.n_layers * wl.n_heads
-        waves = 4 if units > 512 else (16 if nt <= 2 else 12)
+        lens = wl.seq_lens[wl.methods == 1].astype(int)
+        # (short ones have four wavefronts whatever their number)
+        waves = 4 if units > 512 or wl.seq_lens.max() < 512 else (16 if nt <= 2 else 12)
         if not pruning:
             return "fc::fused_unit_kernel<%d, %d, %d>" % (wl.head_dim, nt, waves)
         # long heads of narrow workgroups leave half of the keys to the caches in their first pass
-        lens = wl.seq_lens[wl.methods == 1].astype(int)
         half = waves == 4 and wl.head_dim == 128 and lens.size > 0 and (lens ** 2).sum() >= 2304 * lens.sum() \
             and (nt <= 2 or wl.seq_lens.max() <= 7820)
+        # one request: a launch of its own, without plan_alloc before it (up to 2**20 tokens of all heads, 512 block ids)
+        blocks = -(-wl.seq_lens // 16) - (-wl.budgets // 16)
+        if len(wl.seq_lens) == 1 and units * wl.seq_lens[0] <= 1 << 20 and blocks[0] <= 512 \
+                and (units <= 256 or wl.seq_lens[0] * wl.head_dim >= 400 * 128):
+            return "fc::fused_bounded_only_kernel<%d, %d, %d>" % (wl.head_dim, nt, waves)
         return "fc::fused_bounded_kernel<%d, %d, %d, %s>" % (wl.head_dim, nt, waves, "true" if half else "false")
     if slot == "snapkv_score":
         return "fc::snapkv_score_kernel<%d, %d>" % (wl.head_dim, nt)

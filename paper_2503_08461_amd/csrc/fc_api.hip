@@ -674,7 +674,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
   MetaChunk inline_meta;
   const bool meta_inline = fits_inline(p, image.data(), meta_bytes, &inline_meta);
   // (a call that is timed kernel by kernel has its plan_alloc)
-  const bool only = meta_inline && !p->profiling && n_split == 0 && plan_one_launch(pv, plan, fused.size(), pruned_call);
+  const bool only = meta_inline && n_split == 0 && plan_one_launch(pv, plan, fused.size(), pruned_call);
   if (!meta_inline && (rc = upload_meta(p, image.data(), meta_bytes, dev_meta, no_alloc, stream)) != FC_OK)
     return rc;
 
