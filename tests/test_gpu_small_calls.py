@@ -5,6 +5,7 @@ after the other on the same pool (each may only see its own)."""
 import numpy as np
 import pytest
 
+import launch_shapes
 from oracle import decode_oracle as do
 from oracle import fastcache_oracle as fo
 from test_gpu_parity import _custom
@@ -80,29 +81,118 @@ def test_captured_decode_step(n_req):
         s.close()
 
 
-@pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("L,B,method,n_heads", [
-    (16, 16, fo.METHOD_SNAPKV, 1),       # everything kept, one block
-    (300, 77, fo.METHOD_SNAPKV, 4),      # narrow workgroups, two passes
-    (700, 300, fo.METHOD_SNAPKV, 300),   # more than one head a CU
-    (700, 300, fo.METHOD_KNORM, 5),      # wide
-    (1500, 400, fo.METHOD_SNAPKV, 140),  # wide
-    (6000, 2176, fo.METHOD_SNAPKV, 136),  # 375 + 136 ids: fits
-    (6000, 2192, fo.METHOD_SNAPKV, 136),  # 512 ids: just
-    (6000, 2193, fo.METHOD_SNAPKV, 136),  # 513: has a plan_alloc
-    (700, 300, fo.METHOD_STREAMING, 3),  # has one
-])
-def test_one_request(L, B, method, n_heads, in_place):
-    """A call of one request reads table and stack itself and writes both at its end, whichever row
-    of the table it has; call after call on one pool, also between calls of several requests."""
+def _one_request(L, B, method, n_heads, d, W, in_place=False):
+    """A side-by-side pool whose second of three requests is the one under test."""
     from parity_util import SideBySide
-    lens = [40, L, 33]
-    s = SideBySide(_custom(lens, [20, B, 20], [method] * 3, W=16, d=64, n_heads=n_heads), in_place=in_place)
+    wl = _custom([40 + W, L, 33 + W], [20 + W, B, 20 + W], [method] * 3, W=W, d=d, n_heads=n_heads)
+    return wl, SideBySide(wl, in_place=in_place)
+
+
+def _only(method, r):
+    methods = np.full(3, fo.METHOD_NONE, np.int32)
+    methods[slice(None) if r is None else r] = method
+    return methods
+
+
+SNAP = fo.METHOD_SNAPKV
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("L,B,method,n_heads,d,W,scores,shape,alone", [
+    (16, 16, SNAP, 1, 64, 16, False, "narrow", True),          # everything kept, one block
+    (300, 77, SNAP, 4, 64, 16, False, "narrow", True),         # two passes
+    (300, 77, SNAP, 4, 64, 16, True, "narrow", False),         # asks for the scores
+    (450, 140, SNAP, 129, 128, 64, False, "narrow", True),
+    (700, 300, SNAP, 300, 64, 16, False, "wide", False),       # many short heads
+    (900, 300, SNAP, 300, 64, 33, False, "wide", True),        # more than one head a CU
+    (640, 160, SNAP, 520, 128, 32, False, "narrow", True),     # pruned from here on: narrow, all numbers of query tiles
+    (530, 150, SNAP, 515, 128, 16, False, "narrow", True),
+    (530, 150, SNAP, 515, 128, 48, False, "narrow", True),
+    (700, 300, SNAP, 515, 128, 64, False, "narrow", True),
+    (820, 300, SNAP, 520, 64, 16, False, "narrow", True),
+    (1500, 400, SNAP, 140, 128, 16, False, "wide", True),      # wide
+    (1500, 400, SNAP, 140, 128, 64, False, "wide", True),
+    (4200, 900, SNAP, 136, 64, 32, False, "wide", True),
+    (6000, 2176, SNAP, 136, 64, 16, False, "wide", True),      # 375 + 136 ids: fits
+    (6000, 2192, SNAP, 136, 64, 16, False, "wide", True),      # 512 ids: just
+    (6000, 2193, SNAP, 136, 64, 16, False, "wide", False),     # 513: has a plan_alloc
+    (6000, 2193, SNAP, 136, 64, 16, True, "wide", False),
+    (200, 90, fo.METHOD_KNORM, 5, 64, 16, False, "narrow", True),
+    (700, 300, fo.METHOD_KNORM, 5, 64, 16, True, "wide", True),
+    (450, 300, fo.METHOD_KNORM, 515, 128, 16, False, "narrow", True),
+    (700, 300, fo.METHOD_STREAMING, 3, 64, 16, False, "wide", False),
+])
+def test_one_request(L, B, method, n_heads, d, W, scores, shape, alone, in_place):
+    """A call of one request reads table and stack itself and writes both at its end, whichever row
+    of the table it has; call after call on one pool, also between calls of several requests.
+    `alone`: the library's planner says that it takes that way (in place no ids are new)."""
+    wl, s = _one_request(L, B, method, n_heads, d, W, in_place)
+    if in_place and B == 2193:
+        alone = not scores
+    assert launch_shapes.planned(wl, methods=_only(method, 1), in_place=in_place)[1] == shape
+    assert launch_shapes.without_plan_alloc(wl, scores, methods=_only(method, 1), in_place=in_place) == alone
+    if alone and method == SNAP and W != 33 and L >= 512:
+        assert L >= launch_shapes.prunes_from(d, shape)
     try:
-        for only in (1, 1, None, 0, 2):
-            methods = np.full(3, fo.METHOD_NONE, np.int32)
-            methods[slice(None) if only is None else only] = method
-            budgets = np.maximum(16, np.minimum(s.lens_o, [20, B, 20]) - (only is None)).astype(np.int32)
-            s.compress_and_compare(methods, budgets)
+        for r in (1, 1, None, 0, 2):
+            budgets = np.maximum(W, np.minimum(s.lens_o, [20 + W, B, 20 + W]) - (r is None)).astype(np.int32)
+            s.compress_and_compare(_only(method, r), budgets, scores=scores)
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("L,B,method,n_heads,d,W,shape", [
+    (300, 77, SNAP, 4, 64, 16, "narrow"),
+    (640, 160, SNAP, 520, 128, 32, "narrow"),
+    (1500, 400, SNAP, 140, 128, 64, "wide"),
+    (700, 300, fo.METHOD_KNORM, 5, 64, 16, "wide"),
+])
+def test_captured_call_of_one_request(L, B, method, n_heads, d, W, shape):
+    """Replays between eager calls on the same pool: each leaves cache, table, free list and kept
+    list as the eager call does."""
+    import torch
+    from paper_2503_08461_amd import fastcache as fc
+    wl, s = _one_request(L, B, method, n_heads, d, W)
+    try:
+        methods = _only(method, 1)
+        assert launch_shapes.planned(wl, methods=methods)[1] == shape
+        assert launch_shapes.without_plan_alloc(wl, False, methods=methods)
+        kv0, bt0 = s.kv_dev.clone(), s.bt_dev.clone()
+        stack, top = fc.fc_pool_export_state(s.pool)
+        stack0 = torch.from_numpy(stack).to(s.dev)
+        kept = torch.zeros(int(B) * wl.n_layers * wl.n_heads, dtype=torch.int32, device=s.dev)
+
+        def rewind():
+            fc.fc_pool_import_state_dev(s.pool, stack0, top)
+            s.kv_dev.copy_(kv0)
+            s.bt_dev.copy_(bt0)
+            kept.fill_(-7)
+            torch.cuda.synchronize()
+
+        def call(m, out=None):
+            lens = wl.seq_lens.copy()
+            fc.fc_compress_batch(s.pool, s.bt_dev, lens, s.q_dev, W, m, wl.budgets, wl.pool_kernel, 0.0, None, out)
+            return lens
+
+        def state():
+            torch.cuda.synchronize()
+            return [s.kv_dev.view(torch.int16).clone(), s.bt_dev.clone(),
+                    torch.from_numpy(fc.fc_pool_export_state(s.pool)[0]), kept.clone()]
+
+        rewind()
+        call(methods, kept)
+        want = state()
+        assert fc.fc_pool_export_state(s.pool)[1] == top + (L + 15) // 16 - (B + 15) // 16
+        rewind()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call(methods, kept)
+        for other in (1, None, 0):
+            rewind()
+            call(_only(method, other))     # (the library's own state, in between)
+            rewind()
+            graph.replay()
+            for got, exact in zip(state(), want):
+                assert torch.equal(got, exact)
     finally:
         s.close()
