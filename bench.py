@@ -43,11 +43,10 @@ def kernel_symbol(slot, wl, pruning):
     `slot` on workload wl (None where a slot covers several kernels)."""
     nt = 1 if wl.window <= 16 else (2 if wl.window <= 32 else 4)
     if slot == "fused_unit":
-        # wavefronts per workgroup: 4, or wide workgroups where a chip of 256 CUs gets at most two heads each
+        # wavefronts per workgroup: 4, or wide workgroups where a chip of 256 CUs gets at most one long head each
         units = len(wl.seq_lens) * wl.n_layers * wl.n_heads
         lens = wl.seq_lens[wl.methods == 1].astype(int)
-        # (short ones have four wavefronts whatever their number)
-        waves = 4 if units > 512 or wl.seq_lens.max() < 512 else (16 if nt <= 2 else 12)
+        waves = 4 if units > 256 or wl.seq_lens.max() < (2048 if wl.head_dim == 128 else 896) else (16 if nt <= 2 else 12)
         if not pruning:
             return "fc::fused_unit_kernel<%d, %d, %d>" % (wl.head_dim, nt, waves)
         # long heads of narrow workgroups leave half of the keys to the caches in their first pass

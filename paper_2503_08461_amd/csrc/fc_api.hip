@@ -786,6 +786,7 @@ int compress_batch_impl(fc_pool* p, int32_t* dev_block_tables, int max_blocks_pe
       bc.order_fused = dev_lists + fused_at[i];
       bc.n_fused = (int)l.units.size();
       bc.half_reuse = l.half_reuse ? 1 : 0;
+      bc.prune_from = l.prune_from;
       e = launch_fused(bc, l.query_tiles, l.max_len, l.max_blocks, l.wide, stream);
     }
     return e;

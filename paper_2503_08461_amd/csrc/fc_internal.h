@@ -103,6 +103,7 @@ struct BatchParams {
   int32_t main_reclaims;       // 1: the last kernel of the stage does what reclaim_kernel would
   int32_t bounded;             // 1: the fused kernel prunes the second pass of its SnapKV units
   int32_t half_reuse;          // ... and leaves only half of the keys that it reads first to the caches
+  PruneFrom prune_from;        // ... and prunes heads of these lengths and more
   int32_t* owner;              // ownership checks (debug mode): [n_blocks] 0 free, 1 handed out,
                                // 2 being released; NULL when the checks are off
   // A call of one request whose only launch is a fused one (plan_one_launch): its descriptor;

@@ -38,34 +38,44 @@ constexpr int kMixedQueryTiles = kPlanClasses;
 // (Calls of key-norm requests alone would be better off with a limit of 64 to 96 heads.)
 constexpr int kSplitMinLen = 2048;
 
-// Whether a call of `units` heads of up to 8192 tokens is better off in wide
-// workgroups.  With at most one head per CU it is, from the length on at which a
-// head keeps their wavefronts busy; with up to two per CU, which narrow workgroups
-// run at once and wide ones one after the other, heaviest first, from there on as
-// well unless all heads are alike; with more it is not.  All kernels of a call,
-// narrow / wide in us, at 256 and at 512 heads:
-//   SnapKV, window 32, 128 channels       64 channels
-//     300 tokens   35.9 / 36.9    43.5 / 56.3     30.5 / 30.7    34.0 / 43.5
-//     512          53.9 / 42.3    62.9 / 66.7     48.2 / 33.1    54.3 / 49.0
-//    1300          91.7 / 65.1   106.2 / 112.3    83.6 / 44.2    94.1 / 69.3
-//    2300         132.1 / 92.4   158.5 / 154.9   120.1 / 73.3   137.8 / 126.8
-//    3200         168.2 / 110.2  210.4 / 199.5   169.1 / 90.5   171.8 / 152.5
-//   key-norm
-//     200          29.2 / 28.3    32.3 / 36.7     25.4 / 24.8    26.8 / 32.0
-//     640          46.4 / 34.9    52.9 / 53.7     33.5 / 27.7    38.8 / 41.2
-//     900          56.8 / 39.4    64.9 / 62.4     40.4 / 30.3    46.6 / 45.8
-//    1800          90.6 / 57.6   104.6 / 95.0     62.4 / 38.5    70.3 / 61.0
-// and with lengths that differ (SnapKV, 128 channels, 300-900 tokens): 288 heads
-// 72.0 / 56.5, 384 heads 73.9 / 65.1, 512 heads 79.2 / 74.7.
-bool wide_pays(const CompressPlan& plan, size_t units, int n_cu) {
+// Whether the `units` heads of up to 8192 tokens of a call are better off in wide workgroups.
+// Of these a CU takes one at a time, of the narrow ones three or four.  So wide ones are for
+// calls that one round of them can take: the heaviest head as long as it keeps their wavefronts
+// busy, and all heads together, heaviest first, no more than that for every CU.  All kernels
+// of a call, narrow / wide in us, each pruned or not, whichever is the faster:
+//   heads                4            128          256          320          512
+//   SnapKV, window 32, 128 channels
+//     1000 tokens     35 / 38      39 / 43      45 / 48      54 / 75      66 / 82
+//     2000            52 / 54      62 / 64      74 / 73      89 / 117    108 / 131
+//     3000                                     102 / 95     121 / 154    153 / 176
+//     8000                                     232 / 222    289 / 355    399 / 426
+//   64 channels
+//      700            25 / 26      26 / 28      28 / 29      31 / 43      35 / 47
+//     1000            29 / 28      31 / 30      35 / 33      39 / 51      44 / 54
+//     2000            41 / 37      48 / 43      53 / 47      61 / 73      69 / 81
+//     8000                                     166 / 129    194 / 220    221 / 240
+//   key-norm, 128 channels
+//      256          19.0 / 18.8  19.9 / 19.6  21.0 / 20.4  22.2 / 27.8  24.8 / 32.0
+//      640          24.0 / 20.8  26.6 / 23.1  29.8 / 29.1  33.9 / 40.0  40.5 / 46.1
+//     2000          43.0 / 29.7  52.5 / 43.5  58.5 / 56.6  71.3 / 81.3  93.9 / 99.9
+// (windows 16 and 64 cross where 32 does, streaming where key norms do).  With lengths that
+// differ, 500-4000 tokens, SnapKV: 320 heads 107 / 101 and at 64 channels 81 / 66, 384 heads
+// 109 / 106 and 83 / 66, 512, which are more than a round, 137 / 159 and 92 / 100.
+bool wide_pays(const PoolView& pool, const CompressPlan& plan, size_t units, int n_cu) {
   if (units > 2 * (size_t)n_cu) return false;
-  const bool one_each = units <= (size_t)n_cu;
-  const int snap_from = 512, other_from = one_each ? 256 : 768;
-  for (const ReqDesc& d : plan.descs) {
+  const ReqDesc* heaviest = nullptr;
+  int64_t most = 0, all = 0;
+  for (size_t i = 0; i < plan.descs.size(); ++i) {
+    const ReqDesc& d = plan.descs[i];
     if (d.method != PLAN_METHOD_STREAMING && d.seq_len > kPlanFusedMaxLen) continue;  // (wide anyhow)
-    if (d.seq_len >= (d.method == PLAN_METHOD_SNAPKV ? snap_from : other_from)) return true;
+    all += plan.weights[i] * (int64_t)(pool.n_layers * pool.n_heads);
+    if (!heaviest || plan.weights[i] > most) {
+      heaviest = &d;
+      most = plan.weights[i];
+    }
   }
-  return false;
+  if (!heaviest || all > most * n_cu) return false;
+  return heaviest->seq_len >= (heaviest->method != PLAN_METHOD_SNAPKV ? 256 : pool.head_dim == 128 ? 2048 : 896);
 }
 
 // From what mean length of its SnapKV heads (each weighted by its own) on a launch of
@@ -243,6 +253,38 @@ int plan_compress(const PoolView& pool, const CompressArgs& a, CompressPlan* pla
   return PLAN_OK;
 }
 
+// Shorter heads take the two passes: the tokens of the first step have no bounds, and a step of
+// a wide workgroup is three to four times as many tokens; bounding costs the same next to rows
+// of 128 bytes as next to rows of 256, and more with more query tiles; and where a CU has less
+// than its narrow workgroups to do, it waits for the longer chain of phases and not for K.  All
+// kernels of a call, two passes / pruned in us:
+//   narrow, 128 channels     window 32                     window 64
+//     256 heads     1400 tokens  58 / 60  2000  77 / 74    1400  62 / 64  2000   81 / 79
+//     512            512         41 / 45   700  53 / 53     700  53 / 55  1000   72 / 68
+//     1024           450       60.5 / 59  512   66 / 62     512  76 / 83   640   91 / 95
+//     4096           450        193 / 191  512 218 / 210    580 262 / 262  640  283 / 280
+//     16384          450        756 / 733  512 850 / 810    450 787 / 782  580 1000 / 966
+//   64 channels
+//     256           8000        167 / 166                  5000 126 / 123
+//     512           1400         57 / 57  2000  73 / 69    3000 107 / 105
+//     2048           800         97 / 101  900 108 / 107   1024 126 / 124 1200  148 / 144
+//     4096           800        172 / 173 1024 220 / 214   1200 275 / 280 1400  320 / 312
+//     16384          700        566 / 558  900 738 / 701    900 798 / 817 1200 1040 / 1032
+//   wide, 256 heads
+//     128 channels  1600         66 / 67  2000  78 / 73    1600  68 / 69  2000   80 / 77
+//      64           4500         85 / 85  5500 100 / 97    5500 105 / 105 7000  129 / 127
+//   window 16, wide: 128 channels 1400 57 / 57, 64 channels 3000 61 / 61; window 48 as 64, at
+//   64 channels earlier: narrow, 2048 heads, 900 114 / 113, wide 5500 101 / 100
+// (192 heads of 64 channels cross later, 5000 tokens 83 / 88, 8000 122 / 120.)
+PruneFrom plan_prune_from(int head_dim, bool wide, size_t heads, int n_cu) {
+  if (wide) return head_dim == 128 ? PruneFrom{{1408, 1664, 1664, 1664}} : PruneFrom{{3584, 5120, 5632, 7168}};
+  if (heads > 2 * (size_t)n_cu)
+    return head_dim == 128 ? PruneFrom{{512, 512, 576, 576}} : PruneFrom{{864, 864, 1024, 1152}};
+  if (heads > (size_t)n_cu)
+    return head_dim == 128 ? PruneFrom{{768, 768, 896, 896}} : PruneFrom{{2048, 2048, 2048, 3072}};
+  return head_dim == 128 ? PruneFrom{{1664, 1664, 2048, 2048}} : PruneFrom{{4096, 4096, 4096, 4096}};
+}
+
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu) {
   const size_t n_lh = (size_t)pool.n_layers * pool.n_heads;
   // Narrow workgroups (three or four to a CU) take heads of up to 8192 tokens; wide
@@ -258,7 +300,7 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
   };
   size_t short_units = 0;
   for (int c = 0; c < kPlanClasses; ++c) short_units += plan.lists[LIST_FUSED + c].size() * n_lh;
-  const bool few = wide_pays(plan, short_units, n_cu);
+  const bool few = wide_pays(pool, plan, short_units, n_cu);
   for (int c = 0; c < kPlanClasses; ++c) {
     add(few ? wide : narrow, plan.lists[LIST_FUSED + c]);
     if (pool.score_mode == PLAN_SCORE_AUTO) add(wide, plan.lists[LIST_SNAP + c]);
@@ -283,6 +325,7 @@ std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const Compres
     }
     l->half_reuse = pool.head_dim == 128 && !l->wide && tokens > 0 && weighted >= kHalfReuseLen * tokens &&
                     (l->query_tiles <= 2 || fused_lds(l->max_len, l->max_blocks, false).words <= kPlanHalfReuseWords);
+    l->prune_from = plan_prune_from(pool.head_dim, l->wide, l->units.size() * n_lh, n_cu);
     launches.push_back(std::move(*l));
   }
   return launches;

@@ -103,6 +103,13 @@ struct CompressPlan {
 // meaningful.  A batch with nothing to compress gives PLAN_OK and no descs.
 int plan_compress(const PoolView& pool, const CompressArgs& args, CompressPlan* plan);
 
+// Lengths from which a fused launch of `heads` heads prunes the second pass of its SnapKV
+// heads, by the query tiles of their windows (fc_plan.cpp has the times of both sides).
+struct PruneFrom {
+  int32_t tiles[kPlanClasses - 1];  // of 1..4
+};
+PruneFrom plan_prune_from(int head_dim, bool wide, size_t heads, int n_cu);
+
 // The launches of the fused kernels (score -> select -> gather in one workgroup
 // per unit) of a planned call, heaviest unit first in each.
 struct FusedLaunch {
@@ -112,6 +119,7 @@ struct FusedLaunch {
   int max_len = 0;             // longest head that is scored
   int max_blocks = 0;          // most blocks of a unit
   bool half_reuse = false;     // long heads: a pruned first pass leaves only half of the keys to the caches
+  PruneFrom prune_from = {};
 };
 std::vector<FusedLaunch> plan_fused_launches(const PoolView& pool, const CompressPlan& plan, int n_cu);
 
@@ -122,23 +130,6 @@ bool plan_one_launch(const PoolView& pool, const CompressPlan& plan, size_t n_la
 // Most block ids, old and new, of such a request: the wavefront that takes its old blocks
 // back keeps them in LDS.
 static constexpr int kPlanOnlyMaxIds = 512;
-
-// Length from which the fused kernels prune the second pass of a SnapKV head.  Shorter heads
-// take the two passes: the tokens of the first step have no bounds, and a step of a wide
-// workgroup is three to four times as many tokens; bounding costs the same next to rows of
-// 128 bytes as next to rows of 256.
-// All kernels of a call, window 32, two passes / pruned in us; the heads are of a few
-// prompts, whose K mostly stays in the memory-side cache, but for those of 16 prompts, 32 layers, whose K does not:
-//   narrow, 1024 heads, 128 channels  400 tokens 52.7 / 54.1   512   64.9 / 59.4   640   79.5 / 68.2
-//                        64 channels  512        38.5 / 44.7   700   48.0 / 51.6  1024   66.6 / 62.8
-//           16384 heads, 64 channels  512         414 / 429    700    560 / 551   1024    832 / 769
-//   wide, 256 heads,    128 channels 1024        46.5 / 48.6  1400   58.1 / 58.0  1500   61.2 / 59.3
-//                        64 channels 2048        45.2 / 48.6  3000   58.8 / 61.1  4500   86.3 / 83.9
-//   wide, 512 heads, window 64: 128 channels 1400 115.1 / 114.5, 1800 125.1 / 122.7 (384 heads);
-//                               64 channels 4500 163.3 / 169.7; narrow, 16384 heads 700 613 / 657
-constexpr int plan_prune_from(int head_dim, bool wide) {
-  return wide ? (head_dim == 128 ? 1408 : 4096) : (head_dim == 128 ? 512 : 800);
-}
 
 // A call with so few heads that they are better split over workgroups: segments
 // per head, or 0 (not split).  Otherwise all requests of the call run that way;

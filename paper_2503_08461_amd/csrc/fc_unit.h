@@ -66,8 +66,9 @@ __host__ __device__ constexpr int bound_max_epochs() {
   const int b = 1 + bound_epoch_of_step((full / 16 + WV - 1) / WV, bound_seg<WV>(full));
   return a > b ? a : b;
 }
-template <int D, int WV>
-static constexpr int kBoundMinLen = plan_prune_from(D, WV != kNarrow);
+// (the first step lies before the window)
+template <int WV>
+static constexpr int kBoundMinLen = 16 * WV + 64;
 
 // A block's keys of one (layer, head), from memory to the operand layout of the
 // products: k[ks] of lane (q4, c16) = channels [32 ks + 8 q4, +8) of token c16.
@@ -1252,7 +1253,6 @@ __device__ __forceinline__ void snapkv_bounds(const BatchParams& p, const ReqDes
     else  // (a block past the end is masked whole)
       numerators(std::integral_constant<int, 2>{}, b, kc);
   };
-  static_assert(kBoundMinLen<D, WV> - 64 >= 16 * WV, "the first step lies before the window");
   half8 ka[KS], kb[KS];
   load_even(wave, ka);
   load_odd(wave + WV, kb);
@@ -1943,7 +1943,7 @@ __device__ __forceinline__ void fused_bounded(const BatchParams& p) {
         const int q4 = (threadIdx.x & 63) >> 4;
         half8 qreg[N][KS];
         load_window_queries<D, N>(p, rd, lh, qreg);
-        const bool prune = rd.seq_len >= kBoundMinLen<D, WV>;  // uniform
+        const bool prune = rd.seq_len >= max(p.prune_from.tiles[N - 1], kBoundMinLen<WV>);  // uniform
         if (prune) snapkv_bounds<D, N, WV, kHalf>(p, rd, lh, sm_ids, sh.bound, keep, stage, qreg);
         if (!prune || keep.bad) {  // bad: not representable against a running reference
           snapkv_unit_q<D, N, WV, true>(p, rd, lh, sm_ids, sh.score, qreg, [&](int j, float v) { stage[j] = v; });

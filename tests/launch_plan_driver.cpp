@@ -2,9 +2,8 @@
 // plan_split, plan_fused_launches).  Built, fed and checked by test_launch_plan.py.
 // Input, one case per line (all integers):
 //   nl nh d mode in_place n_cu n_req, then n_req times: length method budget window
-// With any argument: first the lengths from which heads are pruned (64 channels narrow and
-// wide, 128 narrow and wide), then one line per case, whether it goes without plan_alloc
-// (plan_one_launch), as a pruned call and as one that is not.
+// With any argument: one line per case, whether it goes without plan_alloc (plan_one_launch), as
+// a pruned call and as one that is not.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -16,9 +15,6 @@ using namespace fc;
 int main(int argc, char**) {
   PoolView pv;
   int mode, in_place, n_cu, n_req;
-  if (argc > 1)
-    printf("P %d %d %d %d\n", plan_prune_from(64, false), plan_prune_from(64, true), plan_prune_from(128, false),
-           plan_prune_from(128, true));
   while (scanf("%d %d %d %d %d %d %d", &pv.n_layers, &pv.n_heads, &pv.head_dim, &mode, &in_place,
                &n_cu, &n_req) == 7) {
     std::vector<int32_t> lens(n_req), methods(n_req), budgets(n_req), windows(n_req), widths(n_req, 7);
@@ -50,6 +46,8 @@ int main(int argc, char**) {
     for (const FusedLaunch& l : plan_fused_launches(pv, plan, n_cu)) {
       printf("F %d %d %d %d %d", l.wide ? 1 : 0, l.query_tiles, l.max_len, l.max_blocks, l.half_reuse ? 1 : 0);
       for (int32_t i : l.units) printf(" %d", i);
+      printf("\nP");  // the lengths from which it prunes, by query tiles
+      for (int32_t n : l.prune_from.tiles) printf(" %d", n);
       printf("\n");
     }
   }

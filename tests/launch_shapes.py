@@ -50,28 +50,32 @@ def planned(wl, **call):
         for r in idx:
             got[r] = "split"
         return got
-    for line in out[1:]:
+    for line in out[1::2]:
         row = [int(x) for x in line.split()[1:]]
         for i in row[5:]:
             got[idx[i]] = "wide" if row[0] else "narrow"
     return got
 
 
-@functools.lru_cache(None)
-def _prune_limits():
-    out = subprocess.run([_driver(), "limits"], input="", capture_output=True, text=True, check=True).stdout
-    return [int(x) for x in out.split()[1:]]
-
-
-def prunes_from(head_dim, shape):
-    """The length from which heads are pruned in workgroups of a shape, "narrow" or "wide"."""
-    return _prune_limits()[2 * (64, 128).index(head_dim) + ("narrow", "wide").index(shape)]
+def pruned(wl, **call):
+    """Whether a call without scores prunes each request, by the planner's lengths for its launch."""
+    idx, out = _plan(wl, **call)
+    methods, lens = call.get("methods", wl.methods), call.get("lens", wl.seq_lens)
+    windows = call.get("windows", [wl.window] * wl.n_req)
+    got = [False] * wl.n_req
+    if int(out[0].split()[1]):
+        return got
+    for launch, limits in zip(out[1::2], out[2::2]):
+        limits = [int(x) for x in limits.split()[1:]]
+        for r in (idx[int(i)] for i in launch.split()[6:]):
+            got[r] = methods[r] == fo.METHOD_SNAPKV and lens[r] >= limits[(windows[r] + 15) // 16 - 1]
+    return got
 
 
 def without_plan_alloc(wl, scores, **call):
     """Whether a call (of the default scheduling; scores: it asks for them) is one launch that reads
     the table and the stack itself."""
-    return bool(int(_plan(wl, args=["one"], **call)[1][1].split()[2 if scores else 1]))
+    return bool(int(_plan(wl, args=["one"], **call)[1][0].split()[2 if scores else 1]))
 
 
 def leaves_half(wl):

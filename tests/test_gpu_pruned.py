@@ -46,21 +46,18 @@ def _fill(wl, budgets, value=launch_shapes.FILLER_BUDGET):
 
 
 def _assert_prunes(wl, in_place=False, least=1, **kw):
-    """The requests run in this shape (the longest in wide workgroups whatever it is), and at least
-    so many of them are pruned there."""
+    """At least so many requests are pruned in this shape (the longest in wide workgroups whatever it is)."""
     if _shape == "few":
         return
     lens = kw.get("lens", wl.seq_lens)
-    methods = kw.get("methods", wl.methods)
-    pruned = 0
-    for r, got in enumerate(launch_shapes.planned(wl, in_place=in_place, **kw)):
-        if methods[r] != fo.METHOD_SNAPKV:
-            continue
-        want = "wide" if lens[r] > 8192 else _shape
-        if lens[r] >= launch_shapes.prunes_from(wl.head_dim, want):
-            assert got == want, (r, lens[r], got)
-            pruned += got == _shape or lens[r] > 8192
-    assert pruned >= least, (list(lens), pruned)
+    shapes = launch_shapes.planned(wl, in_place=in_place, **kw)
+    got = [r for r, p in enumerate(launch_shapes.pruned(wl, in_place=in_place, **kw))
+           if p and (shapes[r] == _shape or lens[r] > 8192)]
+    assert len(got) >= least, (list(lens), shapes, got)
+
+
+# heads of these lengths and more are pruned in wide and in narrow workgroups, whatever their windows
+_ALWAYS = {("wide", 128): 2048, ("wide", 64): 7168, ("narrow", 128): 576, ("narrow", 64): 1152}
 
 
 def _pruned(wl, **kw):
@@ -87,15 +84,15 @@ def _run_pruned(wl, repeats=1, sbs_kw=None, least=1, **kw):
                                        (2049, 33, 64, 35), (2500, 1, 128, 5), (5000, 17, 64, 3),
                                        (2111, 64, 128, 45), (4097, 64, 64, 99), (512, 32, 128, 50),
                                        (511, 64, 64, 30), (700, 64, 128, 80), (1200, 48, 64, 60),
-                                       (1031, 16, 128, 10), (799, 32, 64, 40), (800, 32, 64, 40),
-                                       (1407, 16, 128, 30), (1408, 64, 128, 30), (4095, 48, 64, 20),
-                                       (4096, 16, 64, 20), (4500, 64, 64, 20)])
+                                       (1031, 16, 128, 10), (863, 32, 64, 40), (864, 32, 64, 40),
+                                       (575, 48, 128, 30), (576, 64, 128, 30), (3583, 16, 64, 20),
+                                       (3584, 16, 64, 20), (7168, 64, 64, 20)])
 def test_pruned_pass_keeps_what_two_passes_keep(L, W, d, pct):
     """Heads on both sides of the length limits of the pruned path (the second
     request of a case has half the length of the first), small and large
     budgets, every number of query tiles, ragged last blocks."""
     B = max(W, L * pct // 100)
-    pruned = _shape != "few" and L >= launch_shapes.prunes_from(d, _shape)
+    pruned = _shape != "few" and L >= _ALWAYS[_shape, d]
     _run_pruned(_custom([L, L // 2 + 9], [B, max(W, (L // 2 + 9) * pct // 100)],
                         [fo.METHOD_SNAPKV] * 2, W=W, d=d, n_heads=4), least=int(pruned))
 
@@ -136,7 +133,7 @@ def test_all_scores_tie(lens, d):
     assert out[0]["units_kept_identical"] == out[0]["units"]
 
 
-@pytest.mark.parametrize("L,d", [(3000, 128), (4300, 64)])
+@pytest.mark.parametrize("L,d", [(3000, 128), (5200, 64)])
 def test_scores_clustered_around_the_threshold(L, d):
     """Keys that are all nearly alike: every column sum lies within a fraction
     of a per cent of the others, so the bounds decide nothing and the exact
@@ -207,7 +204,7 @@ def _keys_by_token(wl, make_key):
     return kv
 
 
-@pytest.mark.parametrize("lens,d", [([3200, 2300], 128), ([4700, 4200], 64)])
+@pytest.mark.parametrize("lens,d", [([3200, 2300], 128), ([5400, 5200], 64)])
 @pytest.mark.parametrize("pattern", ["ramp", "sinks", "late_and_uneven", "giant_sinks", "late_giants"])
 def test_structured_attention_patterns(pattern, lens, d):
     """Inputs on which the factor between a row's running sum and its final sum
@@ -249,7 +246,7 @@ def test_structured_attention_patterns(pattern, lens, d):
 def test_heads_beyond_the_narrow_limit_share_a_call_with_pruned_ones():
     """A request too long for narrow workgroups runs in wide ones whatever the rest
     of the call does; all of them are pruned."""
-    wl = _custom([9000, 4100, 8200], [1500, 600, 4000], [fo.METHOD_SNAPKV] * 3, W=32, d=64, n_heads=2)
+    wl = _custom([9000, 5200, 8200], [1500, 600, 4000], [fo.METHOD_SNAPKV] * 3, W=32, d=64, n_heads=2)
     _run_pruned(wl, least=3)
 
 
@@ -309,7 +306,7 @@ def test_random_long_batches(seed):
         lens.append(L); methods.append(m); budgets.append(B)
     wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=int(rng.integers(1, 3)), seed=300 + seed)
     print("seed", seed, lens, budgets, methods, W, d, flush=True)
-    limit = 1 << 30 if _shape == "few" else launch_shapes.prunes_from(d, _shape)
+    limit = 1 << 30 if _shape == "few" else _ALWAYS[_shape, d]
     pruned = sum(m == fo.METHOD_SNAPKV and L >= limit for L, m in zip(lens, methods))
     _run_pruned(wl, least=pruned, pool_kernel=int(rng.choice([1, 5, 7, 9])))
 
@@ -324,5 +321,5 @@ def test_every_row_is_read_again(n, d):
         n += 15  # (a last tile of another size)
     wl = _custom([n + 32], [n // 5 + 32], [fo.METHOD_SNAPKV], W=32, d=d, n_heads=1)
     q = np.zeros((wl.n_req, 1, 1, 32, d), dtype=np.float16)
-    out = _run_pruned(wl, sbs_kw={"q_host": q}, least=int(_shape == "narrow" or n >= 4095))
+    out = _run_pruned(wl, sbs_kw={"q_host": q}, least=int(_shape == "narrow" or n >= (4095 if d == 128 else 8160)))
     assert out[0]["units_kept_identical"] == out[0]["units"]

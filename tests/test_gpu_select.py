@@ -30,7 +30,7 @@ def test_token_counts_at_layout_edges(width, scores, shape):
     wl = launch_shapes.in_shape(_custom(lens, budgets, [fo.METHOD_SNAPKV] * len(lens), W=W, d=d, n_heads=2), shape)
     if shape != "few":
         assert launch_shapes.planned(wl) == [shape] * wl.n_req
-        assert sum(n >= launch_shapes.prunes_from(d, shape) for n in lens) >= 7
+        assert sum(launch_shapes.pruned(wl)) >= 7
     s = SideBySide(wl)
     try:
         s.compress_and_compare(scores=scores, pool_kernel=width)

@@ -98,41 +98,43 @@ SNAP = fo.METHOD_SNAPKV
 
 
 @pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("L,B,method,n_heads,d,W,scores,shape,alone", [
-    (16, 16, SNAP, 1, 64, 16, False, "narrow", True),          # everything kept, one block
-    (300, 77, SNAP, 4, 64, 16, False, "narrow", True),         # two passes
-    (300, 77, SNAP, 4, 64, 16, True, "narrow", False),         # asks for the scores
-    (450, 140, SNAP, 129, 128, 64, False, "narrow", True),
-    (700, 300, SNAP, 300, 64, 16, False, "wide", False),       # many short heads
-    (900, 300, SNAP, 300, 64, 33, False, "wide", True),        # more than one head a CU
-    (640, 160, SNAP, 520, 128, 32, False, "narrow", True),     # pruned from here on: narrow, all numbers of query tiles
-    (530, 150, SNAP, 515, 128, 16, False, "narrow", True),
-    (530, 150, SNAP, 515, 128, 48, False, "narrow", True),
-    (700, 300, SNAP, 515, 128, 64, False, "narrow", True),
-    (820, 300, SNAP, 520, 64, 16, False, "narrow", True),
-    (1500, 400, SNAP, 140, 128, 16, False, "wide", True),      # wide
-    (1500, 400, SNAP, 140, 128, 64, False, "wide", True),
-    (4200, 900, SNAP, 136, 64, 32, False, "wide", True),
-    (6000, 2176, SNAP, 136, 64, 16, False, "wide", True),      # 375 + 136 ids: fits
-    (6000, 2192, SNAP, 136, 64, 16, False, "wide", True),      # 512 ids: just
-    (6000, 2193, SNAP, 136, 64, 16, False, "wide", False),     # 513: has a plan_alloc
-    (6000, 2193, SNAP, 136, 64, 16, True, "wide", False),
-    (200, 90, fo.METHOD_KNORM, 5, 64, 16, False, "narrow", True),
-    (700, 300, fo.METHOD_KNORM, 5, 64, 16, True, "wide", True),
-    (450, 300, fo.METHOD_KNORM, 515, 128, 16, False, "narrow", True),
-    (700, 300, fo.METHOD_STREAMING, 3, 64, 16, False, "wide", False),
+@pytest.mark.parametrize("L,B,method,n_heads,d,W,scores,shape,pruned,alone", [
+    (16, 16, SNAP, 1, 64, 16, False, "narrow", False, True),        # everything kept, one block
+    (300, 77, SNAP, 4, 64, 16, False, "narrow", False, True),       # two passes
+    (300, 77, SNAP, 4, 64, 16, True, "narrow", False, False),       # asks for the scores
+    (450, 140, SNAP, 129, 128, 64, False, "narrow", False, True),
+    (700, 300, SNAP, 300, 64, 16, False, "narrow", False, False),   # many short heads
+    (900, 300, SNAP, 300, 64, 33, False, "narrow", False, True),    # more than one head a CU
+    (800, 300, SNAP, 300, 128, 32, False, "narrow", True, True),
+    (640, 160, SNAP, 520, 128, 32, False, "narrow", True, True),    # more than two, each number of query tiles
+    (530, 150, SNAP, 515, 128, 16, False, "narrow", True, True),
+    (600, 150, SNAP, 515, 128, 48, False, "narrow", True, True),
+    (700, 300, SNAP, 515, 128, 64, False, "narrow", True, True),
+    (880, 300, SNAP, 520, 64, 16, False, "narrow", True, True),
+    (1000, 400, SNAP, 140, 64, 32, False, "wide", False, True),
+    (2100, 400, SNAP, 140, 128, 16, False, "wide", True, True),
+    (2100, 400, SNAP, 140, 128, 64, False, "wide", True, True),
+    (5200, 900, SNAP, 136, 64, 32, False, "wide", True, True),
+    (6000, 2176, SNAP, 136, 64, 16, False, "wide", True, True),     # 375 + 136 ids: fits
+    (6000, 2192, SNAP, 136, 64, 16, False, "wide", True, True),     # 512 ids: just
+    (6000, 2193, SNAP, 136, 64, 16, False, "wide", True, False),    # 513: has a plan_alloc
+    (6000, 2193, SNAP, 136, 64, 16, True, "wide", True, False),
+    (200, 90, fo.METHOD_KNORM, 5, 64, 16, False, "narrow", False, True),
+    (700, 300, fo.METHOD_KNORM, 5, 64, 16, True, "wide", False, True),
+    (450, 300, fo.METHOD_KNORM, 515, 128, 16, False, "narrow", False, True),
+    (700, 300, fo.METHOD_STREAMING, 3, 64, 16, False, "wide", False, False),
 ])
-def test_one_request(L, B, method, n_heads, d, W, scores, shape, alone, in_place):
+def test_one_request(L, B, method, n_heads, d, W, scores, shape, pruned, alone, in_place):
     """A call of one request reads table and stack itself and writes both at its end, whichever row
     of the table it has; call after call on one pool, also between calls of several requests.
-    `alone`: the library's planner says that it takes that way (in place no ids are new)."""
+    `alone`: the library's planner says that it takes that way (in place no ids are new); `pruned`:
+    that a call without scores prunes it."""
     wl, s = _one_request(L, B, method, n_heads, d, W, in_place)
     if in_place and B == 2193:
         alone = not scores
     assert launch_shapes.planned(wl, methods=_only(method, 1), in_place=in_place)[1] == shape
     assert launch_shapes.without_plan_alloc(wl, scores, methods=_only(method, 1), in_place=in_place) == alone
-    if alone and method == SNAP and W != 33 and L >= 512:
-        assert L >= launch_shapes.prunes_from(d, shape)
+    assert launch_shapes.pruned(wl, methods=_only(method, 1), in_place=in_place)[1] == pruned
     try:
         for r in (1, 1, None, 0, 2):
             budgets = np.maximum(W, np.minimum(s.lens_o, [20 + W, B, 20 + W]) - (r is None)).astype(np.int32)
@@ -144,7 +146,7 @@ def test_one_request(L, B, method, n_heads, d, W, scores, shape, alone, in_place
 @pytest.mark.parametrize("L,B,method,n_heads,d,W,shape", [
     (300, 77, SNAP, 4, 64, 16, "narrow"),
     (640, 160, SNAP, 520, 128, 32, "narrow"),
-    (1500, 400, SNAP, 140, 128, 64, "wide"),
+    (2100, 400, SNAP, 140, 128, 64, "wide"),
     (700, 300, fo.METHOD_KNORM, 5, 64, 16, "wide"),
 ])
 def test_captured_call_of_one_request(L, B, method, n_heads, d, W, shape):

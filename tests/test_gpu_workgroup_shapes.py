@@ -20,7 +20,7 @@ SNAP, KNORM, STREAM = fo.METHOD_SNAPKV, fo.METHOD_KNORM, fo.METHOD_STREAMING
 WIDE, NARROW = 70, 300
 
 
-def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, shape=None, half=None, **kw):
+def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=False, shape=None, half=None, limit=None, **kw):
     from parity_util import SideBySide
     lens = list(lens) + [9] * fillers        # key-norm requests of nine tokens that only add heads
     budgets = list(budgets) + [4] * fillers
@@ -28,6 +28,8 @@ def _run(lens, budgets, methods, W, d, scores, fillers=0, n_heads=2, in_place=Fa
     wl = _custom(lens, budgets, methods, W=W, d=d, n_heads=n_heads)
     if shape:
         assert set(launch_shapes.planned(wl)) == {shape}
+    if limit:
+        assert launch_shapes.pruned(wl) == [m == SNAP and n >= limit for n, m in zip(lens, methods)]
     if half is not None:
         assert launch_shapes.leaves_half(wl) == half
     s = SideBySide(wl, in_place=in_place)
@@ -43,9 +45,10 @@ SHAPES = [(16, 128), (32, 128), (48, 128), (64, 128), (32, 64), (48, 64), (64, 6
 @pytest.mark.parametrize("scores", [True, False])
 @pytest.mark.parametrize("W,d", SHAPES)
 def test_narrow_workgroups(W, d, scores):
-    limit = launch_shapes.prunes_from(d, "narrow")
+    limit = {128: [512, 512, 576, 576], 64: [864, 864, 1024, 1152]}[d][W // 16 - 1]
     lens = [W, limit - 1, limit, 700, 2047, 2049, 4100, 8192]
-    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW, shape="narrow")
+    _run(lens, [max(W, n // 4) for n in lens], [SNAP] * len(lens), W, d, scores, NARROW, shape="narrow",
+         limit=limit)
 
 
 @pytest.mark.parametrize("scores", [True, False])
@@ -53,9 +56,10 @@ def test_narrow_workgroups(W, d, scores):
 def test_wide_workgroups(W, d, scores):
     # both sides of the pruning limit of wide workgroups, of the narrow ones' longest head, of the
     # longer epochs and of a wavefront's last chunk; the longest head of all
-    limit = launch_shapes.prunes_from(d, "wide")
+    limit = {128: [1408, 1664, 1664, 1664], 64: [3584, 5120, 5632, 7168]}[d][W // 16 - 1]
     lens = [W, 300, limit - 1, limit, limit + W, 8192, 8193, 16384, 16385, 32768]
-    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1, shape="wide")
+    _run(lens, [max(W, n // 5) for n in lens], [SNAP] * len(lens), W, d, scores, 2 * WIDE, n_heads=1, shape="wide",
+         limit=limit)
 
 
 @pytest.mark.parametrize("scores", [True, False])

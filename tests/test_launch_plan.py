@@ -41,21 +41,27 @@ def test_launch_plan(tmp_path):
     edges = [
         (_case(1, 128, long1), "split"),                 # one head per two compute units
         (_case(1, 129, long1), "wide"),
-        (_case(1, 128, [(2047, SNAP, 400, 32)]), "wide"),  # too short to split
+        (_case(1, 128, [(2047, SNAP, 400, 32)], d=64), "wide"),  # too short to split
         (_case(1, 128, long1, in_place=1), "wide"),      # one workgroup per head copies in place
-        (_case(1, 512, long1), "wide"),                  # two heads per compute unit
-        (_case(1, 513, long1), "narrow"),
+        (_case(1, 256, long1), "wide"),
+        (_case(1, 257, long1), "narrow"),                # a second round
         (_case(1, 513, [(8192, SNAP, 400, 32)]), "narrow"),
         (_case(1, 513, [(8193, SNAP, 400, 32)]), "wide"),
-        # one head per compute unit at most, and two: wide from the length on that keeps them busy
-        (_case(1, 256, [(511, SNAP, 100, 32)]), "narrow"),
-        (_case(1, 256, [(512, SNAP, 100, 32)]), "wide"),
-        (_case(1, 512, [(511, SNAP, 100, 32)]), "narrow"),
-        (_case(1, 512, [(512, SNAP, 100, 32)]), "wide"),
+        # one round of wide workgroups at most, from the length on that keeps them busy
+        (_case(1, 256, [(2047, SNAP, 100, 32)]), "narrow"),
+        (_case(1, 256, [(2048, SNAP, 100, 32)]), "wide"),
+        (_case(1, 256, [(895, SNAP, 100, 32)], d=64), "narrow"),
+        (_case(1, 256, [(896, SNAP, 100, 32)], d=64), "wide"),
+        (_case(1, 257, [(8000, SNAP, 100, 32)], d=64), "narrow"),
         (_case(1, 256, [(255, KNORM, 100, 32)]), "narrow"),
         (_case(1, 256, [(256, KNORM, 100, 32)]), "wide"),
-        (_case(1, 257, [(767, KNORM, 100, 32)]), "narrow"),
-        (_case(1, 257, [(768, KNORM, 100, 32)]), "wide"),
+        (_case(1, 257, [(8000, KNORM, 100, 32)]), "narrow"),
+        (_case(1, 256, [(255, STREAM, 100, 32)]), "narrow"),
+        (_case(1, 256, [(256, STREAM, 100, 32)]), "wide"),
+        (_case(1, 128, [(4000, SNAP, 1000, 32)] + [(2000, SNAP, 500, 32)] * 2), "wide"),   # as much as 256 of the first
+        (_case(1, 128, [(4000, SNAP, 1000, 32)] + [(2001, SNAP, 500, 32)] * 2), "narrow"),
+        (_case(1, 128, [(1000, SNAP, 200, 32), (1000, KNORM, 200, 32)]), "narrow"),        # the heaviest decides
+        (_case(1, 128, [(1000, SNAP, 200, 32), (4000, KNORM, 200, 32)]), "wide"),
         (_case(1, 4, [(256, SNAP, 64, 16)]), "narrow"),
         (_case(1, 32, [(100, SNAP, 64, 16), (9, KNORM, 4, 16), (20000, STREAM, 4000, 16)]), "wide"),
     ]
@@ -69,7 +75,7 @@ def test_launch_plan(tmp_path):
         row = [int(x) for x in line.split()[1:]]
         if line[0] == "C":
             parsed.append((row, []))
-        else:
+        elif line[0] == "F":
             parsed[-1][1].append(row)
     assert len(parsed) == len(cases)
     for (head, launches), (_, want) in zip(parsed, edges):
@@ -116,7 +122,7 @@ def test_which_launches_leave_half_of_the_keys_to_the_caches():
     cases = [
         (_case(1, 600, snap(2303)), 0),
         (_case(1, 600, snap(2304)), 1),
-        (_case(1, 512, snap(8000)), 0),                      # wide
+        (_case(1, 256, snap(8000)), 0),                      # wide
         (_case(1, 600, snap(8000), d=64), 0),
         (_case(1, 1, snap(2303, 2303) + fillers), 0),        # other methods do not count
         (_case(1, 1, snap(2304, 2304) + fillers), 1),
@@ -172,6 +178,26 @@ def test_which_calls_go_without_plan_alloc():
     text = "".join("%d %d %d %d %d %d %d\n%s\n" % (c[:6] + (len(c[6]), "\n".join("%d %d %d %d" % r for r in c[6])))
                    for c, _ in cases)
     out = subprocess.run([_driver(), "one"], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
-    for (case, want), line in zip(cases, out[1:]):
+    for (case, want), line in zip(cases, out):
         assert tuple(int(x) for x in line.split()[1:]) == want, (case, line)
-    assert len(out) == 1 + len(cases)
+    assert len(out) == len(cases)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_lengths_from_which_heads_are_pruned():
+    """Longer with more query tiles, in wide workgroups and with fewer heads; never so short that a
+    head's first step reaches its window (64 tokens a narrow workgroup, 256 a wide one)."""
+    from launch_shapes import _driver
+    cases = [_case(1, heads, [(L, SNAP, 100, 32)], d=d) for d in (64, 128) for heads, L in
+             ((513, 8192), (512, 8192), (256, 200), (256, 8192))]
+    text = "".join("%d %d %d %d %d %d %d\n%s\n" % (c[:6] + (1, "%d %d %d %d" % c[6][0])) for c in cases)
+    out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    limits = [[int(x) for x in line.split()[1:]] for line in out if line[0] == "P"]
+    assert [line[2] for line in out if line[0] == "F"] == list("00010001")
+    for d, (many, some, few, wide) in ((64, limits[:4]), (128, limits[4:])):
+        for row in (many, some, few, wide):
+            assert row == sorted(row) and row[0] >= 16 * 4 + 64
+        assert wide[0] >= 16 * 16 + 64
+        assert all(a <= b <= c for a, b, c in zip(many, some, few))
+    assert limits[4] == [512, 512, 576, 576] and limits[7] == [1408, 1664, 1664, 1664]
+    assert limits[0] == [864, 864, 1024, 1152] and limits[3] == [3584, 5120, 5632, 7168]

@@ -148,6 +148,6 @@ def test_kernel_names_of_the_benchmark(tmp_path):
             out = subprocess.run([_driver()], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
             assert any(int(line.split()[5]) for line in out if line[0] == "F") == name.endswith("true>"), name
             one = subprocess.run([_driver(), "one"], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
-            assert int(one[1].split()[1]) == ("_only_kernel<" in name), name
+            assert int(one[0].split()[1]) == ("_only_kernel<" in name), name
             launches = [line.split() for line in out if line[0] == "F" and kernel.startswith("fused")]
             assert any((w != "0") == (args[2] != "Li4") for _, w, *_ in launches), name
