@@ -91,8 +91,8 @@ hipError_t launch_append(const DecodeParams& p, const DecodeReqs& inline_reqs, h
 // there its loads' latency shows: it asks for the next block before it works on this one
 // (kCut).  8 caches of 256-1408 tokens, 32 heads: 26.5 us with segments of exactly
 // p.seg_blocks and one block in flight, 25.3 with even segments, 24.2 with both; 4 of
-// 1080-1120: 18.8, 18.0, 16.2.  Whole heads keep one block in flight and more wavefronts (59
-// registers against 92): 957 us against 964 (48 caches of 1280-7040 tokens, 2 layers).
+// 1080-1120: 18.8, 18.0, 16.2.  Whole heads keep one block in flight and more wavefronts (58
+// registers against 94): 957 us against 964 (48 caches of 1280-7040 tokens, 2 layers).
 // (Merged by the workgroup that finishes a head last, the release and acquire fences of
 // all segments cost 170 to 300 us, against the 5 us of a launch.)
 // ---------------------------------------------------------------------------

@@ -27,15 +27,18 @@ constexpr int kMixedQueryTiles = kPlanClasses;
 // the idle CUs.  A call of one layer, window 32, 128 channels, fused / split in us:
 //             4 heads       32            64            128           160 heads
 //   SnapKV
-//     1500    48.3 / 40.8   49.3 / 42.0   51.3 / 46.5   54.6 / 52.8
-//     2048    56.8 / 40.6   61.5 / 41.7   63.8 / 49.0   67.6 / 60.7   69.3 / 67.7
-//     4000    83.0 / 43.0   89.2 / 55.2   93.4 / 63.7  101.7 / 91.3  102.3 / 105.4
-//     16000    244 / 75      255 / 109     277 / 163     297 / 299     326 / 370
-//   key-norm
-//     2048    37.1 / 38.5   36.5 / 37.7   38.8 / 36.6   41.6 / 47.9   43.2 / 55.7
-//     4000    47.9 / 38.0   54.5 / 39.7   59.3 / 49.6   65.3 / 72.2   69.5 / 86.4
-//     16000    161 / 44      178 / 83      194 / 129     225 / 250     242 / 314
-// (Calls of key-norm requests alone would be better off with a limit of 64 to 96 heads.)
+//     1500    48.5 / 38.7   50.4 / 41.3   52.4 / 48.0   56.2 / 55.7   57.0 / 59.2
+//     2048    54.8 / 41.1   57.6 / 42.8   60.3 / 50.9   64.1 / 63.2   65.7 / 71.2
+//     4000    78.4 / 46.0   85.5 / 57.0   89.2 / 66.7   96.8 / 96.9   98.7 / 112
+//     16000    228 / 79      247 / 115     275 / 176     301 / 314     322 / 388
+//   64 channels
+//     2048    43.8 / 38.0   45.1 / 40.3   46.0 / 43.6   49.4 / 48.3   50.0 / 52.1
+//     16000    168 / 74      182 / 83      191 / 109     202 / 170     207 / 207
+//   key-norm, 128 channels
+//     2048    32.6 / 29.8   34.7 / 32.1   37.5 / 36.6   43.5 / 47.6   46.2 / 54.2
+//     4000    49.2 / 33.1   53.4 / 40.2   58.8 / 49.1   68.3 / 69.0   73.6 / 78.4
+//     16000    150 / 45      168 / 80      191 / 118     239 / 231     262 / 288
+// (These are sums of kernels; the launches between them, two to five more, are not in them.)
 constexpr int kSplitMinLen = 2048;
 
 // Whether the `units` heads of up to 8192 tokens of a call are better off in wide workgroups.
@@ -81,10 +84,10 @@ bool wide_pays(const PoolView& pool, const CompressPlan& plan, size_t units, int
 // From what mean length of its SnapKV heads (each weighted by its own) on a launch of
 // narrow workgroups leaves only half of the keys to the caches in its first pass.  All
 // kernels of a pruned call, window 16 to 64, 128 channels, all / half:
-//   8192 heads of  700 tokens  580-681 / 607-692 us     4096 heads of 3000  1237-1324 / 1209-1274
-//   8192          1500         1259-1304 / 1300-1364    2048          4000  799-875 / 768-849
-//   6144          2400         1420-1441 / 1396-1452    2048          6500  1338-1382 / 1279-1338
-//   4096          2000         827-886 / 808-871         768          2500  210-228 / 194-216
+//   8192 heads of  700 tokens  512-538 / 529-558 us     4096 heads of 3000  1118-1125 / 1082-1107
+//   8192          1500         1082-1086 / 1105-1141    2048          4000  744-758 / 718-726
+//   6144          2400         1316-1341 / 1316-1338    2048          6500  1208-1212 / 1139-1162
+//   4096          2000         729-732 / 728-751         768          2500  165-172 / 157-165
 // With three and more query tiles that kernel takes 3 KB more of LDS, so where a head of
 // more than 7820 tokens is in the launch (kPlanHalfReuseWords) two workgroups of it fit a
 // CU, not three, and the plain one is the faster.  1536 heads of 7900-8190 tokens, window
@@ -550,12 +553,12 @@ int plan_decode_attention(const PoolView& pool, int n_req, int max_blocks, const
 // cut, 29.8 whole; 36 of 358-1074, 40 heads, 87.9 and 83.9; 44 of 496-744, 24 heads, 56.6
 // and 57.2).  The attention alone, 32 heads, us:
 //   segments at least of     8      16      24      whole
-//   8 caches of 256-1408    23.7    24.2    24.2    32.5
-//   1 of 4000               17.9    15.5    17.1    82.4
+//   8 caches of 256-1408    23.7    22.8    22.9    32.6
+//   1 of 4000               17.0    14.7    15.9    80.8
 //   a share's            quarter  eighth  sixteenth
-//   16 of 130-16384        377     353     358      417
-//   12 of 4000-16000 (2 layers)  664  648  643      666
-//   48 of 1280-7040 (2 layers)   960  960  984      959
+//   16 of 130-16384        365     353     357      417
+//   12 of 4000-16000 (2 layers)  661  637  641      663
+//   48 of 1280-7040 (2 layers)   957  956  973      954
 // (a ninth, a tenth and a twelfth are equal to an eighth over 60 calls of 1 to 48 caches
 // of 600-32000 tokens, 3 % either way in single ones).
 void plan_decode_segments(const PoolView& pool, int n_cu, bool over_kept, DecodePlan* plan, int max_segments) {
