@@ -523,10 +523,12 @@ hipError_t launch_fused(BatchParams p, int query_tiles, int max_seq_len, int max
   // it doesn't use.  64 channels, one wide workgroup a CU, not two: 512 heads of 3000-6000
   // tokens 83.0 -> 77.3 us; two narrow ones, not eight, from eight heads a CU on: 3840 heads of
   // 1400-4300 341 -> 328, in place 357 -> 329 (128 channels 835 -> 817, 832 -> 820); but 1024
-  // of 640 tokens 25.8 -> 27.8.
+  // of 640 tokens 25.8 -> 27.8, and 2048 of 200-300, 64 channels, 32.3 -> 34.2 (in place 32.4 ->
+  // 34.4; of 640-960 82.0 -> 79.9).
   const bool copies = query_tiles == 0 && max_seq_len == 0;  // (LDS for no score)
   if (copies && wide && p.head_dim == 64) lds = std::max<size_t>(lds, 68 * 1024);
-  if (copies && !wide && p.n_fused * p.n_layers * p.n_heads >= 8 * 256) lds = std::max<size_t>(lds, 39 * 1024);
+  if (copies && !wide && p.n_fused * p.n_layers * p.n_heads >= 8 * 256 && (p.head_dim == 128 || max_blocks > 32))
+    lds = std::max<size_t>(lds, 39 * 1024);
   if (p.head_dim == 128)
     return wide ? launch_fused_wide_128(p, query_tiles, lds, s) : launch_fused_narrow_128(p, query_tiles, lds, s);
   if (p.head_dim == 64)

@@ -1652,7 +1652,8 @@ struct RowCopy {
 // (gather_fused), each row waits for the one before; all at once / in order, half of the tokens
 // kept, 128 channels: 256 heads of 900-1000 tokens 29.0 / 26.9 us, 512 of 3000-6000 252 / 248,
 // of 9000-16000, a third kept, 533 / 520; 64 channels: 256 of 2000-4000 35.4 / 33.8, 512 of
-// 9000-16000 254 / 251.  In place, and narrow ones (see launch_fused), all at once: 256 heads of
+// 9000-16000 254 / 251.  In place, and narrow ones (see launch_fused), all at once (so is what was
+// scored at 64 channels, in place: key norms, 2048 heads of 900-3000 194 / 197): 256 heads of
 // 2000-4000 in place 63.5 / 66.5, 3840 of 1400-4300, 64 channels, 328 / 354.
 template <int D, int WV, bool kStreaming, typename BlockAt, typename NewAt, typename KeptAt>
 __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc& rd, int lh, BlockAt block_at,
@@ -1673,7 +1674,7 @@ __device__ __forceinline__ void gather_unit(const BatchParams& p, const ReqDesc&
     // needed (later chunks read strictly later slots).
     for (int c0 = 0; c0 < nb; c0 += WV) {
       const int nbk = c0 + c.wave;
-      if (nbk < nb) c.template load<!kStreaming>(kv, [&](int row) { return source(nbk, row); });
+      if (nbk < nb) c.template load<!kStreaming && D == 128>(kv, [&](int row) { return source(nbk, row); });
       __syncthreads();  // uniform: c0 and in_place are the same for all threads
       if (nbk < nb) c.store(nbk, block_at(nbk), kv);  // (the request's own first blocks)
     }
